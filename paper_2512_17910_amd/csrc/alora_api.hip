@@ -289,10 +289,10 @@ static int forward_on(const void *x, const int32_t *token_adapter_ids, const int
     }
     // decode-sized bf16 batches: grouping and shrink ride in the projection kernel (two launches in all)
     const bool prep_inside = prep_in_projection(f);
-    int e = (prep_inside || reuse_grouping) ? 0 : launch_classify_group(f);
+    int e = (prep_inside || reuse_grouping || group_in_shrink_f32(f)) ? 0 : launch_classify_group(f);
     if (!e) {
         if (f.dtype == ALORA_F32) {
-            e = launch_shrink_f32(f, ta);
+            e = launch_shrink_f32(f, ta, reuse_grouping);
             if (!e && timed) e = (int)hipEventRecord(g_prof.ev0[g_prof.used], f.stream);
             if (!e) e = launch_gemm_f32(f, tb);
             if (!e && f.rope_cos) e = launch_rope_f32(f);

@@ -83,7 +83,8 @@ void note_hip_error(int hip_error);
 
 // launches (each returns the hipError_t of its launch as int)
 int launch_classify_group(const Fwd &f);
-int launch_shrink_f32(const Fwd &f, const PtrTable &A);
+int launch_shrink_f32(const Fwd &f, const PtrTable &A, bool reuse_grouping);
+bool group_in_shrink_f32(const Fwd &f);   // the grouping runs on workgroups of the fp32 shrink
 int launch_gemm_f32(const Fwd &f, const PtrTable &B);
 int launch_shrink_bf16(const Fwd &f, const PtrTable &A);
 int launch_gemm_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEvent_t after_projection);
