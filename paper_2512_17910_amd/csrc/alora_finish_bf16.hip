@@ -25,7 +25,7 @@ constexpr int FIN_COLS = 256;  // features per workgroup: 32 threads x 8 feature
 
 template <int SPLITS>
 __global__ __launch_bounds__(1024) void finish_bf16_kernel(const float *__restrict__ partial,
-                                                           const void *__restrict__ S_any, int s_splits, PtrTable B,
+                                                           const void *__restrict__ S_any, int s_splits, bool s_f32, PtrTable B,
                                                            RankTable ranks, const bf16_t *__restrict__ bias,
                                                            const int32_t *__restrict__ perm,
                                                            const int32_t *__restrict__ block_rows,
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(1024) void finish_bf16_kernel(const float *__restri
         if (t >= 0) {
             for (int j = c; j < ra; j += 32) {
                 float sj = 0.f;
-                if (s_splits > 1) {
+                if (s_f32) {
                     // all ranges' loads first, then the sum in range order (absent ranges add +0)
                     float sp[ALORA_SHRINK_MAX_SPLITS];
 #pragma unroll
@@ -168,24 +168,25 @@ __global__ __launch_bounds__(1024) void finish_bf16_kernel(const float *__restri
 }
 
 template <int SPLITS>
-static void launch_finish(const Fwd &f, const PtrTable &B, int s_splits, const int32_t *block_rows)
+static void launch_finish(const Fwd &f, const PtrTable &B, int s_splits, const int32_t *block_rows, bool s_f32)
 {
     const dim3 grid(f.n_blocks, (f.N + FIN_COLS - 1) / FIN_COLS);
     hipLaunchKernelGGL(finish_bf16_kernel<SPLITS>, grid, dim3(1024), 0, f.stream, (const float *)f.partial,
-                       f.S, s_splits, B, f.ranks, (const bf16_t *)f.bias, f.perm, block_rows, f.blocktab, f.slot, (bf16_t *)f.q, (bf16_t *)f.kc,
+                       f.S, s_splits, s_f32, B, f.ranks, (const bf16_t *)f.bias, f.perm, block_rows, f.blocktab, f.slot, (bf16_t *)f.q, (bf16_t *)f.kc,
                        (bf16_t *)f.vc, f.T, f.Nq, f.Nkv, f.L, f.r, f.rope_cos, f.rope_sin, f.pos, f.rope_positions);
 }
 
-int launch_finish_bf16(const Fwd &f, const PtrTable &B, int splits, int s_splits, const int32_t *block_rows)
+int launch_finish_bf16(const Fwd &f, const PtrTable &B, int splits, int s_splits, const int32_t *block_rows, bool s_f32)
 {
     switch (splits) {
-    case 2: launch_finish<2>(f, B, s_splits, block_rows); break;
-    case 3: launch_finish<3>(f, B, s_splits, block_rows); break;
-    case 4: launch_finish<4>(f, B, s_splits, block_rows); break;
-    case 5: launch_finish<5>(f, B, s_splits, block_rows); break;
-    case 6: launch_finish<6>(f, B, s_splits, block_rows); break;
-    case 7: launch_finish<7>(f, B, s_splits, block_rows); break;
-    case 8: launch_finish<8>(f, B, s_splits, block_rows); break;
+    case 1: launch_finish<1>(f, B, s_splits, block_rows, s_f32 || s_splits > 1); break;
+    case 2: launch_finish<2>(f, B, s_splits, block_rows, s_f32 || s_splits > 1); break;
+    case 3: launch_finish<3>(f, B, s_splits, block_rows, s_f32 || s_splits > 1); break;
+    case 4: launch_finish<4>(f, B, s_splits, block_rows, s_f32 || s_splits > 1); break;
+    case 5: launch_finish<5>(f, B, s_splits, block_rows, s_f32 || s_splits > 1); break;
+    case 6: launch_finish<6>(f, B, s_splits, block_rows, s_f32 || s_splits > 1); break;
+    case 7: launch_finish<7>(f, B, s_splits, block_rows, s_f32 || s_splits > 1); break;
+    case 8: launch_finish<8>(f, B, s_splits, block_rows, s_f32 || s_splits > 1); break;
     default: return (int)hipErrorInvalidValue;
     }
     return (int)hipGetLastError();

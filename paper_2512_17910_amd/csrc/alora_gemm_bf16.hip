@@ -846,6 +846,8 @@ static std::atomic<int> g_force_tuning{0};
 
 void set_gemm_tuning(int ntw, int splits) { g_force_tuning.store((ntw & 0xff) | (splits << 8), std::memory_order_relaxed); }
 
+bool gemm_tuning_forced() { return g_force_tuning.load(std::memory_order_relaxed) != 0; }
+
 GemmPlan plan_gemm(int T, int H, int N)
 {
     const int forced = g_force_tuning.load(std::memory_order_relaxed);
@@ -905,6 +907,7 @@ static void launch_ntw(const GemmArgs &g, const PtrTable &B, const PtrTable &A, 
 // on workgroups behind its own (the projection of such a batch does not fill every compute unit).
 bool prep_in_projection(const Fwd &f)
 {
+    if (decode_call(f)) return true;
     if (f.dtype != ALORA_BF16 || f.L <= 0 || f.T <= 0 || f.T > GROUP_SMALL_ROWS || f.r > 32 || !f.block_rows) return false;
     const GemmPlan plan = plan_gemm(f.T, f.H, f.N);
     return plan.splits > 1 && plan.ntw == 2;
@@ -913,6 +916,7 @@ bool prep_in_projection(const Fwd &f)
 int launch_gemm_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEvent_t after_projection)
 {
     if (f.T == 0) return 0;
+    if (decode_call(f)) return launch_decode_bf16(f, B, A, after_projection);
     GemmPlan plan = plan_gemm(f.T, f.H, f.N);
     // the fused rotary embedding wants whole heads of 128 in a wavefront's strip: 256-feature tiles (the number
     // of splits, which the shrink's layout depends on, stays what the sizes alone give; with splits the
@@ -948,7 +952,7 @@ int launch_gemm_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEven
     if (!e && after_projection) e = (int)hipEventRecord(after_projection, f.stream);
     if (e || plan.splits == 1) return e;
     return launch_finish_bf16(f, B, plan.splits, prep ? g.prep_ranges : plan_shrink(f.T, f.H, f.N, f.L, f.r).splits,
-                              prep ? f.block_rows : nullptr);
+                              prep ? f.block_rows : nullptr, false);
 }
 
 }  // namespace alora

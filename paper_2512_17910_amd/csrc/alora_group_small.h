@@ -29,7 +29,7 @@ struct GroupSmallArgs {
 
 // Entry `e` of the block table of the batch: returns the group in `grp` (-1: unused entry), the
 // number of rows in `cnt`, writes this entry's share of the results if `write`, and leaves the row ids in scr's last 32 ints (returned pointer; -1 = no
-// row).  All 256 threads call; the caller may use the row ids after the call (it ends in a barrier).
+// row).  All threads call (at least 256); the caller may use the row ids after the call (it ends in a barrier).
 __device__ __forceinline__ const int *group_small(const GroupSmallArgs &ga, int T, int L, int e, bool write, int *scr, int &grp,
                                                   int &cnt)
 {
@@ -41,7 +41,7 @@ __device__ __forceinline__ const int *group_small(const GroupSmallArgs &ga, int 
         const int ae = effective_adapter(ga.aid, ga.seg, ga.pos, ga.start, tid);
         key = ae >= 0 && ae < L ? ae : L;
     }
-    keys[tid] = key;
+    if (tid < GROUP_SMALL_ROWS) keys[tid] = key;
     if (tid <= L) tot[tid] = 0;
     if (tid < 32) rows[tid] = -1;
     __syncthreads();

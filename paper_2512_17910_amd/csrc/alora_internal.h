@@ -89,13 +89,17 @@ int launch_gemm_f32(const Fwd &f, const PtrTable &B);
 int launch_shrink_bf16(const Fwd &f, const PtrTable &A);
 int launch_gemm_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEvent_t after_projection);
 bool prep_in_projection(const Fwd &f);   // grouping and shrink run inside the split projection kernel
-int launch_finish_bf16(const Fwd &f, const PtrTable &B, int splits, int s_splits, const int32_t *block_rows);
+int launch_finish_bf16(const Fwd &f, const PtrTable &B, int splits, int s_splits, const int32_t *block_rows, bool s_f32);
 struct GemmPlan {
     int ntw;     // 32-wide feature tiles per wavefront (tile width 64 * ntw)
     int splits;  // 1: fused kernel; > 1: split hidden dimension + finishing kernel
     int kps;     // 64-wide K-slices per split
 };
 GemmPlan plan_gemm(int T, int H, int N);
+// batches of a few rows (alora_decode_bf16.hip): whether a call takes that path, from its sizes alone
+bool decode_call(const Fwd &f);
+int launch_decode_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEvent_t after_projection);
+bool gemm_tuning_forced();
 size_t gemm_partial_bytes(int T, int H, int N);
 void set_gemm_tuning(int ntw, int splits);
 int group_blocks(int T, int L);
