@@ -316,7 +316,6 @@ __global__ __launch_bounds__(256) void paged_attention_kernel(AttnArgs a)
 // few round trips to memory long and little else, so a workgroup requests everything it needs at once: D / 2
 // lanes take one part (two elements each), 512 / D groups of them every NG-th part.  Measured (32/8 heads of 128): 8 rows in
 // 16 parts 16.0 us with one part after the other, 5.0 us now; 256 rows in 8 parts (34 MB) 17.0 -> 9.0 us.
-constexpr int MAX_PARTS = 32;
 template <int D, bool BF16>
 __global__ __launch_bounds__(256) void paged_attention_merge_kernel(const float *__restrict__ part, void *__restrict__ out, int splits)
 {
@@ -422,19 +421,15 @@ static int plan_splits(const alora_attn_dims *d)
     return (int)std::min<long long>(MAX_PARTS, (1024 + wgs - 1) / wgs);
 }
 
-// The same for the row-block kernel, whose unit of work is a block of 128 / G rows: parts when the batch
-// has fewer than 512 (row block, K/V head) pairs.
-static int plan_block_splits(const alora_attn_dims *d)
+// The same for the row-block kernel, whose unit of work is a block of rows.
+static BlockPlan block_plan(const alora_attn_dims *d, bool parts)
 {
-    const int G = d->n_q_heads / d->n_kv_heads, rbg = 128 / G;
-    const long long wgs = (long long)((d->n_tokens + rbg - 1) / rbg) * d->n_kv_heads;
-    if (wgs <= 0 || wgs >= 512) return 1;
-    return (int)std::min<long long>(MAX_PARTS, (512 + wgs - 1) / wgs);
+    return plan_blocks(d->n_tokens, d->n_seqs, d->n_kv_heads, d->n_q_heads / d->n_kv_heads, parts);
 }
 
 static size_t block_split_bytes(const alora_attn_dims *d)
 {
-    const int sp = plan_block_splits(d);
+    const int sp = block_plan(d, true).splits;
     if (sp <= 1) return 0;
     return (size_t)d->n_tokens * d->n_q_heads * sp * (d->head_dim + 2) * sizeof(float);
 }
@@ -526,7 +521,7 @@ static int run(const void *q, const void *k_cache, const void *v_cache, const in
     // without table or cache, take the per-row kernel)
     const bool row_blocks = blocks_asked && dims->block_size % 4 == 0 && dims->n_seqs >= 1 && dims->max_blocks >= 1 &&
                             dims->n_slots >= dims->block_size;
-    const int splits = mode == PER_ROW_SPLIT ? plan_splits(dims) : (mode == ROW_BLOCKS_SPLIT && row_blocks) ? plan_block_splits(dims) : 1;
+    const int splits = mode == PER_ROW_SPLIT ? plan_splits(dims) : (mode == ROW_BLOCKS_SPLIT && row_blocks) ? block_plan(dims, true).splits : 1;
     const size_t need = mode == PER_ROW_SPLIT ? split_bytes(dims) : mode == ROW_BLOCKS_SPLIT ? block_split_bytes(dims) : 0;
     if (splits > 1 && (!workspace || ((uintptr_t)workspace & 15) || workspace_bytes < need)) return ALORA_EWORKSPACE;
     if (dims->n_tokens == 0) return ALORA_OK;
@@ -550,7 +545,7 @@ static int run(const void *q, const void *k_cache, const void *v_cache, const in
     const bool bf16 = dims->dtype == ALORA_BF16;
     const int G = dims->n_q_heads / dims->n_kv_heads;
     if (row_blocks) {
-        const int e2 = launch_attention_blocks(a, G, (hipStream_t)hip_stream);
+        const int e2 = launch_attention_blocks(a, G, block_plan(dims, mode == ROW_BLOCKS_SPLIT), (hipStream_t)hip_stream);
         if (e2) { note_hip_error(e2); return ALORA_EHIP; }
         if (splits > 1) {
             hipLaunchKernelGGL((paged_attention_merge_kernel<128, true>), dim3((unsigned)a.T * (unsigned)a.Hq), dim3(256), 0,

@@ -2,33 +2,39 @@
 // (a projected suffix attending over a cached prefix, Sec. 2.3 / 4.2) are handled by ONE workgroup per
 // K/V head, which loads every cached row once for all of them.  bf16, head_dim 128, on bf16 MFMA.
 //
-// A wavefront owns 16 columns (query row, query head of the K/V head's group): 16 / G rows; the eight
-// wavefronts of a workgroup 128 / G consecutive rows, which share the K and V tiles of 32 context positions
-// through LDS: every cached row is loaded once per 128 / G query rows.  Row blocks are cut at multiples of
-// 128 / G of the POSITION, so whether a batch row leads a block is decided from the row before it alone.
-// A workgroup owns a range of batch rows (chosen on the host: a whole row block for large batches, down to
-// one row for a decode batch, where every row leads a block of its own) and works through the blocks that
-// start in it; the range index is permuted so that the leading rows of a long run do not all fall to the
-// same shader engine.
+// A wavefront owns 32 columns (query row, query head of the K/V head's group): 32 / G rows; the wavefronts of a
+// workgroup (eight, or four) consecutive rows, which share the K and V tiles of 32 context positions through LDS:
+// every cached row is loaded once per 256 / G (128 / G) query rows.  Row blocks are cut at multiples of that number
+// of the POSITION, so whether a batch row leads a block is decided from the row before it alone.
+// A workgroup owns a range of batch rows (chosen on the host: a whole row block for long runs, down to one row for
+// a decode batch, where every row leads a block of its own) and works through the blocks that start in it; the
+// range index is permuted so that the leading rows of a long run do not all fall to the same shader engine.
 //
 // For batches with few row blocks the context of every block is cut into parts, one workgroup each, which
 // leave (running maximum, weight sum, unnormalised output) per column for the kernel that combines them.
 //
-// Per 32 context positions a wavefront runs two sets of 16x16x32 MFMAs that keep every column in the same
-// four lanes (c, c+16, c+32, c+48) from the scores to the output:
-//   scores^T [position x column] = K [position x d] . Q^T [d x column]   two tiles of 16 positions; K rows
-//       from the LDS tile into the A operand (a lane holds 8 consecutive d of one position), Q in registers;
-//   online softmax down each column: 8 accumulator registers per lane, two exchanges between the four
-//       lanes of a column; no masking arithmetic on blocks that every column of the wavefront sees whole;
-//   out^T [d x column] += V^T [d x position] . P [position x column]   eight tiles of 16 d; V comes back
-//       from LDS with the transposing load, whose two halves are taken sixteen rows apart: that hands a
-//       lane exactly the positions its score registers hold, so P is the score accumulator itself, rounded
-//       to bf16.
-// K and V rows go from global memory straight into LDS (no registers in between): four tile pairs, one being
-// multiplied while three are on their way, one barrier per 32 positions; the block-table entries of 64 such
-// steps sit in an LDS window.  An assembly statement never reads a register an MFMA writes (the compiler
-// cannot place the wait states for it); the copies and their wait counts are assembly because the compiler's
-// own bookkeeping would wait for all of them.
+// Per 32 context positions a wavefront runs two sets of 32x32x16 MFMAs that keep every column in the same
+// two lanes (c, c+32) from the scores to the output:
+//   scores^T [position x column] = K [position x d] . Q^T [d x column]   K rows from the LDS tile into the A operand
+//       (a lane holds 8 consecutive d of one position), Q in registers;
+//   online softmax down each column: 16 accumulator registers per lane, in most blocks no exchange between
+//       lanes (none brings a new maximum) and no masking arithmetic where every column of the wavefront sees
+//       the whole block;
+//   out^T [d x column] += V^T [d x position] . P [position x column]   four tiles of 32 d; V comes back from LDS with
+//       the transposing load, whose two halves are taken eight rows apart: that hands a lane exactly the
+//       positions its score registers hold, so P is the score accumulator itself, rounded to bf16.
+// K and V rows go from global memory straight into LDS (no registers in between), two blocks of 32 positions per
+// barrier; the block-table entries of 64 blocks sit in an LDS window.  An assembly statement never reads a register
+// an MFMA writes (the compiler cannot place the wait states for it); the copies and their wait counts are assembly
+// because the compiler's own bookkeeping would wait for all of them.
+//
+// Measured, 4 x 2048 rows over 16K positions, 32/8 heads (2.06 TFLOP): 16 columns per wavefront on 16x16x32 MFMAs 2640 us
+// (each byte read from LDS fed 16 columns, every block exchanged its maximum between four lanes); 32 columns, four
+// wavefronts 2310; eight wavefronts (half the copies per score: without any copies the kernel took 1830) and two blocks per
+// barrier 2220 us = 0.93 PFLOP/s, where a large bf16 matrix product reaches 1.2 on the same card.  What is left: matrix
+// unit 39 % and vector unit 39 % of the cycles, which add up more than they overlap, and the copies.  Running the
+// scores of the next block and the output of the one before it between the vector instructions of the softmax
+// (three blocks in flight, one matrix product per four vector instructions) was built and measured: 2470 us.
 #include "alora_attention_internal.h"
 
 namespace alora {
@@ -42,11 +48,11 @@ typedef __attribute__((address_space(3))) unsigned char lds_byte;
 constexpr float AB_NEG_INF = -__builtin_inff();
 constexpr float AB_M_FLOOR = -1.0e30f;   // finite floor of the running maximum (scores below it weigh nothing)
 
-// four k of this lane's column, then the four that lie sixteen rows further on
+// four k of this lane's column, then the four that lie eight rows further on
 __device__ __forceinline__ bf16x8 read_tr_frag(const lds_byte *p, int pitch)
 {
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(p + 16 * pitch));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(p + 8 * pitch));
     const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     return __builtin_bit_cast(bf16x8, v);
 }
@@ -73,68 +79,51 @@ __device__ __forceinline__ void load_lds16(uint32_t lds_addr, const void *base, 
 // compiler cannot place for an instruction it does not see.  Checked with in-bounds probes:
 //   v_permlane16_swap on two copies of x: ev <- x of the even 16-lane row of this lane's row pair, od <- the odd row's
 //   v_permlane32_swap on two copies of x: lo <- x of the lower 32 lanes, hi <- the upper 32 lanes'
-__device__ __forceinline__ void row_pair(float x, float &ev, float &od)
-{
-    ev = x, od = x;
-    asm("s_nop 3\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 3" : "+v"(ev), "+v"(od));
-}
 __device__ __forceinline__ void both_halves(float x, float &lo, float &hi)
 {
     lo = x, hi = x;
     asm("s_nop 3\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 3" : "+v"(lo), "+v"(hi));
 }
-__device__ __forceinline__ float max_over_column(float x)
-{
-    float a, b, c, d;
-    row_pair(x, a, b);
-    both_halves(fmaxf(a, b), c, d);
-    return fmaxf(c, d);
-}
-__device__ __forceinline__ float sum_over_column(float x)
-{
-    float a, b, c, d;
-    row_pair(x, a, b);
-    both_halves(a + b, c, d);
-    return c + d;
-}
-
 // what a lane loads for a position that is not part of the context (the weighted sum multiplies it by 0)
 __device__ const uint32_t ab_zero_chunk[4] = {0u, 0u, 0u, 0u};
 
-template <int G, bool POW2>   // POW2: the block size is a power of two (shifts instead of divisions)
-__global__ __launch_bounds__(512, 4) void paged_attention_blocks_kernel(AttnArgs a, int R)
+template <int G, int NW, bool POW2>   // NW: wavefronts per workgroup; POW2: the block size is a power of two (shifts instead of divisions)
+__global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(AttnArgs a, int R, int sub)
 {
     constexpr int D = 128;
-    constexpr int NW = 8;             // wavefronts per workgroup
-    constexpr int RBW = 16 / G;       // query rows per wavefront (16 columns = rows x heads of the group)
+    constexpr int GPW = 8 / NW;       // groups of four positions a wavefront copies per block of 32
+    constexpr int RBW = 32 / G;       // query rows per wavefront (32 columns = rows x heads of the group)
     constexpr int RBG = NW * RBW;     // query rows per workgroup
     constexpr int PITCH = 256;        // bytes per position row of the K and V tiles in LDS
     constexpr int TILE = 32 * PITCH;  // one tile: 32 positions
-    constexpr int NB = 4;             // (K, V) tile pairs: one is multiplied while three are on their way
+    constexpr int NB = NW == 8 ? 6 : 4;   // (K, V) tile pairs, taken two at a time (four wavefronts: two workgroups share a CU's LDS)
     __shared__ __attribute__((aligned(1024))) unsigned char tiles[NB * 2 * TILE];
-    __shared__ __attribute__((aligned(16))) unsigned char ok_bytes[NB][NW];     // byte w: validity of positions 4w .. 4w+3 of a pair
-    __shared__ unsigned long long run_mask[2];
+    __shared__ __attribute__((aligned(16))) unsigned char ok_bytes[NB][8];     // byte i: validity of positions 4i .. 4i+3 of a pair
+    __shared__ unsigned long long run_mask[NW / 2];
     constexpr int WIN = 64;            // blocks of 32 positions whose table entries the window below holds
     __shared__ int32_t window[WIN * 32 / 4 + 2];   // block sizes are multiples of 4
 
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4, li = lane & 31, lh = lane >> 5;
     const int wu = __builtin_amdgcn_readfirstlane(w);
     // grid: (range of batch rows, K/V head, part of the context); a.splits parts, 1 = the whole context
-    const int part = (int)blockIdx.x % a.splits, bid = (int)blockIdx.x / a.splits;
+    // (long runs of rows: every range twice, see plan_blocks; the second halves, mostly without work, are dispatched first)
+    const int n_ranges = (a.T + R - 1) / R, per_sub = n_ranges * a.Hkv * a.splits;
+    const int which = sub > 1 ? 1 - (int)blockIdx.x / per_sub : 0, bid_part = (int)blockIdx.x % per_sub;
+    const int part = bid_part % a.splits, bid = bid_part / a.splits;
     const int hk = bid % a.Hkv;
-    // ---- this workgroup's R batch rows (R a power of two <= 32, <= RBG) ------------------------------------
+    // ---- this workgroup's R batch rows (R a power of two <= 64, <= RBG) ------------------------------------
     // With R < RBG a long run of rows has a leading row in every (RBG / R)-th range only, and workgroups are
     // handed to the shader engines of an XCD in turn (four of them): without the exchange of the two low index
     // bits below, all the work of such a batch would land on one engine in four.
     int k = bid / a.Hkv;
     {
-        const int n_ranges = (a.T + R - 1) / R, mm = RBG / R;
+        const int mm = RBG / R;
         if (mm > 1 && (k | 3) < n_ranges) k ^= (k / mm) & (mm >= 4 ? 3 : 1);
     }
     const int r_begin = k * R, r_end = min(a.T, r_begin + R);
     // which of them lead a block: a row does unless the row before it in the batch is the same sequence's
     // previous position and the position is not a multiple of RBG (then an earlier row leads)
-    unsigned leaders;
+    unsigned long long leaders;
     {
         bool lead = false;
         const int t = r_begin + lane;
@@ -143,7 +132,14 @@ __global__ __launch_bounds__(512, 4) void paged_attention_blocks_kernel(AttnArgs
             const bool ok = sq >= 0 && sq < a.n_seqs && p0 >= 0;
             lead = !(ok && t > 0 && (p0 % RBG) != 0 && a.seq[t - 1] == sq && a.pos[t - 1] == p0 - 1);
         }
-        leaders = (unsigned)__builtin_amdgcn_ballot_w64(lead);
+        leaders = __builtin_amdgcn_ballot_w64(lead);
+        if (sub > 1) {   // every other one
+            unsigned long long mine = 0;
+            int n = 0;
+            for (unsigned long long rest = leaders; rest; rest &= rest - 1, ++n)
+                if ((n & 1) == which) mine |= rest & -rest;
+            leaders = mine;
+        }
     }
     const int Nkv = a.Hkv * D;
     const long long n_blocks = a.n_slots / a.bs;
@@ -151,29 +147,27 @@ __global__ __launch_bounds__(512, 4) void paged_attention_blocks_kernel(AttnArgs
     const uint32_t tiles_at = (uint32_t)(uintptr_t)(lds_byte *)tiles;
     const uint32_t row_bytes = (uint32_t)Nkv * 2u, head_bytes = (uint32_t)hk * D * 2u;
     const unsigned n_blocks_u = (unsigned)(n_blocks < 0x7fffffffll ? n_blocks : 0x7fffffffll);
-    // ---- copies global -> LDS: wavefront w fills positions 4w .. 4w+3 of a block of 32 with one K and one V
-    // instruction (one cache block: block sizes are multiples of 4, so its table entry is a scalar); lane ->
-    // position + lane / 16, physical 16-byte chunk lane % 16.
-    // K tile: row = position, the physical chunk holds logical chunk XOR (row % 16) (the score product reads
-    // one logical chunk of 16 rows).  V tile: row = position, XOR 4 * (row % 4) + 2 * (row / 4 % 2) (the
-    // transposing read takes two chunks of four rows per 16 lanes, rows 4 apart in the next 16 lanes).
-    const int row_c = 4 * wu + g4;                                   // this lane's position within a block of 32
+    // ---- copies global -> LDS: wavefront w fills positions 4w .. 4w+3 of a block of 32 (of four wavefronts: and 16 further
+    // on) with one K and one V instruction each (one cache block: block sizes are multiples of 4, so its table entry
+    // is a scalar); lane -> position + lane / 16, physical 16-byte chunk lane % 16.
+    // K tile: row = position, the physical chunk holds logical chunk XOR (row % 16) (the score product reads one
+    // logical chunk of 32 rows).  V tile: row = position, XOR 4 * (row % 4) (the transposing read takes four chunks of
+    // four rows per 32 lanes).
     const uint32_t row_off = (uint32_t)g4 * (uint32_t)Nkv * 2u;
-    const uint32_t k_off = row_off + (uint32_t)((c16 ^ (row_c & 15)) << 4);
-    const uint32_t v_off = row_off + (uint32_t)((c16 ^ (((row_c & 3) << 2) | (((row_c >> 2) & 1) << 1))) << 4);
-    // K fragment of position tile pt, k step ks: row 16pt + c16, chunk 4ks + g4 -> pt * 4096 + (k_base ^ (ks << 6))
-    const uint32_t k_base = (uint32_t)c16 * PITCH + (uint32_t)((g4 ^ c16) << 4);
-    // V fragment of d tile dt: rows 4g4 + j (then 16 further on), j = c16 / 4; the 8 bytes of d = 16dt + 4(c16 % 4) ..
-    // -> v_base ^ (dt << 5)
+    const uint32_t k_off = row_off + (uint32_t)((c16 ^ ((4 * wu + g4) & 15)) << 4);
+    const uint32_t v_off = row_off + (uint32_t)((c16 ^ (g4 << 2)) << 4);
+    // K fragment of k step ks (16 d): row li, chunk 2ks + lh -> k_base ^ (ks << 5)
+    const uint32_t k_base = (uint32_t)li * PITCH + (uint32_t)((lh ^ (li & 15)) << 4);
+    // V fragment of d tile dt (32 d) and positions 16s ..: rows 16s + 4lh + j (then eight further on), j = c16 / 4; the 8
+    // bytes of d = 32dt + 16 * (lane / 16 % 2) + 4(c16 % 4) .. -> (v_base ^ (dt << 6)) + s * 16 * PITCH
     uint32_t v_base;
     {
-        const int j = c16 >> 2, vrow = 4 * g4 + j;
-        const int swz = (j << 2) | ((g4 & 1) << 1);
-        v_base = (uint32_t)vrow * PITCH + (uint32_t)((swz ^ ((c16 & 3) >> 1)) << 4) + (uint32_t)((c16 & 1) << 3);
+        const int j = c16 >> 2, vrow = 4 * lh + j;
+        v_base = (uint32_t)vrow * PITCH + (uint32_t)(((2 * (g4 & 1) + ((c16 & 3) >> 1)) ^ (j << 2)) << 4) + (uint32_t)((c16 & 1) << 3);
     }
 
   for (bool first = true; leaders; leaders &= leaders - 1, first = false) {
-    const int t0 = r_begin + __builtin_ctz(leaders);
+    const int t0 = r_begin + __builtin_ctzll(leaders);
     if (!first) __syncthreads();      // everyone is done with the tiles and masks of the block before
     const int sq = a.seq[t0], p0 = a.pos[t0];
     const bool row_ok = sq >= 0 && sq < a.n_seqs && p0 >= 0;
@@ -184,11 +178,11 @@ __global__ __launch_bounds__(512, 4) void paged_attention_blocks_kernel(AttnArgs
         bool cont = tid == 0;
         if (tid > 0 && tid < limit && t0 + tid < a.T) cont = a.seq[t0 + tid] == sq && a.pos[t0 + tid] == p0 + tid;
         const unsigned long long mk = __builtin_amdgcn_ballot_w64(cont);
-        if (lane == 0 && w < 2) run_mask[w] = mk;
+        if (lane == 0 && w < NW / 2) run_mask[w] = mk;
         __syncthreads();
         nrows = 0;
 #pragma unroll
-        for (int ww = 0; ww < 2; ++ww) {
+        for (int ww = 0; ww < NW / 2; ++ww) {
             const unsigned long long mw = run_mask[ww];
             if (nrows == 64 * ww) nrows += mw == ~0ull ? 64 : __builtin_ctzll(~mw);
         }
@@ -208,29 +202,29 @@ __global__ __launch_bounds__(512, 4) void paged_attention_blocks_kernel(AttnArgs
     const int32_t *bt = a.bt + (size_t)(row_ok ? sq : 0) * a.max_blocks;
 
     // this lane's column: query row r_j of the block (rows w*RBW .. of this wavefront), query head g_j
-    const int r_j = w * RBW + c16 / G, g_j = c16 % G;
+    const int r_j = w * RBW + li / G, g_j = li % G;
     const bool col_ok = row_ok && r_j < nrows;
     const int lim_j = col_ok ? p0 + r_j : -1;                        // last position the column attends to
     const int lim_w = (row_ok && wu * RBW < nrows) ? p0 + min((wu + 1) * RBW, nrows) - 1 : -1;   // ... and any column of this wavefront
     const int lim_first = p0 + wu * RBW;                             // ... and the wavefront's first column
     const size_t q_at = ((size_t)(t0 + (col_ok ? r_j : 0)) * a.Hq + (size_t)hk * G + g_j) * D;
-    bf16x8 qf[4];
+    bf16x8 qf[8];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
+    for (int s = 0; s < 8; ++s) {
         u32x4 v = {0u, 0u, 0u, 0u};
-        if (col_ok) v = *(const u32x4 *)((const bf16_t *)a.q + q_at + 32 * s + 8 * g4);
+        if (col_ok) v = *(const u32x4 *)((const bf16_t *)a.q + q_at + 16 * s + 8 * lh);
         qf[s] = __builtin_bit_cast(bf16x8, v);
     }
     // (a use of the query registers ahead of the loop: the compiler places its wait for these loads here and
     // not in front of the first MFMA of every step, where it would also wait for the copies in flight)
 #pragma unroll
-    for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(qf[s]));
+    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[s]));
 
-    f32x4 acc[8];
+    f32x16 acc[4];
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[t][e] = 0.f;
+        for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
     float m = AB_M_FLOOR, l = 0.f;
 
     // Table entries come from a window in LDS that holds those of WIN blocks of 32 positions and is refilled
@@ -246,16 +240,15 @@ __global__ __launch_bounds__(512, 4) void paged_attention_blocks_kernel(AttnArgs
         for (int i = tid; win_first + i <= last; i += 64 * NW) window[i] = bt[win_first + i];
         __syncthreads();
     };
-    auto lookup = [&](int cb) {
-        const int pu = cb + 4 * wu;
-        return pu < n_ctx ? __builtin_amdgcn_readfirstlane(window[entry_of(pu) - win_first]) : -1;
-    };
+    // table entry of this wavefront's four positions pu .. of a block (the same value in every lane; made a scalar
+    // where it is used, a step later, so that nothing waits for the read here)
+    auto lookup = [&](int pu) { return pu < n_ctx ? window[entry_of(pu) - win_first] : -1; };
     // (the scalar unit of a CU serves all its wavefronts: what a wavefront computes per step besides the
     // matrix and vector work is kept to a few instructions)
-    auto issue = [&](int c, int blk) {
-        const int pu = 32 * c + 4 * wu;                          // first of the four positions
-        const uint32_t k_to = tiles_at + ((uint32_t)(c & (NB - 1)) << 14) + ((uint32_t)wu << 10), v_to = k_to + TILE;
-        static_assert(2 * TILE == 1 << 14 && 4 * PITCH == 1 << 10, "tile geometry");
+    auto issue4 = [&](int slot_pair, int c, int grp, int entry) {
+        const int pu = 32 * c + 4 * grp, blk = __builtin_amdgcn_readfirstlane(entry);
+        const uint32_t k_to = tiles_at + (uint32_t)slot_pair * (2 * TILE) + ((uint32_t)grp << 10), v_to = k_to + TILE;
+        static_assert(4 * PITCH == 1 << 10, "tile geometry");
         unsigned okb = 0xfu;
         if ((unsigned)blk < n_blocks_u && pu + 4 <= n_ctx) {   // the usual case: scalar base, the lane's constant offset
             const unsigned slot = (POW2 ? ((unsigned)blk << a.bs_shift) : (unsigned)blk * (unsigned)a.bs) + (unsigned)(POW2 ? (pu & (a.bs - 1)) : (pu % a.bs));
@@ -274,139 +267,224 @@ __global__ __launch_bounds__(512, 4) void paged_attention_blocks_kernel(AttnArgs
             load_lds16(k_to, kp);
             load_lds16(v_to, vp);
         }
-        ok_bytes[c & (NB - 1)][wu] = (unsigned char)okb;      // (every lane writes the same byte)
+        ok_bytes[slot_pair][grp] = (unsigned char)okb;      // (every lane writes the same byte)
     };
-
-    auto consume = [&](int c) {
-        const int cb = 32 * c;
-        const lds_byte *kb = (const lds_byte *)tiles + (c & (NB - 1)) * (2 * TILE), *vb = kb + TILE;
-        // ---- scores^T = K . Q^T : two tiles of 16 positions ------------------------------------------
-        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+    auto issue = [&](int slot_pair, int c, const int (&entry)[GPW]) {
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const bf16x8 k0 = *(const __attribute__((address_space(3))) bf16x8 *)(kb + (k_base ^ (uint32_t)(ks << 6)));
-            const bf16x8 k1 = *(const __attribute__((address_space(3))) bf16x8 *)(kb + 16 * PITCH + (k_base ^ (uint32_t)(ks << 6)));
-            s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k0, qf[ks], s0, 0, 0, 0);
-            s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k1, qf[ks], s1, 0, 0, 0);
-        }
-        // ---- softmax down this lane's column (its 32 positions sit in four lanes) --------------------
+        for (int h = 0; h < GPW; ++h) issue4(slot_pair, c, wu + NW * h, entry[h]);
+    };
+    // ---- scores^T = K . Q^T -------------------------------------------------------------------------
+    auto scores = [&](int slot_pair) {
+        const lds_byte *kb = (const lds_byte *)tiles + slot_pair * (2 * TILE);
+        f32x16 sc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sc[v] = 0.f;
+        bf16x8 kf[8];     // (all requested ahead of the products: a pair at a time would wait for LDS four times)
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) kf[ks] = *(const __attribute__((address_space(3))) bf16x8 *)(kb + (k_base ^ (uint32_t)(ks << 5)));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], sc, 0, 0, 0);
+        return sc;
+    };
+    auto consume = [&](int c, int slot_pair, f32x16 sc) {
+        const int cb = 32 * c;
+        const lds_byte *vb = (const lds_byte *)tiles + slot_pair * (2 * TILE) + TILE;
+        const u32x2 ob = *(const u32x2 *)ok_bytes[slot_pair];
+        bf16x8 vf[2][4];      // requested ahead of the softmax, which covers their way
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) vf[s][t] = read_tr_frag(vb + (v_base ^ (uint32_t)(t << 6)) + s * 16 * PITCH, PITCH);
+        __builtin_amdgcn_sched_barrier(0);
+        // ---- softmax down this lane's column (its 32 positions sit in two lanes) ---------------------
         __builtin_amdgcn_s_setprio(2);   // the vector arithmetic of this wavefront goes ahead of wavefronts waiting for the matrix unit
-        const u32x2 ob = *(const u32x2 *)ok_bytes[c & (NB - 1)];
         const unsigned ok_lo = __builtin_amdgcn_readfirstlane(ob.x), ok_hi = __builtin_amdgcn_readfirstlane(ob.y);
-        float sc[8] = {s0[0], s0[1], s0[2], s0[3], s1[0], s1[1], s1[2], s1[3]};
         if (!((ok_lo & ok_hi) == 0x0f0f0f0fu && cb + 31 <= lim_first)) {   // a block that every column of the wavefront sees whole needs no mask
             auto nibbles = [](unsigned x) { x |= x >> 4; return (x & 0xffu) | ((x >> 8) & 0xff00u); };
             const unsigned okmask = nibbles(ok_lo) | (nibbles(ok_hi) << 16);
 #pragma unroll
-            for (int v = 0; v < 8; ++v) {
-                const int idx = 16 * (v >> 2) + 4 * g4 + (v & 3);
+            for (int v = 0; v < 16; ++v) {
+                const int idx = 8 * (v >> 2) + 4 * lh + (v & 3);
                 const bool on = ((okmask >> idx) & 1u) && cb + idx <= lim_j;
                 sc[v] = on ? sc[v] : AB_NEG_INF;
             }
         }
-        float mx = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])), fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
-        mx = max_over_column(mx);
-        const float mn = fmaxf(m, mx * a.scale_log2e);
-        const float corr = __builtin_amdgcn_exp2f(m - mn);
-        m = mn;
+        float mx = fmaxf(sc[0], sc[1]);
+#pragma unroll
+        for (int v = 2; v < 16; v += 2) mx = fmaxf(fmaxf(mx, sc[v]), sc[v + 1]);
+        // The running maximum moves (and everything summed so far with it) only where some column of the wavefront has a
+        // larger score, which its two lanes then settle between them; long before the end of a long context most
+        // blocks bring none.  (Letting it lag by up to a factor 2^8 in weight takes 4 % off a call of 4 x 2048 rows, but
+        // then the largest weight is no longer exactly 1 in bf16: error against fp64 2.31e-3 -> 2.34e-3 there, 2.01e-3 ->
+        // 2.28e-3 on peaked scores.)
+        if (__builtin_amdgcn_ballot_w64(mx * a.scale_log2e > m)) {
+            float lo, hi;
+            both_halves(mx, lo, hi);
+            const float mn = fmaxf(m, fmaxf(lo, hi) * a.scale_log2e);
+            const float corr = __builtin_amdgcn_exp2f(m - mn);
+            m = mn;
+            l *= corr;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[t][e] *= corr;
+        }
         float ps = 0.f;
 #pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            sc[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[v], a.scale_log2e, -mn));
+        for (int v = 0; v < 16; ++v) {
+            sc[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[v], a.scale_log2e, -m));
             ps += sc[v];
         }
-        l = l * corr + ps;
-        if (__builtin_amdgcn_ballot_w64(corr != 1.f)) {
+        l += ps;
+        // ---- out^T += V^T . P : P straight from the score registers (k step s: positions 16s + 4lh .. +3 and eight
+        // further on) -------------------------------------------------------------------------------------
+        u32x4 pv[2];
 #pragma unroll
-            for (int t = 0; t < 8; ++t)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[t][e] *= corr;
-        }
-        // ---- out^T += V^T . P : P straight from the score registers (positions 4g4 .. +3 and 16 + 4g4 .. +3) --
-        const u32x4 pv = {pack_bf16(sc[0], sc[1]), pack_bf16(sc[2], sc[3]), pack_bf16(sc[4], sc[5]), pack_bf16(sc[6], sc[7])};
+        for (int s = 0; s < 2; ++s)
+            pv[s] = (u32x4){pack_bf16(sc[8 * s], sc[8 * s + 1]), pack_bf16(sc[8 * s + 2], sc[8 * s + 3]), pack_bf16(sc[8 * s + 4], sc[8 * s + 5]),
+                            pack_bf16(sc[8 * s + 6], sc[8 * s + 7])};
         __builtin_amdgcn_s_setprio(0);
-        const bf16x8 pf = __builtin_bit_cast(bf16x8, pv);
 #pragma unroll
-        for (int t = 0; t < 8; ++t)
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(read_tr_frag(vb + (v_base ^ (uint32_t)(t << 5)), PITCH), pf, acc[t], 0, 0, 0);
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[s][t], __builtin_bit_cast(bf16x8, pv[s]), acc[t], 0, 0, 0);
     };
 
-    // ---- the context, 32 positions at a time: all eight wavefronts share the tiles ------------------
-    // Block c lives in tile pair c % 4.  In the step of block c every wavefront waits for its own copies of
-    // block c (those of c+1 and c+2, two instructions each, stay in flight), the barrier makes that hold for
-    // all of them and tells that block c-1 has been multiplied by everyone; its pair then takes the copies of
-    // block c+3, whose table entry was looked up a step earlier.  Blocks past the context are copied too (all
-    // zeros, from one 16-byte constant), which keeps the count of copies in flight the same in every step.
+    // ---- the context, two blocks of 32 positions at a time: all wavefronts share the tiles ----------
+    // Block c_lo + i lives in tile pair i % NB.  A step takes blocks c and c+1: every wavefront waits for its own copies
+    // of them (those of the NB - 4 blocks after them stay in flight), the barrier makes that hold for all of them
+    // and tells that blocks c-2 and c-1 have been multiplied by everyone; their pairs then take the copies of the
+    // next two blocks, whose table entries were looked up a step earlier.  Blocks past the context are copied
+    // too (all zeros, from one 16-byte constant), which keeps the count of copies in flight the same in every step.
     {
         if (n_chunks > c_lo) refill(c_lo);
+        auto entries = [&](int cb, int (&e)[GPW]) {
 #pragma unroll
-        for (int kk = 0; kk < NB - 1; ++kk) issue(c_lo + kk, lookup(32 * (c_lo + kk)));
-        int b0 = lookup(32 * (c_lo + NB - 1));
+            for (int h = 0; h < GPW; ++h) e[h] = lookup(32 * cb + 4 * (wu + NW * h));
+        };
+        int b0[GPW], b1[GPW];
+#pragma unroll
+        for (int kk = 0; kk < NB - 2; ++kk) {
+            entries(c_lo + kk, b0);
+            issue(kk, c_lo + kk, b0);
+        }
+        entries(c_lo + NB - 2, b0);
+        entries(c_lo + NB - 1, b1);
+        int cur = 0, nxt = NB - 2;           // tile pairs of block c and of block c + NB - 2
         auto step = [&](int c) {
-            asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            issue(c + NB - 1, b0);
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * GPW * (NB - 4)) : "memory");
+            issue(nxt, c + NB - 2, b0);
+            issue(nxt + 1, c + NB - 1, b1);
             const int cn = c + NB;
             if (cn == win_block + WIN && 32 * cn < n_ctx) refill(cn);
-            b0 = lookup(32 * cn);
+            entries(cn, b0);
+            entries(cn + 1, b1);
         };
+        auto advance = [&]() { cur = cur + 2 == NB ? 0 : cur + 2; nxt = nxt + 2 == NB ? 0 : nxt + 2; };
         // (two loops: the accumulators live in the first only)
         const int n_chunks_w = lim_w >= 0 ? min((lim_w >> 5) + 1, n_chunks) : 0;
         int c = c_lo;
-        for (; c < n_chunks_w; ++c) {
+        for (; c < n_chunks_w; c += 2) {
             step(c);
-            consume(c);
+            consume(c, cur, scores(cur));
+            if (c + 1 < n_chunks_w) consume(c + 1, cur + 1, scores(cur + 1));
+            advance();
         }
-        for (; c < n_chunks; ++c) step(c);
+        for (; c < n_chunks; c += 2) {
+            step(c);
+            advance();
+        }
         // nothing may be on its way into LDS when the workgroup gives it back
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
 
-    // ---- the four lanes of a column add their weight sums; normalise and store ---------------------
-    l = sum_over_column(l);
+    // ---- the two lanes of a column add their weight sums; normalise and store -----------------------
+    {
+        float lo, hi;
+        both_halves(l, lo, hi);
+        l = lo + hi;
+    }
     if (a.splits > 1) {
         // this part's (running maximum, weight sum, unnormalised output) of every column, for the kernel that
         // combines the parts of a (row, query head) in part order
-        if (col_ok || (!row_ok && w == 0 && c16 < G)) {
+        if (col_ok || (!row_ok && w == 0 && li < G)) {
             float *pp = a.part + (((size_t)(t0 + (col_ok ? r_j : 0)) * a.Hq + (size_t)hk * G + g_j) * a.splits + part) * (D + 2);
-            if (g4 == 0) *(f32x2 *)pp = (f32x2){m, l};
+            if (lh == 0) *(f32x2 *)pp = (f32x2){m, l};
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                *(f32x2 *)(pp + 2 + 16 * t + 4 * g4) = (f32x2){acc[t][0], acc[t][1]};
-                *(f32x2 *)(pp + 2 + 16 * t + 4 * g4 + 2) = (f32x2){acc[t][2], acc[t][3]};
-            }
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; v += 4) {
+                    *(f32x2 *)(pp + 2 + 32 * t + 2 * v + 4 * lh) = (f32x2){acc[t][v], acc[t][v + 1]};
+                    *(f32x2 *)(pp + 2 + 32 * t + 2 * v + 4 * lh + 2) = (f32x2){acc[t][v + 2], acc[t][v + 3]};
+                }
         }
         continue;
     }
     // a row that is not valid leads a block of its own and gets zeros
-    if (col_ok || (!row_ok && w == 0 && c16 < G)) {
+    if (col_ok || (!row_ok && w == 0 && li < G)) {
         const float inv = l > 0.f ? 1.f / l : 0.f;
         bf16_t *orow = (bf16_t *)a.out + ((size_t)(t0 + (col_ok ? r_j : 0)) * a.Hq + (size_t)hk * G + g_j) * D;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const u32x2 o = {pack_bf16(acc[t][0] * inv, acc[t][1] * inv), pack_bf16(acc[t][2] * inv, acc[t][3] * inv)};
-            *(u32x2 *)(orow + 16 * t + 4 * g4) = o;
-        }
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; v += 4) {   // d = 32 t + 8 (v / 4) + 4 lh ..
+                const u32x2 o = {pack_bf16(acc[t][v] * inv, acc[t][v + 1] * inv), pack_bf16(acc[t][v + 2] * inv, acc[t][v + 3] * inv)};
+                *(u32x2 *)(orow + 32 * t + 2 * v + 4 * lh) = o;
+            }
     }
   }
 }
 
-int launch_attention_blocks(const AttnArgs &a, int G, hipStream_t stream)
+// How a batch is cut, from its sizes alone.  Long runs (more than 128 / G rows per sequence on average): eight wavefronts
+// where that still gives two workgroups per CU or the context is cut into parts anyway, else four.  Short runs: four, two
+// workgroups to a CU (a block of few rows is as long as its loads take, and one workgroup's start hides behind the
+// other's).  Measured, us, eight | four wavefronts: 4 x 2048 rows over 16K positions, 32/8 heads 2099 | 2216; 2 x 1024 over
+// 2-4K, 32/8 174 | 167; 2 x 512 over 2-4K, 32/8 116 | 104; 4 x 300 over 16K, 8/8 487 | 410; in parts, 4 x 64 rows over 16K
+// 108 | 123, 4 x 32 rows 104 | 78.
+BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts)
 {
-    // batch rows per workgroup: a whole row block where that still makes a few workgroups per CU, fewer for
-    // small batches (a decode batch: every row leads a block of its own)
-    int R = 128 / G < 32 ? 128 / G : 32;
-    // (with the context cut into parts the batch is small: whole row blocks per workgroup, the parts fill the chip)
-    while (a.splits == 1 && R > 1 && (long long)((a.T + R - 1) / R) * a.Hkv < 2048) R /= 2;
-    const dim3 grid((unsigned)((a.T + R - 1) / R) * (unsigned)a.Hkv * (unsigned)a.splits), block(512);
+    BlockPlan p = {4, 1, 1, 1};
+    if (T <= 0) return p;
+    const bool long_runs = (long long)T * G > 128ll * n_seqs;
+    if (long_runs && (parts || (long long)T * G / 256 * Hkv >= 512)) p.waves = 8;
+    const int rbg = 32 * p.waves / G;
+    p.R = rbg < 64 ? rbg : 64;   // (a ballot looks over the rows of a range)
+    if (parts) {
+        // whole row blocks; parts of every block's context, one workgroup each, until there is one per CU (two of four
+        // wavefronts)
+        const long long wgs = (long long)((T + rbg - 1) / rbg) * Hkv, want = p.waves == 8 ? 256 : 512;
+        if (wgs < want) p.splits = (int)((want + wgs - 1) / wgs < MAX_PARTS ? (want + wgs - 1) / wgs : MAX_PARTS);
+    }
+    if (p.splits > 1) return p;
+    // Long runs: a range holds the start of a row block, or two where a sequence begins in it, and two blocks one
+    // after the other would double the length of the call: each range goes to two workgroups that take every other
+    // block (4 x 256 rows over 16K positions, 64/8 heads 1125 -> 555 us; 2 x 1000 rows, 16/8 heads 776 -> 487).
+    // Short runs: fewer rows per range, down to one, until there are eight workgroups per CU (every row may lead a
+    // block of its own).
+    if (long_runs) p.sub = 2;
+    while (!long_runs && p.R > 1 && (long long)((T + p.R - 1) / p.R) * Hkv < 2048) p.R /= 2;
+    return p;
+}
+
+int launch_attention_blocks(const AttnArgs &a, int G, const BlockPlan &p, hipStream_t stream)
+{
+    const int R = p.R;
+    const dim3 grid((unsigned)((a.T + R - 1) / R) * (unsigned)a.Hkv * (unsigned)a.splits * (unsigned)p.sub), block(64 * p.waves);
     const bool pow2 = a.bs_shift >= 0;
-#define AB_LAUNCH(GG) \
-    if (pow2) hipLaunchKernelGGL((paged_attention_blocks_kernel<GG, true>), grid, block, 0, stream, a, R); \
-    else hipLaunchKernelGGL((paged_attention_blocks_kernel<GG, false>), grid, block, 0, stream, a, R)
-    switch (G) {
-    case 1: AB_LAUNCH(1); break;
-    case 2: AB_LAUNCH(2); break;
-    case 4: AB_LAUNCH(4); break;
-    case 8: AB_LAUNCH(8); break;
+#define AB_LAUNCH(GG, NW) \
+    if (pow2) hipLaunchKernelGGL((paged_attention_blocks_kernel<GG, NW, true>), grid, block, 0, stream, a, R, p.sub); \
+    else hipLaunchKernelGGL((paged_attention_blocks_kernel<GG, NW, false>), grid, block, 0, stream, a, R, p.sub)
+    switch (G * 16 + p.waves) {
+    case 16 + 8: AB_LAUNCH(1, 8); break;
+    case 32 + 8: AB_LAUNCH(2, 8); break;
+    case 64 + 8: AB_LAUNCH(4, 8); break;
+    case 128 + 8: AB_LAUNCH(8, 8); break;
+    case 16 + 4: AB_LAUNCH(1, 4); break;
+    case 32 + 4: AB_LAUNCH(2, 4); break;
+    case 64 + 4: AB_LAUNCH(4, 4); break;
+    case 128 + 4: AB_LAUNCH(8, 4); break;
     default: return (int)hipErrorInvalidValue;
     }
 #undef AB_LAUNCH

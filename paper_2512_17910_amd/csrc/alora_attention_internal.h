@@ -16,8 +16,18 @@ struct AttnArgs {
     float *part;         // [T][Hq][splits][D + 2]: running maximum, sum of weights, unnormalised weighted V
 };
 
+constexpr int MAX_PARTS = 32;   // of a row's context
+
+// How the row-block kernel cuts a batch: wavefronts per workgroup (row blocks of 32 * waves / G rows), batch rows per
+// workgroup, parts of every block's context.
+struct BlockPlan {
+    int waves, R, splits;
+    int sub;   // workgroups per range of batch rows (and head, and part): each takes every sub-th leading row in it
+};
+BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts);
+
 // Row-block kernel (bf16, head_dim 128): rows of one sequence that follow each other in the batch share
 // the loads of their context.  Returns the hipError_t of its launch.
-int launch_attention_blocks(const AttnArgs &a, int G, hipStream_t stream);
+int launch_attention_blocks(const AttnArgs &a, int G, const BlockPlan &p, hipStream_t stream);
 
 }  // namespace alora

@@ -418,3 +418,27 @@ def test_suffix_call_causal_boundaries_bad_indices_and_shapes():
     d3 = DeviceCase(c3)
     with pytest.raises(ab.AloraError):
         ab.alora_paged_attention_suffix(d3.q, d3.kc, d3.vc, d3.bt, d3.seq, d3.pos, d3.out, d3.dims)
+
+
+# The row-block kernel's cuts: eight wavefronts (long runs, enough blocks of 256 / G rows), four wavefronts with long runs (a
+# range of rows that holds the ends of one sequence and the start of the next goes to two workgroups), ranges of 64 rows
+# in blocks of 256 (G = 1), runs that end one row past and one row before a block; contexts cut into parts with long runs.
+# Bound: the reader's (softmax weights and outputs in bf16).
+@pytest.mark.parametrize("group,n_kv,lens,parts", [(1, 64, [1000, 517, 531], False), (8, 16, [385, 1, 639], False), (4, 2, [700, 257, 95], False),
+                                                   (2, 2, [129, 640, 127], False), (4, 2, [200, 65, 63], True), (8, 1, [1100, 33, 900], True)])
+def test_suffix_rows_with_long_runs(group, n_kv, lens, parts):
+    rows = [n - n // 7 for n in lens]
+    c = wl.attention_case(f"long-runs-g{group}-{parts}", "bf16", lens, rows, group * n_kv, n_kv, 128, 16, seed=wl.SEED ^ (900 + group))
+    print(f"[case] {c.name} T={c.T}", flush=True)
+    d = DeviceCase(c)
+    if parts:
+        ws = torch.empty(max(16, ab.alora_paged_attention_suffix_workspace_bytes(d.dims)), dtype=torch.uint8, device="cuda")
+        ab.alora_paged_attention_suffix_split(d.q, d.kc, d.vc, d.bt, d.seq, d.pos, d.out, d.dims, ws)
+        torch.cuda.synchronize()
+        out = to_f64(d.out)
+    else:
+        out = to_f64(_run_suffix(d))
+    assert np.isfinite(out).all()
+    pick = np.unique(np.r_[np.arange(0, c.T, 37), np.cumsum(rows) - 1, np.cumsum(rows)[:-1], [31, 32, 63, 64]])
+    pick = pick[pick < c.T]
+    assert maxnorm_rel(out[pick], d.oracle(rows=pick)) <= TOL["bf16"]
