@@ -16,7 +16,7 @@
 //   - x arrives in whole 128-byte lines, eight lanes to a token's piece, and is turned into operands through LDS that
 //     a wavefront shares with no other.  (Loaded as the operand wants it, neighbouring lanes would read different
 //     rows: 16 bytes per clock and compute unit, measured, against 43 for the line pattern.)
-// Token tiles of 16, 32 or 64 rows: no matrix work is spent on rows a small batch does not have.
+// Token tiles of 16, 32, 48 or 64 rows: no matrix work is spent on rows a small batch does not have.
 // Measured, 4096 -> 6144 with 50 MB of W from memory: 16.0 us for the 256-row tile of the projection kernel at one
 // row, 11.5 us here (4.4 TB/s over the whole kernel; non-temporal loads of W included, 78.7 -> 71.0 us for four
 // layers); 8192 -> 10240, four layers at eight rows, 235 -> 160 us.  From 65 rows on W would be read once per token
@@ -120,37 +120,38 @@ __device__ __forceinline__ void decode_products(const bf16_t *x, uint32_t x_byte
     }
 }
 
-// The wavefronts' sums of one 16-token tile meet in LDS; thread -> four consecutive columns of two tokens.
-// Calls out(token, column, value) for every element of the tile, twice per thread and call of a tile.
+// The wavefronts' sums meet in LDS, all token tiles at once (one after the other, with two barriers each: 90.0 against
+// 88.3 us for four layers at 37 rows), and are added in fixed order; thread -> four consecutive columns of a token.
+// Calls out(token, column, value) for every four elements of the tile.
 template <int NTT, typename Out>
 __device__ __forceinline__ void decode_reduce(float *red, const f32x4 (&acc)[NTT][8], Out out)
 {
+    constexpr int ROWS = 16 * NTT;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, g4 = lane >> 4;
 #pragma unroll
     for (int nt = 0; nt < NTT; ++nt) {
-        if (nt) __syncthreads();
-        float *mine = red + (w * 16 + c) * DEC_PITCH + 32 * g4;
+        float *mine = red + (w * ROWS + 16 * nt + c) * DEC_PITCH + 32 * g4;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             *(f32x4 *)(mine + 8 * i) = (f32x4){acc[nt][0][i], acc[nt][1][i], acc[nt][2][i], acc[nt][3][i]};
             *(f32x4 *)(mine + 8 * i + 4) = (f32x4){acc[nt][4][i], acc[nt][5][i], acc[nt][6][i], acc[nt][7][i]};
         }
-        __syncthreads();
+    }
+    __syncthreads();
 #pragma unroll
-        for (int h = 0; h < 16 * DEC_FEATURES / 4 / DEC_THREADS; ++h) {
-            const int idx = h * DEC_THREADS + tid, tok = idx / (DEC_FEATURES / 4), cc = (idx % (DEC_FEATURES / 4)) * 4;
-            f32x4 s = *(const f32x4 *)(red + tok * DEC_PITCH + cc);
+    for (int h = 0; h < ROWS * DEC_FEATURES / 4 / DEC_THREADS; ++h) {
+        const int idx = h * DEC_THREADS + tid, tok = idx / (DEC_FEATURES / 4), cc = (idx % (DEC_FEATURES / 4)) * 4;
+        f32x4 s = *(const f32x4 *)(red + tok * DEC_PITCH + cc);
 #pragma unroll
-            for (int ww = 1; ww < DEC_WAVES; ++ww) s += *(const f32x4 *)(red + (ww * 16 + tok) * DEC_PITCH + cc);
-            out(nt * 16 + tok, cc, s);
-        }
+        for (int ww = 1; ww < DEC_WAVES; ++ww) s += *(const f32x4 *)(red + (ww * ROWS + tok) * DEC_PITCH + cc);
+        out(tok, cc, s);
     }
 }
 
 template <int NTT, int DEPTH>
-__global__ __launch_bounds__(DEC_THREADS, NTT == 4 ? 1 : 2) void decode_projection_kernel(DecodeArgs g, PtrTable A)
+__global__ __launch_bounds__(DEC_THREADS, NTT > 2 ? 1 : 2) void decode_projection_kernel(DecodeArgs g, PtrTable A)
 {
-    constexpr int RED_BYTES = DEC_WAVES * 16 * DEC_PITCH * 4, XS_TILES = NTT < 2 ? 2 : NTT, XS_BYTES = XS_TILES * 2048;   // (the shrink takes two tiles)
+    constexpr int XS_TILES = NTT < 2 ? 2 : NTT, RED_BYTES = DEC_WAVES * 16 * XS_TILES * DEC_PITCH * 4, XS_BYTES = XS_TILES * 2048;   // (the shrink takes two tiles)
     __shared__ __attribute__((aligned(16))) unsigned char lds[RED_BYTES > DEC_WAVES * XS_BYTES ? RED_BYTES : DEC_WAVES * XS_BYTES];
     __shared__ int scr[GROUP_SMALL_SCRATCH];
     float *const red = (float *)lds;
@@ -233,6 +234,7 @@ int launch_decode_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEv
     const dim3 grid((g.ntiles * g.splits + 7) / 8 * 8 + g.prep_wgs), block(DEC_THREADS);
     if (f.T <= 16) hipLaunchKernelGGL((decode_projection_kernel<1, 2>), grid, block, 0, f.stream, g, A);
     else if (f.T <= 32) hipLaunchKernelGGL((decode_projection_kernel<2, 2>), grid, block, 0, f.stream, g, A);
+    else if (f.T <= 48) hipLaunchKernelGGL((decode_projection_kernel<3, 2>), grid, block, 0, f.stream, g, A);
     else hipLaunchKernelGGL((decode_projection_kernel<4, 2>), grid, block, 0, f.stream, g, A);
     int e = (int)hipGetLastError();
     if (!e && after_projection) e = (int)hipEventRecord(after_projection, f.stream);

@@ -465,11 +465,11 @@ def test_fp32_tiles_and_batch_sizes(kw):
     _check_full(wl.small_mixed("f32", seed=21, **kw))
 
 
-# Batches of at most 64 rows have a projection kernel of their own: each token tile (16, 32, 64 rows) less than, just and
+# Batches of at most 64 rows have a projection kernel of their own: each token tile (16, 32, 48, 64 rows) less than, just and
 # one more than full, the first batch past it; fewer 64-wide slices than wavefronts, slices that do not divide among
 # wavefronts and splits; a feature tile that ends inside the 128, ranks from 8 to 64 columns of the shrink's tile.
 # Bounds: those of every bf16 case in _check_full.
-@pytest.mark.parametrize("rows", [1, 15, 16, 17, 32, 33, 64, 65])
+@pytest.mark.parametrize("rows", [1, 15, 16, 17, 32, 33, 48, 49, 64, 65])
 @pytest.mark.parametrize("kw", [dict(hidden=64, rank=8), dict(hidden=448, rank=64, n_q_heads=5, n_kv_heads=2, head_dim=40),
                                 dict(hidden=1088, rank=24, n_adapters=5, n_q_heads=3, n_kv_heads=1, head_dim=128)], ids=["1slice", "7", "17"])
 def test_few_rows(rows, kw):
