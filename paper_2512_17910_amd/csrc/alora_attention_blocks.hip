@@ -457,7 +457,12 @@ BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts)
         const long long wgs = (long long)((T + rbg - 1) / rbg) * Hkv, want = p.waves == 8 ? 256 : 512;
         if (wgs < want) p.splits = (int)((want + wgs - 1) / wgs < MAX_PARTS ? (want + wgs - 1) / wgs : MAX_PARTS);
     }
-    if (p.splits > 1) return p;
+    if (p.splits > 1) {
+        // ranges no longer than a sequence's rows on average, so that few hold the starts of several blocks (six
+        // sequences of 50 rows, 8/8 heads: ranges of 64 rows 161 us, of 32 137; six single rows: 106 -> 87)
+        while (p.R > 1 && (long long)p.R * n_seqs > T && (long long)((T + p.R / 2 - 1) / (p.R / 2)) * Hkv * p.splits <= 4096) p.R /= 2;
+        return p;
+    }
     // Long runs: a range holds the start of a row block, or two where a sequence begins in it, and two blocks one
     // after the other would double the length of the call: each range goes to two workgroups that take every other
     // block (4 x 256 rows over 16K positions, 64/8 heads 1125 -> 555 us; 2 x 1000 rows, 16/8 heads 776 -> 487).
