@@ -13,7 +13,7 @@
 //   4. round once to bf16 and store: columns [0,Nq) to q_out, K and V columns to the slot the
 //      row maps to (rows with slot -1 write no K/V)
 // Small-batch (split) mode stops after 3 over its range of the hidden dimension and stores fp32
-// partials; for batches of at most 256 rows extra workgroups behind the projection's own classify,
+// partials; for batches of 65 to 256 rows extra workgroups behind the projection's own classify,
 // group and shrink the batch (alora_group_small.h, alora_shrink_rows.h) out of the same LDS stages.
 //
 // Data movement (gfx950):
@@ -903,7 +903,8 @@ static void launch_ntw(const GemmArgs &g, const PtrTable &B, const PtrTable &A, 
         hipLaunchKernelGGL((alora_gemm_bf16_kernel<NTW, false>), dim3(g.tiles8), block, 0, stream, g, B, A);
 }
 
-// Decode-sized bf16 batches: classification, grouping and shrink run inside the split projection kernel,
+// Decode-sized bf16 batches: classification, grouping and shrink run inside the projection kernel (up to 64 rows
+// that of alora_decode_bf16.hip; above, the split kernel here),
 // on workgroups behind its own (the projection of such a batch does not fill every compute unit).
 bool prep_in_projection(const Fwd &f)
 {
