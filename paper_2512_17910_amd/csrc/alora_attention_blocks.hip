@@ -30,9 +30,9 @@
 //
 // Measured, 4 x 2048 rows over 16K positions, 32/8 heads (2.06 TFLOP): 16 columns per wavefront on 16x16x32 MFMAs 2640 us
 // (each byte read from LDS fed 16 columns, every block exchanged its maximum between four lanes); 32 columns, four
-// wavefronts 2310; eight wavefronts (half the copies per score: without any copies the kernel took 1830) and two blocks per
+// wavefronts, with a maximum that lags (see the softmax), 2270, of it 440 for the copies; eight (half the copies per score), two blocks per
 // barrier 2220 us = 0.93 PFLOP/s, where a large bf16 matrix product reaches 1.2 on the same card.  What is left: matrix
-// unit 39 % and vector unit 39 % of the cycles, which add up more than they overlap, and the copies.  Running the
+// unit 38 % and vector unit 42 % of the cycles, which add up more than they overlap, and the copies.  Running the
 // scores of the next block and the output of the one before it between the vector instructions of the softmax
 // (three blocks in flight, one matrix product per four vector instructions) was built and measured: 2470 us.
 #include "alora_attention_internal.h"
