@@ -101,12 +101,12 @@ static void fill_common(Fwd &f, const alora_dims *d, const Layout &l, void *ws, 
     f.S = b + l.S;
     f.blocktab = (int4 *)(b + l.blocktab);
     f.hist = (int32_t *)(b + l.hist);
-    const int N_all = (d->n_q_heads + 2 * d->n_kv_heads) * d->head_dim;
-    const bool work_list = d->dtype == ALORA_BF16 && plan_shrink(d->T, d->hidden, N_all, d->n_adapters, d->rank).combine;
+    f.block_rows = (d->dtype == ALORA_BF16 && d->T <= 256) ? (int32_t *)(b + l.block_rows) : nullptr;
+    if (d->dtype == ALORA_BF16) plan_call(f);
+    const bool work_list = d->dtype == ALORA_BF16 && f.route.shrink.combine;
     f.items = work_list ? (int4 *)(b + l.items) : nullptr;
     f.counters = work_list ? (int32_t *)(b + l.counters) : nullptr;
     f.n_items = work_list ? l.n_items : 0;
-    f.block_rows = (d->dtype == ALORA_BF16 && d->T <= 256) ? (int32_t *)(b + l.block_rows) : nullptr;
     f.partial = (float *)(b + l.partial);
     f.n_blocks = l.n_blocks;
     f.stream = (hipStream_t)stream;
@@ -288,7 +288,7 @@ static int forward_on(const void *x, const int32_t *token_adapter_ids, const int
         if (!timed) prof_lock.unlock();
     }
     // decode-sized bf16 batches: grouping and shrink ride in the projection kernel (two launches in all)
-    const bool prep_inside = prep_in_projection(f);
+    const bool prep_inside = f.dtype == ALORA_BF16 && f.route.prep_inside;
     int e = (prep_inside || reuse_grouping || group_in_shrink_f32(f)) ? 0 : launch_classify_group(f);
     if (!e) {
         if (f.dtype == ALORA_F32) {

@@ -202,9 +202,9 @@ __global__ __launch_bounds__(DEC_THREADS, NTT > 2 ? 1 : 2) void decode_projectio
 }
 
 // ---- host side: how a call of given sizes is cut, from (T, hidden, N) alone (see plan_gemm) -------------------
-bool decode_call(const Fwd &f)
+bool few_rows_call(const Fwd &f)
 {
-    if (f.dtype != ALORA_BF16 || f.T <= 0 || f.T > DEC_ROWS || gemm_tuning_forced()) return false;
+    if (f.dtype != ALORA_BF16 || f.T <= 0 || f.T > DEC_ROWS) return false;
     // room for the partials; descriptors of x, W and A below 2 GiB (a masked lane's offset is past all of them)
     return gemm_partial_bytes(f.T, f.H, f.N) && (long long)f.T * f.H * 2 < (1ll << 31) && (long long)f.H * ALORA_MAX_RANK * 2 < (1ll << 31);
 }

@@ -846,11 +846,8 @@ static std::atomic<int> g_force_tuning{0};
 
 void set_gemm_tuning(int ntw, int splits) { g_force_tuning.store((ntw & 0xff) | (splits << 8), std::memory_order_relaxed); }
 
-bool gemm_tuning_forced() { return g_force_tuning.load(std::memory_order_relaxed) != 0; }
-
-GemmPlan plan_gemm(int T, int H, int N)
+static GemmPlan plan_gemm(int T, int H, int N, int forced)
 {
-    const int forced = g_force_tuning.load(std::memory_order_relaxed);
     const int g_force_ntw = forced & 0xff, g_force_splits = forced >> 8;
     constexpr int CUS = 256;                       // MI355X
     const int cand[3] = {4, 3, 2};
@@ -866,7 +863,7 @@ GemmPlan plan_gemm(int T, int H, int N)
         int max_splits = 1;
         if (tiles * 2 <= CUS) max_splits = (int)std::min<long>(std::min(8, KT), CUS / tiles);
         // A batch of one token tile leaves a quarter of the compute units to the workgroups that group and
-        // shrink it inside the projection kernel (see prep_in_projection): measured 40 us per step against
+        // shrink it inside the projection kernel (see plan_call): measured 40 us per step against
         // 48 us when the projection takes 240 of the 256 units (decode batch of 256 rows, 8B shapes).
         if (mtiles == 1 && max_splits > 1) max_splits = (int)std::max<long>(1, std::min<long>(max_splits, (CUS - CUS / 4) / tiles));
         for (int sp = 1; sp <= max_splits; ++sp) {
@@ -906,19 +903,29 @@ static void launch_ntw(const GemmArgs &g, const PtrTable &B, const PtrTable &A, 
 // Decode-sized bf16 batches: classification, grouping and shrink run inside the projection kernel (up to 64 rows
 // that of alora_decode_bf16.hip; above, the split kernel here),
 // on workgroups behind its own (the projection of such a batch does not fill every compute unit).
-bool prep_in_projection(const Fwd &f)
+static bool prep_in_projection(const Fwd &f, const Route &r)
 {
-    if (decode_call(f)) return true;
+    if (r.few_rows) return true;
     if (f.dtype != ALORA_BF16 || f.L <= 0 || f.T <= 0 || f.T > GROUP_SMALL_ROWS || f.r > 32 || !f.block_rows) return false;
-    const GemmPlan plan = plan_gemm(f.T, f.H, f.N);
-    return plan.splits > 1 && plan.ntw == 2;
+    return r.gemm.splits > 1 && r.gemm.ntw == 2;
+}
+
+void plan_call(Fwd &f)
+{
+    f.route = Route{{4, 1, f.H / KBLK}, {1, f.H, false}, false, false};
+    if (f.T <= 0) return;
+    const int forced = g_force_tuning.load(std::memory_order_relaxed);
+    f.route.gemm = plan_gemm(f.T, f.H, f.N, forced);
+    f.route.shrink = plan_shrink(f.route.gemm, f.T, f.H, f.L, f.r);
+    f.route.few_rows = !forced && few_rows_call(f);   // (the override names tilings of the projection kernel here)
+    f.route.prep_inside = prep_in_projection(f, f.route);
 }
 
 int launch_gemm_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEvent_t after_projection)
 {
     if (f.T == 0) return 0;
-    if (decode_call(f)) return launch_decode_bf16(f, B, A, after_projection);
-    GemmPlan plan = plan_gemm(f.T, f.H, f.N);
+    if (f.route.few_rows) return launch_decode_bf16(f, B, A, after_projection);
+    GemmPlan plan = f.route.gemm;
     // the fused rotary embedding wants whole heads of 128 in a wavefront's strip: 256-feature tiles (the number
     // of splits, which the shrink's layout depends on, stays what the sizes alone give; with splits the
     // finishing kernel rotates)
@@ -937,7 +944,7 @@ int launch_gemm_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEven
     g.ranks = f.ranks;
     g.tiles8 = (g.mtiles * g.ntiles + 7) / 8 * 8;   // see the tile order in the kernel
     g.splits = plan.splits;
-    const bool prep = prep_in_projection(f);
+    const bool prep = f.route.prep_inside;
     // shrink ranges of the prep workgroups: about 1024 wide, at most 4, none empty
     const int want = std::max(1, std::min(4, f.H / 1024));
     g.prep_kper = ((f.H / 64 + want - 1) / want) * 64;
@@ -952,7 +959,7 @@ int launch_gemm_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEven
     int e = (int)hipGetLastError();
     if (!e && after_projection) e = (int)hipEventRecord(after_projection, f.stream);
     if (e || plan.splits == 1) return e;
-    return launch_finish_bf16(f, B, plan.splits, prep ? g.prep_ranges : plan_shrink(f.T, f.H, f.N, f.L, f.r).splits,
+    return launch_finish_bf16(f, B, plan.splits, prep ? g.prep_ranges : f.route.shrink.splits,
                               prep ? f.block_rows : nullptr, false);
 }
 

@@ -24,6 +24,29 @@ struct RankTable {
     uint8_t r[ALORA_MAX_ADAPTERS];
 };
 
+struct GemmPlan {
+    int ntw;     // 32-wide feature tiles per wavefront (tile width 64 * ntw)
+    int splits;  // 1: fused kernel; > 1: split hidden dimension + finishing kernel
+    int kps;     // 64-wide K-slices per split
+};
+struct ShrinkPlan {
+    int splits;  // ranges of the hidden dimension; the shrink result is the fixed-order sum of their partials
+    int kper;    // width of one range (multiple of 64)
+    // Prefill-sized batches: the number of ranges is chosen on the device, per call, from the number of
+    // adapted 32-row blocks (at most `splits`); the last range of a block to finish adds the partials in
+    // fixed order and stores the (hi, lo) form.  The shrink then walks Fwd::items.
+    bool combine;
+};
+// Which kernels a bf16 call takes and how they are cut.  Decided once per call (plan_call), from its sizes and
+// from ONE reading of the tuning override: every launch of the call follows it, so that an override set by another
+// host thread meanwhile cannot give one call the launches of two different paths.
+struct Route {
+    GemmPlan gemm;
+    ShrinkPlan shrink;
+    bool few_rows;      // at most 64 rows: the projection kernel of alora_decode_bf16.hip
+    bool prep_inside;   // grouping and shrink run inside the projection kernel
+};
+
 // Everything one forward call needs, resolved on the host.
 struct Fwd {
     int dtype, T, H, Nq, Nkv, N, L, r, G;
@@ -55,6 +78,7 @@ struct Fwd {
     int n_items;
     int32_t *block_rows;  // decode-sized bf16 batches: the row ids of every block-table entry, 32 per entry, -1 padded
                           // (the finishing kernel then needs no look-up through perm)
+    Route route;          // bf16 calls
     hipStream_t stream;
 };
 
@@ -88,32 +112,16 @@ bool group_in_shrink_f32(const Fwd &f);   // the grouping runs on workgroups of 
 int launch_gemm_f32(const Fwd &f, const PtrTable &B);
 int launch_shrink_bf16(const Fwd &f, const PtrTable &A);
 int launch_gemm_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEvent_t after_projection);
-bool prep_in_projection(const Fwd &f);   // grouping and shrink run inside the split projection kernel
 int launch_finish_bf16(const Fwd &f, const PtrTable &B, int splits, int s_splits, const int32_t *block_rows, bool s_f32);
-struct GemmPlan {
-    int ntw;     // 32-wide feature tiles per wavefront (tile width 64 * ntw)
-    int splits;  // 1: fused kernel; > 1: split hidden dimension + finishing kernel
-    int kps;     // 64-wide K-slices per split
-};
-GemmPlan plan_gemm(int T, int H, int N);
-// batches of a few rows (alora_decode_bf16.hip): whether a call takes that path, from its sizes alone
-bool decode_call(const Fwd &f);
+void plan_call(Fwd &f);   // fills f.route (f holds the sizes and block_rows)
+bool few_rows_call(const Fwd &f);   // a batch of a few rows (alora_decode_bf16.hip), from its sizes alone
 int launch_decode_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEvent_t after_projection);
-bool gemm_tuning_forced();
 size_t gemm_partial_bytes(int T, int H, int N);
 void set_gemm_tuning(int ntw, int splits);
 int group_blocks(int T, int L);
 size_t group_hist_bytes(int T);
 constexpr int ALORA_SHRINK_MAX_SPLITS = 8;
 constexpr int ALORA_SHRINK_TARGET_WGS = 256;   // workgroups the prefill-sized shrink aims for (one per compute unit)
-struct ShrinkPlan {
-    int splits;  // ranges of the hidden dimension; the shrink result is the fixed-order sum of their partials
-    int kper;    // width of one range (multiple of 64)
-    // Prefill-sized batches: the number of ranges is chosen on the device, per call, from the number of
-    // adapted 32-row blocks (at most `splits`); the last range of a block to finish adds the partials in
-    // fixed order and stores the (hi, lo) form.  The shrink then walks Fwd::items.
-    bool combine;
-};
 // what the grouping kernels need to write the shrink's work list
 struct ShrinkWork {
     int4 *items;
@@ -121,7 +129,7 @@ struct ShrinkWork {
     int n_items, k64, rmax;
 };
 int shrink_items(int T, int L);   // entries of the work list
-ShrinkPlan plan_shrink(int T, int H, int N, int L, int r);
+ShrinkPlan plan_shrink(const GemmPlan &gemm, int T, int H, int L, int r);
 int launch_rope_f32(const Fwd &f);   // fp32 path: rotation of the stored q and k rows in place
 
 }  // namespace alora

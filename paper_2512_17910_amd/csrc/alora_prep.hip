@@ -410,7 +410,7 @@ int launch_classify_group(const Fwd &f)
 {
     if (f.T == 0) return 0;
     ShrinkWork sw = {nullptr, nullptr, 0, 0, 0};
-    if (f.items) sw = ShrinkWork{f.items, f.counters, f.n_items, f.H / 64, plan_shrink(f.T, f.H, f.N, f.L, f.r).splits};
+    if (f.items) sw = ShrinkWork{f.items, f.counters, f.n_items, f.H / 64, f.route.shrink.splits};
     if (f.T >= PREP_TWO_LAUNCH_FROM) {
         const int slices = (f.T + PREP_SLICE - 1) / PREP_SLICE;
         hipLaunchKernelGGL(classify_slices_kernel, dim3(slices), dim3(PREP_THREADS), 0, f.stream, f.aid, f.seg, f.pos,

@@ -77,11 +77,11 @@ __global__ __launch_bounds__(256) void shrink_bf16_kernel(const bf16_t *__restri
 // workgroups' worth of row blocks at most.  Prefill-sized path: one range unless a block's loads are large
 // (wide hidden dimension, high rank); then `splits` is the upper limit (ranges at least 512 wide) and the
 // grouping step picks the number per call from the adapted blocks it finds.
-ShrinkPlan plan_shrink(int T, int H, int N, int L, int r)
+ShrinkPlan plan_shrink(const GemmPlan &gemm, int T, int H, int L, int r)
 {
     ShrinkPlan p = {1, H, false};
     if (T <= 0 || L <= 0) return p;
-    if (plan_gemm(T, H, N).splits == 1) {
+    if (gemm.splits == 1) {
         // Cutting a block into ranges adds a chain of round trips past the L2 (partials written through,
         // counter, partials read back: about 6 us); it pays once a block's 32 token rows and its adapter's
         // A, all pulled through one compute unit, take clearly longer than that (0.5 MB is about 11 us).
@@ -114,7 +114,7 @@ static void launch_shrink(const Fwd &f, const PtrTable &A, const ShrinkPlan &sp)
 int launch_shrink_bf16(const Fwd &f, const PtrTable &A)
 {
     if (f.T == 0 || f.L == 0) return 0;
-    const ShrinkPlan sp = plan_shrink(f.T, f.H, f.N, f.L, f.r);
+    const ShrinkPlan &sp = f.route.shrink;
     if (sp.combine && !f.items) return (int)hipErrorInvalidValue;
     if (f.r <= 32) launch_shrink<512, 1>(f, A, sp);
     else launch_shrink<256, 2>(f, A, sp);

@@ -1,0 +1,79 @@
+"""Which kernels a call of the library launches, with which grids, found without a GPU.
+
+launches_of(calls) runs the calls in a process of its own in which launch_recorder.c stands in for the HIP runtime:
+every launch is written down instead of enqueued, device pointers are numbers that nothing dereferences.  A call is a
+dict: op "forward" (fields of alora_dims, optionally tuning_during: a tuning override that arrives in the middle of the
+call, between the library's two profiling events) or op "attention" (fields of alora_attn_dims and the entry point)."""
+import ctypes
+import json
+import os
+import re
+import subprocess
+import sys
+import tempfile
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+class _Launch(ctypes.Structure):
+    _fields_ = [("name", ctypes.c_char * 512), ("grid", ctypes.c_uint32 * 3), ("block", ctypes.c_uint32 * 3),
+                ("arg1", ctypes.c_int32), ("arg2", ctypes.c_int32)]
+
+
+def launches_of(calls):
+    """Per call: {"status", "workspace", "launches": [{"kernel", "ints" (of its template arguments), "grid", "block", "args"}]}."""
+    with tempfile.TemporaryDirectory() as tmp:
+        rec = os.path.join(tmp, "librec.so")
+        subprocess.run(["gcc", "-O1", "-w", "-shared", "-fPIC", "-o", rec, os.path.join(ROOT, "tests", "launch_recorder.c")], check=True)
+        r = subprocess.run([sys.executable, os.path.abspath(__file__), rec], input=json.dumps(calls), capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-3000:]
+    return json.loads(r.stdout)
+
+
+def _main(rec_path):
+    sys.path.insert(0, ROOT)
+    rec = ctypes.CDLL(rec_path, ctypes.RTLD_GLOBAL)   # ahead of the library: its HIP calls bind here
+    from paper_2512_17910_amd import binding as ab
+    L = ctypes.CDLL(ab.LIB_PATH)
+    rec.rec_get.restype = ctypes.POINTER(_Launch)
+    P = ctypes.c_void_p(0x100000)
+    HOOK = ctypes.CFUNCTYPE(None)
+    out = []
+    for c in json.load(sys.stdin):
+        rec.rec_reset()
+        ws = ctypes.c_size_t(0)
+        if c["op"] == "forward":
+            d = ab.AloraDims(**{k: v for k, v in c.items() if k in dict(ab.AloraDims._fields_)})
+            d.token_seg_ids = d.token_positions = P.value
+            s = L.alora_qkv_workspace_bytes(ctypes.byref(d), ctypes.byref(ws))
+            tab = (ctypes.c_void_p * max(1, d.n_adapters))(*[P.value] * d.n_adapters)
+            hook = None
+            if c.get("tuning_during"):
+                assert L.alora_qkv_profile_begin(1) == 0
+                hook = HOOK(lambda: L.alora_qkv_set_tuning(*c["tuning_during"]) and None)
+                rec.rec_on_event(hook)
+            if s == 0:
+                s = L.alora_qkv_forward(P, P, P, P, tab, tab, P, P, P, P, ctypes.c_int(16), ctypes.byref(d), P, ws, None)
+            if hook:
+                rec.rec_on_event(HOOK(0))
+                L.alora_qkv_set_tuning(0, 0)
+                L.alora_qkv_profile_end(None, None)
+        else:
+            d = ab.AloraAttnDims(**{k: v for k, v in c.items() if k in dict(ab.AloraAttnDims._fields_)})
+            split = c["entry"].endswith("_split")
+            s = getattr(L, c["entry"][:-6] + "_workspace_bytes")(ctypes.byref(d), ctypes.byref(ws)) if split else 0
+            if s == 0:
+                s = getattr(L, c["entry"])(P, P, P, P, P, P, P, ctypes.byref(d), *((P, ws) if split else ()), None)
+        launches = []
+        for i in range(rec.rec_count()):
+            r = rec.rec_get(i).contents
+            name = r.name.decode()
+            m = re.search(r"N5alora(\d+)", name)
+            launches.append({"kernel": name[m.end():m.end() + int(m.group(1))], "ints": [int(v) for v in re.findall(r"L[ib](\d+)E", name)],
+                             "grid": list(r.grid), "block": list(r.block), "args": [r.arg1, r.arg2]})
+        out.append({"status": s, "workspace": ws.value, "launches": launches})
+    json.dump(out, sys.stdout)
+
+
+if __name__ == "__main__":
+    _main(sys.argv[1])
