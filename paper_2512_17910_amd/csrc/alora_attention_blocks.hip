@@ -6,9 +6,8 @@
 // workgroup (eight, or four) consecutive rows, which share the K and V tiles of 32 context positions through LDS:
 // every cached row is loaded once per 256 / G (128 / G) query rows.  Row blocks are cut at multiples of that number
 // of the POSITION, so whether a batch row leads a block is decided from the row before it alone.
-// A workgroup owns a range of batch rows (chosen on the host: a whole row block for long runs, down to one row for
-// a decode batch, where every row leads a block of its own) and works through the blocks that start in it; the
-// range index is permuted so that the leading rows of a long run do not all fall to the same shader engine.
+// The workgroups of a range of batch rows look the whole range over for leading rows and take them in turn: how many
+// there are, a few of a prompt chunk or every row of a decode batch, is known on the device only.
 //
 // For batches with few row blocks the context of every block is cut into parts, one workgroup each, which
 // leave (running maximum, weight sum, unnormalised output) per column for the kernel that combines them.
@@ -88,7 +87,7 @@ __device__ __forceinline__ void both_halves(float x, float &lo, float &hi)
 __device__ const uint32_t ab_zero_chunk[4] = {0u, 0u, 0u, 0u};
 
 template <int G, int NW, bool POW2>   // NW: wavefronts per workgroup; POW2: the block size is a power of two (shifts instead of divisions)
-__global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(AttnArgs a, int R, int sub)
+__global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(AttnArgs a, int range, int wgs)
 {
     constexpr int D = 128;
     constexpr int GPW = 8 / NW;       // groups of four positions a wavefront copies per block of 32
@@ -100,47 +99,57 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
     __shared__ __attribute__((aligned(1024))) unsigned char tiles[NB * 2 * TILE];
     __shared__ __attribute__((aligned(16))) unsigned char ok_bytes[NB][8];     // byte i: validity of positions 4i .. 4i+3 of a pair
     __shared__ unsigned long long run_mask[NW / 2];
+    __shared__ unsigned long long lead_mask[RANGE_SCANS * NW];   // bit i of word j: row 64 j + i of the range leads a block
     constexpr int WIN = 64;            // blocks of 32 positions whose table entries the window below holds
     __shared__ int32_t window[WIN * 32 / 4 + 2];   // block sizes are multiples of 4
 
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4, li = lane & 31, lh = lane >> 5;
     const int wu = __builtin_amdgcn_readfirstlane(w);
-    // grid: (range of batch rows, K/V head, part of the context); a.splits parts, 1 = the whole context
-    // (long runs of rows: every range twice, see plan_blocks; the second halves, mostly without work, are dispatched first)
-    const int n_ranges = (a.T + R - 1) / R, per_sub = n_ranges * a.Hkv * a.splits;
-    const int which = sub > 1 ? 1 - (int)blockIdx.x / per_sub : 0, bid_part = (int)blockIdx.x % per_sub;
-    const int part = bid_part % a.splits, bid = bid_part / a.splits;
-    const int hk = bid % a.Hkv;
-    // ---- this workgroup's R batch rows (R a power of two <= 64, <= RBG) ------------------------------------
-    // With R < RBG a long run of rows has a leading row in every (RBG / R)-th range only, and workgroups are
-    // handed to the shader engines of an XCD in turn (four of them): without the exchange of the two low index
-    // bits below, all the work of such a batch would land on one engine in four.
-    int k = bid / a.Hkv;
+    // grid: (range of batch rows, workgroup of the range, K/V head, part of the context); a.splits parts, 1 = the whole context
+    const int part = (int)blockIdx.x % a.splits, bid = (int)blockIdx.x / a.splits;
+    const int hk = bid % a.Hkv, which = bid / a.Hkv % wgs, r_begin = bid / a.Hkv / wgs * range, r_end = min(a.T, r_begin + range);
+    // ---- the rows of the range that lead a block (range <= RANGE_SCANS * 64 * NW) ---------------------------
+    // A row does unless the row before it in the batch is the same sequence's previous position and the position
+    // is not a multiple of RBG (then an earlier row leads).  The workgroups of a range take them in turn: the leading rows
+    // of a long run are RBG rows apart, those of a decode batch next to each other, and how they lie is known here only.
     {
-        const int mm = RBG / R;
-        if (mm > 1 && (k | 3) < n_ranges) k ^= (k / mm) & (mm >= 4 ? 3 : 1);
-    }
-    const int r_begin = k * R, r_end = min(a.T, r_begin + R);
-    // which of them lead a block: a row does unless the row before it in the batch is the same sequence's
-    // previous position and the position is not a multiple of RBG (then an earlier row leads)
-    unsigned long long leaders;
-    {
-        bool lead = false;
-        const int t = r_begin + lane;
-        if (lane < R && t < r_end) {
-            const int sq = a.seq[t], p0 = a.pos[t];
-            const bool ok = sq >= 0 && sq < a.n_seqs && p0 >= 0;
-            lead = !(ok && t > 0 && (p0 % RBG) != 0 && a.seq[t - 1] == sq && a.pos[t - 1] == p0 - 1);
+        int sq[RANGE_SCANS], p0[RANGE_SCANS], sq1[RANGE_SCANS], p1[RANGE_SCANS];
+#pragma unroll
+        for (int i = 0; i < RANGE_SCANS; ++i) {
+            const int t = r_begin + i * 64 * NW + tid;
+            sq[i] = sq1[i] = p0[i] = p1[i] = -1;
+            if (t < r_end) { sq[i] = a.seq[t]; p0[i] = a.pos[t]; }
+            if (t < r_end && t > 0) { sq1[i] = a.seq[t - 1]; p1[i] = a.pos[t - 1]; }
         }
-        leaders = __builtin_amdgcn_ballot_w64(lead);
-        if (sub > 1) {   // every other one
-            unsigned long long mine = 0;
-            int n = 0;
-            for (unsigned long long rest = leaders; rest; rest &= rest - 1, ++n)
-                if ((n & 1) == which) mine |= rest & -rest;
-            leaders = mine;
+#pragma unroll
+        for (int i = 0; i < RANGE_SCANS; ++i) {
+            const int t = r_begin + i * 64 * NW + tid;
+            const bool ok = sq[i] >= 0 && sq[i] < a.n_seqs && p0[i] >= 0;
+            const bool lead = t < r_end && !(ok && t > 0 && (p0[i] % RBG) != 0 && sq1[i] == sq[i] && p1[i] == p0[i] - 1);
+            const unsigned long long mk = __builtin_amdgcn_ballot_w64(lead);
+            if (lane == 0) lead_mask[i * NW + w] = mk;
         }
+        __syncthreads();
     }
+    // batch row of the n-th of them, -1 when there are not as many: lane j counts word j
+    auto leader = [&](int n) {
+        static_assert(RANGE_SCANS * NW <= 32, "a lane per word, two rows of lanes");
+        const unsigned long long mk = lane < RANGE_SCANS * NW ? lead_mask[lane] : 0ull;
+        const int c = __builtin_popcountll(mk);
+        int upto = c;                                   // leading rows in words 0 .. lane
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xf, 0xf, false);
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xf, 0xf, false);
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xf, 0xf, false);
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x142, 0xa, 0xf, false);   // row_bcast:15 into the second row
+        if (n >= __builtin_amdgcn_readlane(upto, 31)) return -1;
+        const int word = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(n < upto));
+        n -= __builtin_amdgcn_readlane(upto - c, word);
+        const unsigned lo = __builtin_amdgcn_readlane((unsigned)mk, word), hi = __builtin_amdgcn_readlane((unsigned)(mk >> 32), word);
+        const int before = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));   // set bits below this lane's
+        const unsigned long long m2 = ((unsigned long long)hi << 32) | lo;
+        return r_begin + 64 * word + (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(((m2 >> lane) & 1ull) && before == n));
+    };
     const int Nkv = a.Hkv * D;
     const long long n_blocks = a.n_slots / a.bs;
     const long long cap = (long long)a.max_blocks * a.bs;
@@ -166,9 +175,10 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
         v_base = (uint32_t)vrow * PITCH + (uint32_t)(((2 * (g4 & 1) + ((c16 & 3) >> 1)) ^ (j << 2)) << 4) + (uint32_t)((c16 & 1) << 3);
     }
 
-  for (bool first = true; leaders; leaders &= leaders - 1, first = false) {
-    const int t0 = r_begin + __builtin_ctzll(leaders);
-    if (!first) __syncthreads();      // everyone is done with the tiles and masks of the block before
+  for (int turn = which;; turn += wgs) {
+    const int t0 = leader(turn);
+    if (t0 < 0) break;
+    if (turn != which) __syncthreads();      // everyone is done with the tiles and masks of the block before
     const int sq = a.seq[t0], p0 = a.pos[t0];
     const bool row_ok = sq >= 0 && sq < a.n_seqs && p0 >= 0;
     // rows of the block: up to the next multiple of RBG, as long as the run continues
@@ -386,12 +396,16 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
         // (two loops: the accumulators live in the first only)
         const int n_chunks_w = lim_w >= 0 ? min((lim_w >> 5) + 1, n_chunks) : 0;
         int c = c_lo;
+        // (the loop on a line of the instruction cache: 8 single rows at 16K positions 398 us without, 393 with; 4 x 1024 rows at
+        // 8192, 594 and 581)
+        asm volatile(".p2align 6");
         for (; c < n_chunks_w; c += 2) {
             step(c);
             consume(c, cur, scores(cur));
             if (c + 1 < n_chunks_w) consume(c + 1, cur + 1, scores(cur + 1));
             advance();
         }
+        asm volatile(".p2align 6");
         for (; c < n_chunks; c += 2) {
             step(c);
             advance();
@@ -445,42 +459,47 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
 // 108 | 123, 4 x 32 rows 104 | 78.
 BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts)
 {
-    BlockPlan p = {4, 1, 1, 1};
+    BlockPlan p = {4, 64, 1, 1};
     if (T <= 0) return p;
     const bool long_runs = (long long)T * G > 128ll * n_seqs;
     if (long_runs && (parts || (long long)T * G / 256 * Hkv >= 512)) p.waves = 8;
     const int rbg = 32 * p.waves / G;
-    p.R = rbg < 64 ? rbg : 64;   // (a ballot looks over the rows of a range)
     if (parts) {
-        // whole row blocks; parts of every block's context, one workgroup each, until there is one per CU (two of four
-        // wavefronts)
+        // parts of every block's context, one workgroup each, until there is one per CU (two of four wavefronts)
         const long long wgs = (long long)((T + rbg - 1) / rbg) * Hkv, want = p.waves == 8 ? 256 : 512;
         if (wgs < want) p.splits = (int)((want + wgs - 1) / wgs < MAX_PARTS ? (want + wgs - 1) / wgs : MAX_PARTS);
     }
-    if (p.splits > 1) {
-        // ranges no longer than a sequence's rows on average, so that few hold the starts of several blocks (six
-        // sequences of 50 rows, 8/8 heads: ranges of 64 rows 161 us, of 32 137; six single rows: 106 -> 87)
-        while (p.R > 1 && (long long)p.R * n_seqs > T && (long long)((T + p.R / 2 - 1) / (p.R / 2)) * Hkv * p.splits <= 4096) p.R /= 2;
-        return p;
-    }
-    // Long runs: a range holds the start of a row block, or two where a sequence begins in it, and two blocks one
-    // after the other would double the length of the call: each range goes to two workgroups that take every other
-    // block (4 x 256 rows over 16K positions, 64/8 heads 1125 -> 555 us; 2 x 1000 rows, 16/8 heads 776 -> 487).
-    // Short runs: fewer rows per range, down to one, until there are eight workgroups per CU (every row may lead a
-    // block of its own).
-    if (long_runs) p.sub = 2;
-    while (!long_runs && p.R > 1 && (long long)((T + p.R - 1) / p.R) * Hkv < 2048) p.R /= 2;
+    // Ranges as long as a workgroup looks over at once, each with a workgroup per row block it can hold: T / rbg of long runs and
+    // two more for every sequence (its first and its last block), as far as 2048 workgroups allow; where there are more
+    // blocks than that, a workgroup takes several.  In parts, where the chip is full with a workgroup per rbg rows: no more than
+    // the sequences say there are.  A workgroup that finds no block of its own costs the chip 7 ns.
+    // How rows lie is not known here, and one workgroup with several blocks is the whole call's length: with ranges of at most a
+    // block's rows, each shared by one or two workgroups, decode rows beside a prompt chunk were up to 16 contexts in a row.
+    // us, 32/8 heads, such ranges | the ranges before them (128 / G rows, halved until 2048 workgroups) | now: 2048 rows and 32 single
+    // rows at 4096 positions 1690 | 825 | 274, 1024 and 16 at 8192 1635 | 800 | 317, 4 x 512 and 32 at 4096 1730 | 905 | 299, in
+    // parts 1490 | 904 | 291; 5 x 61 rows at 8190 442 | 325 | 229; equal runs the same (4 x 1024 rows at 8192 622 | 1280 | 584).
+    const int most = RANGE_SCANS * 64 * p.waves;
+    int ranges = (T + most - 1) / most;
+    p.range = ((T + ranges - 1) / ranges + 63) / 64 * 64;
+    ranges = (T + p.range - 1) / p.range;
+    const int rows = p.range < T ? p.range : T;
+    const long long blocks = (rows + rbg - 1) / rbg, heads = (long long)ranges * Hkv * p.splits;
+    long long wgs = 0;
+    if (p.splits > 1) wgs = n_seqs < 4096 / heads ? n_seqs : 4096 / heads;
+    else wgs = blocks + (2ll * n_seqs < 2048 / heads ? 2ll * n_seqs : 2048 / heads);
+    if (wgs < blocks) wgs = blocks;
+    p.wgs = (int)(wgs < rows ? wgs : rows);
     return p;
 }
 
 int launch_attention_blocks(const AttnArgs &a, int G, const BlockPlan &p, hipStream_t stream)
 {
-    const int R = p.R;
-    const dim3 grid((unsigned)((a.T + R - 1) / R) * (unsigned)a.Hkv * (unsigned)a.splits * (unsigned)p.sub), block(64 * p.waves);
+    const int ranges = (a.T + p.range - 1) / p.range;
+    const dim3 grid((unsigned)ranges * (unsigned)p.wgs * (unsigned)a.Hkv * (unsigned)a.splits), block(64 * p.waves);
     const bool pow2 = a.bs_shift >= 0;
 #define AB_LAUNCH(GG, NW) \
-    if (pow2) hipLaunchKernelGGL((paged_attention_blocks_kernel<GG, NW, true>), grid, block, 0, stream, a, R, p.sub); \
-    else hipLaunchKernelGGL((paged_attention_blocks_kernel<GG, NW, false>), grid, block, 0, stream, a, R, p.sub)
+    if (pow2) hipLaunchKernelGGL((paged_attention_blocks_kernel<GG, NW, true>), grid, block, 0, stream, a, p.range, p.wgs); \
+    else hipLaunchKernelGGL((paged_attention_blocks_kernel<GG, NW, false>), grid, block, 0, stream, a, p.range, p.wgs)
     switch (G * 16 + p.waves) {
     case 16 + 8: AB_LAUNCH(1, 8); break;
     case 32 + 8: AB_LAUNCH(2, 8); break;

@@ -442,3 +442,30 @@ def test_suffix_rows_with_long_runs(group, n_kv, lens, parts):
     pick = np.unique(np.r_[np.arange(0, c.T, 37), np.cumsum(rows) - 1, np.cumsum(rows)[:-1], [31, 32, 63, 64]])
     pick = pick[pick < c.T]
     assert maxnorm_rel(out[pick], d.oracle(rows=pick)) <= TOL["bf16"]
+
+
+# Row blocks dealt to the workgroups of a range: decode rows beside a prompt chunk (every one leads a block), and rows of two
+# sequences in no order, each a block of its own: many more than workgroups, so that one takes dozens, in two ranges.
+# Bound: the reader's (softmax weights and outputs in bf16).
+@pytest.mark.parametrize("parts", [False, True], ids=["whole", "parts"])
+@pytest.mark.parametrize("kind,group,n_kv", [("chunk+decode", 4, 2), ("decode+chunk", 8, 1), ("shuffled", 2, 1), ("shuffled", 1, 2)])
+def test_suffix_row_blocks_that_lie_unevenly(kind, group, n_kv, parts):
+    lens, rows = {"chunk+decode": ([1100] + [200 + 9 * i for i in range(40)], [1030] + [1] * 40),
+                  "decode+chunk": ([90 + 31 * i for i in range(70)] + [700], [1] * 70 + [650]), "shuffled": ([700, 620], [690, 610])}[kind]
+    c = wl.attention_case(f"uneven-{kind}-g{group}", "bf16", lens, rows, group * n_kv, n_kv, 128, 16, seed=wl.SEED ^ (940 + group))
+    if kind == "shuffled":
+        order = np.random.default_rng(7).permutation(c.T)
+        c.q, c.token_seq_ids, c.token_positions = c.q[order].copy(), c.token_seq_ids[order].copy(), c.token_positions[order].copy()
+    print(f"[case] {c.name} T={c.T} parts={parts}", flush=True)
+    d = DeviceCase(c)
+    if parts:
+        ws = torch.full((max(16, ab.alora_paged_attention_suffix_workspace_bytes(d.dims)),), 0xff, dtype=torch.uint8, device="cuda")
+        d.out.fill_(float("nan"))
+        ab.alora_paged_attention_suffix_split(d.q, d.kc, d.vc, d.bt, d.seq, d.pos, d.out, d.dims, ws)
+        torch.cuda.synchronize()
+        out = to_f64(d.out)
+    else:
+        out = to_f64(_run_suffix(d))
+    assert np.isfinite(out).all()
+    pick = np.unique(np.r_[np.arange(0, c.T, 29), np.arange(c.T - 45, c.T), np.arange(0, 75, 2)])
+    assert maxnorm_rel(out[pick], d.oracle(rows=pick)) <= TOL["bf16"]

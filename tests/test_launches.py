@@ -1,4 +1,5 @@
 """The launches of a call -- kernels, grids, order -- found without a GPU (see launches.py)."""
+import numpy as np
 import pytest
 
 from launches import launches_of
@@ -19,3 +20,62 @@ def test_a_tuning_override_during_a_call_leaves_the_call_whole(T):
                                       dict(QKV_8B, T=T, n_adapters=4)])
     assert len(plain["launches"]) == 2, kernels(plain)
     assert torn == plain and after == plain, (kernels(plain), kernels(torn))
+
+
+# ---- the row-block reader ------------------------------------------------------------------------
+def reader(entry, T, n_seqs, n_q, n_kv, capacity=16384):
+    return dict(op="attention", entry=entry, dtype=1, n_tokens=T, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=128, n_seqs=n_seqs,
+                max_blocks=capacity // 16, block_size=16, n_slots=1 << 20)
+
+
+def cut_of(call):
+    """(group size, wavefronts, rows per range, workgroups per range) of a recorded reader call."""
+    l = call["launches"][0]
+    assert l["kernel"] == "paged_attention_blocks_kernel", l
+    G, waves, _ = l["ints"]
+    assert l["block"][0] == 64 * waves
+    return G, waves, l["args"][0], l["args"][1]
+
+
+def longest_chain(runs, G, waves, rows_per_range, wgs):
+    """Row blocks one workgroup takes at most, for runs of (first position, rows) laid one after the other in a batch."""
+    rbg = 32 * waves // G
+    at, lead = 0, []
+    for first, rows in runs:
+        pos = first + np.arange(rows)
+        lead += list(at + np.flatnonzero((pos % rbg == 0) | (np.arange(rows) == 0)))
+        at += rows
+    per_range = np.bincount(np.array(lead) // rows_per_range)
+    return int(-(-per_range.max() // wgs)), len(lead)
+
+
+UNEVEN = {"chunk-2048+32": [(2048, 2048)] + [(4095, 1)] * 32, "chunk-1024+16": [(7168, 1024)] + [(8191, 1)] * 16,
+          "4x512+32": [(3584, 512)] * 4 + [(4095, 1)] * 32, "decode-first": [(4095, 1)] * 32 + [(1000, 2048)],
+          "5x61": [(8129 + 7 * i, 61) for i in range(5)]}
+
+
+@pytest.mark.parametrize("n_q,n_kv", [(32, 8), (64, 8), (16, 8), (8, 8)])
+@pytest.mark.parametrize("runs", UNEVEN.values(), ids=UNEVEN.keys())
+def test_no_workgroup_of_the_reader_takes_several_contexts_one_after_the_other(runs, n_q, n_kv):
+    """A prompt chunk beside decode rows: the workgroup with the most row blocks is the length of the call."""
+    T = sum(r for _, r in runs)
+    for table_rows in (len(runs), 256):
+        (call,) = launches_of([reader("alora_paged_attention_suffix", T, table_rows, n_q, n_kv)])
+        G, waves, rows_per_range, wgs = cut_of(call)
+        chain, blocks = longest_chain(runs, G, waves, rows_per_range, wgs)
+        assert chain == 1, (chain, blocks, waves, rows_per_range, wgs)
+
+
+def test_the_ranges_of_the_reader_fit_what_a_workgroup_looks_over():
+    rng = np.random.default_rng(5)
+    sizes = [(int(np.exp(rng.uniform(0, np.log(2e5)))), int(rng.integers(1, 400)), int(rng.choice([1, 2, 4, 8])), int(rng.choice([1, 2, 8, 16])))
+             for _ in range(60)] + [(1, 1, 8, 1), (1024, 1, 4, 1), (1025, 1, 4, 1), (2048, 1, 1, 64), (2049, 1, 1, 64)]
+    for entry in ("alora_paged_attention_suffix", "alora_paged_attention_suffix_split"):
+        for (T, n, G, n_kv), call in zip(sizes, launches_of([reader(entry, T, n, G * n_kv, n_kv) for T, n, G, n_kv in sizes])):
+            assert call["status"] == 0
+            _, waves, rows_per_range, wgs = cut_of(call)
+            assert rows_per_range % 64 == 0 and 64 <= rows_per_range <= 4 * 64 * waves and 1 <= wgs <= max(T, 1)
+            ranges, parts = -(-T // rows_per_range), call["launches"][0]["grid"][0] // (-(-T // rows_per_range) * wgs * n_kv)
+            assert call["launches"][0]["grid"][0] == ranges * wgs * n_kv * parts and 1 <= parts <= 32
+            assert (parts > 1) == (len(call["launches"]) == 2)
+            assert call["workspace"] == (T * G * n_kv * parts * 130 * 4 if parts > 1 else 0)
