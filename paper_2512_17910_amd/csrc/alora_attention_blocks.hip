@@ -98,8 +98,9 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
     constexpr int NB = NW == 8 ? 6 : 4;   // (K, V) tile pairs, taken two at a time (four wavefronts: two workgroups share a CU's LDS)
     __shared__ __attribute__((aligned(1024))) unsigned char tiles[NB * 2 * TILE];
     __shared__ __attribute__((aligned(16))) unsigned char ok_bytes[NB][8];     // byte i: validity of positions 4i .. 4i+3 of a pair
-    __shared__ unsigned long long run_mask[NW / 2];
-    __shared__ unsigned long long lead_mask[RANGE_SCANS * NW];   // bit i of word j: row 64 j + i of the range leads a block
+    constexpr int LOOK = LOOKED_OVER * NW, SCANS = LOOKED_OVER / 64;   // batch rows a workgroup looks over, and each of its threads
+    __shared__ unsigned long long lead_mask[LOOK / 64];          // bit i of word j: row 64 j + i from the range's first leads a block
+    __shared__ int32_t row_seq[LOOK], row_pos[LOOK];
     constexpr int WIN = 64;            // blocks of 32 positions whose table entries the window below holds
     __shared__ int32_t window[WIN * 32 / 4 + 2];   // block sizes are multiples of 4
 
@@ -108,47 +109,62 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
     // grid: (range of batch rows, workgroup of the range, K/V head, part of the context); a.splits parts, 1 = the whole context
     const int part = (int)blockIdx.x % a.splits, bid = (int)blockIdx.x / a.splits;
     const int hk = bid % a.Hkv, which = bid / a.Hkv % wgs, r_begin = bid / a.Hkv / wgs * range, r_end = min(a.T, r_begin + range);
-    // ---- the rows of the range that lead a block (range <= RANGE_SCANS * 64 * NW) ---------------------------
+    // ---- the rows of the range that lead a block (range <= LOOK - RBG: the RBG rows behind it say where its last block ends) ----
     // A row does unless the row before it in the batch is the same sequence's previous position and the position
     // is not a multiple of RBG (then an earlier row leads).  The workgroups of a range take them in turn: the leading rows
     // of a long run are RBG rows apart, those of a decode batch next to each other, and how they lie is known here only.
     {
-        int sq[RANGE_SCANS], p0[RANGE_SCANS], sq1[RANGE_SCANS], p1[RANGE_SCANS];
+        int sq[SCANS], p0[SCANS], sq1[SCANS], p1[SCANS];
 #pragma unroll
-        for (int i = 0; i < RANGE_SCANS; ++i) {
+        for (int i = 0; i < SCANS; ++i) {
             const int t = r_begin + i * 64 * NW + tid;
             sq[i] = sq1[i] = p0[i] = p1[i] = -1;
-            if (t < r_end) { sq[i] = a.seq[t]; p0[i] = a.pos[t]; }
-            if (t < r_end && t > 0) { sq1[i] = a.seq[t - 1]; p1[i] = a.pos[t - 1]; }
+            if (t < a.T && t < r_end + RBG) {
+                sq[i] = a.seq[t];
+                p0[i] = a.pos[t];
+                if (t > 0) { sq1[i] = a.seq[t - 1]; p1[i] = a.pos[t - 1]; }
+            }
         }
 #pragma unroll
-        for (int i = 0; i < RANGE_SCANS; ++i) {
-            const int t = r_begin + i * 64 * NW + tid;
+        for (int i = 0; i < SCANS; ++i) {
             const bool ok = sq[i] >= 0 && sq[i] < a.n_seqs && p0[i] >= 0;
-            const bool lead = t < r_end && !(ok && t > 0 && (p0[i] % RBG) != 0 && sq1[i] == sq[i] && p1[i] == p0[i] - 1);
+            const bool lead = !(ok && (p0[i] % RBG) != 0 && sq1[i] == sq[i] && p1[i] == p0[i] - 1);   // (row 0 has none before it)
             const unsigned long long mk = __builtin_amdgcn_ballot_w64(lead);
             if (lane == 0) lead_mask[i * NW + w] = mk;
+            row_seq[i * 64 * NW + tid] = sq[i];
+            row_pos[i * 64 * NW + tid] = p0[i];
         }
         __syncthreads();
     }
-    // batch row of the n-th of them, -1 when there are not as many: lane j counts word j
-    auto leader = [&](int n) {
-        static_assert(RANGE_SCANS * NW <= 32, "a lane per word, two rows of lanes");
-        const unsigned long long mk = lane < RANGE_SCANS * NW ? lead_mask[lane] : 0ull;
-        const int c = __builtin_popcountll(mk);
-        int upto = c;                                   // leading rows in words 0 .. lane
+    // n-th leading row of the range (counted from its first row; -1: it has not as many) and the rows of its block, up to the next
+    // leading row or the end of the batch.  Lane j counts word j.
+    struct Block { int at, rows; };
+    auto block_of = [&](int n) -> Block {
+        static_assert(LOOK / 64 <= 32, "a lane per word, two rows of lanes");
+        const unsigned long long mk = lane < LOOK / 64 ? lead_mask[lane] : 0ull;
+        const int own = min(64, r_end - r_begin - 64 * lane);      // rows of the word that are the range's
+        const int c = own > 0 ? __builtin_popcountll(mk << (64 - own)) : 0;
+        int upto = c;                                              // leading rows in words 0 .. lane
         upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
         upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xf, 0xf, false);
         upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xf, 0xf, false);
         upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xf, 0xf, false);
         upto += __builtin_amdgcn_update_dpp(0, upto, 0x142, 0xa, 0xf, false);   // row_bcast:15 into the second row
-        if (n >= __builtin_amdgcn_readlane(upto, 31)) return -1;
+        if (n >= __builtin_amdgcn_readlane(upto, 31)) return {-1, 0};
+        auto word_of = [&](int j) {
+            const unsigned lo = __builtin_amdgcn_readlane((unsigned)mk, j), hi = __builtin_amdgcn_readlane((unsigned)(mk >> 32), j);
+            return ((unsigned long long)hi << 32) | lo;
+        };
         const int word = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(n < upto));
         n -= __builtin_amdgcn_readlane(upto - c, word);
-        const unsigned lo = __builtin_amdgcn_readlane((unsigned)mk, word), hi = __builtin_amdgcn_readlane((unsigned)(mk >> 32), word);
-        const int before = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));   // set bits below this lane's
-        const unsigned long long m2 = ((unsigned long long)hi << 32) | lo;
-        return r_begin + 64 * word + (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(((m2 >> lane) & 1ull) && before == n));
+        const unsigned long long m = word_of(word);
+        const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));   // set bits below this lane's
+        const int bit = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(((m >> lane) & 1ull) && before == n));
+        const unsigned long long rest = m & (~1ull << bit), later = __builtin_amdgcn_ballot_w64(mk != 0ull) & (~1ull << word);
+        int end = LOOK;
+        if (rest) end = 64 * word + (int)__builtin_ctzll(rest);
+        else if (later) { const int j = (int)__builtin_ctzll(later); end = 64 * j + (int)__builtin_ctzll(word_of(j)); }
+        return {64 * word + bit, end - 64 * word - bit};
     };
     const int Nkv = a.Hkv * D;
     const long long n_blocks = a.n_slots / a.bs;
@@ -176,28 +192,12 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
     }
 
   for (int turn = which;; turn += wgs) {
-    const int t0 = leader(turn);
-    if (t0 < 0) break;
-    if (turn != which) __syncthreads();      // everyone is done with the tiles and masks of the block before
-    const int sq = a.seq[t0], p0 = a.pos[t0];
+    const Block block = block_of(turn);
+    if (block.at < 0) break;
+    if (turn != which) __syncthreads();      // everyone is done with the tiles of the block before
+    const int t0 = r_begin + block.at, nrows = block.rows;
+    const int sq = __builtin_amdgcn_readfirstlane(row_seq[block.at]), p0 = __builtin_amdgcn_readfirstlane(row_pos[block.at]);
     const bool row_ok = sq >= 0 && sq < a.n_seqs && p0 >= 0;
-    // rows of the block: up to the next multiple of RBG, as long as the run continues
-    int nrows = 1;
-    if (row_ok) {
-        const int limit = RBG - (p0 % RBG);
-        bool cont = tid == 0;
-        if (tid > 0 && tid < limit && t0 + tid < a.T) cont = a.seq[t0 + tid] == sq && a.pos[t0 + tid] == p0 + tid;
-        const unsigned long long mk = __builtin_amdgcn_ballot_w64(cont);
-        if (lane == 0 && w < NW / 2) run_mask[w] = mk;
-        __syncthreads();
-        nrows = 0;
-#pragma unroll
-        for (int ww = 0; ww < NW / 2; ++ww) {
-            const unsigned long long mw = run_mask[ww];
-            if (nrows == 64 * ww) nrows += mw == ~0ull ? 64 : __builtin_ctzll(~mw);
-        }
-        nrows = __builtin_amdgcn_readfirstlane(nrows);
-    }
     int n_ctx = 0;
     if (row_ok) n_ctx = (int)((long long)p0 + nrows < cap ? (long long)p0 + nrows : cap);
     // this workgroup's part of the context: blocks c_lo .. c_hi - 1 of 32 positions (all of them without parts)
@@ -478,7 +478,7 @@ BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts)
     // us, 32/8 heads, such ranges | the ranges before them (128 / G rows, halved until 2048 workgroups) | now: 2048 rows and 32 single
     // rows at 4096 positions 1690 | 825 | 274, 1024 and 16 at 8192 1635 | 800 | 317, 4 x 512 and 32 at 4096 1730 | 905 | 299, in
     // parts 1490 | 904 | 291; 5 x 61 rows at 8190 442 | 325 | 229; equal runs the same (4 x 1024 rows at 8192 622 | 1280 | 584).
-    const int most = RANGE_SCANS * 64 * p.waves;
+    const int most = LOOKED_OVER * p.waves - (rbg + 63) / 64 * 64;   // (they look rbg rows further)
     int ranges = (T + most - 1) / most;
     p.range = ((T + ranges - 1) / ranges + 63) / 64 * 64;
     ranges = (T + p.range - 1) / p.range;

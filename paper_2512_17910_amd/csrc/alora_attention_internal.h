@@ -18,11 +18,10 @@ struct AttnArgs {
 
 constexpr int MAX_PARTS = 32;   // of a row's context
 
-constexpr int RANGE_SCANS = 4;   // batch rows per thread of a row-block workgroup, of which it looks for those that lead a block
+constexpr int LOOKED_OVER = 256;   // batch rows per wavefront of which a row-block workgroup finds those that lead a block
 
 // How the row-block kernel cuts a batch: wavefronts per workgroup (row blocks of 32 * waves / G rows), batch rows per
-// range (a multiple of 64, at most RANGE_SCANS per thread), workgroups that share a range's row blocks (per K/V head and part),
-// parts of every block's context.
+// range (a multiple of 64), workgroups that share a range's row blocks (per K/V head and part), parts of every block's context.
 struct BlockPlan {
     int waves, range, wgs, splits;
 };

@@ -66,7 +66,7 @@ def test_no_workgroup_of_the_reader_takes_several_contexts_one_after_the_other(r
         assert chain == 1, (chain, blocks, waves, rows_per_range, wgs)
 
 
-def test_the_ranges_of_the_reader_fit_what_a_workgroup_looks_over():
+def test_the_cut_of_a_reader_call_and_its_workspace():
     rng = np.random.default_rng(5)
     sizes = [(int(np.exp(rng.uniform(0, np.log(2e5)))), int(rng.integers(1, 400)), int(rng.choice([1, 2, 4, 8])), int(rng.choice([1, 2, 8, 16])))
              for _ in range(60)] + [(1, 1, 8, 1), (1024, 1, 4, 1), (1025, 1, 4, 1), (2048, 1, 1, 64), (2049, 1, 1, 64)]
@@ -74,7 +74,8 @@ def test_the_ranges_of_the_reader_fit_what_a_workgroup_looks_over():
         for (T, n, G, n_kv), call in zip(sizes, launches_of([reader(entry, T, n, G * n_kv, n_kv) for T, n, G, n_kv in sizes])):
             assert call["status"] == 0
             _, waves, rows_per_range, wgs = cut_of(call)
-            assert rows_per_range % 64 == 0 and 64 <= rows_per_range <= 4 * 64 * waves and 1 <= wgs <= max(T, 1)
+            behind = -(-(32 * waves // G) // 64) * 64      # rows of the next range that a block may reach into
+            assert rows_per_range % 64 == 0 and 64 <= rows_per_range <= 256 * waves - behind and 1 <= wgs <= max(T, 1)
             ranges, parts = -(-T // rows_per_range), call["launches"][0]["grid"][0] // (-(-T // rows_per_range) * wgs * n_kv)
             assert call["launches"][0]["grid"][0] == ranges * wgs * n_kv * parts and 1 <= parts <= 32
             assert (parts > 1) == (len(call["launches"]) == 2)
