@@ -66,6 +66,13 @@ def test_no_workgroup_of_the_reader_takes_several_contexts_one_after_the_other(r
         assert chain == 1, (chain, blocks, waves, rows_per_range, wgs)
 
 
+def test_no_workgroup_takes_two_parts_one_after_the_other():
+    runs = UNEVEN["chunk-1024+16"]
+    (call,) = launches_of([reader("alora_paged_attention_suffix_split", 1040, len(runs), 32, 8)])
+    G, waves, rows_per_range, wgs = cut_of(call)
+    assert len(call["launches"]) == 2 and longest_chain(runs, G, waves, rows_per_range, wgs)[0] == 1
+
+
 def test_the_cut_of_a_reader_call_and_its_workspace():
     rng = np.random.default_rng(5)
     sizes = [(int(np.exp(rng.uniform(0, np.log(2e5)))), int(rng.integers(1, 400)), int(rng.choice([1, 2, 4, 8])), int(rng.choice([1, 2, 8, 16])))
