@@ -451,18 +451,26 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
   }
 }
 
-// How a batch is cut, from its sizes alone.  Long runs (more than 128 / G rows per sequence on average): eight wavefronts
-// where that still gives two workgroups per CU or the context is cut into parts anyway, else four.  Short runs: four, two
-// workgroups to a CU (a block of few rows is as long as its loads take, and one workgroup's start hides behind the
-// other's).  Measured, us, eight | four wavefronts: 4 x 2048 rows over 16K positions, 32/8 heads 2099 | 2216; 2 x 1024 over
-// 2-4K, 32/8 174 | 167; 2 x 512 over 2-4K, 32/8 116 | 104; 4 x 300 over 16K, 8/8 487 | 410; in parts, 4 x 64 rows over 16K
-// 108 | 123, 4 x 32 rows 104 | 78.
+// How a batch is cut, from its sizes alone.
+// Eight wavefronts share a context's copies among twice the rows and keep six tile pairs in LDS where four keep four, but a CU holds
+// one such workgroup: nothing covers its start and its stores.  They take
+//   - runs of 1024 rows on average, where that gives two workgroups per CU: the copies count, starts do not;
+//   - few short blocks, at most one per CU and all of them at once: only the depth of the copies counts;
+//   - long runs whose contexts are cut into parts.
+// us, eight | four wavefronts: 4 x 2048 rows at 16K positions, 32/8 heads 2211 | 2337, 4 x 1024 at 8192 591 | 619, 3 x 1300 at 5-6K 510 |
+// 510, 12 x 700 at 3K 537 | 525, 30 prompts of 200-600 153 | 140, 100 of 128 117 | 97, 200 of 30-90 107 | 88; 8 single rows at 16K
+// 330 | 390, 32 at 300 37 | 42, 4 x 64 rows at 16K, 8/8 heads 357 | 414; in parts, 4 x 64 rows over 16K 108 | 123, 4 x 32 104 | 78.
 BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts)
 {
     BlockPlan p = {4, 64, 1, 1};
     if (T <= 0) return p;
-    const bool long_runs = (long long)T * G > 128ll * n_seqs;
-    if (long_runs && (parts || (long long)T * G / 256 * Hkv >= 512)) p.waves = 8;
+    const bool long_runs = (long long)T * G > 128ll * n_seqs;   // longer than a block of four wavefronts
+    if (long_runs) {
+        if (parts || (T >= 1024ll * n_seqs && (long long)T * G / 256 * Hkv >= 512)) p.waves = 8;
+    } else if (!parts) {
+        const long long blocks8 = n_seqs + 2 * (((long long)T * G + 255) / 256);   // (a run of r rows lies in two with a chance of r G / 256)
+        if ((blocks8 < T ? blocks8 : T) * Hkv <= 256) p.waves = 8;
+    }
     const int rbg = 32 * p.waves / G;
     if (parts) {
         // parts of every block's context, one workgroup each, until there is one per CU (two of four wavefronts)

@@ -87,3 +87,13 @@ def test_the_cut_of_a_reader_call_and_its_workspace():
             assert call["launches"][0]["grid"][0] == ranges * wgs * n_kv * parts and 1 <= parts <= 32
             assert (parts > 1) == (len(call["launches"]) == 2)
             assert call["workspace"] == (T * G * n_kv * parts * 130 * 4 if parts > 1 else 0)
+
+
+@pytest.mark.parametrize("runs,n_q,n_kv,waves", [
+    ([(16383, 1)] * 8, 32, 8, 8), ([(1997, 4)] * 16, 32, 8, 8), ([(16320, 64)] * 4, 8, 8, 8), ([(8142, 50)] * 6, 8, 8, 8),       # few short blocks
+    ([(4095, 1)] * 64, 32, 8, 4), ([(16320, 64)] * 4, 32, 8, 4), ([(4091, 5)] * 32, 64, 8, 4),     # more than one per CU, or long runs
+    ([(0, 128)] * 100, 32, 8, 4), ([(2301, 700)] * 12, 32, 8, 4),                                  # prompts that start and store often
+    ([(14336, 2048)] * 4, 32, 8, 8), ([(7168, 1024)] * 4, 64, 8, 8)])
+def test_wavefronts_of_the_reader(runs, n_q, n_kv, waves):
+    (call,) = launches_of([reader("alora_paged_attention_suffix", sum(r for _, r in runs), len(runs), n_q, n_kv)])
+    assert cut_of(call)[1] == waves
