@@ -476,6 +476,7 @@ BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts)
         // parts of every block's context, one workgroup each, until there is one per CU (two of four wavefronts)
         const long long wgs = (long long)((T + rbg - 1) / rbg) * Hkv, want = p.waves == 8 ? 256 : 512;
         if (wgs < want) p.splits = (int)((want + wgs - 1) / wgs < MAX_PARTS ? (want + wgs - 1) / wgs : MAX_PARTS);
+        if (p.splits == 1) return plan_blocks(T, n_seqs, Hkv, G, false);   // nothing is cut: the call is the one without parts
     }
     // Ranges as long as a workgroup looks over at once, each with a workgroup per row block it can hold: T / rbg of long runs and
     // two more for every sequence (its first and its last block), as far as 2048 workgroups allow; where there are more

@@ -97,3 +97,14 @@ def test_the_cut_of_a_reader_call_and_its_workspace():
 def test_wavefronts_of_the_reader(runs, n_q, n_kv, waves):
     (call,) = launches_of([reader("alora_paged_attention_suffix", sum(r for _, r in runs), len(runs), n_q, n_kv)])
     assert cut_of(call)[1] == waves
+
+
+def test_a_reader_call_in_one_part_is_the_call_without_parts():
+    """The suffix_split call promises to be the suffix call, same launch, where nothing is cut."""
+    rng = np.random.default_rng(9)
+    sizes = [(2048, 2, 4, 8), (1024, 1, 8, 8), (4096, 4, 4, 8), (1600, 8, 8, 8), (256, 256, 8, 64), (4096, 256, 1, 16)]
+    sizes += [(int(rng.integers(500, 9000)), int(rng.integers(1, 300)), int(rng.choice([1, 2, 4, 8])), int(rng.choice([4, 8, 16]))) for _ in range(40)]
+    calls = [reader("alora_paged_attention_suffix" + e, T, n, G * n_kv, n_kv) for T, n, G, n_kv in sizes for e in ("_split", "")]
+    out = launches_of(calls)
+    whole = [(a, b) for a, b in zip(out[::2], out[1::2]) if len(a["launches"]) == 1]
+    assert len(whole) >= 20 and all(a == b for a, b in whole), [(a, b) for a, b in whole if a != b][:3]
