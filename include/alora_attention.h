@@ -73,7 +73,7 @@ int alora_paged_attention(const void *q, const void *k_cache, const void *v_cach
  * -- a few sequences with long contexts, the shape of an adapter evaluated on one long conversation
  * (Sec. 4.2): every row's context is cut into parts, one workgroup each (about 1024 workgroups, at
  * most 32 parts), the parts leave (running maximum, sum of weights, unnormalised output) in the
- * workspace and a second kernel combines them in part order.  Results equal those of
+ * workspace and a second kernel combines them in a fixed order.  Results equal those of
  * alora_paged_attention up to fp32 summation order and do not depend on timing.
  *   workspace  device, 16-byte aligned, >= alora_paged_attention_workspace_bytes() bytes (0 when the
  *              batch is large enough for one part: then this IS alora_paged_attention and the
@@ -89,7 +89,8 @@ int alora_paged_attention_split(const void *q, const void *k_cache, const void *
  * The same computation for the rows of a projected suffix (Sec. 2.3 / 4.2: the tokens of an aLoRA
  * request that are not served from the cache, attending over the cached prefix and over each other):
  * batch rows that follow each other with the same sequence id and consecutive positions are handled
- * in blocks of 128 / (n_q_heads / n_kv_heads) rows that load every cached row once, on bf16 matrix
+ * in blocks of 256 / G or 128 / G rows, G = n_q_heads / n_kv_heads (chosen from n_tokens, n_seqs and the head
+ * counts; cut at multiples of that of the position), that load every cached row once, on bf16 matrix
  * instructions (the softmax weights are rounded to bf16 for the weighted sum of V; scores, maxima
  * and sums stay fp32).  Any batch is accepted -- rows that do not continue a run form blocks of
  * their own -- and results equal those of alora_paged_attention within the bf16 tolerance; they do
@@ -104,10 +105,13 @@ int alora_paged_attention_suffix(const void *q, const void *k_cache, const void 
 /*
  * alora_paged_attention_suffix for batches with few row blocks -- the common aLoRA request: a short invocation
  * suffix over a long cached context (Sec. 4.2) -- where one workgroup per (row block, K/V head) would leave
- * most of the chip idle: every row block's context is cut into parts, one workgroup each (about 512
- * workgroups, at most 32 parts; one part when the batch has 512 or more (row block, K/V head) pairs: then
- * this IS alora_paged_attention_suffix and the workspace may be NULL), the parts leave (running maximum,
- * sum of weights, unnormalised output) in the workspace and a second kernel combines them in part order.
+ * most of the chip idle: every row block's context is cut into parts (at most 32), as many as
+ * give the chip one workgroup per compute unit with blocks of 256 / G rows, two with blocks of 128 / G.  One part
+ * when n_tokens alone gives that many (always from 512 (block of 128 / G rows, K/V head) pairs on): then
+ * alora_paged_attention_suffix_workspace_bytes returns 0, this IS alora_paged_attention_suffix, and the workspace
+ * may be NULL.  Otherwise the parts leave (running maximum, sum of weights, unnormalised output) in the workspace
+ * and a second kernel combines them in a fixed order.  The number of parts, and with it the workspace, depends on
+ * n_tokens, n_seqs and the head counts, and is not monotonic in them: ask for the dims of the call.
  * Results equal those of alora_paged_attention_suffix up to fp32 summation order and do not depend on timing.
  *   workspace  device, 16-byte aligned, >= alora_paged_attention_suffix_workspace_bytes() bytes; contents on
  *              entry irrelevant; calls that share it must be stream-ordered.  ALORA_EWORKSPACE otherwise.
