@@ -167,6 +167,8 @@ __global__ __launch_bounds__(DEC_THREADS, NTT > 2 ? 1 : 2) void decode_projectio
         // works the grouping out for itself, the first of them writes the entry's share of its results
         const int e = (int)blockIdx.x / g.prep_ranges, range = (int)blockIdx.x - e * g.prep_ranges;
         int grp, cnt;
+        if (e == 0 && range == 0)   // entries no workgroup stands for
+            for (int i = g.prep_wgs / g.prep_ranges + threadIdx.x; i < g.group.n_blocks; i += DEC_THREADS) g.group.blocktab[i] = make_int4(-1, 0, 0, 0);
         const int *rows = group_small(g.group, g.T, g.L, e, range == 0, scr, grp, cnt);
         if (grp < 0 || grp >= g.L) return;   // unused entry or the rows that keep the base output
         const int rk = g.ranks.r[grp];
@@ -216,8 +218,9 @@ int launch_decode_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEv
     g.T = f.T; g.H = f.H; g.N = f.N; g.L = f.L; g.r = f.r;
     const int units = f.H / 64;
     g.ntiles = (f.N + DEC_FEATURES - 1) / DEC_FEATURES;
-    // One workgroup per compute unit, shrink workgroups included (a unit that got two took twice as long), hence 200
-    // for the projection.  Four layers of 4096 -> 6144 at one row, us: 144 workgroups 80, 192 73, 240 81, 384 78;
+    // One workgroup per compute unit, shrink workgroups of a few adapters included (a unit that got two took twice as long),
+    // hence 200 for the projection.  (The shrink has two for every 32 rows of an adapter, at most two per row, and its workgroups come
+    // first: 64 rows of 32 adapters each get to 262 in all.)  Four layers of 4096 -> 6144 at one row, us: 144 workgroups 80, 192 73, 240 81, 384 78;
     // 3072 -> 5120 at eight rows: 160 67, 200 65, 240 70; 8192 -> 10240: 80 251, 160 160, 240 159, 320 174.
     g.splits = std::max(1, std::min(std::min(8, units / DEC_WAVES), 200 / g.ntiles));   // (a slice per wavefront at least)
     g.units_per_split = (units + g.splits - 1) / g.splits;
@@ -227,7 +230,7 @@ int launch_decode_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEv
     const int ranges = f.L > 0 && units >= 2 ? 2 : 1;
     g.prep_units = (units + ranges - 1) / ranges;
     g.prep_ranges = (units + g.prep_units - 1) / g.prep_units;
-    g.prep_wgs = f.n_blocks * g.prep_ranges;
+    g.prep_wgs = used_blocks(f) * g.prep_ranges;
     g.partial = f.partial; g.S = (float *)f.S;
     g.group = GroupSmallArgs{f.aid, f.seg, f.pos, f.start, f.active, f.aeff, f.perm, f.offsets, f.blocktab, f.n_blocks, f.block_rows};
     g.ranks = f.ranks;

@@ -170,7 +170,7 @@ __global__ __launch_bounds__(1024) void finish_bf16_kernel(const float *__restri
 template <int SPLITS>
 static void launch_finish(const Fwd &f, const PtrTable &B, int s_splits, const int32_t *block_rows, bool s_f32)
 {
-    const dim3 grid(f.n_blocks, (f.N + FIN_COLS - 1) / FIN_COLS);
+    const dim3 grid(used_blocks(f), (f.N + FIN_COLS - 1) / FIN_COLS);
     hipLaunchKernelGGL(finish_bf16_kernel<SPLITS>, grid, dim3(1024), 0, f.stream, (const float *)f.partial,
                        f.S, s_splits, s_f32, B, f.ranks, (const bf16_t *)f.bias, f.perm, block_rows, f.blocktab, f.slot, (bf16_t *)f.q, (bf16_t *)f.kc,
                        (bf16_t *)f.vc, f.T, f.Nq, f.Nkv, f.L, f.r, f.rope_cos, f.rope_sin, f.pos, f.rope_positions);

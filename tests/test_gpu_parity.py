@@ -475,3 +475,32 @@ def test_fp32_tiles_and_batch_sizes(kw):
 def test_few_rows(rows, kw):
     lens = (rows,) if rows < 4 else (rows - 3, 1, 2)
     _check_full(wl.small_mixed("bf16", seed=31, seq_lens=lens, pad_every=7, **kw))
+
+
+# The few-row kernel with no adapters, and with more than its rows can use: the block-table entries no workgroup stands for are marked
+# unused in whatever the workspace held, which a later layer under another tiling walks (reuse_grouping).
+# Bounds: those of every bf16 case in _check_full.
+@pytest.mark.parametrize("rows", [1, 5, 33, 64])
+@pytest.mark.parametrize("n_adapters", [0, 128])
+def test_few_rows_with_no_adapters_and_with_many(rows, n_adapters, tuning):
+    lens = (rows,) if rows < 4 else (rows - 3, 1, 2)
+    w = wl.small_mixed("bf16", seed=33, seq_lens=lens, rank=8, n_adapters=max(n_adapters, 1))
+    if n_adapters == 0:
+        w.n_adapters = 0; w.A = []; w.B = []
+        w.token_adapter_ids[:] = -1
+    db = DeviceBatch(w)
+    db.ws.fill_(0x01)
+    _check_full(w, db)
+    first = raw_bits(db.q).copy()
+    tuning(2, 1)
+    fresh = DeviceBatch(w)
+    fresh.forward()
+    db.reset()
+    ab.alora_qkv_forward_ex(db.x, db.aid, db.start, db.W, db.A, db.B, db.q, db.kc, db.vc, db.slot, w.block_size, db.dims, db.ws,
+                            reuse_grouping=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(raw_bits(db.q), raw_bits(fresh.q)) and np.array_equal(raw_bits(db.kc), raw_bits(fresh.kc))
+    tuning(0, 0)
+    db.reset()
+    db.forward()
+    assert np.array_equal(raw_bits(db.q), first)

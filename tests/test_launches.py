@@ -22,6 +22,19 @@ def test_a_tuning_override_during_a_call_leaves_the_call_whole(T):
     assert torn == plain and after == plain, (kernels(plain), kernels(torn))
 
 
+@pytest.mark.parametrize("T,hidden", [(1, 4096), (3, 64), (40, 4096), (64, 4096), (65, 4096)])
+def test_a_few_rows_start_no_workgroups_for_adapters_they_cannot_use(T, hidden):
+    """An entry of the block table holds at least one row: at most T of its ceil(T / 32) + L + 1 are in use."""
+    for call, L in zip(launches_of([dict(QKV_8B, T=T, hidden=hidden, n_adapters=L) for L in (1, 8, 32, 128)]), (1, 8, 32, 128)):
+        entries = min(-(-T // 32) + L + 1, T)
+        if T <= 64:
+            assert kernels(call) == ["decode_projection_kernel", "finish_bf16_kernel"]
+            ranges = 2 if hidden > 64 else 1
+            projection = launches_of([dict(QKV_8B, T=T, hidden=hidden, n_adapters=0)])[0]["launches"][0]["grid"][0] - min(-(-T // 32) + 1, T)
+            assert call["launches"][0]["grid"][0] == projection + ranges * entries
+        assert call["launches"][1]["grid"][0] == entries, call["launches"][1]
+
+
 # ---- the row-block reader ------------------------------------------------------------------------
 def reader(entry, T, n_seqs, n_q, n_kv, capacity=16384):
     return dict(op="attention", entry=entry, dtype=1, n_tokens=T, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=128, n_seqs=n_seqs,
