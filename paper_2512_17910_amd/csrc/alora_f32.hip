@@ -72,8 +72,8 @@ __global__ __launch_bounds__(F32_THREADS) void shrink_f32_kernel(const float *__
 // x[row c][4g .. 4g+3] (one 16-byte load) and W[4g+j][4c .. 4c+3], j = 0..3; multiplication j of feature tile e
 // takes element j of the former and element e of load j of the latter, so the 64 features of the tile are
 // 4c + e.  Partial sums of the wavefronts meet in LDS and are added in fixed order.
-// MT = 4 where that alone fills the chip (a weight element then serves 64 rows), else 1: the call is as long as
-// its chain of round trips and wants many short workgroups.
+// MT = 1 for small calls, as long as their chain of round trips: many short workgroups.  MT = 4 where the products count: a weight
+// element serves 64 rows, but 64 KB of partial sums leave a CU two workgroups.  MT = 2 between (see launch_gemm_f32).
 template <int MT>
 __global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(
     const float *__restrict__ x, const float *__restrict__ W, const float *__restrict__ bias, PtrTable B,
@@ -233,7 +233,13 @@ static void launch_gemm_f32_rows(const Fwd &f, const PtrTable &B)
 int launch_gemm_f32(const Fwd &f, const PtrTable &B)
 {
     if (f.T == 0) return 0;
-    if ((long long)((f.T + 63) / 64) * ((f.N + 63) / 64) >= 256) launch_gemm_f32_rows<4>(f, B);
+    // us for MT = 1 | 2 | 4 (and the 64 x 64 LDS tile before them): 256 -> 512, two layers, 1500 rows 28 | 30 | 33 (49), 2048 rows 32 | 31 |
+    // 33 (49), 6000 rows 69 | 70 | 81 (73), 16384 rows 148 | 137 | 154 (145); 1024 -> 1536, two layers, 512 rows 61 | 62 | 65 (141), 1024
+    // rows 115 | 95 | 115 (158), 4096 rows 385 | 322 | 309 (366); 4096 -> 6144, 100 rows 102 | 94 | 108 (281), 256 rows 214 | 147 | 174
+    // (286), 512 rows 437 | 338 | 323 (386), 2048 rows 1822 | 1212 | 973 (1308).
+    const long long tiles = (f.N + 63) / 64, tiles32 = (f.T + 31) / 32 * tiles, tiles64 = (f.T + 63) / 64 * tiles;
+    if (tiles64 >= 768 && f.H >= 1024 && tiles64 * f.H >= 5ll << 18) launch_gemm_f32_rows<4>(f, B);
+    else if (tiles32 >= 400) launch_gemm_f32_rows<2>(f, B);
     else launch_gemm_f32_rows<1>(f, B);
     return (int)hipGetLastError();
 }

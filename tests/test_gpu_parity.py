@@ -456,11 +456,12 @@ def test_per_module_factors_as_block_structured_adapters(dtype, rank, seq_lens):
 
 # fp32 projection: one row; a row tile less / exactly / more than full; the largest batch whose grouping rides in the
 # shrink's launch and the next one; hidden sizes that end inside a block of 16 and give some wavefronts nothing; the
-# tile of 64 rows (from 256 tiles on) with a ragged last tile.  Bounds: those of every fp32 case in _check_full.
+# tiles of 32 and of 64 rows with a ragged last tile.  Bounds: those of every fp32 case in _check_full.
 @pytest.mark.parametrize("kw", [dict(seq_lens=(1,), hidden=4), dict(seq_lens=(7, 8), hidden=20), dict(seq_lens=(16,), hidden=36, rank=64),
                                 dict(seq_lens=(9, 8), hidden=260, rank=3), dict(seq_lens=(200, 56), rank=7), dict(seq_lens=(200, 57)),
-                                dict(seq_lens=(1000, 30), hidden=52, n_q_heads=12, n_kv_heads=2, head_dim=68, rank=24)],
-                         ids=["1", "15", "16", "17", "256", "257", "tiles-of-64"])
+                                dict(seq_lens=(1000, 30), hidden=52, n_q_heads=12, n_kv_heads=2, head_dim=68, rank=24),
+                                dict(seq_lens=(2900, 30), hidden=1700, n_q_heads=12, n_kv_heads=2, head_dim=68, rank=24)],
+                         ids=["1", "15", "16", "17", "256", "257", "tiles-of-32", "tiles-of-64"])
 def test_fp32_tiles_and_batch_sizes(kw):
     _check_full(wl.small_mixed("f32", seed=21, **kw))
 

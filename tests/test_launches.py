@@ -35,6 +35,16 @@ def test_a_few_rows_start_no_workgroups_for_adapters_they_cannot_use(T, hidden):
         assert call["launches"][1]["grid"][0] == entries, call["launches"][1]
 
 
+def test_rows_per_tile_of_the_fp32_projection():
+    sizes = {(64, 256, 2, 4): 1, (1500, 256, 4, 64): 1, (6000, 256, 4, 64): 2, (32768, 256, 4, 64): 2, (1030, 52, 12, 68): 2, (160, 4096, 32, 128): 2,
+             (2930, 1700, 12, 68): 4, (512, 4096, 32, 128): 4}
+    calls = [dict(op="forward", dtype=0, T=T, hidden=h, n_q_heads=hq, n_kv_heads=8 if hq == 32 else 2, head_dim=d, n_adapters=0, rank=0,
+                  n_segments=1, n_slots=16) for T, h, hq, d in sizes]
+    for call, (size, mt) in zip(launches_of(calls), sizes.items()):
+        l = [l for l in call["launches"] if l["kernel"] == "gemm_f32_kernel"]
+        assert len(l) == 1 and l[0]["ints"] == [mt] and l[0]["grid"][1] == -(-size[0] // (16 * mt)), (size, l)
+
+
 # ---- the row-block reader ------------------------------------------------------------------------
 def reader(entry, T, n_seqs, n_q, n_kv, capacity=16384):
     return dict(op="attention", entry=entry, dtype=1, n_tokens=T, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=128, n_seqs=n_seqs,
