@@ -10,6 +10,7 @@ import torch
 from oracle import attention as oatt
 from paper_2512_17910_amd import binding as ab
 from paper_2512_17910_amd import workloads as wl
+from test_launches import CUTS
 from gpu_util import TOL, maxnorm_rel, raw_bits, to_dev, to_f64
 
 pytestmark = pytest.mark.gpu
@@ -420,9 +421,8 @@ def test_suffix_call_causal_boundaries_bad_indices_and_shapes():
         ab.alora_paged_attention_suffix(d3.q, d3.kc, d3.vc, d3.bt, d3.seq, d3.pos, d3.out, d3.dims)
 
 
-# The row-block kernel's cuts: eight wavefronts (long runs, enough blocks of 256 / G rows), four wavefronts with long runs (a
-# range of rows that holds the ends of one sequence and the start of the next goes to two workgroups), ranges of 64 rows
-# in blocks of 256 (G = 1), runs that end one row past and one row before a block; contexts cut into parts with long runs.
+# Long runs on workgroups of four wavefronts (blocks of 128 / G rows) that end one row past and one row before a block or a
+# sequence's neighbour, on eight where the contexts are cut into parts.
 # Bound: the reader's (softmax weights and outputs in bf16).
 @pytest.mark.parametrize("group,n_kv,lens,parts", [(1, 64, [1000, 517, 531], False), (8, 16, [385, 1, 639], False), (4, 2, [700, 257, 95], False),
                                                    (2, 2, [129, 640, 127], False), (4, 2, [200, 65, 63], True), (8, 1, [1100, 33, 900], True)])
@@ -468,4 +468,26 @@ def test_suffix_row_blocks_that_lie_unevenly(kind, group, n_kv, parts):
         out = to_f64(_run_suffix(d))
     assert np.isfinite(out).all()
     pick = np.unique(np.r_[np.arange(0, c.T, 29), np.arange(c.T - 45, c.T), np.arange(0, 75, 2)])
+    assert maxnorm_rel(out[pick], d.oracle(rows=pick)) <= TOL["bf16"]
+
+
+# Every instantiation of the row-block kernel (group size, four or eight wavefronts, block size a power of two or not) with whole
+# contexts and with parts; that these sizes lead to them is checked where the launches are recorded.
+# Bound: the reader's (softmax weights and outputs in bf16).
+@pytest.mark.parametrize("group,n_kv,block_size,lens,rows,parts,waves", CUTS)
+def test_suffix_every_cut(group, n_kv, block_size, lens, rows, parts, waves):
+    c = wl.attention_case(f"cut-g{group}w{waves}", "bf16", lens, rows, group * n_kv, n_kv, 128, block_size, seed=wl.SEED ^ (980 + group + waves))
+    print(f"[case] {c.name} T={c.T} rows={rows} parts={parts}", flush=True)
+    d = DeviceCase(c)
+    if parts:
+        ws = torch.full((max(16, ab.alora_paged_attention_suffix_workspace_bytes(d.dims)),), 0xff, dtype=torch.uint8, device="cuda")
+        ab.alora_paged_attention_suffix_split(d.q, d.kc, d.vc, d.bt, d.seq, d.pos, d.out, d.dims, ws)
+        torch.cuda.synchronize()
+        out = to_f64(d.out)
+    else:
+        out = to_f64(_run_suffix(d))
+    assert np.isfinite(out).all()
+    ends = np.cumsum(rows)
+    pick = np.unique(np.r_[np.arange(0, c.T, 61), ends - 1, ends[:-1], [1, 31, 32, 63, 64, 127, 128, 255, 256]])
+    pick = pick[pick < c.T]
     assert maxnorm_rel(out[pick], d.oracle(rows=pick)) <= TOL["bf16"]

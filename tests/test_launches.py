@@ -46,9 +46,9 @@ def test_rows_per_tile_of_the_fp32_projection():
 
 
 # ---- the row-block reader ------------------------------------------------------------------------
-def reader(entry, T, n_seqs, n_q, n_kv, capacity=16384):
+def reader(entry, T, n_seqs, n_q, n_kv, block_size=16):
     return dict(op="attention", entry=entry, dtype=1, n_tokens=T, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=128, n_seqs=n_seqs,
-                max_blocks=capacity // 16, block_size=16, n_slots=1 << 20)
+                max_blocks=1024, block_size=block_size, n_slots=1 << 20)
 
 
 def cut_of(call):
@@ -131,3 +131,32 @@ def test_a_reader_call_in_one_part_is_the_call_without_parts():
     out = launches_of(calls)
     whole = [(a, b) for a, b in zip(out[::2], out[1::2]) if len(a["launches"]) == 1]
     assert len(whole) >= 20 and all(a == b for a, b in whole), [(a, b) for a, b in whole if a != b][:3]
+
+
+# (group, K/V heads, block size, contexts, query rows, in parts, wavefronts): every instantiation of the row-block kernel, where the sizes
+# lead to it; test_gpu_attention.py runs them.
+CUTS = [
+    # long runs, whole contexts: eight wavefronts from 1024 rows a sequence and two workgroups per CU on, else four
+    (1, 64, 16, [2100], [2079], False, 8), (2, 64, 16, [1300, 900], [1290, 800], False, 8), (4, 32, 12, [1200], [1100], False, 8),
+    (8, 16, 16, [1153], [1030], False, 8), (8, 16, 16, [900, 400], [700, 399], False, 4), (1, 2, 16, [700, 260], [640, 258], False, 4),
+    (2, 2, 20, [129, 640, 127], [111, 549, 109], False, 4), (4, 2, 16, [700, 257, 95], [600, 221, 82], False, 4),
+    # short runs, whole contexts: eight where their blocks fit the chip at once, else four
+    (1, 8, 16, [300, 900, 41], [100, 127, 3], False, 8), (2, 4, 12, [500, 77], [60, 1], False, 8), (4, 8, 16, [1000, 513, 64], [32, 5, 1], False, 8),
+    (8, 2, 16, [400, 30, 199], [16, 1, 9], False, 8), (1, 64, 16, [130, 90, 60, 200, 155], [3, 1, 60, 99, 2], False, 4),
+    (2, 64, 16, [130, 90, 60, 200, 155], [3, 1, 60, 64, 2], False, 4), (4, 64, 20, [130, 90, 60, 200, 155], [3, 1, 31, 32, 2], False, 4),
+    (8, 64, 16, [130, 90, 60, 200, 155], [3, 1, 16, 9, 2], False, 4),
+    # contexts in parts: eight wavefronts for long runs, four for short ones
+    (1, 2, 16, [900, 500], [300, 201], True, 8), (2, 2, 12, [900, 500], [150, 65], True, 8), (4, 2, 16, [200, 65, 63], [171, 56, 54], True, 8),
+    (8, 1, 16, [1100, 33, 900], [943, 28, 771], True, 8), (1, 2, 20, [1500, 300], [100, 28], True, 4), (2, 2, 16, [1500, 300], [40, 64], True, 4),
+    (4, 2, 16, [2000, 301], [32, 17], True, 4), (8, 1, 16, [1700, 64], [16, 1], True, 4)]
+
+
+def test_the_reader_cases_run_on_the_gpu_reach_every_instantiation():
+    calls = launches_of([reader("alora_paged_attention_suffix" + ("_split" if parts else ""), sum(rows), len(rows), g * n_kv, n_kv, block_size=bs)
+                         for g, n_kv, bs, lens, rows, parts, waves in CUTS])
+    for call, (g, n_kv, bs, lens, rows, parts, waves) in zip(calls, CUTS):
+        assert cut_of(call)[:2] == (g, waves) and (len(call["launches"]) == 2) == parts, (g, n_kv, rows, parts, call["launches"])
+    got = {(tuple(c["launches"][0]["ints"]), len(c["launches"]) == 2) for c in calls}
+    for parts in (False, True):
+        assert {(i[0], i[1]) for i, p in got if p == parts} == {(g, w) for g in (1, 2, 4, 8) for w in (4, 8)}
+        assert {(i[1], i[2]) for i, p in got if p == parts} == {(w, pow2) for w in (4, 8) for pow2 in (0, 1)}
