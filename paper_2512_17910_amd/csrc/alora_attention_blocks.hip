@@ -479,11 +479,11 @@ BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts)
         if (p.splits == 1) return plan_blocks(T, n_seqs, Hkv, G, false);   // nothing is cut: the call is the one without parts
     }
     // Ranges as long as a workgroup looks over at once, each with a workgroup per row block it can hold: T / rbg of long runs and
-    // two more for every sequence (its first and its last block), as far as 2048 workgroups allow; where there are more
-    // blocks than that, a workgroup takes several.  In parts, where a workgroup per rbg rows fills the chip and one that finds no
-    // block waits for a place on it: one more for every sequence unless T is whole blocks for each, and 4096 in all.  (us, in parts,
-    // without | with one more: 3 x 150 rows at 9000, 8/8 heads 83 | 73, 5 x 200 at 30K 430 | 341, 1024 and 16 single rows at 8192,
-    // 32/8 heads 375 | 310; 4 x 64 at 4096 42.5 | 44.1.)
+    // two more for every sequence (its first and its last block; one where there are several ranges, since few sequences start in
+    // each), as far as 2048 workgroups allow; where there are more blocks than that, a workgroup takes several.  In parts, where a
+    // workgroup per rbg rows fills the chip and one that finds no block waits for a place on it: one more for every sequence unless
+    // T is whole blocks for each, and 4096 in all.  (us, in parts, without | with one more: 3 x 150 rows at 9000, 8/8 heads 83 | 73,
+    // 5 x 200 at 30K 430 | 341, 1024 and 16 single rows at 8192, 32/8 heads 375 | 310; 4 x 64 at 4096 42.5 | 44.1.)
     // How rows lie is not known here, and one workgroup with several blocks is the whole call's length: with ranges of at most a
     // block's rows, each shared by one or two workgroups, decode rows beside a prompt chunk were up to 16 contexts in a row.
     // us, 32/8 heads, such ranges | the ranges before them (128 / G rows, halved until 2048 workgroups) | now: 2048 rows and 32 single
@@ -496,7 +496,8 @@ BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts)
     const int rows = p.range < T ? p.range : T;
     const long long blocks = (rows + rbg - 1) / rbg, heads = (long long)ranges * Hkv * p.splits;
     const bool whole = n_seqs > 0 && T % n_seqs == 0 && T / n_seqs % rbg == 0;   // every sequence may bring whole blocks
-    const long long ends = p.splits > 1 ? (whole ? 0 : n_seqs) : 2ll * n_seqs, spare = p.splits > 1 ? 4096 / heads - blocks : 2048 / heads;
+    const long long ends = p.splits > 1 ? (whole ? 0 : n_seqs) : ranges > 1 ? n_seqs + 1ll : 2ll * n_seqs;
+    const long long spare = p.splits > 1 ? 4096 / heads - blocks : 2048 / heads;
     const long long wgs = blocks + (spare < 0 ? 0 : spare < ends ? spare : ends);
     p.wgs = (int)(wgs < rows ? wgs : rows);
     return p;
