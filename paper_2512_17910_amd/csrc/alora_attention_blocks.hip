@@ -34,6 +34,7 @@
 // unit 38 % and vector unit 42 % of the cycles, which add up more than they overlap, and the copies.  Running the
 // scores of the next block and the output of the one before it between the vector instructions of the softmax
 // (three blocks in flight, one matrix product per four vector instructions) was built and measured: 2470 us.
+#include <numeric>
 #include "alora_attention_internal.h"
 
 namespace alora {
@@ -491,13 +492,22 @@ BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts)
     // parts 1490 | 904 | 291; 5 x 61 rows at 8190 442 | 325 | 229; equal runs the same (4 x 1024 rows at 8192 622 | 1280 | 584).
     const int most = LOOKED_OVER * p.waves - (rbg + 63) / 64 * 64;   // (they look rbg rows further)
     int ranges = (T + most - 1) / most;
-    p.range = ((T + ranges - 1) / ranges + 63) / 64 * 64;
+    const int unit = rbg > 64 ? rbg : 64;
+    p.range = ((T + ranges - 1) / ranges + unit - 1) / unit * unit;
     ranges = (T + p.range - 1) / p.range;
     const int rows = p.range < T ? p.range : T;
     const long long blocks = (rows + rbg - 1) / rbg, heads = (long long)ranges * Hkv * p.splits;
     const bool whole = n_seqs > 0 && T % n_seqs == 0 && T / n_seqs % rbg == 0;   // every sequence may bring whole blocks
-    const long long ends = p.splits > 1 ? (whole ? 0 : n_seqs) : ranges > 1 ? n_seqs + 1ll : 2ll * n_seqs;
-    const long long spare = p.splits > 1 ? 4096 / heads - blocks : 2048 / heads;
+    long long ends = p.splits > 1 ? (whole ? 0 : n_seqs) : ranges > 1 ? n_seqs + 1ll : 2ll * n_seqs, spare = p.splits > 1 ? 4096 / heads - blocks : 2048 / heads;
+    if (ranges > 1) {
+        // Workgroups go to the eight XCDs in turn, and on each to its four shader engines; one whose engine is full holds up all
+        // behind it.  Between the blocks of one range and the next, workgroups without any in other than whole turns leave places
+        // empty for as long as a block takes: 4 x 2048 rows at 16K positions, five ranges, 5 of them 2530 us, 8 of them 2216; 4 x 1024
+        // at 8192 813 and 591.  (Ranges are whole blocks for the same reason.)
+        const long long m = 32 / std::gcd(32, Hkv * p.splits);
+        ends = (ends + m - 1) / m * m;
+        spare = spare / m * m;
+    }
     const long long wgs = blocks + (spare < 0 ? 0 : spare < ends ? spare : ends);
     p.wgs = (int)(wgs < rows ? wgs : rows);
     return p;

@@ -109,6 +109,8 @@ def test_the_cut_of_a_reader_call_and_its_workspace():
             ranges, parts = -(-T // rows_per_range), call["launches"][0]["grid"][0] // (-(-T // rows_per_range) * wgs * n_kv)
             assert call["launches"][0]["grid"][0] == ranges * wgs * n_kv * parts and 1 <= parts <= 32
             assert (parts > 1) == (len(call["launches"]) == 2)
+            if ranges > 1:     # whole blocks, and whole turns over the chip's 32 shader engines of workgroups that may find none
+                assert rows_per_range % (32 * waves // G) == 0 and (wgs - rows_per_range * G // (32 * waves)) * n_kv * parts % 32 == 0
             assert call["workspace"] == (T * G * n_kv * parts * 130 * 4 if parts > 1 else 0)
 
 
