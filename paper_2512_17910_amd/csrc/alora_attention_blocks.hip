@@ -74,10 +74,9 @@ __device__ __forceinline__ void load_lds16(uint32_t lds_addr, const void *base, 
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voffset), "s"(base) : "memory");
 }
-// Exchanges between the four lanes of a column (lanes c, c+16, c+32, c+48), as assembly statements (the
-// builtin of the 32-lane swap returned its first result twice) with wait states on both sides, which the
-// compiler cannot place for an instruction it does not see.  Checked with in-bounds probes:
-//   v_permlane16_swap on two copies of x: ev <- x of the even 16-lane row of this lane's row pair, od <- the odd row's
+// Exchange between the two lanes of a column (lanes c, c+32), as an assembly statement (the builtin returned its
+// first result twice) with wait states on both sides, which the compiler cannot place for an instruction it does
+// not see.  Checked with an in-bounds probe:
 //   v_permlane32_swap on two copies of x: lo <- x of the lower 32 lanes, hi <- the upper 32 lanes'
 __device__ __forceinline__ void both_halves(float x, float &lo, float &hi)
 {

@@ -3,24 +3,26 @@
 // the same launch.  The finishing kernel adds the ranges, the low-rank term, rounds and stores.
 //
 // Such a call is as long as W takes to arrive, so the kernel is built around requesting W early and once:
-//   - an operand element passes through no LDS on its way to the matrix unit.  W is stored k-major while an MFMA
+//   - an element of W passes through no LDS on its way to the matrix unit.  W is stored k-major while an MFMA
 //     operand wants eight consecutive k of one feature per lane: a lane loads 16 bytes (eight features) of eight
 //     consecutive rows and turns the 8 x 8 block around in registers (one v_perm per two elements), so that
-//     MFMA f of eight takes feature 8 * (lane % 16) + f.  x needs no turning: a lane's 16 bytes are eight
-//     consecutive k of one token.
+//     MFMA f of eight takes feature 8 * (lane % 16) + f.
 //   - the wavefronts of a workgroup take different ranges of the hidden dimension (no element of W is loaded
 //     twice for a token tile, no barrier in the loop) and keep several 32-wide slices in flight in registers;
 //     their sums meet in LDS at the end and are added in fixed order.
 //   - the ends of a wavefront's range are the ends of its buffer descriptors: slices past them are requested
 //     like any other and come back as zeros without memory traffic, so the loop has no tail.
-//   - x arrives in whole 128-byte lines, eight lanes to a token's piece, and is turned into operands through LDS that
-//     a wavefront shares with no other.  (Loaded as the operand wants it, neighbouring lanes would read different
-//     rows: 16 bytes per clock and compute unit, measured, against 43 for the line pattern.)
+//   - x arrives in whole 128-byte lines, eight lanes to a token's piece, and becomes operands (eight consecutive k of
+//     one token per lane) through LDS that a wavefront shares with no other.  (Loaded as the operand wants it,
+//     neighbouring lanes would read different rows: 16 bytes per clock and compute unit, measured, against 43 for
+//     the line pattern.)
 // Token tiles of 16, 32, 48 or 64 rows: no matrix work is spent on rows a small batch does not have.
 // Measured, 4096 -> 6144 with 50 MB of W from memory: 16.0 us for the 256-row tile of the projection kernel at one
 // row, 11.5 us here (4.4 TB/s over the whole kernel; non-temporal loads of W included, 78.7 -> 71.0 us for four
-// layers); 8192 -> 10240, four layers at eight rows, 235 -> 160 us.  From 65 rows on W would be read once per token
-// tile, and the projection kernel's 256-row tile is the better one (128 rows: equal; 256 rows: 163 against 200 us).
+// layers); 8192 -> 10240, four layers at eight rows, 235 -> 160 us.  64 rows, four adapters, twelve layers (nothing of
+// W in the memory-side cache), 311 -> 287 us; with four layers, which that cache holds, the 256-row tile is the faster from
+// 41 rows on (64 rows 88 against 95).  From 65 rows on W would be read once per token tile, and the 256-row tile is the better
+// one (128 rows: equal; 256 rows: 163 against 200 us).
 #include <algorithm>
 #include "alora_internal.h"
 #include "alora_group_small.h"
