@@ -505,3 +505,22 @@ def test_few_rows_with_no_adapters_and_with_many(rows, n_adapters, tuning):
     db.reset()
     db.forward()
     assert np.array_equal(raw_bits(db.q), first)
+
+
+# The finishing kernel's tiles: entries of 1 to 33 rows of an adapter (half an entry per workgroup), ranks of one and of two 32-wide
+# rank tiles, full and partial, a feature tile that ends inside the 256.  Bounds: those of every bf16 case in _check_full.
+@pytest.mark.parametrize("rank", [8, 32, 40, 64])
+def test_finishing_kernel_at_the_edges_of_its_tiles(rank):
+    sizes = [1, 15, 16, 17, 31, 32, 33]
+    segs = [wl.Segment(s, 0, n, s - 1, 0) for s, n in enumerate(sizes)]      # the first is a base-model request
+    w = wl.assemble(f"entries-r{rank}", "bf16", 256, 5, 2, 40, 6, rank, 16, segs, sizes, seed=300 + rank, extra_blocks=2)
+    db = DeviceBatch(w)
+    _check_full(w, db)
+    # a row whose shrink result overflows fp32 keeps that to itself
+    first = raw_bits(db.q).copy()
+    row = sum(sizes[:4]) + 5
+    db.x[row] = 3e38
+    db.reset()
+    db.forward()
+    q = raw_bits(db.q)
+    assert not np.isfinite(to_f64(db.q)[row]).all() and np.array_equal(np.delete(q, row, 0), np.delete(first, row, 0))
