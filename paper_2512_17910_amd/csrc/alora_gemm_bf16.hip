@@ -69,9 +69,9 @@ struct GemmArgs {
     float *partial;   // split mode: [splits][T][N] fp32
     const bf16_t *bias;   // [N] or null: added to every row before rounding (fused mode)
     RankTable ranks;      // per adapter: B_a has ranks.r[a] rows
-    // split mode: the grid is one-dimensional, tiles8 workgroups per split, followed by `prep_wgs`
+    // the grid is one-dimensional: main_wgs workgroups for the tiles (of every split), in split mode followed by `prep_wgs`
     // workgroups that classify, group and shrink the batch (0: separate kernels did that)
-    int tiles8, splits, prep_wgs;
+    int main_wgs, splits, prep_wgs;
     int prep_ranges, prep_kper;   // ranges of the hidden dimension per block-table entry, and their width
     GroupSmallArgs prep;
     void *S_out;          // shrink result written by the prep workgroups ((hi, lo) form)
@@ -220,49 +220,52 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     // own L2: XCD k = blockIdx.x % 8 takes a contiguous range of a tile order that walks panels of
     // 4 token tiles, feature tile by feature tile, so that the ~32 tiles an XCD runs at a time form
     // a 4 x 8 patch sharing their token and weight slices in that L2.
-    // split mode: blockIdx.x = split * tiles8 + tile, then the prep workgroups (dispatched last, so
-    // that they take the compute units the projection leaves free)
-    int bx = (int)blockIdx.x, by = 0;
-    if (SPLIT) {
-        by = bx / g.tiles8;
-        bx -= by * g.tiles8;
-        if (by >= g.splits) {
-            if constexpr (SPLIT && NTW == 2) {
-                // One entry of the 32-row block table: group the batch, then the shrink of the block over
-                // the whole hidden dimension, out of this kernel's stages (token buffers, A buffers,
-                // reduction array, scratch).
-                static_assert(STAGE_BYTES >= (uint32_t)ShrinkLds<256, 1>::X_BYTES && STAGE_BYTES >= (uint32_t)ShrinkLds<256, 1>::A_BYTES &&
-                              STAGE_BYTES >= (uint32_t)ShrinkLds<256, 1>::RED_BYTES && STAGE_BYTES >= (GROUP_SMALL_SCRATCH + 4) * 4u,
-                              "stages hold the shrink's buffers");
-                // prep_ranges workgroups per entry, one per range of the hidden dimension; each works the
-                // grouping out for itself, the first of them writes the entry's share of its results
-                const int p = (int)blockIdx.x - g.tiles8 * g.splits;
-                const int e = p / g.prep_ranges, range = p - e * g.prep_ranges;
-                unsigned char *const stage0 = ring, *const stage1 = ring + STAGE_BYTES, *const stage2 = ring + 2 * STAGE_BYTES,
-                                    *const stage3 = ring + 3 * STAGE_BYTES, *const stage4 = ring + 4 * STAGE_BYTES;
-                int *scr = (int *)(ring + 5 * STAGE_BYTES);
-                int grp, cnt;
-                const int *rows = group_small(g.prep, g.T, g.L, e, range == 0, scr, grp, cnt);
-                if (grp < 0 || grp >= g.L) { PROBE_STAMP(7); return; }   // unused entry or the rows that keep the base output
-                const int kbeg = range * g.prep_kper;
-                shrink_rows<256, 1, false>(g.x, (const bf16_t *)A.p[grp], g.ranks.r[grp], rows, g.H, g.r,
-                                           (uint32_t)((size_t)g.T * g.H * 2), g.T, kbeg, min(g.H, kbeg + g.prep_kper), range,
-                                           g.prep_ranges, nullptr, g.S_out, stage0, stage1, stage2, stage3,
-                                           (float (*)[1][32][33])stage4, scr + GROUP_SMALL_SCRATCH);
-                PROBE_STAMP(7);   // grouping and shrink of this entry done
-            }
-            return;
+    // Split mode: the same over the list of (split, tile), split by split, then the prep workgroups (dispatched last, so
+    // that they take the compute units the projection leaves free).  An XCD's share of the whole list is at most 32 workgroups where the
+    // list has 256; shares of every split, rounded up each, made 33 of 81 tiles in three splits, a second round on seven of the eight XCDs
+    // (640 rows, 3072 -> 5120: the call 63.8 us, now 46.2; elsewhere within 1 %).
+    const int bx = (int)blockIdx.x;
+    int by = 0;
+    if (SPLIT && bx >= g.main_wgs) {
+        if constexpr (SPLIT && NTW == 2) {
+            // One entry of the 32-row block table: group the batch, then the shrink of the block over
+            // the whole hidden dimension, out of this kernel's stages (token buffers, A buffers,
+            // reduction array, scratch).
+            static_assert(STAGE_BYTES >= (uint32_t)ShrinkLds<256, 1>::X_BYTES && STAGE_BYTES >= (uint32_t)ShrinkLds<256, 1>::A_BYTES &&
+                          STAGE_BYTES >= (uint32_t)ShrinkLds<256, 1>::RED_BYTES && STAGE_BYTES >= (GROUP_SMALL_SCRATCH + 4) * 4u,
+                          "stages hold the shrink's buffers");
+            // prep_ranges workgroups per entry, one per range of the hidden dimension; each works the
+            // grouping out for itself, the first of them writes the entry's share of its results
+            const int p = bx - g.main_wgs;
+            const int e = p / g.prep_ranges, range = p - e * g.prep_ranges;
+            unsigned char *const stage0 = ring, *const stage1 = ring + STAGE_BYTES, *const stage2 = ring + 2 * STAGE_BYTES,
+                                *const stage3 = ring + 3 * STAGE_BYTES, *const stage4 = ring + 4 * STAGE_BYTES;
+            int *scr = (int *)(ring + 5 * STAGE_BYTES);
+            int grp, cnt;
+            const int *rows = group_small(g.prep, g.T, g.L, e, range == 0, scr, grp, cnt);
+            if (grp < 0 || grp >= g.L) { PROBE_STAMP(7); return; }   // unused entry or the rows that keep the base output
+            const int kbeg = range * g.prep_kper;
+            shrink_rows<256, 1, false>(g.x, (const bf16_t *)A.p[grp], g.ranks.r[grp], rows, g.H, g.r,
+                                       (uint32_t)((size_t)g.T * g.H * 2), g.T, kbeg, min(g.H, kbeg + g.prep_kper), range,
+                                       g.prep_ranges, nullptr, g.S_out, stage0, stage1, stage2, stage3,
+                                       (float (*)[1][32][33])stage4, scr + GROUP_SMALL_SCRATCH);
+            PROBE_STAMP(7);   // grouping and shrink of this entry done
         }
+        return;
     }
     int mt, nt;
     {
-        const int total = g.mtiles * g.ntiles, chunk = (total + 7) >> 3;
-        const int l = (bx & 7) * chunk + (bx >> 3);
+        const int tiles = g.mtiles * g.ntiles, total = SPLIT ? tiles * g.splits : tiles, chunk = (total + 7) >> 3;
+        int l = (bx & 7) * chunk + (bx >> 3);
         if (l >= total) return;  // grid is padded to a multiple of 8; uniform across the workgroup
         // (token tiles per panel.  Measured, L2-miss reads and kernel time at T = 8192, 8192 -> 10240 / T = 4096,
         // 4096 -> 6144: 4: 2.79 GB, 993 us / 351 MB, 180 us; 8: 2.50 GB, 993 us / 380 MB, 180 us; 2: 3.80 GB, 1019 us /
         // 636 MB, 182 us; 16: 4.15 GB, 1016 us / 619 MB, 183 us.)
         constexpr int PANEL = 4;
+        if (SPLIT) {
+            by = l / tiles;
+            l -= by * tiles;
+        }
         const int panel = l / (PANEL * g.ntiles), rem = l - panel * PANEL * g.ntiles;
         const int pm = min(PANEL, g.mtiles - PANEL * panel);
         nt = rem / pm;
@@ -893,11 +896,11 @@ static void launch_ntw(const GemmArgs &g, const PtrTable &B, const PtrTable &A, 
 {
     const dim3 block(GEMM_THREADS);
     if (g.splits > 1)
-        hipLaunchKernelGGL((alora_gemm_bf16_kernel<NTW, true>), dim3(g.tiles8 * g.splits + g.prep_wgs), block, 0, stream, g, B, A);
+        hipLaunchKernelGGL((alora_gemm_bf16_kernel<NTW, true>), dim3(g.main_wgs + g.prep_wgs), block, 0, stream, g, B, A);
     else if (NTW == 4 && g.rope_cos)
-        hipLaunchKernelGGL((alora_gemm_bf16_kernel<4, false, true>), dim3(g.tiles8), block, 0, stream, g, B, A);
+        hipLaunchKernelGGL((alora_gemm_bf16_kernel<4, false, true>), dim3(g.main_wgs), block, 0, stream, g, B, A);
     else
-        hipLaunchKernelGGL((alora_gemm_bf16_kernel<NTW, false>), dim3(g.tiles8), block, 0, stream, g, B, A);
+        hipLaunchKernelGGL((alora_gemm_bf16_kernel<NTW, false>), dim3(g.main_wgs), block, 0, stream, g, B, A);
 }
 
 // Decode-sized bf16 batches: classification, grouping and shrink run inside the projection kernel (up to 64 rows
@@ -942,8 +945,8 @@ int launch_gemm_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEven
     g.partial = f.partial;
     g.bias = (const bf16_t *)f.bias;
     g.ranks = f.ranks;
-    g.tiles8 = (g.mtiles * g.ntiles + 7) / 8 * 8;   // see the tile order in the kernel
     g.splits = plan.splits;
+    g.main_wgs = (g.mtiles * g.ntiles * g.splits + 7) / 8 * 8;   // see the tile order in the kernel
     const bool prep = f.route.prep_inside;
     // shrink ranges of the prep workgroups: about 1024 wide, at most 4, none empty
     const int want = std::max(1, std::min(4, f.H / 1024));
