@@ -114,6 +114,11 @@ __device__ __forceinline__ void set_lds_base(uint32_t lds_addr)
     // (one wait state between a write of M0 and an LDS-direct load)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" : : "s"(lds_addr) : "memory");
 }
+// the same from a 64-bit address, one copy
+__device__ __forceinline__ void load_lds16_global(uint32_t lds_addr, const void *p)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr), "v"(p) : "memory");
+}
 template <int IMM>
 __device__ __forceinline__ void load_lds16_imm(rsrc_t rsrc, uint32_t voffset, uint32_t soffset)
 {
@@ -211,7 +216,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     int *const arow = PAIRED ? (int *)(ring + 4 * X_AREA) : arow_s;
     int *const present = PAIRED ? (int *)(ring + 4 * X_AREA + 4 * BM) : present_s;
     int *const plist = PAIRED ? (int *)(ring + 4 * X_AREA + 4 * BM + 4 * ALORA_MAX_ADAPTERS) : plist_s;
-    int64_t *const slot_lds = PAIRED ? (int64_t *)(ring + 20 * 1024) : slot_s;
+    int64_t *const slot_lds = PAIRED ? (int64_t *)(ring + (ROPE ? 36 : 20) * 1024) : slot_s;
     int &n_present = PAIRED ? *(int *)(ring + 4 * X_AREA + 4 * BM + 8 * ALORA_MAX_ADAPTERS) : n_present_s;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -283,12 +288,17 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     // would also wait for every copy issued in between.
     int a_row = -1;
     int64_t slot_row = -1;
+    int pos_row = 0;
     if (!SPLIT && m0 + tid < g.T) {
         const int64_t *ps = g.slot + (m0 + tid);
         asm volatile("global_load_dwordx2 %0, %1, off" : "=v"(slot_row) : "v"(ps) : "memory");
         if (g.L > 0) {
             const int8_t *pa = g.aeff + (m0 + tid);
             asm volatile("global_load_sbyte %0, %1, off" : "=v"(a_row) : "v"(pa) : "memory");
+        }
+        if constexpr (ROPE) {
+            const int32_t *pp = g.pos + (m0 + tid);
+            asm volatile("global_load_dword %0, %1, off" : "=v"(pos_row) : "v"(pp) : "memory");
         }
     }
 
@@ -452,7 +462,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     int n_exp = 0;           // expand slices ahead of the base slices
     int epa = 0;             // expand slices per adapter
     if (!SPLIT) {
-        asm volatile("s_waitcnt vmcnt(%2)" : "+v"(a_row), "+v"(slot_row) : "n"(PRO) : "memory");
+        asm volatile("s_waitcnt vmcnt(%3)" : "+v"(a_row), "+v"(slot_row), "+v"(pos_row) : "n"(PRO) : "memory");
         if (a_row >= g.L) a_row = -1;   // (a workspace that holds no grouping of this batch: stay inside the tables)
         if constexpr (!PAIRED) slot_lds[tid] = slot_row;
         arow[tid] = a_row;
@@ -625,9 +635,13 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     // writes of four consecutive features, 16-byte reads along the row), so that global stores are
     // whole row segments: 64*NTW contiguous bytes of q_out or of one cache slot per token.
     __syncthreads();  // every wavefront has finished reading the K-slice stages
-    constexpr uint32_t STRIP_STEP = PAIRED ? 32768 : STAGE_BYTES;   // a wavefront's strip starts at w * STRIP_STEP
+    constexpr uint32_t STRIP_STEP = ROPE ? 9216 : PAIRED ? 32768 : STAGE_BYTES;   // a wavefront's strip starts at w * STRIP_STEP
+    // ROPE: the rows' positions (clamped into the tables) behind the four strips, then the angles' areas
+    constexpr uint32_t POS_AT = 39 * 1024, ANGLES_AT = 40 * 1024, ANGLES_BYTES = 16 * 1024;
+    int *const pos_lds = (int *)(ring + POS_AT);
     if constexpr (PAIRED && !SPLIT) {
-        slot_lds[tid] = slot_row;   // (behind wavefront 0's strip; the barrier below precedes every use)
+        slot_lds[tid] = slot_row;   // (behind the strips in use at 36 or 20 KB; the barrier below precedes every use)
+        if constexpr (ROPE) pos_lds[tid] = min(max(pos_row, 0), g.rope_positions - 1);
         __syncthreads();
     }
     if (SPLIT) {
@@ -658,100 +672,6 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
                 *(f32x4 *)(out + (size_t)t * g.N + n) = v;
             }
         }
-    } else if (ROPE) {
-        // Rotary embedding between the accumulators and the store.  NTW == 4 and heads of 128: a wavefront's
-        // 128 features are one head, so both halves of every plane (i, i + 64) pass through its strip.  The
-        // strip holds the unrounded fp32 rows (bias added); a lane takes 8 planes of a row -- features
-        // 8c .. 8c+7 and the 8 that lie 64 further on, which share their angles -- turns them and rounds once.
-        static_assert(!ROPE || NTW == 4, "a wavefront's strip must hold whole heads");
-        constexpr int EP = 128 * NTW + 16;     // strip row pitch in bytes (fp32)
-        constexpr int LPR = 2 * NTW;           // lanes per row (2 x 8 features each)
-        constexpr int RPI = 64 / LPR;          // rows per store instruction
-        lds_byte *strip = ring0 + w * STRIP_STEP;
-        const int er = lane / LPR, ec = lane % LPR;
-        const int n = n0 + wn * 32 * NTW + ec * 8;         // first of the lower 8 features; the upper 8 are n + 64
-        u32x2 bias4[NTW][4];
-#pragma unroll
-        for (int a = 0; a < NTW; ++a)
-#pragma unroll
-            for (int gq = 0; gq < 4; ++gq) {
-                const int nf = n0 + wn * 32 * NTW + a * 32 + 8 * gq + 4 * lh;
-                bias4[a][gq] = (u32x2){0u, 0u};
-                if (g.bias && nf < g.N) bias4[a][gq] = *(const u32x2 *)(g.bias + nf);
-            }
-        int region = -1, col = 0;                          // the head lies in one region (N is a multiple of 128)
-        if (n < g.N) {
-            if (n < g.Nq) { region = 0; col = n; }
-            else if (n < g.Nq + g.Nkv) { region = 1; col = n - g.Nq; }
-            else { region = 2; col = n - g.Nq - g.Nkv; }
-        }
-        // positions of the tile's rows (clamped into the tables), kept behind the last wavefront's strip
-        int *pos_lds = (int *)(ring + 120 * 1024);
-        if (tid < BM) pos_lds[tid] = m0 + tid < g.T ? min(max(g.pos[m0 + tid], 0), g.rope_positions - 1) : 0;
-        __syncthreads();
-        auto angles = [&](int row, f32x4 (&cs)[4]) {      // cos and sin of the lane's 8 planes at the row's position
-            const size_t at = (size_t)pos_lds[row] * 64 + 8 * ec;
-            cs[0] = *(const f32x4 *)(g.rope_cos + at); cs[1] = *(const f32x4 *)(g.rope_cos + at + 4);
-            cs[2] = *(const f32x4 *)(g.rope_sin + at); cs[3] = *(const f32x4 *)(g.rope_sin + at + 4);
-        };
-        constexpr int ITERS = 32 / RPI;
-        f32x4 cs[4] = {}, cs_next[4] = {};
-        if (region == 0 || region == 1) angles(wt * 128 + er, cs);
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-#pragma unroll
-            for (int a = 0; a < NTW; ++a)
-#pragma unroll
-                for (int gq = 0; gq < 4; ++gq) {
-                    f32x4 v = {acc[a][b][4 * gq + 0], acc[a][b][4 * gq + 1], acc[a][b][4 * gq + 2], acc[a][b][4 * gq + 3]};
-                    v += (f32x4){__uint_as_float(bias4[a][gq].x << 16), __uint_as_float(bias4[a][gq].x & 0xffff0000u),
-                                 __uint_as_float(bias4[a][gq].y << 16), __uint_as_float(bias4[a][gq].y & 0xffff0000u)};
-                    *(__attribute__((address_space(3))) f32x4 *)(strip + li * EP + (a * 32 + 8 * gq + 4 * lh) * 4) = v;
-                }
-#pragma unroll
-            for (int i = 0; i < ITERS; ++i) {
-                const int r = i * RPI + er;
-                const int row = wt * 128 + b * 32 + r;
-                // the angles of the next row this lane handles are requested before this row's stores go out
-                const int nxt = i + 1 < ITERS ? row + RPI : (b < 3 ? wt * 128 + (b + 1) * 32 + er : -1);
-                if ((region == 0 || region == 1) && nxt >= 0) angles(nxt, cs_next);
-                if (region >= 0 && m0 + row < g.T) {
-                    const lds_byte *sr = strip + r * EP;
-                    f32x4 lo0 = *(const __attribute__((address_space(3))) f32x4 *)(sr + ec * 32);
-                    f32x4 lo1 = *(const __attribute__((address_space(3))) f32x4 *)(sr + ec * 32 + 16);
-                    f32x4 hi0 = *(const __attribute__((address_space(3))) f32x4 *)(sr + 256 + ec * 32);
-                    f32x4 hi1 = *(const __attribute__((address_space(3))) f32x4 *)(sr + 256 + ec * 32 + 16);
-                    if (region != 2) {
-                        const f32x4 a0 = lo0, a1 = lo1;
-                        lo0 = a0 * cs[0] - hi0 * cs[2];
-                        lo1 = a1 * cs[1] - hi1 * cs[3];
-                        hi0 = hi0 * cs[0] + a0 * cs[2];
-                        hi1 = hi1 * cs[1] + a1 * cs[3];
-                    }
-                    u32x4 vl, vh;
-                    vl.x = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo0.x, lo0.y}, bf16x2));
-                    vl.y = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo0.z, lo0.w}, bf16x2));
-                    vl.z = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo1.x, lo1.y}, bf16x2));
-                    vl.w = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo1.z, lo1.w}, bf16x2));
-                    vh.x = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){hi0.x, hi0.y}, bf16x2));
-                    vh.y = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){hi0.z, hi0.w}, bf16x2));
-                    vh.z = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){hi1.x, hi1.y}, bf16x2));
-                    vh.w = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){hi1.z, hi1.w}, bf16x2));
-                    bf16_t *dst = nullptr;
-                    if (region == 0) dst = g.q + (size_t)(m0 + row) * g.Nq + col;
-                    else {
-                        const int64_t sl = slot_lds[row];
-                        if (sl >= 0) dst = (region == 1 ? g.kc : g.vc) + (size_t)sl * g.Nkv + col;
-                    }
-                    if (dst) {
-                        *(u32x4 *)dst = vl;
-                        *(u32x4 *)(dst + 64) = vh;
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) cs[u] = cs_next[u];
-            }
-        }
     } else {
         constexpr int EP = 64 * NTW + 16;      // strip row pitch in bytes
         constexpr int LPR = 4 * NTW;           // lanes per row (16 bytes each)
@@ -772,6 +692,32 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
         // only touched by calls that have one (two copies of the loop).
         bf16_t *const dbase = (region <= 0 ? g.q : region == 1 ? g.kc : g.vc) + col;
         const int64_t dpitch = region <= 0 ? g.Nq : g.Nkv;
+        // Rotary embedding between the accumulators and the rounding.  NTW == 4 and heads of 128: a wavefront's 128 features are
+        // one head, and a lane holds both halves of its planes (i, i + 64): feature tiles a and a + 2.  The angles of 32 rows
+        // (64 planes, cos and sin: 16 KB) go to LDS without passing registers, once for the two wavefronts that hold the
+        // tile's two heads, two blocks of 32 rows ahead of their use: a lane wants 16 bytes of a row of its own, which from memory
+        // would be a line per lane (16 bytes per clock).  Row = position in the block, 16-byte chunks XOR-swizzled by row % 16.
+        // (Turned in fp32 strips with the angles loaded a row ahead by every wavefront: 13.2 us per 256 x 256 tile where the
+        // epilogue without rotation takes 4.8; all of a block's rows ahead 13.4; now 11.4.  13757 rows 618 -> 604, 4096 rows 218 -> 212.)
+        static_assert(!ROPE || (NTW == 4 && PAIRED), "a wavefront holds whole heads");
+        const bool tile_turns = ROPE && n0 < g.Nq + g.Nkv, turns = ROPE && n0 + wn * 32 * NTW < g.Nq + g.Nkv;   // any of the workgroup's heads, this wavefront's head
+        auto fetch_angles = [&](int b) {       // this wavefront's half: 16 rows' cos and sin
+            if constexpr (ROPE) {
+                const uint32_t to = lds_addr_of(ring0 + ANGLES_AT + (2 * wt + (b & 1)) * ANGLES_BYTES) + wn * 4096;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int row = 16 * wn + 4 * j + (lane >> 4);
+                    const size_t at = (size_t)pos_lds[wt * 128 + b * 32 + row] * 256 + (((lane & 15) ^ (row & 15)) << 4);
+                    load_lds16_global(to + 1024 * j, (const char *)g.rope_cos + at);
+                    load_lds16_global(to + 1024 * j + 8192, (const char *)g.rope_sin + at);
+                }
+            }
+        };
+        if (tile_turns) {
+            fetch_angles(0);
+            fetch_angles(1);
+            asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        }
         auto rounds = [&](auto has_bias) {
             constexpr bool BIAS = decltype(has_bias)::value;
             // bias of the four consecutive features this lane holds per (feature tile, register quad): part of the
@@ -789,20 +735,50 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
             }
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
+                if constexpr (ROPE) {
+                    if (tile_turns) __syncthreads();   // this block's angles have landed, both wavefronts' halves (each waited for its own)
+                }
+                auto features = [&](int a, int gq) {   // the lane's four consecutive features, bias added
+                    f32x4 v = {acc[a][b][4 * gq + 0], acc[a][b][4 * gq + 1], acc[a][b][4 * gq + 2], acc[a][b][4 * gq + 3]};
+                    if constexpr (BIAS)
+                        v += (f32x4){__uint_as_float(bias4[a][gq].x << 16), __uint_as_float(bias4[a][gq].x & 0xffff0000u),
+                                     __uint_as_float(bias4[a][gq].y << 16), __uint_as_float(bias4[a][gq].y & 0xffff0000u)};
+                    return v;
+                };
+                auto to_strip = [&](int a, int gq, f32x4 f) {
+                    u32x2 v;
+                    v.x = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){f.x, f.y}, bf16x2));
+                    v.y = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){f.z, f.w}, bf16x2));
+                    *(__attribute__((address_space(3))) u32x2 *)(strip + li * EP + (a * 32 + 8 * gq + 4 * lh) * 2) = v;
+                };
+                if (ROPE && turns) {
+                    const lds_byte *cs = ring0 + ANGLES_AT + (2 * wt + (b & 1)) * ANGLES_BYTES + li * 256;
 #pragma unroll
-                for (int a = 0; a < NTW; ++a) {
+                    for (int a = 0; a < NTW / 2; ++a)
 #pragma unroll
-                    for (int gq = 0; gq < 4; ++gq) {
-                        f32x2 p0 = {acc[a][b][4 * gq + 0], acc[a][b][4 * gq + 1]};
-                        f32x2 p1 = {acc[a][b][4 * gq + 2], acc[a][b][4 * gq + 3]};
-                        if constexpr (BIAS) {
-                            p0 += (f32x2){__uint_as_float(bias4[a][gq].x << 16), __uint_as_float(bias4[a][gq].x & 0xffff0000u)};
-                            p1 += (f32x2){__uint_as_float(bias4[a][gq].y << 16), __uint_as_float(bias4[a][gq].y & 0xffff0000u)};
+                        for (int gq = 0; gq < 4; ++gq) {
+                            const int chunk = (8 * a + 2 * gq + lh) ^ (li & 15);
+                            const f32x4 c = *(const __attribute__((address_space(3))) f32x4 *)(cs + chunk * 16);
+                            const f32x4 s = *(const __attribute__((address_space(3))) f32x4 *)(cs + 8192 + chunk * 16);
+                            const f32x4 lo = features(a, gq), hi = features(a + NTW / 2, gq);
+                            to_strip(a, gq, lo * c - hi * s);
+                            to_strip(a + NTW / 2, gq, hi * c + lo * s);
                         }
-                        u32x2 v;
-                        v.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(p0, bf16x2));
-                        v.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(p1, bf16x2));
-                        *(__attribute__((address_space(3))) u32x2 *)(strip + li * EP + (a * 32 + 8 * gq + 4 * lh) * 2) = v;
+                } else {
+#pragma unroll
+                    for (int a = 0; a < NTW; ++a)
+#pragma unroll
+                        for (int gq = 0; gq < 4; ++gq) to_strip(a, gq, features(a, gq));
+                }
+                if constexpr (ROPE) {
+                    if (tile_turns && b < 3) {
+                        if (b < 2) {
+                            __syncthreads();      // everyone has turned with the angles of block b
+                            fetch_angles(b + 2);
+                            asm volatile("s_waitcnt vmcnt(8)" ::: "memory");   // those of b + 1 (loads complete in order; stores, which count along, only add)
+                        } else {
+                            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                        }
                     }
                 }
 #pragma unroll
