@@ -1,7 +1,7 @@
 // Fused bf16 projection kernel: base GEMM on bf16 MFMA (fp32 accumulate) with the low-rank
 // expand, the per-row activation select, the q_out store and the paged K/V store in one pass.
 //
-// Per 256(token) x 256|192|128(feature) tile, one workgroup of four wavefronts (one per SIMD):
+// Per 256(token) x 256|192|128(feature) tile -- or 128 x 128, for the last rows of a call -- one workgroup of four wavefronts (one per SIMD):
 //   1. fetch the tile's rows' effective adapters (the grouping step's classification, App. B mask)
 //      and cache slots; list the adapters its adapted rows use
 //   2. expand first: for each such adapter a, accumulate [S_hi | S_lo](rows of a, else 0) . [B_a ; B_a]
@@ -21,7 +21,7 @@
 //     descriptor's range check returns zeros for token rows past T, masked lanes get an
 //     out-of-range offset.
 //   - the K dimension runs through rings of LDS areas, 32 k per slice: six 24 KB stages (token
-//     slice + weight slice) for the 128-wide tile; for the 192- and 256-wide tiles six token areas
+//     slice + weight slice) for the 128-wide tile, eight of 16 KB for the 128 x 128 one; for the 192- and 256-wide tiles six token areas
 //     and four weight areas of 16 KB, where a step's token copies cover half the rows of TWO
 //     slices so that both halves of a 128-byte line of x are asked for by neighbouring
 //     instructions (see PAIRED in the kernel).  While slice i is multiplied, the first fragments of
@@ -45,10 +45,9 @@
 
 namespace alora {
 
-constexpr int BM = 256, BK = 32;
+constexpr int BK = 32;
 constexpr int KBLK = 64;     // granularity of the hidden dimension the host plans splits in
 constexpr int GEMM_THREADS = 256;
-constexpr uint32_t W_OFF = 16384;      // a stage is the token tile (256 rows x 64 B) followed by the weight tile
 constexpr uint32_t OOR = 0x80000000u;  // buffer offset that is out of range for every descriptor
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
@@ -64,18 +63,19 @@ struct GemmArgs {
     bf16_t *q, *kc, *vc;
     int T, H, Nq, Nkv, N, L, r;
     int kx;  // length of the expand K dimension: (hi | lo) x r
-    int mtiles, ntiles;
+    int mtiles, ntiles;   // tiles of 256 rows, tiles of 64 * NTW features
+    int tail_mtiles;      // fused mode: tiles of 128 rows behind them
     int kps;          // split mode: 32-wide K-slices per split
     float *partial;   // split mode: [splits][T][N] fp32
     const bf16_t *bias;   // [N] or null: added to every row before rounding (fused mode)
     RankTable ranks;      // per adapter: B_a has ranks.r[a] rows
-    // the grid is one-dimensional: main_wgs workgroups for the tiles (of every split), in split mode followed by `prep_wgs`
+    // the grid is one-dimensional: main_wgs workgroups for the 256-row tiles (of every split), in split mode followed by `prep_wgs`
     // workgroups that classify, group and shrink the batch (0: separate kernels did that)
     int main_wgs, splits, prep_wgs;
     int prep_ranges, prep_kper;   // ranges of the hidden dimension per block-table entry, and their width
     GroupSmallArgs prep;
     void *S_out;          // shrink result written by the prep workgroups ((hi, lo) form)
-    // rotary embedding fused into the store (fused mode, 256-feature tiles, heads of 128): [rope_positions][64]
+    // rotary embedding fused into the store (fused mode, tiles of 256 and 128 features, heads of 128): [rope_positions][64]
     const float *rope_cos, *rope_sin;
     const int32_t *pos;
     int rope_positions;
@@ -144,7 +144,7 @@ __device__ __forceinline__ bf16x8 read_w_frag(const lds_byte *p, int pitch)
     return __builtin_bit_cast(bf16x8, v);
 }
 
-// NTW: 32-wide feature tiles per wavefront; the workgroup tile is 256 tokens x 64*NTW features.
+// MT, NTW: 32-row token tiles and 32-wide feature tiles per wavefront; the workgroup tile is 64*MT tokens x 64*NTW features.
 // SPLIT: small-batch mode.  The workgroup index selects a tile and a range of K-slices; the kernel only accumulates the
 // base product over that range and stores the fp32 accumulators to g.partial[split][T][N]; adapters,
 // rounding and the q_out / cache stores are left to the finishing kernel.
@@ -170,21 +170,27 @@ __device__ unsigned long long *g_probe;   // [PROBE_MAX_WGS][8] phase stamps, th
 #define PROBE_STAMP(i)
 #endif
 
-template <int NTW, bool SPLIT, bool ROPE = false>
-__global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmArgs g, PtrTable B, PtrTable A)
+// One tile (or, in split mode, one tile's range of the hidden dimension, or one of the grouping and shrink workgroups): workgroup bx of
+// the mtiles x ntiles tiles of 64*MT rows x 64*NTW features that cover the rows from row0 on.  lds: tile_lds_bytes<MT, NTW>() bytes.
+template <int MT, int NTW>
+constexpr uint32_t tile_lds_bytes();
+template <int MT, int NTW, bool SPLIT, bool ROPE>
+__device__ __forceinline__ void project_tile(const GemmArgs &g, const PtrTable &B, const PtrTable &A, unsigned char *const ring, int bx, int row0, int mtiles, int ntiles)
 {
-    PROBE_STAMP(0);   // entry
-    constexpr int BN = 64 * NTW;
+    constexpr int BM = 64 * MT, BN = 64 * NTW;
     // Ring geometry.  128-feature tiles keep weight rows of 256 bytes, which makes a stage 24 KB and
     // leaves room for six stages instead of four: four slices in flight instead of two, which is
     // what the small-batch path needs to keep enough of W on its way from HBM.
     constexpr int WPITCH = NTW == 2 ? 256 : 512;       // bytes per k row of the weight tile in LDS
-    constexpr int NST = NTW == 2 ? 6 : 4;              // stages
-    constexpr uint32_t STAGE_BYTES = W_OFF + BK * WPITCH;
+    static_assert(MT == 4 || (MT == 2 && NTW == 2), "tiles of 256 rows, and of 128 x 128");
+    constexpr int NST = MT == 2 ? 8 : NTW == 2 ? 6 : 4;   // stages
+    constexpr uint32_t X_AREA = BM * BK * 2, W_AREA = BK * WPITCH;
+    constexpr uint32_t STAGE_BYTES = X_AREA + W_AREA;  // the token tile (BM rows x 64 B) followed by the weight tile
     constexpr int LPW = WPITCH / 16;                   // lanes (16-byte chunks) per weight row
     constexpr int RPW = 64 / LPW;                      // weight rows per copy instruction
     constexpr int NCW = BK / RPW / 4;                  // weight-tile copy instructions per wavefront and slice
-    constexpr int NC = 4 + NCW;                        // copy instructions per wavefront and slice
+    constexpr int NCX = MT;                            // token-tile copy instructions per wavefront and slice
+    constexpr int NC = NCX + NCW;                      // copy instructions per wavefront and slice
     // PAIRED (the 192- and 256-wide tiles): token slices and weight slices live in rings of their own, six token
     // areas and four weight areas of 16 KB, and the token copies of a step cover HALF the tile's rows for TWO
     // consecutive slices -- the two 64-byte halves of every 128-byte line of x are requested by neighbouring
@@ -192,32 +198,25 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     // at the clock its power draw allows, and a line fetched once from L2 instead of twice is clock).  A token
     // area then lives one step longer than a weight area, hence the separate rings; all 160 KB are ring, and the
     // small arrays below sit in a token area that the main loop does not reach before they are done with.
-    constexpr bool PAIRED = NTW != 2;
+    constexpr bool PAIRED = MT == 4 && NTW != 2;
     constexpr int NXA = PAIRED ? 6 : NST, NWA = PAIRED ? 4 : NST;          // token areas, weight areas
-    constexpr uint32_t X_AREA = 16384, W_AREA = BK * WPITCH;
     constexpr uint32_t RING_BYTES = PAIRED ? NXA * X_AREA + NWA * W_AREA : NST * STAGE_BYTES;
     static_assert(!PAIRED || RING_BYTES == 160 * 1024, "the paired rings fill the LDS");
-    __shared__ __attribute__((aligned(16))) unsigned char ring[RING_BYTES];
-    __shared__ int arow_s[PAIRED ? 1 : BM];
-    __shared__ int present_s[PAIRED ? 1 : ALORA_MAX_ADAPTERS];
-    __shared__ int plist_s[PAIRED ? 1 : ALORA_MAX_ADAPTERS];
-    __shared__ int n_present_s;
-    __shared__ int64_t slot_s[PAIRED ? 1 : BM];
     lds_byte *const ring0 = (lds_byte *)ring;
     // token area k and weight area k of the ring(s)
     auto xa = [&](int k) -> lds_byte * { return PAIRED ? ring0 + k * X_AREA : ring0 + k * STAGE_BYTES; };
-    auto wa = [&](int k) -> lds_byte * { return PAIRED ? ring0 + NXA * X_AREA + k * W_AREA : ring0 + k * STAGE_BYTES + W_OFF; };
+    auto wa = [&](int k) -> lds_byte * { return PAIRED ? ring0 + NXA * X_AREA + k * W_AREA : ring0 + k * STAGE_BYTES + X_AREA; };
     // the areas the expand phase works in (the base prologue leaves them free)
     lds_byte *const ex_x = xa(NXA - 1), *const ex_w = wa(NWA - 1);
     // effective adapter per tile row; adapters present in this tile (flags, ascending list, count); cache slot per
     // tile row (-1: no K/V write).  PAIRED: the first three in token area 4, which the main loop's first step is
     // the first to write and which the expand and select phases, their only users, are done with by then; the
     // slots stay in registers through the main loop and are parked behind wavefront 0's strip for the stores.
-    int *const arow = PAIRED ? (int *)(ring + 4 * X_AREA) : arow_s;
-    int *const present = PAIRED ? (int *)(ring + 4 * X_AREA + 4 * BM) : present_s;
-    int *const plist = PAIRED ? (int *)(ring + 4 * X_AREA + 4 * BM + 4 * ALORA_MAX_ADAPTERS) : plist_s;
-    int64_t *const slot_lds = PAIRED ? (int64_t *)(ring + (ROPE ? 36 : 20) * 1024) : slot_s;
-    int &n_present = PAIRED ? *(int *)(ring + 4 * X_AREA + 4 * BM + 8 * ALORA_MAX_ADAPTERS) : n_present_s;
+    unsigned char *const small = ring + (PAIRED ? 4 * X_AREA : RING_BYTES);
+    int *const arow = (int *)small, *const present = arow + BM, *const plist = present + ALORA_MAX_ADAPTERS;
+    int &n_present = plist[ALORA_MAX_ADAPTERS];
+    int64_t *const slot_lds = (int64_t *)(PAIRED ? ring + (ROPE ? 36 : 20) * 1024 : small + 4 * BM + 8 * ALORA_MAX_ADAPTERS + 16);
+    int *const pos_lds = (int *)(PAIRED ? ring + 39 * 1024 : (unsigned char *)(slot_lds + BM));   // ROPE: the rows' positions (clamped into the tables), kept like the slots
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -229,7 +228,6 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     // that they take the compute units the projection leaves free).  An XCD's share of the whole list is at most 32 workgroups where the
     // list has 256; shares of every split, rounded up each, made 33 of 81 tiles in three splits, a second round on seven of the eight XCDs
     // (640 rows, 3072 -> 5120: the call 63.8 us, now 46.2; elsewhere within 1 %).
-    const int bx = (int)blockIdx.x;
     int by = 0;
     if (SPLIT && bx >= g.main_wgs) {
         if constexpr (SPLIT && NTW == 2) {
@@ -260,7 +258,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     }
     int mt, nt;
     {
-        const int tiles = g.mtiles * g.ntiles, total = SPLIT ? tiles * g.splits : tiles, chunk = (total + 7) >> 3;
+        const int tiles = mtiles * ntiles, total = SPLIT ? tiles * g.splits : tiles, chunk = (total + 7) >> 3;
         int l = (bx & 7) * chunk + (bx >> 3);
         if (l >= total) return;  // grid is padded to a multiple of 8; uniform across the workgroup
         // (token tiles per panel.  Measured, L2-miss reads and kernel time at T = 8192, 8192 -> 10240 / T = 4096,
@@ -271,14 +269,17 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
             by = l / tiles;
             l -= by * tiles;
         }
-        const int panel = l / (PANEL * g.ntiles), rem = l - panel * PANEL * g.ntiles;
-        const int pm = min(PANEL, g.mtiles - PANEL * panel);
+        const int panel = l / (PANEL * ntiles), rem = l - panel * PANEL * ntiles;
+        const int pm = min(PANEL, mtiles - PANEL * panel);
         nt = rem / pm;
         mt = PANEL * panel + rem - nt * pm;
     }
-    const int m0 = mt * BM, n0 = nt * BN;
-    const int wt = w & 1, wn = w >> 1;   // wave owns tokens [wt*128,+128) x features [wn*32*NTW,+32*NTW)
+    const int m0 = row0 + mt * BM, n0 = nt * BN;
+    const int wt = w & 1, wn = w >> 1;   // wave owns tokens [wt*32*MT,+32*MT) x features [wn*32*NTW,+32*NTW)
     const int li = lane & 31, lh = lane >> 5;
+    // 32-feature unit of the workgroup's tile that this wavefront's feature tile a covers.  With rotation a wavefront holds both halves
+    // of its planes (i, i + 64): 64 features of a 128-wide tile are two quarters of a head that lie 64 apart.
+    auto unit = [&](int a) { return ROPE && NTW == 2 ? 2 * a + wn : wn * NTW + a; };
     const int rows_valid = min(g.T - m0, BM);
 
     // ---- 1. this tile's rows: effective adapter (from the grouping kernel) and cache slot ------
@@ -289,7 +290,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     int a_row = -1;
     int64_t slot_row = -1;
     int pos_row = 0;
-    if (!SPLIT && m0 + tid < g.T) {
+    if (!SPLIT && tid < BM && m0 + tid < g.T) {
         const int64_t *ps = g.slot + (m0 + tid);
         asm volatile("global_load_dwordx2 %0, %1, off" : "=v"(slot_row) : "v"(ps) : "memory");
         if (g.L > 0) {
@@ -303,9 +304,9 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     }
 
     // ---- per-lane geometry of the global -> LDS copies ----------------------------------------
-    // token tile: instruction ii of wave w fills rows 64w + 16ii .. +15; lane -> row +lane/4, physical
+    // token tile: instruction ii of wave w fills rows 16 (MT w + ii) .. +15; lane -> row +lane/4, physical
     // chunk lane%4, which holds logical chunk (lane%4) ^ swizzle(row)
-    auto x_row = [&](int ii, int ln) { return 64 * w + 16 * ii + (ln >> 2); };
+    auto x_row = [&](int ii, int ln) { return 16 * (NCX * w + ii) + (ln >> 2); };
     auto x_chunk = [&](int ii, int ln) { return (ln & 3) ^ ((x_row(ii, ln) >> 2) & 3); };
     // weight tile: instruction jj of wave w fills the RPW k rows from 8w + RPW*jj; lane -> row
     // +lane/LPW, physical chunk lane%LPW holding logical chunk (lane%LPW) ^ 4*(k%4)
@@ -316,7 +317,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     // ---- per-lane LDS read addresses of the MFMA operands ----------------------------------
     uint32_t xaddr;  // token fragment: row wt*128 + li (+32 b), chunk 2ks + lh
     {
-        const int row0 = wt * 128 + li;
+        const int row0 = wt * 32 * MT + li;
         xaddr = (uint32_t)row0 * (BK * 2) + (uint32_t)((lh ^ ((row0 >> 2) & 3)) << 4);
     }
     uint32_t waddr[NTW];  // weight fragments via transposing read; see read_w_frag
@@ -324,16 +325,16 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
         const int s = lane & 15, j = s >> 2, blk = (lane >> 4) & 1;
 #pragma unroll
         for (int a = 0; a < NTW; ++a) {
-            const int chunk = wn * 4 * NTW + 4 * a + 2 * blk + ((s & 3) >> 1);
+            const int chunk = 4 * unit(a) + 2 * blk + ((s & 3) >> 1);
             waddr[a] = (uint32_t)(8 * lh + j) * WPITCH + (uint32_t)((chunk ^ (j << 2)) << 4) + (uint32_t)((s & 1) << 3);
         }
     }
 
-    f32x16 acc[NTW][4];  // [feature tile a][token tile b]
+    f32x16 acc[NTW][MT];  // [feature tile a][token tile b]
 #pragma unroll
     for (int a = 0; a < NTW; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < MT; ++b)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
 
@@ -353,9 +354,9 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
 #endif
     const int w_pitch = (ALORA_PROBE & 16) ? BN : g.N;   // elements between consecutive k rows of the weight tile
     const rsrc_t rs = make_rsrc_copy(g.S_hl + (size_t)m0 * g.kx, (uint32_t)rows_valid * g.kx * 2);
-    uint32_t vxb[4], vwb[NCW];
+    uint32_t vxb[NCX], vwb[NCW];
 #pragma unroll
-    for (int ii = 0; ii < 4; ++ii) vxb[ii] = lds_copy_voffset((uint32_t)(x_row(ii, lane) * g.H + 8 * x_chunk(ii, lane)) * 2, ii);
+    for (int ii = 0; ii < NCX; ++ii) vxb[ii] = lds_copy_voffset((uint32_t)(x_row(ii, lane) * g.H + 8 * x_chunk(ii, lane)) * 2, ii);
 #pragma unroll
     for (int jj = 0; jj < NCW; ++jj)
         vwb[jj] = w_col_ok(jj, lane) ? lds_copy_voffset((uint32_t)(w_k(jj, lane) * w_pitch + 8 * w_chunk(jj, lane)) * 2, jj) : OOR;
@@ -365,15 +366,15 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     const int KT = SPLIT ? min(g.H / BK, kt0 + g.kps) : g.H / BK;
     const int n_base = KT - kt0;
 
-    // copies of one 32-wide slice: this wavefront's four token-tile (c = 0..3) and NCW weight-tile
-    // (c = 4..) instructions, into the token area at LDS address sta_x and the weight area at sta_w
-    auto copy = [&](int c, rsrc_t r_x, const uint32_t (&vx)[4], uint32_t sx, rsrc_t r_w, const uint32_t (&vw)[NCW],
+    // copies of one 32-wide slice: this wavefront's NCX token-tile (c = 0 ..) and NCW weight-tile
+    // (c = NCX ..) instructions, into the token area at LDS address sta_x and the weight area at sta_w
+    auto copy = [&](int c, rsrc_t r_x, const uint32_t (&vx)[NCX], uint32_t sx, rsrc_t r_w, const uint32_t (&vw)[NCW],
                     uint32_t sw, uint32_t sta_x, uint32_t sta_w) {
         static_assert(16 * BK * 2 == LDS_COPY_STEP && RPW * WPITCH == LDS_COPY_STEP && NCW <= 4, "immediate offsets of the copies");
-        if (c == 0) set_lds_base(sta_x + (uint32_t)(64 * w) * (BK * 2));
-        if (c == 4) set_lds_base(sta_w + (uint32_t)(8 * w) * WPITCH);
-        if (c < 4) load_lds16(c, r_x, vx[c], sx);
-        else load_lds16(c - 4, r_w, vw[c - 4], sw);
+        if (c == 0) set_lds_base(sta_x + (uint32_t)(16 * NCX * w) * (BK * 2));
+        if (c == NCX) set_lds_base(sta_w + (uint32_t)(8 * w) * WPITCH);
+        if (c < NCX) load_lds16(c, r_x, vx[c], sx);
+        else load_lds16(c - NCX, r_w, vw[c - NCX], sw);
     };
     // PAIRED: token unit u = (pair p = u / 2, row half h = u % 2) is rows 128h .. 128h+127 of slices 2p and 2p+1;
     // this wavefront's copy j of it (j = 0..3) is row group 2w + j/2 (16 rows) of slice 2p + j%2, so that the two
@@ -418,21 +419,21 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
         return *(const __attribute__((address_space(3))) bf16x8 *)(base + ((xaddr ^ (ks << 5)) + b * 32 * BK * 2));
     };
     auto read_w = [&](const lds_byte *base, int ks, int a) { return read_w_frag(base + (waddr[a] + ks * 16 * WPITCH), WPITCH); };
-    auto load_frags = [&](const lds_byte *xbase, const lds_byte *wbase, int ks, bf16x8 (&wf)[NTW], bf16x8 (&xf)[4]) {
+    auto load_frags = [&](const lds_byte *xbase, const lds_byte *wbase, int ks, bf16x8 (&wf)[NTW], bf16x8 (&xf)[MT]) {
 #pragma unroll
-        for (int b = 0; b < 4; ++b) xf[b] = read_x(xbase, ks, b);
+        for (int b = 0; b < MT; ++b) xf[b] = read_x(xbase, ks, b);
 #pragma unroll
         for (int a = 0; a < NTW; ++a) wf[a] = read_w(wbase, ks, a);
     };
-    auto mfmas = [&](const bf16x8 (&wf)[NTW], const bf16x8 (&xf)[4]) {
+    auto mfmas = [&](const bf16x8 (&wf)[NTW], const bf16x8 (&xf)[MT]) {
 #pragma unroll
         for (int a = 0; a < NTW; ++a)
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
+            for (int b = 0; b < MT; ++b)
                 acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[a], xf[b], acc[a][b], 0, 0, 0);
     };
 
-    bf16x8 wf0[NTW], xf0[4], wf1[NTW], xf1[4];
+    bf16x8 wf0[NTW], xf0[MT], wf1[NTW], xf1[MT];
 
     // fill the ring with the first base slices; their latency also covers the expand phase.  PAIRED: in the
     // order the steps -4 .. -1 of the main loop would have issued them (step s issues token unit s+4 and weight
@@ -464,8 +465,11 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     if (!SPLIT) {
         asm volatile("s_waitcnt vmcnt(%3)" : "+v"(a_row), "+v"(slot_row), "+v"(pos_row) : "n"(PRO) : "memory");
         if (a_row >= g.L) a_row = -1;   // (a workspace that holds no grouping of this batch: stay inside the tables)
-        if constexpr (!PAIRED) slot_lds[tid] = slot_row;
-        arow[tid] = a_row;
+        if constexpr (!PAIRED) {
+            if (tid < BM) slot_lds[tid] = slot_row;
+            if (ROPE && tid < BM) pos_lds[tid] = min(max(pos_row, 0), g.rope_positions - 1);
+        }
+        if (tid < BM) arow[tid] = a_row;
         if (tid < ALORA_MAX_ADAPTERS) present[tid] = 0;
         __syncthreads();
         if (a_row >= 0) present[a_row] = 1;
@@ -495,9 +499,9 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
             const int ra = __builtin_amdgcn_readfirstlane((int)g.ranks.r[a]);   // rows of B_a; S columns past it are zero, B rows past it do not exist
             const rsrc_t rb =
                 make_rsrc_copy((const bf16_t *)B.p[a] + n0, (uint32_t)(ra * g.N - n0) * 2);
-            uint32_t vx[4], vw[NCW];
+            uint32_t vx[NCX], vw[NCW];
 #pragma unroll
-            for (int ii = 0; ii < 4; ++ii) {
+            for (int ii = 0; ii < NCX; ++ii) {
                 const int row = x_row(ii, lane), kk = k0 + 8 * x_chunk(ii, lane);
                 const bool ok = (arow[row] == a) & (kk < g.kx);
                 vx[ii] = ok ? lds_copy_voffset((uint32_t)(row * g.kx + kk) * 2, ii) : OOR;
@@ -524,8 +528,8 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
         // Assembly statements get no automatic hazard padding: let the last MFMAs drain first.
         asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            if (arow[wt * 128 + b * 32 + li] < 0) {
+        for (int b = 0; b < MT; ++b) {
+            if (arow[(wt * MT + b) * 32 + li] < 0) {
 #pragma unroll
                 for (int a = 0; a < NTW; ++a)
 #pragma unroll
@@ -558,28 +562,29 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
         asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NC * (NST - 3)) : "memory");
         const int kb = kt0 + min(s + NST - 1, n_base - 1);
         const uint32_t sx = kb * xstep, sw = kb * wstep;
-        constexpr int NM = 4 * NTW, CI = NTW == 2 ? 2 : 3;
+        constexpr int NM = MT * NTW, CI = MT == 2 || NTW == 2 ? 2 : 3;
+        static_assert(NC <= 2 * NM / CI, "a place for every copy");
 #pragma unroll
         for (int gm = 0; gm < 2 * NM; ++gm) {
             // token tiles in snake order (0..3, 3..0, ...): across a change of the weight fragment the token
             // fragment stays, so one of the two operands repeats from every MFMA to the next.  The kernel
             // runs at the clock the power limit allows, and less switching on the operand paths is clock:
             // measured 1 to 3 % on the main loop; each accumulator still sees its slices in the same order.
-            const int half = gm / NM, m = gm % NM, a = m / 4, b = (a & 1) ? 3 - m % 4 : m % 4;
+            const int half = gm / NM, m = gm % NM, a = m / MT, b = (a & 1) ? MT - 1 - m % MT : m % MT;
             if (half == 0) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf0[a], xf0[b], acc[a][b], 0, 0, 0);
             else acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf1[a], xf1[b], acc[a][b], 0, 0, 0);
-            // unit u of the other fragment buffer, in the order the MFMAs will want them: the first
-            // five behind MFMAs 0..4, the rest behind every second MFMA after that
-            const int u = m < 5 ? m : ((m - 5) % 2 == 0 ? 5 + (m - 5) / 2 : -1);
-            if (u >= 0 && u < 4 + NTW && !(ALORA_PROBE & 2)) {
+            // unit u of the other fragment buffer, in the order the MFMAs will want them: the first weight
+            // fragment and the token fragments behind MFMAs 0 .. MT, the rest behind every second MFMA after that
+            const int u = m <= MT ? m : ((m - MT - 1) % 2 == 0 ? MT + 1 + (m - MT - 1) / 2 : -1);
+            if (u >= 0 && u < MT + NTW && !(ALORA_PROBE & 2)) {
                 if (half == 0) {
                     if (u == 0) wf1[0] = read_w(cur_w, 1, 0);
-                    else if (u <= 4) xf1[u - 1] = read_x(cur_x, 1, u - 1);
-                    else wf1[u - 4] = read_w(cur_w, 1, u - 4);
+                    else if (u <= MT) xf1[u - 1] = read_x(cur_x, 1, u - 1);
+                    else wf1[u - MT] = read_w(cur_w, 1, u - MT);
                 } else {
                     if (u == 0) wf0[0] = read_w(nxt_w, 0, 0);
-                    else if (u <= 4) xf0[u - 1] = read_x(nxt_x, 0, u - 1);
-                    else wf0[u - 4] = read_w(nxt_w, 0, u - 4);
+                    else if (u <= MT) xf0[u - 1] = read_x(nxt_x, 0, u - 1);
+                    else wf0[u - MT] = read_w(nxt_w, 0, u - MT);
                 }
             }
             if (gm % CI == 1 && gm / CI < NC && !(ALORA_PROBE & 1)) {
@@ -596,10 +601,10 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
 #pragma unroll
         for (int gm = 0; gm < 2 * NM; ++gm) {
             const int m = gm % NM;
-            const int u = m < 5 ? m : ((m - 5) % 2 == 0 ? 5 + (m - 5) / 2 : -1);
+            const int u = m <= MT ? m : ((m - MT - 1) % 2 == 0 ? MT + 1 + (m - MT - 1) / 2 : -1);
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (u >= 0 && u < 4 + NTW) {
-                if (u >= 1 && u <= 4) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            if (u >= 0 && u < MT + NTW) {
+                if (u >= 1 && u <= MT) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                 else __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
             }
         }
@@ -631,14 +636,13 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
 
     // ---- 4. round and store ------------------------------------------------------------------
     // D[i][j]: i = feature (8g + 4*lh + jj, register 4g + jj), j = token (li).  Each wavefront turns
-    // its 128 x 32*NTW block around through a private LDS strip, 32 token rows at a time (8-byte
+    // its 32*MT x 32*NTW block around through a private LDS strip, 32 token rows at a time (8-byte
     // writes of four consecutive features, 16-byte reads along the row), so that global stores are
     // whole row segments: 64*NTW contiguous bytes of q_out or of one cache slot per token.
     __syncthreads();  // every wavefront has finished reading the K-slice stages
     constexpr uint32_t STRIP_STEP = ROPE ? 9216 : PAIRED ? 32768 : STAGE_BYTES;   // a wavefront's strip starts at w * STRIP_STEP
     // ROPE: the rows' positions (clamped into the tables) behind the four strips, then the angles' areas
-    constexpr uint32_t POS_AT = 39 * 1024, ANGLES_AT = 40 * 1024, ANGLES_BYTES = 16 * 1024;
-    int *const pos_lds = (int *)(ring + POS_AT);
+    constexpr uint32_t ANGLES_AT = 40 * 1024, ANGLES_BYTES = 16 * 1024;
     if constexpr (PAIRED && !SPLIT) {
         slot_lds[tid] = slot_row;   // (behind the strips in use at 36 or 20 KB; the barrier below precedes every use)
         if constexpr (ROPE) pos_lds[tid] = min(max(pos_row, 0), g.rope_positions - 1);
@@ -655,7 +659,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
         const int n = n0 + wn * 32 * NTW + ec * 4;
         float *out = g.partial + (size_t)by * g.T * g.N;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
+        for (int b = 0; b < MT; ++b) {
 #pragma unroll
             for (int a = 0; a < NTW; ++a)
 #pragma unroll
@@ -666,7 +670,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
 #pragma unroll
             for (int i = 0; i < (32 + RPI - 1) / RPI; ++i) {
                 const int r = i * RPI + er;
-                const int t = m0 + wt * 128 + b * 32 + r;
+                const int t = m0 + (wt * MT + b) * 32 + r;
                 if (er >= RPI || r >= 32 || t >= g.T || n >= g.N) continue;
                 const f32x4 v = *(const __attribute__((address_space(3))) f32x4 *)(strip + r * EP + ec * 16);
                 *(f32x4 *)(out + (size_t)t * g.N + n) = v;
@@ -678,7 +682,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
         constexpr int RPI = 64 / LPR;          // rows per store instruction
         lds_byte *strip = ring0 + w * STRIP_STEP;
         const int er = lane / LPR, ec = lane % LPR;
-        const int n = n0 + wn * 32 * NTW + ec * 8;
+        const int n = n0 + 32 * unit(ec / 4) + ec % 4 * 8;
         // destination of this lane's 8 features: 0 = q_out, 1 = K cache, 2 = V cache, -1 = none
         int region = -1, col = 0;
         if (er < RPI && n < g.N) {
@@ -692,22 +696,22 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
         // only touched by calls that have one (two copies of the loop).
         bf16_t *const dbase = (region <= 0 ? g.q : region == 1 ? g.kc : g.vc) + col;
         const int64_t dpitch = region <= 0 ? g.Nq : g.Nkv;
-        // Rotary embedding between the accumulators and the rounding.  NTW == 4 and heads of 128: a wavefront's 128 features are
-        // one head, and a lane holds both halves of its planes (i, i + 64): feature tiles a and a + 2.  The angles of 32 rows
+        // Rotary embedding between the accumulators and the rounding.  Heads of 128: a wavefront holds a whole head, or the planes of half
+        // of one (see unit), and a lane both halves of its planes (i, i + 64): feature tiles a and a + NTW / 2.  The angles of 32 rows
         // (64 planes, cos and sin: 16 KB) go to LDS without passing registers, once for the two wavefronts that hold the
         // tile's two heads, two blocks of 32 rows ahead of their use: a lane wants 16 bytes of a row of its own, which from memory
         // would be a line per lane (16 bytes per clock).  Row = position in the block, 16-byte chunks XOR-swizzled by row % 16.
         // (Turned in fp32 strips with the angles loaded a row ahead by every wavefront: 13.2 us per 256 x 256 tile where the
         // epilogue without rotation takes 4.8; all of a block's rows ahead 13.4; now 11.4.  13757 rows 618 -> 604, 4096 rows 218 -> 212.)
-        static_assert(!ROPE || (NTW == 4 && PAIRED), "a wavefront holds whole heads");
-        const bool tile_turns = ROPE && n0 < g.Nq + g.Nkv, turns = ROPE && n0 + wn * 32 * NTW < g.Nq + g.Nkv;   // any of the workgroup's heads, this wavefront's head
+        static_assert(!ROPE || NTW != 3, "a wavefront holds both halves of its planes");
+        const bool tile_turns = ROPE && n0 < g.Nq + g.Nkv, turns = ROPE && n0 + 32 * unit(0) < g.Nq + g.Nkv;   // any of the workgroup's heads, this wavefront's head
         auto fetch_angles = [&](int b) {       // this wavefront's half: 16 rows' cos and sin
             if constexpr (ROPE) {
                 const uint32_t to = lds_addr_of(ring0 + ANGLES_AT + (2 * wt + (b & 1)) * ANGLES_BYTES) + wn * 4096;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int row = 16 * wn + 4 * j + (lane >> 4);
-                    const size_t at = (size_t)pos_lds[wt * 128 + b * 32 + row] * 256 + (((lane & 15) ^ (row & 15)) << 4);
+                    const size_t at = (size_t)pos_lds[(wt * MT + b) * 32 + row] * 256 + (((lane & 15) ^ (row & 15)) << 4);
                     load_lds16_global(to + 1024 * j, (const char *)g.rope_cos + at);
                     load_lds16_global(to + 1024 * j + 8192, (const char *)g.rope_sin + at);
                 }
@@ -728,13 +732,13 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
                 for (int a = 0; a < NTW; ++a)
 #pragma unroll
                     for (int gq = 0; gq < 4; ++gq) {
-                        const int nf = n0 + wn * 32 * NTW + a * 32 + 8 * gq + 4 * lh;
+                        const int nf = n0 + 32 * unit(a) + 8 * gq + 4 * lh;
                         bias4[a][gq] = (u32x2){0u, 0u};
                         if (nf < g.N) bias4[a][gq] = *(const u32x2 *)(g.bias + nf);
                     }
             }
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
+            for (int b = 0; b < MT; ++b) {
                 if constexpr (ROPE) {
                     if (tile_turns) __syncthreads();   // this block's angles have landed, both wavefronts' halves (each waited for its own)
                 }
@@ -757,7 +761,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
                     for (int a = 0; a < NTW / 2; ++a)
 #pragma unroll
                         for (int gq = 0; gq < 4; ++gq) {
-                            const int chunk = (8 * a + 2 * gq + lh) ^ (li & 15);
+                            const int chunk = (8 * (NTW == 2 ? wn : a) + 2 * gq + lh) ^ (li & 15);
                             const f32x4 c = *(const __attribute__((address_space(3))) f32x4 *)(cs + chunk * 16);
                             const f32x4 s = *(const __attribute__((address_space(3))) f32x4 *)(cs + 8192 + chunk * 16);
                             const f32x4 lo = features(a, gq), hi = features(a + NTW / 2, gq);
@@ -771,8 +775,8 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
                         for (int gq = 0; gq < 4; ++gq) to_strip(a, gq, features(a, gq));
                 }
                 if constexpr (ROPE) {
-                    if (tile_turns && b < 3) {
-                        if (b < 2) {
+                    if (tile_turns && b < MT - 1) {
+                        if (b < MT - 2) {
                             __syncthreads();      // everyone has turned with the angles of block b
                             fetch_angles(b + 2);
                             asm volatile("s_waitcnt vmcnt(8)" ::: "memory");   // those of b + 1 (loads complete in order; stores, which count along, only add)
@@ -784,7 +788,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
 #pragma unroll
                 for (int i = 0; i < (32 + RPI - 1) / RPI; ++i) {
                     const int r = i * RPI + er;
-                    const int row = min(wt * 128 + b * 32 + r, BM - 1);   // (r can pass 31 in the last iteration: masked below)
+                    const int row = min((wt * MT + b) * 32 + r, BM - 1);   // (r can pass 31 in the last iteration: masked below)
                     const int64_t idx = region == 0 ? (int64_t)(m0 + row) : slot_lds[row];
                     const bool ok = (region >= 0) & (r < 32) & (m0 + row < g.T) & (idx >= 0);
                     if (ok) {
@@ -802,6 +806,32 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     PROBE_STAMP(6);   // stores left the wavefront
 #endif
+}
+
+template <int MT, int NTW>
+constexpr uint32_t tile_lds_bytes()
+{
+    if (MT == 4 && NTW != 2) return 160 * 1024;
+    // stages, then effective adapter, slot and position of every row, adapters present
+    return (MT == 2 ? 8 : 6) * (64 * MT * BK * 2 + BK * 256) + 64 * MT * (4 + 8 + 4) + 8 * ALORA_MAX_ADAPTERS + 16;
+}
+
+// The rows in tiles of 256 x 64*NTW, and in fused mode the last ones, if the plan says so, in tiles of 128 x 128 behind them (see
+// plan_fused): a last round of a few large tiles lasts as long as a full one, and small ones finish it in less than half the time.
+template <int NTW, bool SPLIT, bool ROPE = false>
+__global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmArgs g, PtrTable B, PtrTable A)
+{
+    PROBE_STAMP(0);   // entry
+    constexpr uint32_t LARGE = tile_lds_bytes<4, NTW>(), SMALL = tile_lds_bytes<2, 2>();
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[LARGE > SMALL ? LARGE : SMALL];
+    const int bx = (int)blockIdx.x;
+    if constexpr (!SPLIT) {
+        if (bx >= g.main_wgs) {
+            project_tile<2, 2, false, ROPE>(g, B, A, lds, bx - g.main_wgs, g.mtiles * 256, g.tail_mtiles, (g.N + 127) / 128);
+            return;
+        }
+    }
+    project_tile<4, NTW, SPLIT, ROPE>(g, B, A, lds, bx, 0, g.mtiles, g.ntiles);
 }
 
 #if ALORA_PROBE
@@ -831,8 +861,8 @@ static GemmPlan plan_gemm(int T, int H, int N, int forced)
     constexpr int CUS = 256;                       // MI355X
     const int cand[3] = {4, 3, 2};
     const double unit[3] = {1.0, 0.78, 0.56};      // time of one K-slice relative to the 256-wide tile
-    const int mtiles = (T + BM - 1) / BM, KT = H / KBLK;
-    GemmPlan best = {4, 1, KT};
+    const int mtiles = (T + 255) / 256, KT = H / KBLK;
+    GemmPlan best = {4, 1, KT, mtiles};
     double best_cost = 1e300;
     for (int i = 0; i < 3; ++i) {
         if (g_force_ntw && cand[i] != g_force_ntw) continue;
@@ -852,7 +882,57 @@ static GemmPlan plan_gemm(int T, int H, int N, int forced)
             if (eff != sp) continue;
             const long rounds = (tiles * sp + CUS - 1) / CUS;
             const double cost = (double)rounds * (kps * unit[i] + 3.0) + (sp > 1 ? 4.0 + 0.6 * sp : 0.0);
-            if (cost < best_cost - 1e-9) { best_cost = cost; best = {cand[i], sp, kps}; }
+            if (cost < best_cost - 1e-9) { best_cost = cost; best = {cand[i], sp, kps, mtiles}; }
+        }
+    }
+    return best;
+}
+
+// A fused call (one split): the width of its 256-row tiles, and how many of its last rows are taken in 128 x 128 tiles instead.
+// The time of a tile, us, on a chip of which `load` (0 .. 1) of the compute units are busy: start + hidden / 4096 * (loop + slope * load) --
+// the fuller the chip, the lower the clock and the longer the way of what misses the L2.  Fitted to 1100 calls, measured one by one:
+// 1100 to 13757 rows of 4096 -> 6144, 3072 -> 5120 and 8192 -> 10240, with and without rotation, all tile widths, the last up to five panels of
+// 256 rows in small tiles.  On those the choice is 0.6 % off the best on average, 7 % at most; by whole rounds of 256-row tiles alone
+// (costs 1, 0.78 and 0.56 by width) it was 6 % off on average and 38 % at most.  The call, us, before | now, on other sizes: 8192 -> 10240 3700
+// rows 730 | 558, 1537 with rotation 362 | 271, 6500 941 | 883; 3072 -> 5120 8192 rows 319 | 248, 3300 with rotation 169 | 129, 1200 with
+// rotation 85 | 64; 4096 -> 6144 2700 rows with rotation 211 | 160, 6500 355 | 309, 13757 with rotation 604 | 579; where whole rounds fit
+// within 1 %.
+static double tile_us(int ntw, bool rope, int H, double load)
+{
+    struct { double start, loop, slope; } const c[5] = {{7.6, 18.7, 14.5}, {}, {7.0, 30.5, 29.5}, {11.0, 32.9, 37.6}, {13.9, 44.6, 44.4}};   // [0]: 128 x 128
+    return c[ntw].start + (rope ? (ntw ? 1.3 * ntw : 2.6) : 0.0) + H / 4096.0 * (c[ntw].loop + c[ntw].slope * load);
+}
+
+static GemmPlan plan_fused(int T, int H, int N, bool rope)
+{
+    constexpr int CUS = 256;
+    const int all = (T + 255) / 256;
+    GemmPlan best = {4, 1, H / KBLK, all};
+    double best_us = 1e300;
+    for (int ntw = 4; ntw >= 2; --ntw) {
+        if (rope && ntw == 3) continue;   // a wavefront would hold one and a half heads
+        const long ntiles = (N + 64 * ntw - 1) / (64 * ntw);
+        for (int panels = all; panels >= 0 && panels >= all - 6; --panels) {
+            // Whole rounds of large tiles, then `rem` of them beside small ones, which the units take as they become free.  (One
+            // after the other small tiles are 40 % dearer than by themselves, and a plan with some has to promise 2 %.)
+            const long large = panels * ntiles, rem = large % CUS, rows = std::max(0, T - 256 * panels);
+            const long small = (rows + 127) / 128 * ((N + 127) / 128);
+            const double tl = rem ? tile_us(ntw, rope, H, (rem + 0.33 * std::min(small, CUS - rem)) / CUS) : 0.0;
+            double us = tl;
+            if (small) {
+                const double ts = tile_us(0, rope, H, std::min(1.0, (rem + small) / (double)CUS)), more = 1.4 * ts;
+                auto taken = [&](double free_for) { return free_for < ts - 1e-6 ? 0l : 1l + (long)((free_for - ts) / more + 1e-6); };
+                for (long a = 0, b = 0;;) {   // the moments at which a unit is through with a small tile
+                    const double ta = ts + a * more, tb = tl + ts + b * more;
+                    us = std::max(tl, std::min(ta, tb));
+                    if ((CUS - rem) * taken(us) + rem * taken(us - tl) >= small) break;
+                    if (ta <= tb) ++a;
+                    else ++b;
+                }
+            }
+            us += large / CUS * tile_us(ntw, rope, H, 1.0);
+            if (panels < all) us *= 1.02;
+            if (us < best_us - 1e-9) { best_us = us; best = {ntw, 1, H / KBLK, panels}; }
         }
     }
     return best;
@@ -862,7 +942,7 @@ size_t gemm_partial_bytes(int T, int H, int N)
 {
     // room for the most splits any plan (or tuning override) can choose for these sizes
     (void)H;
-    const long mtiles = (T + BM - 1) / BM;
+    const long mtiles = (T + 255) / 256;
     const bool may_split = mtiles * ((N + 255) / 256) * 2 <= 256;
     return may_split ? (size_t)8 * T * N * 4 : 0;
 }
@@ -871,12 +951,13 @@ template <int NTW>
 static void launch_ntw(const GemmArgs &g, const PtrTable &B, const PtrTable &A, hipStream_t stream)
 {
     const dim3 block(GEMM_THREADS);
+    const unsigned tail8 = (unsigned)(g.tail_mtiles * ((g.N + 127) / 128) + 7) / 8 * 8;
     if (g.splits > 1)
         hipLaunchKernelGGL((alora_gemm_bf16_kernel<NTW, true>), dim3(g.main_wgs + g.prep_wgs), block, 0, stream, g, B, A);
-    else if (NTW == 4 && g.rope_cos)
-        hipLaunchKernelGGL((alora_gemm_bf16_kernel<4, false, true>), dim3(g.main_wgs), block, 0, stream, g, B, A);
+    else if (NTW != 3 && g.rope_cos)
+        hipLaunchKernelGGL((alora_gemm_bf16_kernel<NTW == 3 ? 4 : NTW, false, true>), dim3(g.main_wgs + tail8), block, 0, stream, g, B, A);
     else
-        hipLaunchKernelGGL((alora_gemm_bf16_kernel<NTW, false>), dim3(g.main_wgs), block, 0, stream, g, B, A);
+        hipLaunchKernelGGL((alora_gemm_bf16_kernel<NTW, false>), dim3(g.main_wgs + tail8), block, 0, stream, g, B, A);
 }
 
 // Decode-sized bf16 batches: classification, grouping and shrink run inside the projection kernel (up to 64 rows
@@ -891,10 +972,20 @@ static bool prep_in_projection(const Fwd &f, const Route &r)
 
 void plan_call(Fwd &f)
 {
-    f.route = Route{{4, 1, f.H / KBLK}, {1, f.H, false}, false, false};
+    const GemmPlan none = {4, 1, f.H / KBLK, (f.T + 255) / 256};
+    f.route = Route{none, none, {1, f.H, false}, false, false};
     if (f.T <= 0) return;
     const int forced = g_force_tuning.load(std::memory_order_relaxed);
-    f.route.gemm = plan_gemm(f.T, f.H, f.N, forced);
+    f.route.gemm = f.route.gemm_rope = plan_gemm(f.T, f.H, f.N, forced);
+    // (the number of splits, which the shrink's layout depends on, is what the sizes alone give)
+    if (f.route.gemm.splits == 1) {
+        if (!forced) {
+            f.route.gemm = plan_fused(f.T, f.H, f.N, false);
+            f.route.gemm_rope = plan_fused(f.T, f.H, f.N, true);
+        } else if (f.route.gemm_rope.ntw == 3) {
+            f.route.gemm_rope.ntw = 4;
+        }
+    }
     f.route.shrink = plan_shrink(f.route.gemm, f.T, f.H, f.L, f.r);
     f.route.few_rows = !forced && few_rows_call(f);   // (the override names tilings of the projection kernel here)
     f.route.prep_inside = prep_in_projection(f, f.route);
@@ -904,18 +995,15 @@ int launch_gemm_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEven
 {
     if (f.T == 0) return 0;
     if (f.route.few_rows) return launch_decode_bf16(f, B, A, after_projection);
-    GemmPlan plan = f.route.gemm;
-    // the fused rotary embedding wants whole heads of 128 in a wavefront's strip: 256-feature tiles (the number
-    // of splits, which the shrink's layout depends on, stays what the sizes alone give; with splits the
-    // finishing kernel rotates)
-    if (f.rope_cos && plan.splits == 1) plan.ntw = 4;
+    const GemmPlan plan = f.rope_cos ? f.route.gemm_rope : f.route.gemm;   // with rotation a wavefront holds both halves of its planes
     GemmArgs g;
     g.x = (const bf16_t *)f.x; g.W = (const bf16_t *)f.W; g.S_hl = (const bf16_t *)f.S;
     g.aeff = f.aeff; g.slot = f.slot;
     g.q = (bf16_t *)f.q; g.kc = (bf16_t *)f.kc; g.vc = (bf16_t *)f.vc;
     g.T = f.T; g.H = f.H; g.Nq = f.Nq; g.Nkv = f.Nkv; g.N = f.N; g.L = f.L; g.r = f.r;
     g.kx = 2 * f.r;
-    g.mtiles = (f.T + BM - 1) / BM;
+    g.mtiles = plan.panels;
+    g.tail_mtiles = f.T > 256 * plan.panels ? (f.T - 256 * plan.panels + 127) / 128 : 0;
     g.ntiles = (f.N + 64 * plan.ntw - 1) / (64 * plan.ntw);
     g.kps = plan.kps * (KBLK / BK);
     g.partial = f.partial;

@@ -28,6 +28,7 @@ struct GemmPlan {
     int ntw;     // 32-wide feature tiles per wavefront (tile width 64 * ntw)
     int splits;  // 1: fused kernel; > 1: split hidden dimension + finishing kernel
     int kps;     // 64-wide K-slices per split
+    int panels;  // 256-row tiles; the rows behind them, if any, in tiles of 128 x 128 (fused kernel)
 };
 struct ShrinkPlan {
     int splits;  // ranges of the hidden dimension; the shrink result is the fixed-order sum of their partials
@@ -41,7 +42,7 @@ struct ShrinkPlan {
 // from ONE reading of the tuning override: every launch of the call follows it, so that an override set by another
 // host thread meanwhile cannot give one call the launches of two different paths.
 struct Route {
-    GemmPlan gemm;
+    GemmPlan gemm, gemm_rope;   // without and with the rotary embedding fused into the store (the same splits)
     ShrinkPlan shrink;
     bool few_rows;      // at most 64 rows: the projection kernel of alora_decode_bf16.hip
     bool prep_inside;   // grouping and shrink run inside the projection kernel

@@ -2,7 +2,7 @@
 
 launches_of(calls) runs the calls in a process of its own in which launch_recorder.c stands in for the HIP runtime:
 every launch is written down instead of enqueued, device pointers are numbers that nothing dereferences.  A call is a
-dict: op "forward" (fields of alora_dims, optionally tuning_during: a tuning override that arrives in the middle of the
+dict: op "forward" (fields of alora_dims, optionally rope: with rotation tables, optionally tuning_during: a tuning override that arrives in the middle of the
 call, between the library's two profiling events) or op "attention" (fields of alora_attn_dims and the entry point)."""
 import ctypes
 import json
@@ -53,7 +53,11 @@ def _main(rec_path):
                 hook = HOOK(lambda: L.alora_qkv_set_tuning(*c["tuning_during"]) and None)
                 rec.rec_on_event(hook)
             if s == 0:
-                s = L.alora_qkv_forward(P, P, P, P, tab, tab, P, P, P, P, ctypes.c_int(16), ctypes.byref(d), P, ws, None)
+                if c.get("rope"):
+                    ex = ab.AloraExtras(None, None, 0, P.value, P.value, 1)
+                    s = L.alora_qkv_forward_ex(P, P, P, P, tab, tab, P, P, P, P, ctypes.c_int(16), ctypes.byref(d), ctypes.byref(ex), P, ws, None)
+                else:
+                    s = L.alora_qkv_forward(P, P, P, P, tab, tab, P, P, P, P, ctypes.c_int(16), ctypes.byref(d), P, ws, None)
             if hook:
                 rec.rec_on_event(HOOK(0))
                 L.alora_qkv_set_tuning(0, 0)

@@ -8,6 +8,7 @@ import torch
 import oracle
 from paper_2512_17910_amd import binding as ab
 from paper_2512_17910_amd import workloads as wl
+from test_launches import TAILS
 from gpu_util import DeviceBatch, TOL, check_grouping, host_operands, maxnorm_rel, raw_bits, to_dev, to_f64
 
 pytestmark = pytest.mark.gpu
@@ -524,3 +525,12 @@ def test_finishing_kernel_at_the_edges_of_its_tiles(rank):
     db.forward()
     q = raw_bits(db.q)
     assert not np.isfinite(to_f64(db.q)[row]).all() and np.array_equal(np.delete(q, row, 0), np.delete(first, row, 0))
+
+
+# The last rows of a fused projection in tiles of 128 x 128: ragged rows behind 256-row tiles of each width and by themselves, a feature
+# tile that ends inside the 128, fewer slices of the hidden dimension than the ring has stages.  Bounds: those of every bf16 case in _check_full.
+@pytest.mark.parametrize("hidden,hq,hkv,d,rows", [t[:5] for t in TAILS if not t[5]])
+def test_small_tiles_behind_large_ones(hidden, hq, hkv, d, rows):
+    w = wl.small_mixed("bf16", seed=41, hidden=hidden, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, n_adapters=4, rank=24, seq_lens=(rows - 301, 170, 130, 1), pad_every=7)
+    _check_full(w)
+    _check_full(wl.small_mixed("bf16", seed=42, hidden=64, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, rank=8, seq_lens=(rows - 30, 30)))

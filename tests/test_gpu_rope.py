@@ -10,6 +10,7 @@ import oracle
 from oracle import rope as orope
 from paper_2512_17910_amd import binding as ab
 from paper_2512_17910_amd import workloads as wl
+from test_launches import TAILS
 from gpu_util import DeviceBatch, TOL, host_operands, maxnorm_rel, raw_bits, to_f64
 
 pytestmark = pytest.mark.gpu
@@ -184,3 +185,11 @@ def test_repeated_calls_give_the_same_bits(tuning):
             assert np.array_equal(raw_bits(db.kc), first[1]) and np.array_equal(raw_bits(db.vc), first[2]), it
     finally:
         ab.alora_qkv_set_tuning(0, 0)
+
+
+@pytest.mark.parametrize("hidden,hq,hkv,d,rows", [t[:5] for t in TAILS if t[5]])
+def test_small_tiles_behind_large_ones_rotate(hidden, hq, hkv, d, rows):
+    """128 x 128 tiles (two quarters of a head per wavefront) behind 256-row tiles and by themselves, layer bias included."""
+    w = wl.small_mixed("bf16", seed=43, hidden=hidden, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, rank=24, seq_lens=(rows - 301, 170, 130, 1), pad_every=7)
+    _check(w)
+    _check(wl.with_variants(w, ranks=(8, 24, 16), bias=True))

@@ -45,6 +45,22 @@ def test_rows_per_tile_of_the_fp32_projection():
         assert len(l) == 1 and l[0]["ints"] == [mt] and l[0]["grid"][1] == -(-size[0] // (16 * mt)), (size, l)
 
 
+# (hidden, query heads, K/V heads, head size, rows, rotation, tile width / 64, 256-row tiles): fused projections whose last rows go in
+# tiles of 128 x 128, behind each width of the large ones and all by themselves; test_gpu_parity.py runs them.
+TAILS = [(512, 5, 2, 40, 1030, False, 4, 1), (512, 60, 2, 128, 1030, False, 3, 4), (192, 22, 3, 128, 1290, False, 2, 3), (512, 24, 8, 128, 700, False, 4, 0),
+         (192, 60, 2, 128, 2100, True, 4, 8), (512, 22, 3, 128, 1290, True, 2, 2), (512, 24, 8, 128, 700, True, 4, 0)]
+
+
+def test_last_rows_of_a_fused_projection_in_small_tiles():
+    calls = launches_of([dict(QKV_8B, T=T, hidden=h, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, n_adapters=3, rope=rope) for h, hq, hkv, d, T, rope, _, _ in TAILS])
+    up8 = lambda n: -(-n // 8) * 8
+    for call, (h, hq, hkv, d, T, rope, width, panels) in zip(calls, TAILS):
+        l = call["launches"][-1]
+        N = (hq + 2 * hkv) * d
+        assert l["kernel"] == "alora_gemm_bf16_kernel" and l["ints"] == [width, 0, int(rope)], l
+        assert l["grid"][0] == up8(panels * -(-N // (64 * width))) + up8(-(-(T - 256 * panels) // 128) * -(-N // 128)) and T > 256 * panels, l
+
+
 # ---- the row-block reader ------------------------------------------------------------------------
 def reader(entry, T, n_seqs, n_q, n_kv, block_size=16):
     return dict(op="attention", entry=entry, dtype=1, n_tokens=T, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=128, n_seqs=n_seqs,
