@@ -166,7 +166,7 @@ def measure(cfg: int, args, cpu_baseline: bool) -> dict:
     rec = {"workload": w.name, "value": tokens_per_s, "ms_per_step": ms_per_step,
            "config": {"workload": w.name, "T": w.T, "hidden": w.hidden, "N": w.N, "n_adapters": w.n_adapters,
                       "rank": w.rank, "active_rows": T_act, "block_size": w.block_size,
-                      "weight_copies_rotated": rotate, "hip_graph": bool(graphs),
+                      "weight_copies_rotated": rotate, "recorded_call": bool(graphs),
                       "grouping_reused_from_an_earlier_call": bool(args.reuse_grouping),
                       "rotary_embedding_fused": bool(args.rope)},
            "host_enqueue_us_per_step": (t_enq - t0) * 1e6 / args.steps,
@@ -236,7 +236,7 @@ def main() -> int:
                     help="gaussian: the workload's recipe (default).  constant: x and W overwritten with 1.0, a probe of "
                          "how far the clock under load depends on operand toggling; not the workload, no parity check")
     ap.add_argument("--graph", action="store_true",
-                    help="replay the call as a HIP graph (alora_qkv_graph_*), one graph per rotated weight copy; the "
+                    help="replay the recorded call (alora_qkv_graph_*), one recording per rotated weight copy; the "
                          "kernel-level roofline figures then come from rocprofv3, not from in-call events")
     ap.add_argument("--reuse-grouping", action="store_true",
                     help="not the headline step: time the per-layer call of a model whose layers share one token batch "

@@ -219,12 +219,13 @@ int alora_qkv_forward_static(const void *x, const int32_t *token_adapter_ids, co
                              const alora_dims *dims, const alora_extras *extras, void *hip_stream);
 
 /*
- * Graph-captured call.  Sec. 3 keeps the activation mask in a tensor of fixed address so that the
+ * Recorded call.  Sec. 3 keeps the activation mask in a tensor of fixed address so that the
  * model's forward pass stays one captured device graph, and App. A's dummy run builds placeholder
  * aLoRA metadata only so that the mask is part of that graph.  Here: alora_qkv_graph_create records
- * ONE alora_qkv_forward with exactly these pointers and sizes into a HIP graph (on a stream of its
- * own; nothing runs) and hands back the instantiated graph; every alora_qkv_graph_launch replays
- * the whole call (classification/grouping, shrink, projection, stores) on `hip_stream`.
+ * ONE alora_qkv_forward with exactly these pointers and sizes (nothing runs) and hands back the
+ * recording; every alora_qkv_graph_launch replays the whole call (classification/grouping, shrink,
+ * projection, stores) on `hip_stream`, as the launches of its kernels and nothing else: a replay may
+ * itself be captured into a HIP graph.
  *   - Arguments, layouts and preconditions are those of alora_qkv_forward_ex (extras may be NULL;
  *     the rank array is read at creation, the bias and rotary-table pointers are baked in); T must be > 0.
  *   - All addresses are baked in: before a launch the caller rewrites the CONTENTS of x,

@@ -264,7 +264,7 @@ def alora_qkv_static_scratch_bytes() -> int:
 def alora_qkv_graph_create(x, token_adapter_ids, activation_start, W_qkv, A: Sequence, B: Sequence,
                            q_out, k_cache, v_cache, slot_mapping, block_size: int, dims: AloraDims, workspace,
                            bias=None, adapter_ranks=None, rope=None):
-    """Record one forward call with these buffers into a HIP graph; returns an opaque handle for
+    """Record one forward call with these buffers for replay; returns an opaque handle for
     alora_qkv_graph_launch / alora_qkv_graph_destroy.  The caller keeps every tensor alive and rewrites
     their contents in place between launches."""
     h = ctypes.c_void_p(None)

@@ -2,7 +2,7 @@
 
 launches_of(calls) runs the calls in a process of its own in which launch_recorder.c stands in for the HIP runtime:
 every launch is written down instead of enqueued, device pointers are numbers that nothing dereferences.  A call is a
-dict: op "forward" (fields of alora_dims, optionally rope: with rotation tables, optionally tuning_during: a tuning override that arrives in the middle of the
+dict: op "forward" (fields of alora_dims, optionally rope: with rotation tables, replays: recorded and replayed, tuning_during: a tuning override that arrives in the middle of the
 call, between the library's two profiling events) or op "attention" (fields of alora_attn_dims and the entry point)."""
 import ctypes
 import json
@@ -58,6 +58,15 @@ def _main(rec_path):
                     s = L.alora_qkv_forward_ex(P, P, P, P, tab, tab, P, P, P, P, ctypes.c_int(16), ctypes.byref(d), ctypes.byref(ex), P, ws, None)
                 else:
                     s = L.alora_qkv_forward(P, P, P, P, tab, tab, P, P, P, P, ctypes.c_int(16), ctypes.byref(d), P, ws, None)
+            if c.get("replays"):     # the same call recorded, then replayed that many times
+                assert s == 0
+                rec.rec_reset()
+                g = ctypes.c_void_p(None)
+                s = L.alora_qkv_graph_create(P, P, P, P, tab, tab, P, P, P, P, ctypes.c_int(16), ctypes.byref(d), None, P, ws, ctypes.byref(g))
+                assert rec.rec_count() == 0
+                for _ in range(c["replays"]):
+                    s = s or L.alora_qkv_graph_launch(g, None)
+                L.alora_qkv_graph_destroy(g)
             if hook:
                 rec.rec_on_event(HOOK(0))
                 L.alora_qkv_set_tuning(0, 0)

@@ -1,4 +1,4 @@
-"""Graph-captured call (alora_qkv_graph_*): one forward recorded into a HIP graph over buffers of
+"""Recorded call (alora_qkv_graph_*): one forward recorded over buffers of
 fixed address, then replayed with the batch rewritten in place; smaller batches are padded with
 rows of adapter -1 / slot -1.  Every replay must equal the eager call bit for bit and match the
 fp64 oracle; eager work and synchronisations sit between the replays on purpose."""
@@ -146,3 +146,31 @@ def test_graph_with_bias_and_per_adapter_ranks():
         assert maxnorm_rel(to_f64(static.q), y[:, : w.Nq]) <= TOL[w.dtype]
     finally:
         ab.alora_qkv_graph_destroy(g)
+
+
+@pytest.mark.parametrize("n_real", [40, 200])
+def test_a_replay_captured_into_a_device_graph(n_real):
+    """A replay is kernel launches and nothing else, so that a caller's own graph may hold it: replayed several times over rewritten
+    batches, with eager work in between."""
+    w0 = _decode_step(11, T_CAP)
+    static = DeviceBatch(w0)
+    g = ab.alora_qkv_graph_create(static.x, static.aid, static.start, static.W, static.A, static.B, static.q,
+                                  static.kc, static.vc, static.slot, w0.block_size, static.dims, static.ws)
+    ab.alora_qkv_graph_launch(g)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ab.alora_qkv_graph_launch(g)
+    for step in (12, 13, 14):
+        w = _decode_step(step, n_real)
+        _load_into(static, w)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        eager = DeviceBatch(w)
+        eager.forward()
+        torch.cuda.synchronize()
+        assert np.array_equal(raw_bits(static.q), raw_bits(eager.q))
+        assert np.array_equal(raw_bits(static.kc), raw_bits(eager.kc)) and np.array_equal(raw_bits(static.vc), raw_bits(eager.vc))
+    del graph
+    ab.alora_qkv_graph_destroy(g)

@@ -45,6 +45,14 @@ def test_rows_per_tile_of_the_fp32_projection():
         assert len(l) == 1 and l[0]["ints"] == [mt] and l[0]["grid"][1] == -(-size[0] // (16 * mt)), (size, l)
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_a_replay_is_the_launches_of_the_call(dtype):
+    for T in (1, 64, 200, 300, 3000):
+        call = dict(QKV_8B, dtype=dtype, T=T, n_adapters=4)
+        once, twice = launches_of([call, dict(call, replays=2)])
+        assert once["launches"] and twice["status"] == 0 and twice["launches"] == 2 * once["launches"], (kernels(once), kernels(twice))
+
+
 # (hidden, query heads, K/V heads, head size, rows, rotation, tile width / 64, 256-row tiles): fused projections whose last rows go in
 # tiles of 128 x 128, behind each width of the large ones and all by themselves; test_gpu_parity.py runs them.
 TAILS = [(512, 5, 2, 40, 1030, False, 4, 1), (512, 60, 2, 128, 1030, False, 3, 4), (192, 22, 3, 128, 1290, False, 2, 3), (512, 24, 8, 128, 700, False, 4, 0),
