@@ -110,8 +110,9 @@ int alora_paged_attention_suffix(const void *q, const void *k_cache, const void 
  * when n_tokens alone gives that many (always from 512 (block of 128 / G rows, K/V head) pairs on): then
  * alora_paged_attention_suffix_workspace_bytes returns 0, this IS alora_paged_attention_suffix, and the workspace
  * may be NULL.  Otherwise the parts leave (running maximum, sum of weights, unnormalised output) in the workspace
- * and a second kernel combines them in a fixed order.  The number of parts, and with it the workspace, depends on
- * n_tokens, n_seqs and the head counts, and is not monotonic in them: ask for the dims of the call.
+ * and a second kernel combines them in a fixed order.  The largest number of parts, and with it the workspace, depends on
+ * n_tokens, n_seqs and the head counts, and is not monotonic in them: ask for the dims of the call.  Where more row blocks
+ * are likely than n_tokens fill, the kernel takes fewer parts, by the blocks and contexts it finds in the positions.
  * Results equal those of alora_paged_attention_suffix up to fp32 summation order and do not depend on timing.
  *   workspace  device, 16-byte aligned, >= alora_paged_attention_suffix_workspace_bytes() bytes; contents on
  *              entry irrelevant; calls that share it must be stream-ordered.  ALORA_EWORKSPACE otherwise.

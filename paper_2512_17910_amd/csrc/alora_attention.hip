@@ -316,7 +316,8 @@ __global__ __launch_bounds__(256) void paged_attention_kernel(AttnArgs a)
 // few round trips to memory long and little else, so a workgroup requests everything it needs at once: D / 2
 // lanes take one part (two elements each), 512 / D groups of them every NG-th part.  Measured (32/8 heads of 128): 8 rows in
 // 16 parts 16.0 us with one part after the other, 5.0 us now; 256 rows in 8 parts (34 MB) 17.0 -> 9.0 us.
-template <int D, bool BF16>
+// COUNTED: the last part's place may hold how many there are instead, (number, -1); what lies between is not read.
+template <int D, bool BF16, bool COUNTED>
 __global__ __launch_bounds__(256) void paged_attention_merge_kernel(const float *__restrict__ part, void *__restrict__ out, int splits)
 {
     constexpr int LP = D / 2, NG = 256 / LP, PER = MAX_PARTS / NG;
@@ -326,15 +327,29 @@ __global__ __launch_bounds__(256) void paged_attention_merge_kernel(const float 
     const int dd = threadIdx.x % LP, grp = threadIdx.x / LP;
     const float *pp = part + rh * splits * (D + 2);
     f32x2 ml[PER], ov[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
+    auto load = [&](int i, bool there) {
         const int s2 = grp + NG * i;
         ml[i] = (f32x2){M_FLOOR, 0.f};
         ov[i] = (f32x2){0.f, 0.f};
-        if (s2 < splits) {
+        if (there) {
             ml[i] = *(const f32x2 *)(pp + (size_t)s2 * (D + 2));
             ov[i] = *(const f32x2 *)(pp + (size_t)s2 * (D + 2) + 2 + 2 * dd);
         }
+    };
+    constexpr int AHEAD = COUNTED ? 2 : PER;   // requested before it is known how many there are
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) load(i, grp + NG * i < splits);
+    if (COUNTED) {
+        const f32x2 last = *(const f32x2 *)(pp + (size_t)(splits - 1) * (D + 2));
+        if (last.y < 0.f) splits = (int)last.x;
+#pragma unroll
+        for (int i = AHEAD; i < PER; ++i) load(i, grp + NG * i < splits);
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i)
+            if (grp + NG * i >= splits) {      // (whatever the workspace held)
+                ml[i] = (f32x2){M_FLOOR, 0.f};
+                ov[i] = (f32x2){0.f, 0.f};
+            }
     }
     float M = M_FLOOR;
 #pragma unroll
@@ -380,8 +395,8 @@ static void launch_dg(const AttnArgs &a, bool bf16, hipStream_t st)
     else hipLaunchKernelGGL((paged_attention_kernel<D, G, false, false>), grid, dim3(256), 0, st, a);
     if (a.splits > 1) {
         const dim3 mgrid((unsigned)a.T * (unsigned)a.Hq);
-        if (bf16) hipLaunchKernelGGL((paged_attention_merge_kernel<D, true>), mgrid, dim3(256), 0, st, a.part, a.out, a.splits);
-        else hipLaunchKernelGGL((paged_attention_merge_kernel<D, false>), mgrid, dim3(256), 0, st, a.part, a.out, a.splits);
+        if (bf16) hipLaunchKernelGGL((paged_attention_merge_kernel<D, true, false>), mgrid, dim3(256), 0, st, a.part, a.out, a.splits);
+        else hipLaunchKernelGGL((paged_attention_merge_kernel<D, false, false>), mgrid, dim3(256), 0, st, a.part, a.out, a.splits);
     }
 }
 
@@ -545,11 +560,13 @@ static int run(const void *q, const void *k_cache, const void *v_cache, const in
     const bool bf16 = dims->dtype == ALORA_BF16;
     const int G = dims->n_q_heads / dims->n_kv_heads;
     if (row_blocks) {
-        const int e2 = launch_attention_blocks(a, G, block_plan(dims, mode == ROW_BLOCKS_SPLIT), (hipStream_t)hip_stream);
+        const BlockPlan plan = block_plan(dims, mode == ROW_BLOCKS_SPLIT);
+        const int e2 = launch_attention_blocks(a, G, plan, (hipStream_t)hip_stream);
         if (e2) { note_hip_error(e2); return ALORA_EHIP; }
         if (splits > 1) {
-            hipLaunchKernelGGL((paged_attention_merge_kernel<128, true>), dim3((unsigned)a.T * (unsigned)a.Hq), dim3(256), 0,
-                               (hipStream_t)hip_stream, a.part, a.out, a.splits);
+            const dim3 grid((unsigned)a.T * (unsigned)a.Hq);
+            if (plan.count) hipLaunchKernelGGL((paged_attention_merge_kernel<128, true, true>), grid, dim3(256), 0, (hipStream_t)hip_stream, a.part, a.out, a.splits);
+            else hipLaunchKernelGGL((paged_attention_merge_kernel<128, true, false>), grid, dim3(256), 0, (hipStream_t)hip_stream, a.part, a.out, a.splits);
             const hipError_t e3 = hipGetLastError();
             if (e3) { note_hip_error((int)e3); return ALORA_EHIP; }
         }

@@ -10,7 +10,8 @@
 // there are, a few of a prompt chunk or every row of a decode batch, is known on the device only.
 //
 // For batches with few row blocks the context of every block is cut into parts, one workgroup each, which
-// leave (running maximum, weight sum, unnormalised output) per column for the kernel that combines them.
+// leave (running maximum, weight sum, unnormalised output) per column for the kernel that combines them; how many,
+// the kernel settles from the blocks it finds, within what the workspace was sized for.
 //
 // Per 32 context positions a wavefront runs two sets of 32x32x16 MFMAs that keep every column in the same
 // two lanes (c, c+32) from the scores to the output:
@@ -83,14 +84,40 @@ __device__ __forceinline__ void both_halves(float x, float &lo, float &hi)
     lo = x, hi = x;
     asm("s_nop 3\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 3" : "+v"(lo), "+v"(hi));
 }
+// sum, and largest from 0 on, over lanes 0 .. lane (row_shr:1, 2, 4, 8, then row_bcast:15 and 31 into the rows above)
+__device__ __forceinline__ int sum_upto64(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+    return x + __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+}
+__device__ __forceinline__ int max_upto64(int x)
+{
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+    return max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+}
 // what a lane loads for a position that is not part of the context (the weighted sum multiplies it by 0)
 __device__ const uint32_t ab_zero_chunk[4] = {0u, 0u, 0u, 0u};
 
-template <int G, int NW, bool POW2>   // NW: wavefronts per workgroup; POW2: the block size is a power of two (shifts instead of divisions)
+// whether the kernel settles the number of parts (a kernel of its own: what the counting adds costs 2 x 2 rows at 2000 positions 1.3 of 13 us)
+struct AsPlanned { static constexpr bool count = false; };
+struct Counted { static constexpr bool count = true; };
+
+// NW: wavefronts per workgroup; POW2: the block size is a power of two (shifts instead of divisions)
+template <int G, int NW, bool POW2, typename PARTS>
 __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(AttnArgs a, int range, int wgs)
 {
+    constexpr bool count = PARTS::count;
     constexpr int D = 128;
     constexpr int GPW = 8 / NW;       // groups of four positions a wavefront copies per block of 32
+    constexpr int PLACES = NW == 8 ? 256 : 512;   // workgroups the chip holds at once
     constexpr int RBW = 32 / G;       // query rows per wavefront (32 columns = rows x heads of the group)
     constexpr int RBG = NW * RBW;     // query rows per workgroup
     constexpr int PITCH = 256;        // bytes per position row of the K and V tiles in LDS
@@ -101,14 +128,16 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
     constexpr int LOOK = LOOKED_OVER * NW, SCANS = LOOKED_OVER / 64;   // batch rows a workgroup looks over, and each of its threads
     __shared__ unsigned long long lead_mask[LOOK / 64];          // bit i of word j: row 64 j + i from the range's first leads a block
     __shared__ int32_t row_seq[LOOK], row_pos[LOOK];
+    __shared__ int wave_furthest[NW], wave_total[NW];
     constexpr int WIN = 64;            // blocks of 32 positions whose table entries the window below holds
     __shared__ int32_t window[WIN * 32 / 4 + 2];   // block sizes are multiples of 4
 
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4, li = lane & 31, lh = lane >> 5;
     const int wu = __builtin_amdgcn_readfirstlane(w);
     // grid: (range of batch rows, workgroup of the range, K/V head, part of the context); a.splits parts, 1 = the whole context
-    const int part = (int)blockIdx.x % a.splits, bid = (int)blockIdx.x / a.splits;
-    const int hk = bid % a.Hkv, which = bid / a.Hkv % wgs, r_begin = bid / a.Hkv / wgs * range, r_end = min(a.T, r_begin + range);
+    int splits = a.splits, part = (int)blockIdx.x % splits, bid = (int)blockIdx.x / splits;
+    int hk = bid % a.Hkv, which = bid / a.Hkv % wgs;
+    const int r_begin = bid / a.Hkv / wgs * range, r_end = min(a.T, r_begin + range);
     // ---- the rows of the range that lead a block (range <= LOOK - RBG: the RBG rows behind it say where its last block ends) ----
     // A row does unless the row before it in the batch is the same sequence's previous position and the position
     // is not a multiple of RBG (then an earlier row leads).  The workgroups of a range take them in turn: the leading rows
@@ -125,6 +154,7 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
                 if (t > 0) { sq1[i] = a.seq[t - 1]; p1[i] = a.pos[t - 1]; }
             }
         }
+        int furthest = 0, total = 0;           // last position of a row; blocks of 32 positions before the leading rows
 #pragma unroll
         for (int i = 0; i < SCANS; ++i) {
             const bool ok = sq[i] >= 0 && sq[i] < a.n_seqs && p0[i] >= 0;
@@ -133,6 +163,14 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
             if (lane == 0) lead_mask[i * NW + w] = mk;
             row_seq[i * 64 * NW + tid] = sq[i];
             row_pos[i * 64 * NW + tid] = p0[i];
+            if (count && ok && i * 64 * NW + tid < a.T) {
+                furthest = max(furthest, p0[i]);
+                if (lead) total += min(p0[i] >> 5, 1 << 18);
+            }
+        }
+        if constexpr (count) {
+            wave_furthest[w] = __builtin_amdgcn_readlane(max_upto64(furthest), 63);      // (every lane writes the same)
+            wave_total[w] = __builtin_amdgcn_readlane(sum_upto64(total), 63);
         }
         __syncthreads();
     }
@@ -144,12 +182,7 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
         const unsigned long long mk = lane < LOOK / 64 ? lead_mask[lane] : 0ull;
         const int own = min(64, r_end - r_begin - 64 * lane);      // rows of the word that are the range's
         const int c = own > 0 ? __builtin_popcountll(mk << (64 - own)) : 0;
-        int upto = c;                                              // leading rows in words 0 .. lane
-        upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
-        upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xf, 0xf, false);
-        upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xf, 0xf, false);
-        upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xf, 0xf, false);
-        upto += __builtin_amdgcn_update_dpp(0, upto, 0x142, 0xa, 0xf, false);   // row_bcast:15 into the second row
+        const int upto = sum_upto64(c);                            // leading rows in words 0 .. lane
         if (n >= __builtin_amdgcn_readlane(upto, 31)) return {-1, 0};
         auto word_of = [&](int j) {
             const unsigned lo = __builtin_amdgcn_readlane((unsigned)mk, j), hi = __builtin_amdgcn_readlane((unsigned)(mk >> 32), j);
@@ -166,6 +199,44 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
         else if (later) { const int j = (int)__builtin_ctzll(later); end = 64 * j + (int)__builtin_ctzll(word_of(j)); }
         return {64 * word + bit, end - 64 * word - bit};
     };
+    // ---- parts of every context, at most a.splits: what the partial sums have room for, and right only if rows fill their blocks and
+    // nothing is cut off at a block's end.  How many blocks there are and how long the contexts is known here: lane i prices i + 1
+    // parts in eighths of a us (a workgroup starts and stores in 8 us, 64 positions take 2.5, a part's sums are written and read at
+    // about 4 TB/s), by whole turns of the chip's places; unequal contexts, which fill a last turn, by the work there is where that
+    // is less.  us, 32/8 heads, always a.splits parts | now: 4 x 16 rows over 2-3K positions 39 | 27, 8 x 7 over
+    // 1-4K 51 | 35, 32 single rows at 500-2000 96 | 55, 64 at 2-8K 329 | 263, 2 x 200 rows at 7-9K 124 | 98, 500 at 9000 151 | 128;
+    // 4 x 60 at 9-16K 130 | 131.
+    if constexpr (count) {
+        const int own = min(64, r_end - 64 * lane);
+        const int blocks = __builtin_amdgcn_readlane(sum_upto64(lane < LOOK / 64 && own > 0 ? (int)__builtin_popcountll(lead_mask[lane] << (64 - own)) : 0), 63);
+        int longest = 0;
+        float total = 0.f;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            longest = max(longest, wave_furthest[i]);
+            total += (float)wave_total[i];
+        }
+        const int parts = lane + 1, items = blocks * a.Hkv * parts;
+        const float one = 8.f + 0.0390625f * (float)longest / (float)parts;
+        float us = (float)((items + PLACES - 1) / PLACES) * one;
+        if (items > PLACES && 32.f * total < .9f * (float)blocks * (float)longest)
+            us = fminf(us, (float)a.Hkv * (8.f * (float)(blocks * parts) + 1.25f * total) / (float)PLACES + .5f * one);
+        us += (float)a.T * (float)a.Hq * (float)parts * 2.6e-4f;
+        if (parts == splits) us *= .9f;        // (what the prices are good to)
+        unsigned key = parts <= splits ? (unsigned)fminf(us * 8.f, 1.0e8f) << 5 | (unsigned)lane : ~0u;
+        static_assert(MAX_PARTS <= 32, "five bits, two rows of lanes");
+        key = min(key, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)key, 0x111, 0xf, 0xf, false));
+        key = min(key, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)key, 0x112, 0xf, 0xf, false));
+        key = min(key, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)key, 0x114, 0xf, 0xf, false));
+        key = min(key, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)key, 0x118, 0xf, 0xf, false));
+        key = min(key, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)key, 0x142, 0xa, 0xf, false));
+        splits = (int)(__builtin_amdgcn_readlane(key, 31) & 31u) + 1;
+        // the grid's workgroups, dealt out again
+        wgs = (int)gridDim.x / (a.Hkv * splits);
+        part = (int)blockIdx.x % splits, bid = (int)blockIdx.x / splits;
+        hk = bid % a.Hkv, which = bid / a.Hkv;
+        if (which >= wgs) return;
+    }
     const int Nkv = a.Hkv * D;
     const long long n_blocks = a.n_slots / a.bs;
     const long long cap = (long long)a.max_blocks * a.bs;
@@ -203,7 +274,7 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
     // this workgroup's part of the context: blocks c_lo .. c_hi - 1 of 32 positions (all of them without parts)
     int c_lo = 0, c_hi = (n_ctx + 31) >> 5;
     if (a.splits > 1) {
-        const int per = (c_hi + a.splits - 1) / a.splits;
+        const int per = (c_hi + splits - 1) / splits;
         c_lo = min(part * per, c_hi);
         c_hi = min(c_lo + per, c_hi);
         n_ctx = min(n_ctx, 32 * c_hi);                 // positions past the part are not loaded
@@ -225,11 +296,6 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
         if (col_ok) v = *(const u32x4 *)((const bf16_t *)a.q + q_at + 16 * s + 8 * lh);
         qf[s] = __builtin_bit_cast(bf16x8, v);
     }
-    // (a use of the query registers ahead of the loop: the compiler places its wait for these loads here and
-    // not in front of the first MFMA of every step, where it would also wait for the copies in flight)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[s]));
-
     f32x16 acc[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t)
@@ -370,6 +436,10 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
     // too (all zeros, from one 16-byte constant), which keeps the count of copies in flight the same in every step.
     {
         if (n_chunks > c_lo) refill(c_lo);
+        // (a use of the query registers ahead of the loop: the compiler places its wait for these loads here, behind that for the
+        // table entries, and not in front of the first MFMA of every step, where it would also wait for the copies in flight)
+#pragma unroll
+        for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[s]));
         auto entries = [&](int cb, int (&e)[GPW]) {
 #pragma unroll
             for (int h = 0; h < GPW; ++h) e[h] = lookup(32 * cb + 4 * (wu + NW * h));
@@ -424,8 +494,10 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
         // this part's (running maximum, weight sum, unnormalised output) of every column, for the kernel that
         // combines the parts of a (row, query head) in part order
         if (col_ok || (!row_ok && w == 0 && li < G)) {
-            float *pp = a.part + (((size_t)(t0 + (col_ok ? r_j : 0)) * a.Hq + (size_t)hk * G + g_j) * a.splits + part) * (D + 2);
+            float *p0 = a.part + ((size_t)(t0 + (col_ok ? r_j : 0)) * a.Hq + (size_t)hk * G + g_j) * a.splits * (D + 2), *pp = p0 + part * (D + 2);
             if (lh == 0) *(f32x2 *)pp = (f32x2){m, l};
+            // fewer parts than there is room for: the last place tells how many (a sum of weights is never negative)
+            if (count && lh == 0 && part == 0 && splits < a.splits) *(f32x2 *)(p0 + (a.splits - 1) * (D + 2)) = (f32x2){(float)splits, -1.f};
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -436,17 +508,29 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
         }
         continue;
     }
-    // a row that is not valid leads a block of its own and gets zeros
-    if (col_ok || (!row_ok && w == 0 && li < G)) {
-        const float inv = l > 0.f ? 1.f / l : 0.f;
-        bf16_t *orow = (bf16_t *)a.out + ((size_t)(t0 + (col_ok ? r_j : 0)) * a.Hq + (size_t)hk * G + g_j) * D;
+    // Columns are rows of the result: a wavefront turns its 32 around through LDS, in the tiles nobody reads any more, so that a store
+    // instruction writes four pieces of 256 bytes.  (Straight from the registers it would be 8 bytes of 32 rows: one
+    // run of 300 rows at 2048 positions 85.1 us, now 83.6; the sums of parts, few columns to a workgroup, go straight: through LDS
+    // one row at 1000 positions pays 0.5 of 9 us.)
+    __syncthreads();
+    lds_byte *strip = (lds_byte *)tiles + wu * (int)(sizeof(tiles) / NW);
+    constexpr int SP = 256 + 16;             // bytes per column of 128 bf16
+    static_assert(32 * SP <= sizeof(tiles) / NW, "a strip per wavefront");
+    auto column_ok = [&](int c) { return row_ok ? wu * RBW + c / G < nrows : wu == 0 && c < G; };   // a row that is not valid leads a block of its own
+    auto result_at = [&](int c) { return (size_t)(t0 + wu * RBW + c / G) * a.Hq + (size_t)hk * G + c % G; };   // (row, query head) of column c
+    // a row that is not valid gets zeros
+    const float inv = l > 0.f ? 1.f / l : 0.f;
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int v = 0; v < 16; v += 4) {   // d = 32 t + 8 (v / 4) + 4 lh ..
-                const u32x2 o = {pack_bf16(acc[t][v] * inv, acc[t][v + 1] * inv), pack_bf16(acc[t][v + 2] * inv, acc[t][v + 3] * inv)};
-                *(u32x2 *)(orow + 32 * t + 2 * v + 4 * lh) = o;
-            }
+        for (int v = 0; v < 16; v += 4)       // d = 32 t + 8 (v / 4) + 4 lh ..
+            *(__attribute__((address_space(3))) u32x2 *)(strip + li * SP + (32 * t + 2 * v + 4 * lh) * 2) =
+                (u32x2){pack_bf16(acc[t][v] * inv, acc[t][v + 1] * inv), pack_bf16(acc[t][v + 2] * inv, acc[t][v + 3] * inv)};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int c = 4 * i + g4;
+        const u32x4 o = *(const __attribute__((address_space(3))) u32x4 *)(strip + c * SP + 16 * c16);
+        if (column_ok(c)) *(u32x4 *)((bf16_t *)a.out + result_at(c) * D + 8 * c16) = o;
     }
   }
 }
@@ -462,7 +546,7 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
 // 330 | 390, 32 at 300 37 | 42, 4 x 64 rows at 16K, 8/8 heads 357 | 414; in parts, 4 x 64 rows over 16K 108 | 123, 4 x 32 104 | 78.
 BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts)
 {
-    BlockPlan p = {4, 64, 1, 1};
+    BlockPlan p = {4, 64, 1, 1, false};
     if (T <= 0) return p;
     const bool long_runs = (long long)T * G > 128ll * n_seqs;   // longer than a block of four wavefronts
     if (long_runs) {
@@ -473,7 +557,8 @@ BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts)
     }
     const int rbg = 32 * p.waves / G;
     if (parts) {
-        // parts of every block's context, one workgroup each, until there is one per CU (two of four wavefronts)
+        // parts of every block's context, one workgroup each, until there is one per CU (two of four wavefronts); the kernel
+        // takes fewer where there turn out to be more than T / rbg blocks
         const long long wgs = (long long)((T + rbg - 1) / rbg) * Hkv, want = p.waves == 8 ? 256 : 512;
         if (wgs < want) p.splits = (int)((want + wgs - 1) / wgs < MAX_PARTS ? (want + wgs - 1) / wgs : MAX_PARTS);
         if (p.splits == 1) return plan_blocks(T, n_seqs, Hkv, G, false);   // nothing is cut: the call is the one without parts
@@ -509,6 +594,11 @@ BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts)
     }
     const long long wgs = blocks + (spare < 0 ? 0 : spare < ends ? spare : ends);
     p.wgs = (int)(wgs < rows ? wgs : rows);
+    // Parts counted by the kernel (one range: every workgroup sees all blocks) where as many blocks as runs that start anywhere
+    // make on average would not fit the chip at once: a call that fits pays 1 us for nothing (2 x 2 rows at 2000 positions 12.8 us,
+    // counted 14.1).
+    const long long n = n_seqs < T ? n_seqs : T, likely = whole ? T / rbg : n + (T - n) / rbg;
+    p.count = p.splits > 1 && ranges == 1 && likely * Hkv * p.splits > (p.waves == 8 ? 256 : 512);
     return p;
 }
 
@@ -517,9 +607,12 @@ int launch_attention_blocks(const AttnArgs &a, int G, const BlockPlan &p, hipStr
     const int ranges = (a.T + p.range - 1) / p.range;
     const dim3 grid((unsigned)ranges * (unsigned)p.wgs * (unsigned)a.Hkv * (unsigned)a.splits), block(64 * p.waves);
     const bool pow2 = a.bs_shift >= 0;
+#define AB_LAUNCH_AS(GG, NW, POW2, PARTS) hipLaunchKernelGGL((paged_attention_blocks_kernel<GG, NW, POW2, PARTS>), grid, block, 0, stream, a, p.range, p.wgs)
 #define AB_LAUNCH(GG, NW) \
-    if (pow2) hipLaunchKernelGGL((paged_attention_blocks_kernel<GG, NW, true>), grid, block, 0, stream, a, p.range, p.wgs); \
-    else hipLaunchKernelGGL((paged_attention_blocks_kernel<GG, NW, false>), grid, block, 0, stream, a, p.range, p.wgs)
+    if (p.count && pow2) AB_LAUNCH_AS(GG, NW, true, Counted); \
+    else if (p.count) AB_LAUNCH_AS(GG, NW, false, Counted); \
+    else if (pow2) AB_LAUNCH_AS(GG, NW, true, AsPlanned); \
+    else AB_LAUNCH_AS(GG, NW, false, AsPlanned)
     switch (G * 16 + p.waves) {
     case 16 + 8: AB_LAUNCH(1, 8); break;
     case 32 + 8: AB_LAUNCH(2, 8); break;
@@ -532,6 +625,7 @@ int launch_attention_blocks(const AttnArgs &a, int G, const BlockPlan &p, hipStr
     default: return (int)hipErrorInvalidValue;
     }
 #undef AB_LAUNCH
+#undef AB_LAUNCH_AS
     return (int)hipGetLastError();
 }
 

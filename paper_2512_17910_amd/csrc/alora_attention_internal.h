@@ -24,6 +24,7 @@ constexpr int LOOKED_OVER = 256;   // batch rows per wavefront of which a row-bl
 // range (a multiple of 64), workgroups that share a range's row blocks (per K/V head and part), parts of every block's context.
 struct BlockPlan {
     int waves, range, wgs, splits;
+    bool count;          // the kernel settles the number of parts (at most splits) once it sees the row blocks
 };
 BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts);
 

@@ -10,7 +10,7 @@ import torch
 from oracle import attention as oatt
 from paper_2512_17910_amd import binding as ab
 from paper_2512_17910_amd import workloads as wl
-from test_launches import CUTS
+from test_launches import COUNTED, CUTS
 from gpu_util import TOL, maxnorm_rel, raw_bits, to_dev, to_f64
 
 pytestmark = pytest.mark.gpu
@@ -491,3 +491,26 @@ def test_suffix_every_cut(group, n_kv, block_size, lens, rows, parts, waves):
     pick = np.unique(np.r_[np.arange(0, c.T, 61), ends - 1, ends[:-1], [1, 31, 32, 63, 64, 127, 128, 255, 256]])
     pick = pick[pick < c.T]
     assert maxnorm_rel(out[pick], d.oracle(rows=pick)) <= TOL["bf16"]
+
+
+# Parts whose number the kernel settles, with a row that is no row (zeros; it leads a block, whose place in the partial sums has to
+# tell the number too).  The workspace holds NaN: a part's place that is read was written.  Bound: the reader's.
+@pytest.mark.parametrize("group,n_kv,block_size,lens,rows,waves", COUNTED)
+def test_suffix_split_with_counted_parts(group, n_kv, block_size, lens, rows, waves):
+    c = wl.attention_case(f"counted-g{group}w{waves}", "bf16", lens, rows, group * n_kv, n_kv, 128, block_size, seed=wl.SEED ^ (1020 + group + waves))
+    print(f"[case] {c.name} T={c.T} rows={rows}", flush=True)
+    d = DeviceCase(c)
+    nbytes = ab.alora_paged_attention_suffix_workspace_bytes(d.dims)
+    want = d.oracle()
+    for bad in (None, c.T - 1):
+        if bad is not None:
+            d.seq[bad] = -1
+            want[bad] = 0.0
+        ws = torch.full((nbytes,), 0xff, dtype=torch.uint8, device="cuda")
+        d.out.fill_(float("nan"))
+        ab.alora_paged_attention_suffix_split(d.q, d.kc, d.vc, d.bt, d.seq, d.pos, d.out, d.dims, ws)
+        torch.cuda.synchronize()
+        out = to_f64(d.out)
+        assert np.isfinite(out).all() and maxnorm_rel(out, want) <= TOL["bf16"]
+        if bad is not None:
+            assert not out[bad].any()

@@ -186,3 +186,20 @@ def test_the_reader_cases_run_on_the_gpu_reach_every_instantiation():
     for parts in (False, True):
         assert {(i[0], i[1]) for i, p in got if p == parts} == {(g, w) for g in (1, 2, 4, 8) for w in (4, 8)}
         assert {(i[1], i[2]) for i, p in got if p == parts} == {(w, pow2) for w in (4, 8) for pow2 in (0, 1)}
+
+
+# (group, K/V heads, block size, contexts, query rows, wavefronts): contexts in parts whose number the kernel settles, since more blocks
+# than rows fill are likely; single rows, runs that end inside a block, unequal contexts; test_gpu_attention.py runs them.
+COUNTED = [(1, 8, 16, [300 + 41 * i for i in range(9)], [1] * 9, 4), (2, 8, 20, [40, 2100, 700, 33, 1], [3, 1, 7, 33, 1], 4),
+           (4, 2, 16, [64 * i + 1 for i in range(10)], [1] * 10, 4), (8, 2, 12, [5000] + [200] * 11, [2] + [3] * 11, 4),
+           (1, 8, 16, [900, 1500], [150, 140], 8), (2, 8, 20, [900, 1500], [150, 140], 8), (4, 8, 16, [1200, 700, 90], [100, 61, 33], 8),
+           (8, 8, 12, [500, 3900], [50, 70], 8)]
+
+
+def test_parts_are_counted_by_the_kernel_only_where_they_may_not_fit_the_chip():
+    merge = "paged_attention_merge_kernel"
+    calls = launches_of([reader("alora_paged_attention_suffix_split", sum(rows), len(rows), g * n_kv, n_kv, block_size=bs) for g, n_kv, bs, _, rows, _ in COUNTED])
+    for call, case in zip(calls, COUNTED):
+        assert cut_of(call)[1] == case[5] and call["launches"][1]["kernel"] == merge and call["launches"][1]["ints"] == [128, 1, 1], (case, call)
+    for call in launches_of([reader("alora_paged_attention_suffix_split", T, n, 32, 8) for T, n in [(1, 1), (2, 2), (4, 2), (16, 1), (256, 4)]]):
+        assert call["launches"][1]["kernel"] == merge and call["launches"][1]["ints"] == [128, 1, 0], call
