@@ -11,7 +11,7 @@
 //
 // The low-rank term runs on bf16 MFMA without giving up a bit of S: the fp32 shrink result (the fixed-order sum of the
 // shrink's partials, or hi + lo of the bf16 pair it stored) is cut into three bf16 that add up to it exactly, B is
-// bf16 as it is, every product is exact in the fp32 accumulator.  (As fp32 multiply-adds, rank x 8 per thread, it was what
+// bf16 as it is, every product is exact in the fp32 accumulator; sums that are not finite are done again the plain way.  (As fp32 multiply-adds, rank x 8 per thread, it was what
 // bounded the kernel: a vector instruction takes four cycles, 640 of them per wavefront at rank 32.)
 //
 // What bounds it is a chain of dependent round trips, and for larger batches the partials' way in (25 MB at 256 rows and
@@ -188,7 +188,29 @@ __global__ __launch_bounds__(FIN_THREADS) void finish_bf16_kernel(const float *_
 #pragma unroll
         for (int h = 0; h < 2; ++h) *(f32x4 *)(d_lds + c16 * D_PITCH + 32 * w + 16 * h + 4 * g4) = acc[h];
         __syncthreads();
-        const f32x4 d0 = *(const f32x4 *)(d_lds + i * D_PITCH + 8 * c), d1 = *(const f32x4 *)(d_lds + i * D_PITCH + 8 * c + 4);
+        float *const dl = d_lds + i * D_PITCH + 8 * c;
+        f32x4 d0 = *(const f32x4 *)dl, d1 = *(const f32x4 *)(dl + 4);
+        // An infinite element of B times S is +-inf, but times a part of S that is zero, as the third one mostly is, NaN: a sum that is
+        // not finite is done again with S whole, product by product.  (0 times such a sum is NaN, 0 times all others 0.)
+        float none = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) none = fmaf(0.f, d0[e], fmaf(0.f, d1[e], none));
+        if (none != 0.f) {
+            const int a6 = a & 63, ra = (__builtin_amdgcn_readlane(rk, a6) >> (a < 64 ? 0 : 8)) & 0xff;
+#pragma unroll 1
+            for (int e = 0; e < 8; ++e) {
+                if (fabsf(dl[e]) < __builtin_inff()) continue;
+                float sum = 0.f;
+#pragma unroll 1
+                for (int j = 0; j < ra; ++j) {
+                    const bf16_t *sr = (const bf16_t *)(s_lds + i * S_PITCH) + j;
+                    const float s = bf16_bits_to_f32(sr[0]) + (bf16_bits_to_f32(sr[K]) + bf16_bits_to_f32(sr[2 * K]));   // exact
+                    sum = fmaf(s, bf16_bits_to_f32(*(const bf16_t *)(b_lds + j * B_PITCH + 16 * c + 2 * e)), sum);
+                }
+                dl[e] = sum;
+            }
+            d0 = *(const f32x4 *)dl, d1 = *(const f32x4 *)(dl + 4);
+        }
         d[0] = d0.x; d[1] = d0.y; d[2] = d0.z; d[3] = d0.w;
         d[4] = d1.x; d[5] = d1.y; d[6] = d1.z; d[7] = d1.w;
     }

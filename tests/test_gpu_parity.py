@@ -527,6 +527,32 @@ def test_finishing_kernel_at_the_edges_of_its_tiles(rank):
     assert not np.isfinite(to_f64(db.q)[row]).all() and np.array_equal(np.delete(q, row, 0), np.delete(first, row, 0))
 
 
+# Infinite adapter weights: infinite where S . B is, with its sign, NaN where two of them meet with opposite signs or one meets a zero, and
+# nothing else moves by a bit.  Few rows, and more than 64.
+@pytest.mark.parametrize("sizes", [[10, 3, 20, 17], [40, 3, 33, 24]])
+@pytest.mark.parametrize("rank", [8, 32, 64])
+def test_finishing_kernel_with_infinite_adapter_weights(rank, sizes):
+    segs = [wl.Segment(s, 0, n, s - 1, 0) for s, n in enumerate(sizes)]      # the first is a base-model request
+    w = wl.assemble(f"infinite-r{rank}-{sum(sizes)}", "bf16", 1024, 5, 2, 40, 3, rank, 16, segs, sizes, seed=320 + rank, extra_blocks=2)
+    rows = [np.flatnonzero(w.token_adapter_ids == b) for b in range(3)]
+    db = DeviceBatch(w)
+    db.x[int(rows[1][4])] = 0.0                                              # its shrink result is zero
+    db.forward()
+    first, same = raw_bits(db.q).copy(), np.ones((w.T, w.Nq), bool)
+    for b, j, n, v in [(0, 0, 3, np.inf), (1, rank - 1, 9, -np.inf), (1, 2, 10, np.inf), (1, 5, 10, np.inf), (2, 7, w.Nq - 1, np.inf)]:
+        db.B[b][j, n] = v
+        same[rows[b], n] = False
+    db.reset()
+    db.forward()
+    q, x = to_f64(db.q), to_f64(db.x)
+    assert np.array_equal(raw_bits(db.q)[same], first[same])
+    for b in range(3):
+        cols = np.flatnonzero(~same[rows[b][0]])
+        with np.errstate(invalid="ignore"):
+            want = ((x[rows[b]] @ to_f64(db.A[b]))[:, :, None] * to_f64(db.B[b])[None, :, cols]).sum(1)
+        assert not np.isfinite(want).any() and np.array_equal(q[rows[b]][:, cols], want, equal_nan=True), (b, cols)
+
+
 # The last rows of a fused projection in tiles of 128 x 128: ragged rows behind 256-row tiles of each width and by themselves, a feature
 # tile that ends inside the 128, fewer slices of the hidden dimension than the ring has stages.  Bounds: those of every bf16 case in _check_full.
 @pytest.mark.parametrize("hidden,hq,hkv,d,rows", [t[:5] for t in TAILS if not t[5]])
