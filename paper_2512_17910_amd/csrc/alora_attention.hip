@@ -16,6 +16,7 @@
 // (lane groups by shuffles, wavefronts through LDS), so the result does not depend on timing.
 #include "alora_internal.h"
 #include "alora_attention.h"
+#include <type_traits>
 #include "alora_attention_internal.h"
 #include <new>
 #include <algorithm>
@@ -337,31 +338,42 @@ __global__ __launch_bounds__(256) void paged_attention_merge_kernel(const float 
         }
     };
     constexpr int AHEAD = COUNTED ? 2 : PER;   // requested before it is known how many there are
+    const int room = splits;
+    f32x2 last = {};
+    if (COUNTED) last = *(const f32x2 *)(pp + (size_t)(room - 1) * (D + 2));
 #pragma unroll
-    for (int i = 0; i < AHEAD; ++i) load(i, grp + NG * i < splits);
+    for (int i = 0; i < AHEAD; ++i) load(i, grp + NG * i < room);
+    float M = M_FLOOR, L = 0.f;
+    f32x2 o = {0.f, 0.f};
+    auto combine = [&](auto n) {
+#pragma unroll
+        for (int i = 0; i < decltype(n)::value; ++i) M = fmaxf(M, ml[i].x);
+#pragma unroll
+        for (int i = 0; i < decltype(n)::value; ++i) {
+            const float f = __builtin_amdgcn_exp2f(ml[i].x - M);
+            L += ml[i].y * f;
+            o.x += ov[i].x * f;
+            o.y += ov[i].y * f;
+        }
+    };
     if (COUNTED) {
-        const f32x2 last = *(const f32x2 *)(pp + (size_t)(splits - 1) * (D + 2));
-        if (last.y < 0.f) splits = (int)last.x;
+        splits = __builtin_amdgcn_readfirstlane(last.y < 0.f ? (int)last.x : room);
+        if (room > AHEAD * NG) {
 #pragma unroll
-        for (int i = AHEAD; i < PER; ++i) load(i, grp + NG * i < splits);
+            for (int i = AHEAD; i < PER; ++i) load(i, grp + NG * i < splits);
+        }
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i)
             if (grp + NG * i >= splits) {      // (whatever the workspace held)
                 ml[i] = (f32x2){M_FLOOR, 0.f};
                 ov[i] = (f32x2){0.f, 0.f};
             }
-    }
-    float M = M_FLOOR;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) M = fmaxf(M, ml[i].x);
-    float L = 0.f;
-    f32x2 o = {0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const float f = __builtin_amdgcn_exp2f(ml[i].x - M);
-        L += ml[i].y * f;
-        o.x += ov[i].x * f;
-        o.y += ov[i].y * f;
+        // (Where there is room for no more than these, the instructions of the others are left out: 21 thousand rows and heads in 3 parts
+        // 15.2 us as a call without counted parts, 17.3 with and all the instructions, now 11.7.)
+        if (room > AHEAD * NG) combine(std::integral_constant<int, PER>{});
+        else combine(std::integral_constant<int, AHEAD>{});
+    } else {
+        combine(std::integral_constant<int, PER>{});
     }
     if (dd == 0) { gm[grp] = M; gl[grp] = L; }
     go[grp][dd] = o;

@@ -84,7 +84,7 @@ __device__ __forceinline__ void both_halves(float x, float &lo, float &hi)
     lo = x, hi = x;
     asm("s_nop 3\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 3" : "+v"(lo), "+v"(hi));
 }
-// sum, and largest from 0 on, over lanes 0 .. lane (row_shr:1, 2, 4, 8, then row_bcast:15 and 31 into the rows above)
+// sums, and largest from 0 on, over lanes 0 .. lane (row_shr:1, 2, 4, 8, then row_bcast:15 and 31 into the rows above)
 __device__ __forceinline__ int sum_upto64(int x)
 {
     x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
@@ -93,6 +93,15 @@ __device__ __forceinline__ int sum_upto64(int x)
     x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
     x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
     return x + __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+}
+__device__ __forceinline__ float sum_upto64(float x)
+{
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x111, 0xf, 0xf, false));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x112, 0xf, 0xf, false));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x114, 0xf, 0xf, false));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x118, 0xf, 0xf, false));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x142, 0xa, 0xf, false));
+    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x143, 0xc, 0xf, false));
 }
 __device__ __forceinline__ int max_upto64(int x)
 {
@@ -128,16 +137,24 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
     constexpr int LOOK = LOOKED_OVER * NW, SCANS = LOOKED_OVER / 64;   // batch rows a workgroup looks over, and each of its threads
     __shared__ unsigned long long lead_mask[LOOK / 64];          // bit i of word j: row 64 j + i from the range's first leads a block
     __shared__ int32_t row_seq[LOOK], row_pos[LOOK];
-    __shared__ int wave_furthest[NW], wave_total[NW];
+    __shared__ int wave_furthest[NW], wave_blocks[NW];
+    __shared__ float wave_us[NW];
+    // what 64 positions of a row block cost, us, and what every row of it adds (for the number of parts, see there)
+    constexpr float US_BLOCK = NW == 8 ? 1.4f : 1.8f, US_ROW = NW == 8 ? .6f / RBG : 0.f;
     constexpr int WIN = 64;            // blocks of 32 positions whose table entries the window below holds
     __shared__ int32_t window[WIN * 32 / 4 + 2];   // block sizes are multiples of 4
 
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4, li = lane & 31, lh = lane >> 5;
     const int wu = __builtin_amdgcn_readfirstlane(w);
     // grid: (range of batch rows, workgroup of the range, K/V head, part of the context); a.splits parts, 1 = the whole context
-    int splits = a.splits, part = (int)blockIdx.x % splits, bid = (int)blockIdx.x / splits;
-    int hk = bid % a.Hkv, which = bid / a.Hkv % wgs;
-    const int r_begin = bid / a.Hkv / wgs * range, r_end = min(a.T, r_begin + range);
+    // (counted parts: one range, and the workgroups are dealt out once the row blocks are known)
+    int splits = a.splits, part = 0, hk = 0, which = 0, r_begin = 0, r_end = a.T;
+    if constexpr (!count) {
+        part = (int)blockIdx.x % splits;
+        const int bid = (int)blockIdx.x / splits;
+        hk = bid % a.Hkv, which = bid / a.Hkv % wgs;
+        r_begin = bid / a.Hkv / wgs * range, r_end = min(a.T, r_begin + range);
+    }
     // ---- the rows of the range that lead a block (range <= LOOK - RBG: the RBG rows behind it say where its last block ends) ----
     // A row does unless the row before it in the batch is the same sequence's previous position and the position
     // is not a multiple of RBG (then an earlier row leads).  The workgroups of a range take them in turn: the leading rows
@@ -154,7 +171,8 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
                 if (t > 0) { sq1[i] = a.seq[t - 1]; p1[i] = a.pos[t - 1]; }
             }
         }
-        int furthest = 0, total = 0;           // last position of a row; blocks of 32 positions before the leading rows
+        int furthest = 0, blocks = 0;          // last position of a row; leading rows
+        float us = 0.f;                        // all their positions cost
 #pragma unroll
         for (int i = 0; i < SCANS; ++i) {
             const bool ok = sq[i] >= 0 && sq[i] < a.n_seqs && p0[i] >= 0;
@@ -165,12 +183,15 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
             row_pos[i * 64 * NW + tid] = p0[i];
             if (count && ok && i * 64 * NW + tid < a.T) {
                 furthest = max(furthest, p0[i]);
-                if (lead) total += min(p0[i] >> 5, 1 << 18);
+                us += (float)p0[i] * (1.f / 64) * (lead ? US_BLOCK + US_ROW : US_ROW);
             }
+            const int own = min(64, a.T - 64 * (i * NW + wu));     // rows of the word that are the batch's
+            if (count && own > 0) blocks += (int)__builtin_popcountll(mk << (64 - own));
         }
         if constexpr (count) {
             wave_furthest[w] = __builtin_amdgcn_readlane(max_upto64(furthest), 63);      // (every lane writes the same)
-            wave_total[w] = __builtin_amdgcn_readlane(sum_upto64(total), 63);
+            wave_us[w] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sum_upto64(us)), 63));
+            wave_blocks[w] = blocks;
         }
         __syncthreads();
     }
@@ -201,28 +222,38 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
     };
     // ---- parts of every context, at most a.splits: what the partial sums have room for, and right only if rows fill their blocks and
     // nothing is cut off at a block's end.  How many blocks there are and how long the contexts is known here: lane i prices i + 1
-    // parts in eighths of a us (a workgroup starts and stores in 8 us, 64 positions take 2.5, a part's sums are written and read at
-    // about 4 TB/s), by whole turns of the chip's places; unequal contexts, which fill a last turn, by the work there is where that
-    // is less.  us, 32/8 heads, always a.splits parts | now: 4 x 16 rows over 2-3K positions 39 | 27, 8 x 7 over
-    // 1-4K 51 | 35, 32 single rows at 500-2000 96 | 55, 64 at 2-8K 329 | 263, 2 x 200 rows at 7-9K 124 | 98, 500 at 9000 151 | 128;
-    // 4 x 60 at 9-16K 130 | 131.
+    // parts, in us.  A workgroup takes START and US_BLOCK for 64 positions, and with eight wavefronts, which share a CU's matrix units, US_ROW
+    // for every row besides.  As many as the chip has places for last as long as the longest one; more of them whole turns of it if
+    // all are alike, and the more they differ the work there is and the end of a long one: a place whose part is short takes another.  A part's
+    // sums are written and read at about 5 TB/s.  10 us of the call depend on none of it, and fewer parts have to promise 5 %.
+    // Fitted to 1000 calls, and measured against always a.splits parts on 540 (1 to 64 sequences of 1 to 256 rows at 256 to 32K positions, 8 to
+    // 64 heads): 1.14 times as fast on average, seven calls under 0.97 (the counting takes 1 to 1.5 us; the worst, 0.86 and 0.89, are
+    // 3 x 39 rows at 14-28K, 64/8 heads, 158 and 184 us, and 12 x 18 at 2-5.5K, 70 and 79).  With one length for all contexts and 8 us for a
+    // start, which are the call's: 1.11 times, one call in 30 under 0.97.  us, always a.splits parts | priced like that | now, 32/8 heads: 4 x 16
+    // rows over 2-3K positions 38.6 | 26.9 | 26.3, 8 x 7 over 1-4K 49.6 | 34.0 | 32.8, 32 single rows at 500-2000 88 | 48.7 | 47.1, 64 at 2-8K 325 |
+    // 254 | 247, 2 x 200 rows at 7-9K 137 | 100 | 96, 4 x 60 at 9-16K 130 | 116 | 115, 8 x 30 at 6-12K 111 | 106 | 106, 3 x 155 at 1-3K
+    // 46 | 53 | 46; 8/8 heads 3 x 212 at 3-10K 63 | 69 | 64; 64/8 heads 47 x 2 at 2-7K 200 | 211 | 194.
     if constexpr (count) {
-        const int own = min(64, r_end - 64 * lane);
-        const int blocks = __builtin_amdgcn_readlane(sum_upto64(lane < LOOK / 64 && own > 0 ? (int)__builtin_popcountll(lead_mask[lane] << (64 - own)) : 0), 63);
-        int longest = 0;
+        int longest = 0, blocks = 0;
         float total = 0.f;
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
             longest = max(longest, wave_furthest[i]);
-            total += (float)wave_total[i];
+            blocks += wave_blocks[i];
+            total += wave_us[i];
         }
+        constexpr float START = NW == 8 ? 2.f : 3.f, SUMS = NW == 8 ? 1.6e-4f : 2.4e-4f;
         const int parts = lane + 1, items = blocks * a.Hkv * parts;
-        const float one = 8.f + 0.0390625f * (float)longest / (float)parts;
-        float us = (float)((items + PLACES - 1) / PLACES) * one;
-        if (items > PLACES && 32.f * total < .9f * (float)blocks * (float)longest)
-            us = fminf(us, (float)a.Hkv * (8.f * (float)(blocks * parts) + 1.25f * total) / (float)PLACES + .5f * one);
-        us += (float)a.T * (float)a.Hq * (float)parts * 2.6e-4f;
-        if (parts == splits) us *= .9f;        // (what the prices are good to)
+        const float share = __builtin_amdgcn_rcpf((float)parts), turns = (float)((items + PLACES - 1) / PLACES);
+        const float each = __builtin_amdgcn_rcpf((float)blocks);
+        const float one = START + (US_BLOCK + US_ROW * (float)a.T * each) * (1.f / 64) * (float)longest * share, mean = START + total * each * share;
+        float us = turns * one;
+        if (turns > 1.f) {
+            const float differ = fminf(fmaxf(4.f - 4.f * mean * __builtin_amdgcn_rcpf(one), 0.f), 1.f);
+            us += differ * fminf((float)items * (1.f / PLACES) * mean + (NW == 8 ? .35f : .5f) * one - us, 0.f);
+        }
+        us += 10.f + (float)a.T * (float)a.Hq * (float)parts * SUMS;
+        if (parts == splits) us *= .95f;
         unsigned key = parts <= splits ? (unsigned)fminf(us * 8.f, 1.0e8f) << 5 | (unsigned)lane : ~0u;
         static_assert(MAX_PARTS <= 32, "five bits, two rows of lanes");
         key = min(key, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)key, 0x111, 0xf, 0xf, false));
@@ -231,9 +262,10 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
         key = min(key, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)key, 0x118, 0xf, 0xf, false));
         key = min(key, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)key, 0x142, 0xa, 0xf, false));
         splits = (int)(__builtin_amdgcn_readlane(key, 31) & 31u) + 1;
-        // the grid's workgroups, dealt out again
+        // the grid's workgroups, dealt out
         wgs = (int)gridDim.x / (a.Hkv * splits);
-        part = (int)blockIdx.x % splits, bid = (int)blockIdx.x / splits;
+        part = (int)blockIdx.x % splits;
+        const int bid = (int)blockIdx.x / splits;
         hk = bid % a.Hkv, which = bid / a.Hkv;
         if (which >= wgs) return;
     }
@@ -596,7 +628,8 @@ BlockPlan plan_blocks(int T, int n_seqs, int Hkv, int G, bool parts)
     p.wgs = (int)(wgs < rows ? wgs : rows);
     // Parts counted by the kernel (one range: every workgroup sees all blocks) where as many blocks as runs that start anywhere
     // make on average would not fit the chip at once: a call that fits pays 1 us for nothing (2 x 2 rows at 2000 positions 12.8 us,
-    // counted 14.1).
+    // counted 14.1).  And where there are four parts to choose from: of 54 calls cut into two or three, 26 lost more than they gained
+    // (3 x 222 rows at 1-4K 68.5 us, counted 71.4; 4 x 241, 64/8 heads, at 500-1600 114 and 125), six gained 3 to 9 %.
     const long long n = n_seqs < T ? n_seqs : T, likely = whole ? T / rbg : n + (T - n) / rbg;
     p.count = p.splits > 1 && ranges == 1 && likely * Hkv * p.splits > (p.waves == 8 ? 256 : 512);
     return p;

@@ -514,3 +514,20 @@ def test_suffix_split_with_counted_parts(group, n_kv, block_size, lens, rows, wa
         assert np.isfinite(out).all() and maxnorm_rel(out, want) <= TOL["bf16"]
         if bad is not None:
             assert not out[bad].any()
+
+
+# How many parts the kernel settles on: contexts that differ keep all of them, since a workgroup whose part is short takes another;
+# alike and short, they go together.  A context in fewer parts than there is room for tells so in its last place.
+@pytest.mark.parametrize("n_q,rows,lens,parts", [(8, 212, [7987, 9054, 2831], 11), (16, 219, [6775, 7681, 2401], 6), (32, 1, list(range(500, 2000, 47)), 2)])
+def test_suffix_split_parts_of_unequal_contexts(n_q, rows, lens, parts):
+    c = wl.attention_case(f"parts-{n_q}x{rows}", "bf16", lens, [rows] * len(lens), n_q, 8, 128, 16, seed=wl.SEED ^ (1040 + n_q))
+    d = DeviceCase(c)
+    ws = torch.zeros(ab.alora_paged_attention_suffix_workspace_bytes(d.dims), dtype=torch.uint8, device="cuda")
+    ab.alora_paged_attention_suffix_split(d.q, d.kc, d.vc, d.bt, d.seq, d.pos, d.out, d.dims, ws)
+    room = ws.numel() // (c.T * n_q * 130 * 4)
+    last = ws.view(torch.float32).view(c.T, n_q, room, 130)[:, :, room - 1, :2]
+    settled = torch.where(last[..., 1] < 0, last[..., 0], float(room)).unique().tolist()
+    print(f"[case] {c.name} room for {room} settled {settled}", flush=True)
+    assert settled == [parts]
+    pick = np.arange(0, c.T, 37)
+    assert maxnorm_rel(to_f64(d.out)[pick], d.oracle(rows=pick)) <= TOL["bf16"]
