@@ -113,7 +113,10 @@ int alora_paged_attention_suffix(const void *q, const void *k_cache, const void 
  * and a second kernel combines them in a fixed order.  The largest number of parts, and with it the workspace, depends on
  * n_tokens, n_seqs and the head counts, and is not monotonic in them: ask for the dims of the call.  Where more row blocks
  * are likely than n_tokens fill, the kernel takes fewer parts, by the blocks and contexts it finds in the positions.
- * Results equal those of alora_paged_attention_suffix up to fp32 summation order and do not depend on timing.
+ * Results equal those of alora_paged_attention_suffix up to fp32 summation order and do not depend on timing: the same call
+ * gives the same bits.  But where the kernel settles the number of parts, the summation order of a row, and with it its last
+ * bits, depends on the positions of all sequences of the call, not on its own alone; a caller who wants a request to keep its
+ * bits whatever else is in the batch calls alora_paged_attention_suffix, where they depend on the request only.
  *   workspace  device, 16-byte aligned, >= alora_paged_attention_suffix_workspace_bytes() bytes; contents on
  *              entry irrelevant; calls that share it must be stream-ordered.  ALORA_EWORKSPACE otherwise.
  */

@@ -531,3 +531,31 @@ def test_suffix_split_parts_of_unequal_contexts(n_q, rows, lens, parts):
     assert settled == [parts]
     pick = np.arange(0, c.T, 37)
     assert maxnorm_rel(to_f64(d.out)[pick], d.oracle(rows=pick)) <= TOL["bf16"]
+
+
+def test_what_the_bits_of_a_row_depend_on():
+    """Whole contexts: its own sequence.  In parts also on the other sequences' positions, which settle how many parts there are (then
+    equal within the reader's bound); the same call twice gives the same bits either way."""
+    lens, rows = [7987, 9054, 2831], [212, 212, 212]
+    c = wl.attention_case("bits", "bf16", lens, rows, 8, 8, 128, 16, seed=wl.SEED ^ 1060)
+    d = DeviceCase(c)
+    ws = torch.zeros(ab.alora_paged_attention_suffix_workspace_bytes(d.dims), dtype=torch.uint8, device="cuda")
+    own = slice(424, 636)                # the rows of the third sequence
+
+    def both():
+        whole = raw_bits(_run_suffix(d)).copy()
+        ws.fill_(0xff)
+        ab.alora_paged_attention_suffix_split(d.q, d.kc, d.vc, d.bt, d.seq, d.pos, d.out, d.dims, ws)
+        torch.cuda.synchronize()
+        return whole, raw_bits(d.out).copy()
+
+    whole, parts = both()
+    again = both()
+    assert np.array_equal(whole, again[0]) and np.array_equal(parts, again[1])
+    d.pos[:424] -= 6000                  # the others' contexts are shorter now
+    whole2, parts2 = both()
+    assert np.array_equal(whole[own], whole2[own])
+    want = oatt.paged_attention(wl.widen_f64(c.q, c.dtype), wl.widen_f64(c.k_cache, c.dtype), wl.widen_f64(c.v_cache, c.dtype), c.block_tables,
+                                c.token_seq_ids, c.token_positions, c.block_size, 8, 8, 128, scale=None, rows=np.arange(424, 636, 9))
+    for bits in (parts, parts2):
+        assert maxnorm_rel(wl.widen_f64(bits[own][::9], "bf16"), want) <= TOL["bf16"]
