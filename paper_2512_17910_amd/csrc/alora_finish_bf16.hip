@@ -15,11 +15,12 @@
 // bounded the kernel: a vector instruction takes four cycles, 640 of them per wavefront at rank 32.)
 //
 // What bounds it is a chain of dependent round trips, and for larger batches the partials' way in (25 MB at 256 rows and
-// four splits).  So there are three round trips: table entry, row ids and the adapters' tables (a lane per adapter);
-// then all splits' partials, the S row, the B slice, slot and position; then the angles.  And workgroups are small: of 32 rows and
+// four splits).  So there are few round trips: table entry and row ids, then (adapted rows, which wait for them in the shadow of all other loads) the adapters'
+// tables, a lane per adapter; all splits' partials, the S row, slot and position, and the B slice; then the angles.  And workgroups are small: of 32 rows and
 // 1024 threads one fits a CU (106 registers), and the 12 rows an adapter has in a decode batch leave two thirds of
 // it idle while it loads its slice of B; of 16 rows two fit.
-// Measured, us: one row 5.7 -> 4.5, 256 rows of 16 adapters, rank 32 11.9 -> 9.3 (32 rows per workgroup 12.0), 777 rows in two splits 17.7 -> 13.0 (48 MB: 3.7 TB/s), 256 base rows 6.8 -> 7.0;
+// Measured, us: one row 5.7 -> 4.5, 256 rows of 16 adapters, rank 32 11.9 -> 9.3 (32 rows per workgroup 12.0), 777 rows in two splits 17.7 -> 13.0 (48 MB: 3.7 TB/s), 256 base rows 6.0 -> 6.2
+// (6.4 with the tables in front of the row ids), 1024 in three splits beside adapters of rank 64 13.7 -> 14.4 (15.5 with S . B in LDS of its own);
 // the whole call of 256 rows at rank 64 54.4 -> 47.5.
 #include <type_traits>
 #include "alora_internal.h"
@@ -71,28 +72,34 @@ __global__ __launch_bounds__(FIN_THREADS) void finish_bf16_kernel(const float *_
     constexpr int B_PITCH = FIN_COLS * 2 + 32;      // bytes per rank row of B (the transposing read takes 16 rows at once: 8 banks further each)
     constexpr int S_PITCH = 3 * K * 2 + 16;         // bytes per row of S: the three parts, K each
     constexpr int D_PITCH = FIN_COLS + 4;           // floats per row of S . B
+    // Two rank tiles: S . B takes the place of B, whose columns 32w .. 32w+31 are wavefront w's alone (row r, features 16h .. 16h+15 in
+    // row 2r + h), so that three workgroups fit a CU's LDS instead of two: 777 rows in two splits at rank 64 122.8 us a call, now 119.3,
+    // 1000 rows 136.8 and 134.7; one rank tile gains no place by it, and decode batches lose 1 %.
+    constexpr bool IN_B = RT == 2;
     __shared__ __attribute__((aligned(16))) unsigned char b_lds[K * B_PITCH], s_lds[FIN_ROWS * S_PITCH];
-    __shared__ __attribute__((aligned(16))) float d_lds[FIN_ROWS * D_PITCH];
+    __shared__ __attribute__((aligned(16))) float d_lds[IN_B ? 4 : FIN_ROWS * D_PITCH];
 
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = tid >> 5, c = tid & 31, n0 = blockIdx.y * FIN_COLS, n = n0 + 8 * c;
     const int half = FIN_ROWS * blockIdx.z;
-    // row ids straight from the per-entry list when there is one: the load does not wait for the entry
-    int t_direct = -1;
-    if (block_rows) t_direct = block_rows[32 * blockIdx.x + half + i];
-    // The adapters' tables, a lane per adapter: a look-up that waits for the entry would be a round trip of its own.
-    uint64_t bp0 = 0, bp1 = 0;
-    if (lane < L) bp0 = (uint64_t)B.p[lane];
-    if (64 + lane < L) bp1 = (uint64_t)B.p[64 + lane];
-    const int rk = ranks.r[lane] | ranks.r[64 + lane] << 8;
     const int4 entry = blocktab[blockIdx.x];
+    // row ids straight from the per-entry list when there is one: the load does not wait for the entry
+    int t = -1;
+    if (block_rows) t = block_rows[32 * blockIdx.x + half + i];
     const int a = __builtin_amdgcn_readfirstlane(entry.x), j0 = entry.y, cnt = entry.z;
     if (a < 0 || cnt <= half) return;  // unused table entry, or no rows in this half; uniform across the workgroup
     if (a > L || j0 < 0 || cnt > 32 || j0 + cnt > T) return;   // not a table of this batch
     const int N = Nq + 2 * Nkv;
     const bool adapted = a < L;
-    int t = half + i < cnt ? (block_rows ? t_direct : perm[j0 + half + i]) : -1;
-    if (t >= T) t = -1;
+    if (!block_rows && half + i < cnt) t = perm[j0 + half + i];
+    // The adapters' tables, a lane per adapter, on the way together with the row ids and behind them: rows of the base group do not wait for them.
+    uint64_t bp0 = 0, bp1 = 0;
+    int rk = 0;
+    if (adapted) {
+        bp0 = (uint64_t)B.p[lane], bp1 = (uint64_t)B.p[64 + lane];
+        rk = ranks.r[lane] | ranks.r[64 + lane] << 8;
+    }
+    if (half + i >= cnt || t >= T) t = -1;
     const bool live = t >= 0 && n < N;
 
     // everything that depends on the row id, issued together (the position first: the angles wait for it)
@@ -186,9 +193,10 @@ __global__ __launch_bounds__(FIN_THREADS) void finish_bf16_kernel(const float *_
             }
         }
 #pragma unroll
-        for (int h = 0; h < 2; ++h) *(f32x4 *)(d_lds + c16 * D_PITCH + 32 * w + 16 * h + 4 * g4) = acc[h];
+        for (int h = 0; h < 2; ++h)
+            *(f32x4 *)(IN_B ? (float *)(b_lds + (2 * c16 + h) * B_PITCH + 64 * w + 16 * g4) : d_lds + c16 * D_PITCH + 32 * w + 16 * h + 4 * g4) = acc[h];
         __syncthreads();
-        float *const dl = d_lds + i * D_PITCH + 8 * c;
+        float *const dl = IN_B ? (float *)(b_lds + (2 * i + (c >> 1 & 1)) * B_PITCH + 64 * (c >> 2) + 32 * (c & 1)) : d_lds + i * D_PITCH + 8 * c;
         f32x4 d0 = *(const f32x4 *)dl, d1 = *(const f32x4 *)(dl + 4);
         // An infinite element of B times S is +-inf, but times a part of S that is zero, as the third one mostly is, NaN: a sum that is
         // not finite is done again with S whole, product by product.  (0 times such a sum is NaN, 0 times all others 0.)
@@ -197,15 +205,16 @@ __global__ __launch_bounds__(FIN_THREADS) void finish_bf16_kernel(const float *_
         for (int e = 0; e < 4; ++e) none = fmaf(0.f, d0[e], fmaf(0.f, d1[e], none));
         if (none != 0.f) {
             const int a6 = a & 63, ra = (__builtin_amdgcn_readlane(rk, a6) >> (a < 64 ? 0 : 8)) & 0xff;
+            const bf16_t *const Ba = (const bf16_t *)B.p[a];
 #pragma unroll 1
             for (int e = 0; e < 8; ++e) {
-                if (fabsf(dl[e]) < __builtin_inff()) continue;
+                if (fabsf(dl[e]) < __builtin_inff() || n >= N) continue;
                 float sum = 0.f;
 #pragma unroll 1
                 for (int j = 0; j < ra; ++j) {
                     const bf16_t *sr = (const bf16_t *)(s_lds + i * S_PITCH) + j;
                     const float s = bf16_bits_to_f32(sr[0]) + (bf16_bits_to_f32(sr[K]) + bf16_bits_to_f32(sr[2 * K]));   // exact
-                    sum = fmaf(s, bf16_bits_to_f32(*(const bf16_t *)(b_lds + j * B_PITCH + 16 * c + 2 * e)), sum);
+                    sum = fmaf(s, bf16_bits_to_f32(Ba[(size_t)j * N + n + e]), sum);
                 }
                 dl[e] = sum;
             }
