@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2512_17910_amd import binding as ab
 from paper_2512_17910_amd import workloads as wl
-from test_launches import TAILS
+from test_launches import FINISHED, TAILS
 from gpu_util import DeviceBatch, TOL, check_grouping, host_operands, maxnorm_rel, raw_bits, to_dev, to_f64
 
 pytestmark = pytest.mark.gpu
@@ -509,12 +509,13 @@ def test_few_rows_with_no_adapters_and_with_many(rows, n_adapters, tuning):
 
 
 # The finishing kernel's tiles: entries of 1 to 33 rows of an adapter (half an entry per workgroup), ranks of one and of two 32-wide
-# rank tiles, full and partial, a feature tile that ends inside the 256.  Bounds: those of every bf16 case in _check_full.
-@pytest.mark.parametrize("rank", [8, 32, 40, 64])
+# rank tiles, full and partial, a feature tile that ends inside the 256; that these sizes lead to it is checked where the launches are
+# recorded.  Bounds: those of every bf16 case in _check_full.
+@pytest.mark.parametrize("rank", FINISHED["ranks"])
 def test_finishing_kernel_at_the_edges_of_its_tiles(rank):
-    sizes = [1, 15, 16, 17, 31, 32, 33]
+    sizes = FINISHED["entries"]
     segs = [wl.Segment(s, 0, n, s - 1, 0) for s, n in enumerate(sizes)]      # the first is a base-model request
-    w = wl.assemble(f"entries-r{rank}", "bf16", 256, 5, 2, 40, 6, rank, 16, segs, sizes, seed=300 + rank, extra_blocks=2)
+    w = wl.assemble(f"entries-r{rank}", "bf16", *FINISHED["shape"], len(sizes) - 1, rank, 16, segs, sizes, seed=300 + rank, extra_blocks=2)
     db = DeviceBatch(w)
     _check_full(w, db)
     # a row whose shrink result overflows fp32 keeps that to itself
@@ -529,11 +530,11 @@ def test_finishing_kernel_at_the_edges_of_its_tiles(rank):
 
 # Infinite adapter weights: infinite where S . B is, with its sign, NaN where two of them meet with opposite signs or one meets a zero, and
 # nothing else moves by a bit.  Few rows, and more than 64.
-@pytest.mark.parametrize("sizes", [[10, 3, 20, 17], [40, 3, 33, 24]])
+@pytest.mark.parametrize("sizes", FINISHED["infinite"])
 @pytest.mark.parametrize("rank", [8, 32, 64])
 def test_finishing_kernel_with_infinite_adapter_weights(rank, sizes):
     segs = [wl.Segment(s, 0, n, s - 1, 0) for s, n in enumerate(sizes)]      # the first is a base-model request
-    w = wl.assemble(f"infinite-r{rank}-{sum(sizes)}", "bf16", 1024, 5, 2, 40, 3, rank, 16, segs, sizes, seed=320 + rank, extra_blocks=2)
+    w = wl.assemble(f"infinite-r{rank}-{sum(sizes)}", "bf16", *FINISHED["shape"], 3, rank, 16, segs, sizes, seed=320 + rank, extra_blocks=2)
     rows = [np.flatnonzero(w.token_adapter_ids == b) for b in range(3)]
     db = DeviceBatch(w)
     db.x[int(rows[1][4])] = 0.0                                              # its shrink result is zero
@@ -554,9 +555,31 @@ def test_finishing_kernel_with_infinite_adapter_weights(rank, sizes):
 
 
 # The last rows of a fused projection in tiles of 128 x 128: ragged rows behind 256-row tiles of each width and by themselves, a feature
-# tile that ends inside the 128, fewer slices of the hidden dimension than the ring has stages.  Bounds: those of every bf16 case in _check_full.
+# tile that ends inside the 128, half as many slices of the hidden dimension as the ring has stages; with a layer bias and ranks of
+# their own too.  They sum in the order of the large tiles: the same bits where these take all rows, and for rows that keep the
+# base output where no row is adapted.  Bounds: those of every bf16 case in _check_full.
+@pytest.mark.parametrize("variants", [False, True])
 @pytest.mark.parametrize("hidden,hq,hkv,d,rows", [t[:5] for t in TAILS if not t[5]])
-def test_small_tiles_behind_large_ones(hidden, hq, hkv, d, rows):
+def test_small_tiles_behind_large_ones(hidden, hq, hkv, d, rows, variants, tuning):
     w = wl.small_mixed("bf16", seed=41, hidden=hidden, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, n_adapters=4, rank=24, seq_lens=(rows - 301, 170, 130, 1), pad_every=7)
-    _check_full(w)
-    _check_full(wl.small_mixed("bf16", seed=42, hidden=64, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, rank=8, seq_lens=(rows - 30, 30)))
+    if variants:
+        w = wl.with_variants(w, ranks=(8, 24, 16, 24), bias=True)
+    db, ref = _check_full(w)
+
+    def bits():
+        return [raw_bits(t).copy() for t in (db.q, db.kc, db.vc)]
+
+    small = bits()
+    for width in (4, 2):
+        tuning(width, 1)
+        db.reset()
+        db.forward()
+        assert all(np.array_equal(a, b) for a, b in zip(bits(), small)), width
+    tuning(0, 0)
+    db.reset()
+    db.forward(aid=torch.full_like(db.aid, -1))
+    keep = np.flatnonzero(ref.active == 0)
+    slots = w.slot_mapping[keep]
+    slots = slots[slots >= 0]
+    base = bits()
+    assert np.array_equal(base[0][keep], small[0][keep]) and all(np.array_equal(base[i][slots], small[i][slots]) for i in (1, 2))

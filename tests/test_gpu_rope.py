@@ -189,7 +189,21 @@ def test_repeated_calls_give_the_same_bits(tuning):
 
 @pytest.mark.parametrize("hidden,hq,hkv,d,rows", [t[:5] for t in TAILS if t[5]])
 def test_small_tiles_behind_large_ones_rotate(hidden, hq, hkv, d, rows):
-    """128 x 128 tiles (two quarters of a head per wavefront) behind 256-row tiles and by themselves, layer bias included."""
+    """128 x 128 tiles (two quarters of a head per wavefront) behind 256-row tiles and by themselves, layer bias included; the same bits
+    as from 256-row tiles of both widths."""
     w = wl.small_mixed("bf16", seed=43, hidden=hidden, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, rank=24, seq_lens=(rows - 301, 170, 130, 1), pad_every=7)
     _check(w)
-    _check(wl.with_variants(w, ranks=(8, 24, 16), bias=True))
+    v = wl.with_variants(w, ranks=(8, 24, 16), bias=True)
+    _check(v)
+    for w in (w, v):
+        db, tables = DeviceBatch(w), _tables(w)[2]
+        first = None
+        for tuning in ((0, 0), (4, 1), (2, 1)):
+            ab.alora_qkv_set_tuning(*tuning)
+            try:
+                _run(db, tables)
+            finally:
+                ab.alora_qkv_set_tuning(0, 0)
+            bits = [raw_bits(t).copy() for t in (db.q, db.kc, db.vc)]
+            first = first or bits
+            assert all(np.array_equal(a, b) for a, b in zip(bits, first)), tuning

@@ -54,9 +54,10 @@ def test_a_replay_is_the_launches_of_the_call(dtype):
 
 
 # (hidden, query heads, K/V heads, head size, rows, rotation, tile width / 64, 256-row tiles): fused projections whose last rows go in
-# tiles of 128 x 128, behind each width of the large ones and all by themselves; test_gpu_parity.py runs them.
+# tiles of 128 x 128, behind each width of the large ones and all by themselves, down to four slices of the hidden dimension; test_gpu_parity.py
+# and test_gpu_rope.py run them.
 TAILS = [(512, 5, 2, 40, 1030, False, 4, 1), (512, 60, 2, 128, 1030, False, 3, 4), (192, 22, 3, 128, 1290, False, 2, 3), (512, 24, 8, 128, 700, False, 4, 0),
-         (192, 60, 2, 128, 2100, True, 4, 8), (512, 22, 3, 128, 1290, True, 2, 2), (512, 24, 8, 128, 700, True, 4, 0)]
+         (128, 60, 2, 128, 2100, False, 4, 8), (128, 24, 8, 128, 3100, True, 4, 9), (192, 60, 2, 128, 2100, True, 4, 8), (512, 22, 3, 128, 1290, True, 2, 2), (512, 24, 8, 128, 700, True, 4, 0)]
 
 
 def test_last_rows_of_a_fused_projection_in_small_tiles():
@@ -67,6 +68,21 @@ def test_last_rows_of_a_fused_projection_in_small_tiles():
         N = (hq + 2 * hkv) * d
         assert l["kernel"] == "alora_gemm_bf16_kernel" and l["ints"] == [width, 0, int(rope)], l
         assert l["grid"][0] == up8(panels * -(-N // (64 * width))) + up8(-(-(T - 256 * panels) // 128) * -(-N // 128)) and T > 256 * panels, l
+
+
+# Batches whose rows the finishing kernel makes, run by test_gpu_parity.py: (hidden, query heads, K/V heads, head size), rows of the base
+# request and of each adapter, ranks.
+FINISHED = dict(shape=(1024, 5, 2, 40), entries=[1, 15, 16, 17, 31, 32, 33], infinite=[[10, 3, 20, 17], [40, 3, 33, 24]], ranks=[8, 32, 40, 64])
+
+
+def test_the_finishing_kernels_cases_reach_it():
+    h, hq, hkv, d = FINISHED["shape"]
+    sizes = [(rows, r) for rows in [FINISHED["entries"], *FINISHED["infinite"]] for r in FINISHED["ranks"]]
+    calls = launches_of([dict(QKV_8B, T=sum(rows), hidden=h, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, n_adapters=len(rows) - 1, rank=r, n_segments=len(rows))
+                         for rows, r in sizes])
+    for call, (rows, r) in zip(calls, sizes):
+        last = call["launches"][-1]
+        assert last["kernel"] == "finish_bf16_kernel" and last["ints"][1] == (1 if r <= 32 else 2) and last["grid"][2] == 2, (rows, r, call)
 
 
 # ---- the row-block reader ------------------------------------------------------------------------
