@@ -277,11 +277,11 @@ static int prepare(Call &c, const void *x, const int32_t *token_adapter_ids, con
     f = {};
     if (dims->T == 0) return ALORA_OK;
 
-    fill_common(f, dims, l, workspace, nullptr);
+    if (extras && extras->rope_cos) { f.rope_cos = extras->rope_cos; f.rope_sin = extras->rope_sin; f.rope_positions = extras->rope_positions; }
+    fill_common(f, dims, l, workspace, nullptr);   // (plans the call, which depends on whether it rotates)
     f.bias = bias;
     f.ranks = ranks;
     f.D = dims->head_dim;
-    if (extras && extras->rope_cos) { f.rope_cos = extras->rope_cos; f.rope_sin = extras->rope_sin; f.rope_positions = extras->rope_positions; }
     f.block_size = block_size;
     f.x = x; f.W = W_qkv; f.aid = token_adapter_ids; f.start = activation_start; f.slot = slot_mapping;
     f.q = q_out; f.kc = k_cache; f.vc = v_cache;

@@ -922,13 +922,17 @@ static GemmPlan plan_fused(int T, int H, int N, bool rope)
             if (small) {
                 const double ts = tile_us(0, rope, H, std::min(1.0, (rem + small) / (double)CUS)), more = 1.4 * ts;
                 auto taken = [&](double free_for) { return free_for < ts - 1e-6 ? 0l : 1l + (long)((free_for - ts) / more + 1e-6); };
+                // (once all units take small tiles, every `more` finishes one on each: of a wide matrix' thousands all but the first few rounds
+                // are skipped, 1.2 ms of host time for 7.7 million features)
+                const long skipped = std::max(0l, small / CUS - (long)(tl / more) - 3), left = small - skipped * CUS;
                 for (long a = 0, b = 0;;) {   // the moments at which a unit is through with a small tile
                     const double ta = ts + a * more, tb = tl + ts + b * more;
                     us = std::max(tl, std::min(ta, tb));
-                    if ((CUS - rem) * taken(us) + rem * taken(us - tl) >= small) break;
+                    if ((CUS - rem) * taken(us) + rem * taken(us - tl) >= left) break;
                     if (ta <= tb) ++a;
                     else ++b;
                 }
+                us += skipped * more;
             }
             us += large / CUS * tile_us(ntw, rope, H, 1.0);
             if (panels < all) us *= 1.02;
@@ -973,18 +977,15 @@ static bool prep_in_projection(const Fwd &f, const Route &r)
 void plan_call(Fwd &f)
 {
     const GemmPlan none = {4, 1, f.H / KBLK, (f.T + 255) / 256};
-    f.route = Route{none, none, {1, f.H, false}, false, false};
+    f.route = Route{none, {1, f.H, false}, false, false};
     if (f.T <= 0) return;
     const int forced = g_force_tuning.load(std::memory_order_relaxed);
-    f.route.gemm = f.route.gemm_rope = plan_gemm(f.T, f.H, f.N, forced);
-    // (the number of splits, which the shrink's layout depends on, is what the sizes alone give)
+    f.route.gemm = plan_gemm(f.T, f.H, f.N, forced);
+    // (the number of splits, which the shrink's layout depends on, is what the sizes alone give; with rotation a wavefront of a fused
+    // call holds both halves of its planes)
     if (f.route.gemm.splits == 1) {
-        if (!forced) {
-            f.route.gemm = plan_fused(f.T, f.H, f.N, false);
-            f.route.gemm_rope = plan_fused(f.T, f.H, f.N, true);
-        } else if (f.route.gemm_rope.ntw == 3) {
-            f.route.gemm_rope.ntw = 4;
-        }
+        if (!forced) f.route.gemm = plan_fused(f.T, f.H, f.N, f.rope_cos != nullptr);
+        else if (f.rope_cos && f.route.gemm.ntw == 3) f.route.gemm.ntw = 4;
     }
     f.route.shrink = plan_shrink(f.route.gemm, f.T, f.H, f.L, f.r);
     f.route.few_rows = !forced && few_rows_call(f);   // (the override names tilings of the projection kernel here)
@@ -995,7 +996,7 @@ int launch_gemm_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEven
 {
     if (f.T == 0) return 0;
     if (f.route.few_rows) return launch_decode_bf16(f, B, A, after_projection);
-    const GemmPlan plan = f.rope_cos ? f.route.gemm_rope : f.route.gemm;   // with rotation a wavefront holds both halves of its planes
+    const GemmPlan plan = f.route.gemm;
     GemmArgs g;
     g.x = (const bf16_t *)f.x; g.W = (const bf16_t *)f.W; g.S_hl = (const bf16_t *)f.S;
     g.aeff = f.aeff; g.slot = f.slot;

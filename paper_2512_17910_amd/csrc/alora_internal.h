@@ -38,11 +38,11 @@ struct ShrinkPlan {
     // fixed order and stores the (hi, lo) form.  The shrink then walks Fwd::items.
     bool combine;
 };
-// Which kernels a bf16 call takes and how they are cut.  Decided once per call (plan_call), from its sizes and
+// Which kernels a bf16 call takes and how they are cut.  Decided once per call (plan_call), from its sizes, from whether it rotates and
 // from ONE reading of the tuning override: every launch of the call follows it, so that an override set by another
 // host thread meanwhile cannot give one call the launches of two different paths.
 struct Route {
-    GemmPlan gemm, gemm_rope;   // without and with the rotary embedding fused into the store (the same splits)
+    GemmPlan gemm;
     ShrinkPlan shrink;
     bool few_rows;      // at most 64 rows: the projection kernel of alora_decode_bf16.hip
     bool prep_inside;   // grouping and shrink run inside the projection kernel
@@ -114,7 +114,7 @@ int launch_gemm_f32(const Fwd &f, const PtrTable &B);
 int launch_shrink_bf16(const Fwd &f, const PtrTable &A);
 int launch_gemm_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEvent_t after_projection);
 int launch_finish_bf16(const Fwd &f, const PtrTable &B, int splits, int s_splits, const int32_t *block_rows, bool s_f32);
-void plan_call(Fwd &f);   // fills f.route (f holds the sizes and block_rows)
+void plan_call(Fwd &f);   // fills f.route (f holds the sizes, block_rows and rope_cos)
 bool few_rows_call(const Fwd &f);   // a batch of a few rows (alora_decode_bf16.hip), from its sizes alone
 int launch_decode_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEvent_t after_projection);
 size_t gemm_partial_bytes(int T, int H, int N);

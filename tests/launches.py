@@ -2,7 +2,8 @@
 
 launches_of(calls) runs the calls in a process of its own in which launch_recorder.c stands in for the HIP runtime:
 every launch is written down instead of enqueued, device pointers are numbers that nothing dereferences.  A call is a
-dict: op "forward" (fields of alora_dims, optionally rope: with rotation tables, replays: recorded and replayed, tuning_during: a tuning override that arrives in the middle of the
+dict: op "forward" (fields of alora_dims, optionally rope: with rotation tables, replays: recorded and replayed, timed: the shortest host time of so many
+classifications and calls, tuning_during: a tuning override that arrives in the middle of the
 call, between the library's two profiling events) or op "attention" (fields of alora_attn_dims and the entry point)."""
 import ctypes
 import json
@@ -11,6 +12,7 @@ import re
 import subprocess
 import sys
 import tempfile
+import time
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -67,6 +69,13 @@ def _main(rec_path):
                 for _ in range(c["replays"]):
                     s = s or L.alora_qkv_graph_launch(g, None)
                 L.alora_qkv_graph_destroy(g)
+            host_us = []
+            for _ in range(c.get("timed", 0)):
+                rec.rec_reset()
+                t = time.perf_counter()
+                s = s or L.alora_qkv_classify_group(P, P, ctypes.byref(d), P, ws, None)
+                s = s or L.alora_qkv_forward(P, P, P, P, tab, tab, P, P, P, P, ctypes.c_int(16), ctypes.byref(d), P, ws, None)
+                host_us.append((time.perf_counter() - t) * 1e6)
             if hook:
                 rec.rec_on_event(HOOK(0))
                 L.alora_qkv_set_tuning(0, 0)
@@ -84,7 +93,7 @@ def _main(rec_path):
             m = re.search(r"N5alora(\d+)", name)
             launches.append({"kernel": name[m.end():m.end() + int(m.group(1))], "ints": [int(v) for v in re.findall(r"L[ib](\d+)E", name)],
                              "grid": list(r.grid), "block": list(r.block), "args": [r.arg1, r.arg2]})
-        out.append({"status": s, "workspace": ws.value, "launches": launches})
+        out.append({"status": s, "workspace": ws.value, "launches": launches, **({"host_us": min(host_us)} if c.get("timed") else {})})
     json.dump(out, sys.stdout)
 
 

@@ -70,6 +70,12 @@ def test_last_rows_of_a_fused_projection_in_small_tiles():
         assert l["grid"][0] == up8(panels * -(-N // (64 * width))) + up8(-(-(T - 256 * panels) // 128) * -(-N // 128)) and T > 256 * panels, l
 
 
+def test_planning_a_wide_projection_takes_no_longer_than_a_narrow_one():
+    """Half a million tiles are not walked one by one on the host (1.2 ms of it; bound: fifty times what the calls take)."""
+    for call in launches_of([dict(QKV_8B, T=2000, hidden=64, n_q_heads=n, n_adapters=4, timed=20) for n in (32, 8000, 60000)]):
+        assert call["status"] == 0 and call["host_us"] < 250, call
+
+
 # Batches whose rows the finishing kernel makes, run by test_gpu_parity.py: (hidden, query heads, K/V heads, head size), rows of the base
 # request and of each adapter, ranks.
 FINISHED = dict(shape=(1024, 5, 2, 40), entries=[1, 15, 16, 17, 31, 32, 33], infinite=[[10, 3, 20, 17], [40, 3, 33, 24]], ranks=[8, 32, 40, 64])
