@@ -401,14 +401,14 @@ static void launch_dg(const AttnArgs &a, bool bf16, hipStream_t st)
 {
     const dim3 grid((unsigned)a.T * (unsigned)a.Hkv * (unsigned)a.splits);
     const bool pow2 = a.bs_shift >= 0;
-    if (bf16 && pow2) hipLaunchKernelGGL((paged_attention_kernel<D, G, true, true>), grid, dim3(256), 0, st, a);
-    else if (bf16) hipLaunchKernelGGL((paged_attention_kernel<D, G, true, false>), grid, dim3(256), 0, st, a);
-    else if (pow2) hipLaunchKernelGGL((paged_attention_kernel<D, G, false, true>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((paged_attention_kernel<D, G, false, false>), grid, dim3(256), 0, st, a);
+    if (bf16 && pow2) launch_kernel((paged_attention_kernel<D, G, true, true>), grid, dim3(256), 0, st, a);
+    else if (bf16) launch_kernel((paged_attention_kernel<D, G, true, false>), grid, dim3(256), 0, st, a);
+    else if (pow2) launch_kernel((paged_attention_kernel<D, G, false, true>), grid, dim3(256), 0, st, a);
+    else launch_kernel((paged_attention_kernel<D, G, false, false>), grid, dim3(256), 0, st, a);
     if (a.splits > 1) {
         const dim3 mgrid((unsigned)a.T * (unsigned)a.Hq);
-        if (bf16) hipLaunchKernelGGL((paged_attention_merge_kernel<D, true, false>), mgrid, dim3(256), 0, st, a.part, a.out, a.splits);
-        else hipLaunchKernelGGL((paged_attention_merge_kernel<D, false, false>), mgrid, dim3(256), 0, st, a.part, a.out, a.splits);
+        if (bf16) launch_kernel((paged_attention_merge_kernel<D, true, false>), mgrid, dim3(256), 0, st, a.part, a.out, a.splits);
+        else launch_kernel((paged_attention_merge_kernel<D, false, false>), mgrid, dim3(256), 0, st, a.part, a.out, a.splits);
     }
 }
 
@@ -577,18 +577,18 @@ static int run(const void *q, const void *k_cache, const void *v_cache, const in
         if (e2) { note_hip_error(e2); return ALORA_EHIP; }
         if (splits > 1) {
             const dim3 grid((unsigned)a.T * (unsigned)a.Hq);
-            if (plan.count) hipLaunchKernelGGL((paged_attention_merge_kernel<128, true, true>), grid, dim3(256), 0, (hipStream_t)hip_stream, a.part, a.out, a.splits);
-            else hipLaunchKernelGGL((paged_attention_merge_kernel<128, true, false>), grid, dim3(256), 0, (hipStream_t)hip_stream, a.part, a.out, a.splits);
-            const hipError_t e3 = hipGetLastError();
-            if (e3) { note_hip_error((int)e3); return ALORA_EHIP; }
+            if (plan.count) launch_kernel((paged_attention_merge_kernel<128, true, true>), grid, dim3(256), 0, (hipStream_t)hip_stream, a.part, a.out, a.splits);
+            else launch_kernel((paged_attention_merge_kernel<128, true, false>), grid, dim3(256), 0, (hipStream_t)hip_stream, a.part, a.out, a.splits);
+            const int e3 = launch_status();
+            if (e3) { note_hip_error(e3); return ALORA_EHIP; }
         }
         return ALORA_OK;
     }
     const bool launched = dims->head_dim == 128 ? launch_d<128>(a, G, bf16, (hipStream_t)hip_stream)
                                                 : launch_d<64>(a, G, bf16, (hipStream_t)hip_stream);
     if (!launched) return ALORA_ESHAPE;
-    const hipError_t e = hipGetLastError();
-    if (e) { note_hip_error((int)e); return ALORA_EHIP; }
+    const int e = launch_status();
+    if (e) { note_hip_error(e); return ALORA_EHIP; }
     return ALORA_OK;
 }
 

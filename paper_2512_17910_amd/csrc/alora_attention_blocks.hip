@@ -640,7 +640,7 @@ int launch_attention_blocks(const AttnArgs &a, int G, const BlockPlan &p, hipStr
     const int ranges = (a.T + p.range - 1) / p.range;
     const dim3 grid((unsigned)ranges * (unsigned)p.wgs * (unsigned)a.Hkv * (unsigned)a.splits), block(64 * p.waves);
     const bool pow2 = a.bs_shift >= 0;
-#define AB_LAUNCH_AS(GG, NW, POW2, PARTS) hipLaunchKernelGGL((paged_attention_blocks_kernel<GG, NW, POW2, PARTS>), grid, block, 0, stream, a, p.range, p.wgs)
+#define AB_LAUNCH_AS(GG, NW, POW2, PARTS) launch_kernel((paged_attention_blocks_kernel<GG, NW, POW2, PARTS>), grid, block, 0, stream, a, p.range, p.wgs)
 #define AB_LAUNCH(GG, NW) \
     if (p.count && pow2) AB_LAUNCH_AS(GG, NW, true, Counted); \
     else if (p.count) AB_LAUNCH_AS(GG, NW, false, Counted); \
@@ -659,7 +659,7 @@ int launch_attention_blocks(const AttnArgs &a, int G, const BlockPlan &p, hipStr
     }
 #undef AB_LAUNCH
 #undef AB_LAUNCH_AS
-    return (int)hipGetLastError();
+    return launch_status();
 }
 
 }  // namespace alora

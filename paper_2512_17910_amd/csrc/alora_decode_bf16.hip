@@ -237,11 +237,11 @@ int launch_decode_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEv
     g.group = GroupSmallArgs{f.aid, f.seg, f.pos, f.start, f.active, f.aeff, f.perm, f.offsets, f.blocktab, f.n_blocks, f.block_rows};
     g.ranks = f.ranks;
     const dim3 grid((g.ntiles * g.splits + 7) / 8 * 8 + g.prep_wgs), block(DEC_THREADS);
-    if (f.T <= 16) hipLaunchKernelGGL((decode_projection_kernel<1, 2>), grid, block, 0, f.stream, g, A);
-    else if (f.T <= 32) hipLaunchKernelGGL((decode_projection_kernel<2, 2>), grid, block, 0, f.stream, g, A);
-    else if (f.T <= 48) hipLaunchKernelGGL((decode_projection_kernel<3, 2>), grid, block, 0, f.stream, g, A);
-    else hipLaunchKernelGGL((decode_projection_kernel<4, 2>), grid, block, 0, f.stream, g, A);
-    int e = (int)hipGetLastError();
+    if (f.T <= 16) launch_kernel((decode_projection_kernel<1, 2>), grid, block, 0, f.stream, g, A);
+    else if (f.T <= 32) launch_kernel((decode_projection_kernel<2, 2>), grid, block, 0, f.stream, g, A);
+    else if (f.T <= 48) launch_kernel((decode_projection_kernel<3, 2>), grid, block, 0, f.stream, g, A);
+    else launch_kernel((decode_projection_kernel<4, 2>), grid, block, 0, f.stream, g, A);
+    int e = launch_status();
     if (!e && after_projection) e = (int)hipEventRecord(after_projection, f.stream);
     if (e) return e;
     return launch_finish_bf16(f, B, g.splits, g.prep_ranges, f.block_rows, true);

@@ -203,9 +203,9 @@ __global__ __launch_bounds__(256) void rope_f32_kernel(float *__restrict__ q, fl
 int launch_rope_f32(const Fwd &f)
 {
     if (f.T == 0) return 0;
-    hipLaunchKernelGGL(rope_f32_kernel, dim3(f.T), dim3(256), 0, f.stream, (float *)f.q, (float *)f.kc, f.slot, f.pos,
+    launch_kernel(rope_f32_kernel, dim3(f.T), dim3(256), 0, f.stream, (float *)f.q, (float *)f.kc, f.slot, f.pos,
                        f.rope_cos, f.rope_sin, f.rope_positions, f.Nq, f.Nkv, f.D);
-    return (int)hipGetLastError();
+    return launch_status();
 }
 
 // The grouping step of a small batch rides in the shrink's launch (its results are the caller's to read; the
@@ -217,15 +217,15 @@ int launch_shrink_f32(const Fwd &f, const PtrTable &A, bool reuse_grouping)
     if (f.T == 0 || f.L == 0) return 0;
     const GroupSmallArgs ga = {f.aid, f.seg, f.pos, f.start, f.active, f.aeff, f.perm, f.offsets, f.blocktab, f.n_blocks, nullptr};
     const int group_wgs = group_in_shrink_f32(f) && !reuse_grouping ? f.n_blocks : 0;
-    hipLaunchKernelGGL(shrink_f32_kernel, dim3(f.T + group_wgs), dim3(F32_THREADS), 0, f.stream, (const float *)f.x, A, f.ranks, ga,
+    launch_kernel(shrink_f32_kernel, dim3(f.T + group_wgs), dim3(F32_THREADS), 0, f.stream, (const float *)f.x, A, f.ranks, ga,
                        f.T, f.L, f.H, f.r, (float *)f.S);
-    return (int)hipGetLastError();
+    return launch_status();
 }
 
 template <int MT>
 static void launch_gemm_f32_rows(const Fwd &f, const PtrTable &B)
 {
-    hipLaunchKernelGGL(gemm_f32_kernel<MT>, dim3((f.N + 63) / 64, (f.T + 16 * MT - 1) / (16 * MT)), dim3(F32_THREADS), 0, f.stream,
+    launch_kernel(gemm_f32_kernel<MT>, dim3((f.N + 63) / 64, (f.T + 16 * MT - 1) / (16 * MT)), dim3(F32_THREADS), 0, f.stream,
                        (const float *)f.x, (const float *)f.W, (const float *)f.bias, B, f.ranks, (const float *)f.S, f.aid, f.seg,
                        f.pos, f.start, f.slot, (float *)f.q, (float *)f.kc, (float *)f.vc, f.T, f.H, f.Nq, f.Nkv, f.r);
 }
@@ -241,7 +241,7 @@ int launch_gemm_f32(const Fwd &f, const PtrTable &B)
     if (tiles64 >= 768 && f.H >= 1024 && tiles64 * f.H >= 5ll << 18) launch_gemm_f32_rows<4>(f, B);
     else if (tiles32 >= 400) launch_gemm_f32_rows<2>(f, B);
     else launch_gemm_f32_rows<1>(f, B);
-    return (int)hipGetLastError();
+    return launch_status();
 }
 
 }  // namespace alora

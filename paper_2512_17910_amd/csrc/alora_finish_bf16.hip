@@ -277,7 +277,7 @@ static void launch_finish(const Fwd &f, const PtrTable &B, int s_splits, const i
 {
     const dim3 grid(used_blocks(f), (f.N + FIN_COLS - 1) / FIN_COLS, f.T > FIN_ROWS ? 2 : 1);
     auto launch = [&](auto rank_tiles) {
-        hipLaunchKernelGGL((finish_bf16_kernel<SPLITS, decltype(rank_tiles)::value>), grid, dim3(FIN_THREADS), 0, f.stream, (const float *)f.partial,
+        launch_kernel((finish_bf16_kernel<SPLITS, decltype(rank_tiles)::value>), grid, dim3(FIN_THREADS), 0, f.stream, (const float *)f.partial,
                            f.S, s_splits, s_f32, B, f.ranks, (const bf16_t *)f.bias, f.perm, block_rows, f.blocktab, f.slot, (bf16_t *)f.q, (bf16_t *)f.kc,
                            (bf16_t *)f.vc, f.T, f.Nq, f.Nkv, f.L, f.r, f.rope_cos, f.rope_sin, f.pos, f.rope_positions);
     };
@@ -298,7 +298,7 @@ int launch_finish_bf16(const Fwd &f, const PtrTable &B, int splits, int s_splits
     case 8: launch_finish<8>(f, B, s_splits, block_rows, s_f32 || s_splits > 1); break;
     default: return (int)hipErrorInvalidValue;
     }
-    return (int)hipGetLastError();
+    return launch_status();
 }
 
 }  // namespace alora

@@ -957,11 +957,11 @@ static void launch_ntw(const GemmArgs &g, const PtrTable &B, const PtrTable &A, 
     const dim3 block(GEMM_THREADS);
     const unsigned tail8 = (unsigned)(g.tail_mtiles * ((g.N + 127) / 128) + 7) / 8 * 8;
     if (g.splits > 1)
-        hipLaunchKernelGGL((alora_gemm_bf16_kernel<NTW, true>), dim3(g.main_wgs + g.prep_wgs), block, 0, stream, g, B, A);
+        launch_kernel((alora_gemm_bf16_kernel<NTW, true>), dim3(g.main_wgs + g.prep_wgs), block, 0, stream, g, B, A);
     else if (NTW != 3 && g.rope_cos)
-        hipLaunchKernelGGL((alora_gemm_bf16_kernel<NTW == 3 ? 4 : NTW, false, true>), dim3(g.main_wgs + tail8), block, 0, stream, g, B, A);
+        launch_kernel((alora_gemm_bf16_kernel<NTW == 3 ? 4 : NTW, false, true>), dim3(g.main_wgs + tail8), block, 0, stream, g, B, A);
     else
-        hipLaunchKernelGGL((alora_gemm_bf16_kernel<NTW, false>), dim3(g.main_wgs + tail8), block, 0, stream, g, B, A);
+        launch_kernel((alora_gemm_bf16_kernel<NTW, false>), dim3(g.main_wgs + tail8), block, 0, stream, g, B, A);
 }
 
 // Decode-sized bf16 batches: classification, grouping and shrink run inside the projection kernel (up to 64 rows
@@ -1024,7 +1024,7 @@ int launch_gemm_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEven
     if (plan.ntw == 4) launch_ntw<4>(g, B, A, f.stream);
     else if (plan.ntw == 3) launch_ntw<3>(g, B, A, f.stream);
     else launch_ntw<2>(g, B, A, f.stream);
-    int e = (int)hipGetLastError();
+    int e = launch_status();
     if (!e && after_projection) e = (int)hipEventRecord(after_projection, f.stream);
     if (e || plan.splits == 1) return e;
     return launch_finish_bf16(f, B, plan.splits, prep ? g.prep_ranges : f.route.shrink.splits,

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 #include "alora_qkv.h"
 
 namespace alora {
@@ -105,6 +106,25 @@ __device__ __forceinline__ int effective_adapter(const int32_t *aid, const int32
 
 // remember a failed HIP call for alora_last_hip_error() (per host thread)
 void note_hip_error(int hip_error);
+
+// Launches, and the first failure among those since the last look.  The launch's own status, not hipGetLastError's: that holds what any
+// earlier call of the program left behind, which is neither this library's failure nor its to take away.
+inline thread_local int first_launch_error = 0;
+template <typename... P>
+inline void launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, unsigned lds_bytes, hipStream_t stream, typename std::common_type<P>::type... args)
+{
+    void *at[] = {(void *)&args...};
+    const int e = (int)hipLaunchKernel((const void *)kernel, grid, block, at, lds_bytes, stream);
+    if (!e) return;
+    (void)hipGetLastError();   // reported from here
+    if (!first_launch_error) first_launch_error = e;
+}
+inline int launch_status()
+{
+    const int e = first_launch_error;
+    first_launch_error = 0;
+    return e;
+}
 
 // launches (each returns the hipError_t of its launch as int)
 int launch_classify_group(const Fwd &f);

@@ -413,16 +413,16 @@ int launch_classify_group(const Fwd &f)
     if (f.items) sw = ShrinkWork{f.items, f.counters, f.n_items, f.H / 64, f.route.shrink.splits};
     if (f.T >= PREP_TWO_LAUNCH_FROM) {
         const int slices = (f.T + PREP_SLICE - 1) / PREP_SLICE;
-        hipLaunchKernelGGL(classify_slices_kernel, dim3(slices), dim3(PREP_THREADS), 0, f.stream, f.aid, f.seg, f.pos,
+        launch_kernel(classify_slices_kernel, dim3(slices), dim3(PREP_THREADS), 0, f.stream, f.aid, f.seg, f.pos,
                            f.start, f.T, f.L, f.active, f.aeff, f.hist);
-        hipLaunchKernelGGL(place_slices_kernel, dim3(slices), dim3(PREP_THREADS), 0, f.stream, (const int8_t *)f.aeff,
+        launch_kernel(place_slices_kernel, dim3(slices), dim3(PREP_THREADS), 0, f.stream, (const int8_t *)f.aeff,
                            (const int32_t *)f.hist, f.T, f.L, f.perm, f.offsets, f.blocktab, f.n_blocks, sw);
-        return (int)hipGetLastError();
+        return launch_status();
     }
     static_assert(PREP_TWO_LAUNCH_FROM <= PREP_CACHE_ROWS, "smaller batches fit the single workgroup's LDS row cache");
-    hipLaunchKernelGGL(classify_group_kernel<true>, dim3(1), dim3(PREP_THREADS), 0, f.stream, f.aid, f.seg, f.pos,
+    launch_kernel(classify_group_kernel<true>, dim3(1), dim3(PREP_THREADS), 0, f.stream, f.aid, f.seg, f.pos,
                        f.start, f.T, f.L, f.active, f.aeff, f.perm, f.offsets, f.blocktab, f.n_blocks, sw);
-    return (int)hipGetLastError();
+    return launch_status();
 }
 
 }  // namespace alora

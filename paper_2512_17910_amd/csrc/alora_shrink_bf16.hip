@@ -103,10 +103,10 @@ static void launch_shrink(const Fwd &f, const PtrTable &A, const ShrinkPlan &sp)
 {
     const uint32_t x_bytes = (uint32_t)((size_t)f.T * f.H * 2);
     if (sp.combine)
-        hipLaunchKernelGGL((shrink_bf16_kernel<KSL, NT, true>), dim3(f.n_items), dim3(256), 0, f.stream, (const bf16_t *)f.x, A,
+        launch_kernel((shrink_bf16_kernel<KSL, NT, true>), dim3(f.n_items), dim3(256), 0, f.stream, (const bf16_t *)f.x, A,
                            f.ranks, f.perm, (const int4 *)f.items, f.counters, f.L, f.H, f.r, x_bytes, f.T, 0, f.S);
     else
-        hipLaunchKernelGGL((shrink_bf16_kernel<KSL, NT, false>), dim3(f.n_blocks, sp.splits), dim3(256), 0, f.stream,
+        launch_kernel((shrink_bf16_kernel<KSL, NT, false>), dim3(f.n_blocks, sp.splits), dim3(256), 0, f.stream,
                            (const bf16_t *)f.x, A, f.ranks, f.perm, (const int4 *)f.blocktab, (int32_t *)nullptr, f.L, f.H, f.r,
                            x_bytes, f.T, sp.kper, f.S);
 }
@@ -118,7 +118,7 @@ int launch_shrink_bf16(const Fwd &f, const PtrTable &A)
     if (sp.combine && !f.items) return (int)hipErrorInvalidValue;
     if (f.r <= 32) launch_shrink<512, 1>(f, A, sp);
     else launch_shrink<256, 2>(f, A, sp);
-    return (int)hipGetLastError();
+    return launch_status();
 }
 
 }  // namespace alora

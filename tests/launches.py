@@ -2,7 +2,8 @@
 
 launches_of(calls) runs the calls in a process of its own in which launch_recorder.c stands in for the HIP runtime:
 every launch is written down instead of enqueued, device pointers are numbers that nothing dereferences.  A call is a
-dict: op "forward" (fields of alora_dims, optionally rope: with rotation tables, replays: recorded and replayed, timed: the shortest host time of so many
+dict: op "forward" (fields of alora_dims, optionally rope: with rotation tables, replays: recorded and replayed, errors: a HIP error that an earlier call of the program left, and one that every
+launch fails with (then: what the library reports, and what is left), timed: the shortest host time of so many
 classifications and calls, tuning_during: a tuning override that arrives in the middle of the
 call, between the library's two profiling events) or op "attention" (fields of alora_attn_dims and the entry point)."""
 import ctypes
@@ -43,6 +44,7 @@ def _main(rec_path):
     out = []
     for c in json.load(sys.stdin):
         rec.rec_reset()
+        rec.rec_set_error(*c.get("errors", (0, 0)))
         ws = ctypes.c_size_t(0)
         if c["op"] == "forward":
             d = ab.AloraDims(**{k: v for k, v in c.items() if k in dict(ab.AloraDims._fields_)})
@@ -93,7 +95,8 @@ def _main(rec_path):
             m = re.search(r"N5alora(\d+)", name)
             launches.append({"kernel": name[m.end():m.end() + int(m.group(1))], "ints": [int(v) for v in re.findall(r"L[ib](\d+)E", name)],
                              "grid": list(r.grid), "block": list(r.block), "args": [r.arg1, r.arg2]})
-        out.append({"status": s, "workspace": ws.value, "launches": launches, **({"host_us": min(host_us)} if c.get("timed") else {})})
+        out.append({"status": s, "workspace": ws.value, "launches": launches, **({"host_us": min(host_us)} if c.get("timed") else {}),
+                    **({"errors": [L.alora_last_hip_error(), rec.rec_error()]} if "errors" in c else {})})
     json.dump(out, sys.stdout)
 
 

@@ -70,6 +70,27 @@ def test_last_rows_of_a_fused_projection_in_small_tiles():
         assert l["grid"][0] == up8(panels * -(-N // (64 * width))) + up8(-(-(T - 256 * panels) // 128) * -(-N // 128)) and T > 256 * panels, l
 
 
+CALLS = [dict(QKV_8B, T=T, n_adapters=4, dtype=dtype) for dtype in (0, 1) for T in (1, 200, 700, 3000, 9000)]
+READERS = [dict(op="attention", entry=entry, dtype=1, n_tokens=64, n_q_heads=32, n_kv_heads=8, head_dim=128, n_seqs=4, max_blocks=64, block_size=16, n_slots=4096)
+           for entry in ("alora_paged_attention", "alora_paged_attention_split", "alora_paged_attention_suffix", "alora_paged_attention_suffix_split")]
+
+
+def test_an_error_the_program_left_behind_is_not_the_librarys():
+    """hipGetLastError holds whatever an earlier call left; neither a call nor a replay fails for it, nor takes it away."""
+    calls = [*CALLS, *[dict(c, replays=2) for c in CALLS], *READERS]
+    plain = launches_of(calls)
+    for call, want in zip(launches_of([dict(c, errors=[101, 0]) for c in calls]), plain):
+        assert call["status"] == 0 and call["launches"] == want["launches"] and call["errors"][1] == 101, call
+
+
+def test_a_launch_that_fails_is_reported_with_its_error():
+    both = [call for c in [*CALLS, *READERS] for call in (dict(c, errors=[101, 98]), c)]
+    calls = launches_of(both)
+    for failed, after in zip(calls[::2], calls[1::2]):
+        assert failed["status"] == -4 and failed["launches"] == [] and failed["errors"] == [98, 0], failed
+        assert after["status"] == 0, after
+
+
 def test_planning_a_wide_projection_takes_no_longer_than_a_narrow_one():
     """Half a million tiles are not walked one by one on the host (1.2 ms of it; bound: fifty times what the calls take)."""
     for call in launches_of([dict(QKV_8B, T=2000, hidden=64, n_q_heads=n, n_adapters=4, timed=20) for n in (32, 8000, 60000)]):
