@@ -137,8 +137,7 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
     constexpr int LOOK = LOOKED_OVER * NW, SCANS = LOOKED_OVER / 64;   // batch rows a workgroup looks over, and each of its threads
     __shared__ unsigned long long lead_mask[LOOK / 64];          // bit i of word j: row 64 j + i from the range's first leads a block
     __shared__ int32_t row_seq[LOOK], row_pos[LOOK];
-    __shared__ int wave_furthest[NW], wave_blocks[NW];
-    __shared__ float wave_us[NW];
+    __shared__ u32x4 wave_found[NW];      // last position of a row, leading rows, what they cost in us (see there)
     // what 64 positions of a row block cost, us, and what every row of it adds (for the number of parts, see there)
     constexpr float US_BLOCK = NW == 8 ? 1.4f : 1.8f, US_ROW = NW == 8 ? .6f / RBG : 0.f;
     constexpr int WIN = 64;            // blocks of 32 positions whose table entries the window below holds
@@ -189,9 +188,8 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
             if (count && own > 0) blocks += (int)__builtin_popcountll(mk << (64 - own));
         }
         if constexpr (count) {
-            wave_furthest[w] = __builtin_amdgcn_readlane(max_upto64(furthest), 63);      // (every lane writes the same)
-            wave_us[w] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sum_upto64(us)), 63));
-            wave_blocks[w] = blocks;
+            wave_found[w] = (u32x4){(unsigned)__builtin_amdgcn_readlane(max_upto64(furthest), 63), (unsigned)blocks,   // (every lane writes the same)
+                                    (unsigned)__builtin_amdgcn_readlane(__float_as_int(sum_upto64(us)), 63), 0u};
         }
         __syncthreads();
     }
@@ -227,21 +225,26 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
     // all are alike, and the more they differ the work there is and the end of a long one: a place whose part is short takes another.  A part's
     // sums are written and read at about 5 TB/s.  10 us of the call depend on none of it, and fewer parts have to promise 5 %.
     // Fitted to 1000 calls, and measured against always a.splits parts on 540 (1 to 64 sequences of 1 to 256 rows at 256 to 32K positions, 8 to
-    // 64 heads): 1.14 times as fast on average, seven calls under 0.97 (the counting takes 1 to 1.5 us; the worst, 0.86 and 0.89, are
-    // 3 x 39 rows at 14-28K, 64/8 heads, 158 and 184 us, and 12 x 18 at 2-5.5K, 70 and 79).  With one length for all contexts and 8 us for a
+    // 64 heads): 1.15 times as fast on average, five calls under 0.97 (the counting takes up to 1 us; the worst, 0.87 and 0.89, are
+    // 3 x 39 rows at 14-28K, 64/8 heads, 158 and 181 us, and 12 x 18 at 2-5.5K, 70 and 79).  With one length for all contexts and 8 us for a
     // start, which are the call's: 1.11 times, one call in 30 under 0.97.  us, always a.splits parts | priced like that | now, 32/8 heads: 4 x 16
-    // rows over 2-3K positions 38.6 | 26.9 | 26.3, 8 x 7 over 1-4K 49.6 | 34.0 | 32.8, 32 single rows at 500-2000 88 | 48.7 | 47.1, 64 at 2-8K 325 |
-    // 254 | 247, 2 x 200 rows at 7-9K 137 | 100 | 96, 4 x 60 at 9-16K 130 | 116 | 115, 8 x 30 at 6-12K 111 | 106 | 106, 3 x 155 at 1-3K
-    // 46 | 53 | 46; 8/8 heads 3 x 212 at 3-10K 63 | 69 | 64; 64/8 heads 47 x 2 at 2-7K 200 | 211 | 194.
+    // rows over 2-3K positions 39.4 | 26.8 | 25.8, 8 x 7 over 1-4K 50.0 | 33.9 | 31.7, 32 single rows at 500-2000 88 | 48.9 | 45.5, 64 at 2-8K 325 |
+    // 254 | 247, 2 x 200 rows at 7-9K 136 | 98 | 95, 4 x 60 at 9-16K 130 | 116 | 115, 8 x 30 at 6-12K 111 | 107 | 105, 3 x 155 at 1-3K
+    // 47 | 54 | 44; 8/8 heads 3 x 212 at 3-10K 63 | 69 | 64; 64/8 heads 4 x 241 at 500-1600 113 | 125 | 112.
+    // (What the counting itself took was a workgroup's start longer by 1 to 2 us, two of them in a row in a call of two turns: every value
+    // of every wavefront added up in turn, and the plan's divisions twice.)
     if constexpr (count) {
-        int longest = 0, blocks = 0;
-        float total = 0.f;
-#pragma unroll
-        for (int i = 0; i < NW; ++i) {
-            longest = max(longest, wave_furthest[i]);
-            blocks += wave_blocks[i];
-            total += wave_us[i];
-        }
+        const u32x4 found = wave_found[lane % NW];        // (quad_perm with the neighbour and with the other pair, then the row's other quad)
+        int longest = (int)found.x, blocks = (int)found.y;
+        float total = __uint_as_float(found.z);
+#define AB_MEET(CTRL)                                                                                             \
+        longest = max(longest, __builtin_amdgcn_update_dpp(0, longest, CTRL, 0xf, 0xf, false));                   \
+        blocks += __builtin_amdgcn_update_dpp(0, blocks, CTRL, 0xf, 0xf, false);                                  \
+        total += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(total), CTRL, 0xf, 0xf, false))
+        AB_MEET(0xb1);
+        AB_MEET(0x4e);
+        if (NW == 8) { AB_MEET(0x141); }
+#undef AB_MEET
         constexpr float START = NW == 8 ? 2.f : 3.f, SUMS = NW == 8 ? 1.6e-4f : 2.4e-4f;
         const int parts = lane + 1, items = blocks * a.Hkv * parts;
         const float share = __builtin_amdgcn_rcpf((float)parts), turns = (float)((items + PLACES - 1) / PLACES);
@@ -262,11 +265,14 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
         key = min(key, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)key, 0x118, 0xf, 0xf, false));
         key = min(key, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)key, 0x142, 0xa, 0xf, false));
         splits = (int)(__builtin_amdgcn_readlane(key, 31) & 31u) + 1;
-        // the grid's workgroups, dealt out
-        wgs = (int)gridDim.x / (a.Hkv * splits);
-        part = (int)blockIdx.x % splits;
-        const int bid = (int)blockIdx.x / splits;
-        hk = bid % a.Hkv, which = bid / a.Hkv;
+        // the grid's workgroups, dealt out (quotients of numbers far below 2^21, half way between two whole ones at the nearest)
+        auto over = [](int x, float each) { return __builtin_amdgcn_readfirstlane((int)(((float)x + .5f) * each)); };
+        const float part_each = __builtin_amdgcn_rcpf((float)splits), head_each = __builtin_amdgcn_rcpf((float)a.Hkv);
+        const int bid = over((int)blockIdx.x, part_each);
+        part = (int)blockIdx.x - bid * splits;
+        which = over(bid, head_each);
+        hk = bid - which * a.Hkv;
+        wgs = over(over((int)gridDim.x, part_each), head_each);
         if (which >= wgs) return;
     }
     const int Nkv = a.Hkv * D;
