@@ -702,7 +702,7 @@ __device__ __forceinline__ void project_tile(const GemmArgs &g, const PtrTable &
         // tile's two heads, two blocks of 32 rows ahead of their use: a lane wants 16 bytes of a row of its own, which from memory
         // would be a line per lane (16 bytes per clock).  Row = position in the block, 16-byte chunks XOR-swizzled by row % 16.
         // (Turned in fp32 strips with the angles loaded a row ahead by every wavefront: 13.2 us per 256 x 256 tile where the
-        // epilogue without rotation takes 4.8; all of a block's rows ahead 13.4; now 11.4.  13757 rows 618 -> 604, 4096 rows 218 -> 212.)
+        // epilogue without rotation takes 4.8; all of a block's rows ahead 13.4; now 11.4.  Whole calls: 13757 rows in 256-row tiles 618 -> 604, 4096 rows 218 -> 212.)
         static_assert(!ROPE || NTW != 3, "a wavefront holds both halves of its planes");
         const bool tile_turns = ROPE && n0 < g.Nq + g.Nkv, turns = ROPE && n0 + 32 * unit(0) < g.Nq + g.Nkv;   // any of the workgroup's heads, this wavefront's head
         auto fetch_angles = [&](int b) {       // this wavefront's half: 16 rows' cos and sin
