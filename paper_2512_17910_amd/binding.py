@@ -164,8 +164,8 @@ def alora_qkv_workspace_layout(dims: AloraDims) -> AloraWsLayout:
 
 # Marshalling is what bounds the smallest calls (one row, a small fp32 layer: a projection's kernels take 10 to 17 us, its arguments took
 # about as long), so the common path makes no Python object it can do without: the current stream's handle instead of a
-# stream object, pointer tables as machine words, the extras in one constructor call.  Host time of a pass, us, one after the other on one
-# box: a small fp32 projection and its attention 17.0 -> 11.8 (the pass itself 17.8 -> 13.7), one row through four layers 57.7 -> 47.4.
+# stream object, pointer tables as machine words, the extras in one constructor call.  Host time of a pass, us, measured in turn on one
+# card: a small fp32 projection and its attention 17.0 -> 11.8 (the pass itself 17.8 -> 13.7), one row through four layers 57.7 -> 47.4.
 _current_device = _current_raw_stream = None
 
 
