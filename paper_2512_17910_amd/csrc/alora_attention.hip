@@ -5,7 +5,9 @@
 // that share the K/V head are processed together, so every cached byte is loaded once per row.
 // The work is a stream of K and V rows (2 * head_dim elements per context position and K/V head)
 // against 4 * G * head_dim flops: memory-bound, so plain fp32 vector arithmetic, no LDS staging and
-// no matrix instructions.
+// no matrix instructions.  Contexts of a decode batch, which differ, are started longest first (see
+// longest_first) and read with non-temporal loads (launch_dg): equal contexts come at 6.2 TB/s, where a plain
+// read of a large buffer reaches 6.3 with ordinary and 7.05 with non-temporal loads (ordinary loads here: 5.6).
 //
 // Lane layout: head_dim / 8 lanes share one context position, 8 consecutive elements (16 bytes of
 // bf16) each, so a wavefront's load instruction covers 64 / (head_dim / 8) positions with whole
@@ -48,7 +50,12 @@ template <bool BF16> struct Raw8;
 template <> struct Raw8<true> {
     u32x4 v;
     __device__ __forceinline__ void zero() { v = u32x4{0u, 0u, 0u, 0u}; }
-    __device__ __forceinline__ void load(const void *base, size_t elem) { v = *(const u32x4 *)((const bf16_t *)base + elem); }
+    template <bool STREAM = false>
+    __device__ __forceinline__ void load(const void *base, size_t elem)
+    {
+        const u32x4 *p = (const u32x4 *)((const bf16_t *)base + elem);
+        v = STREAM ? __builtin_nontemporal_load(p) : *p;
+    }
     __device__ __forceinline__ void widen(float f[8]) const
     {
         f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
@@ -60,10 +67,12 @@ template <> struct Raw8<true> {
 template <> struct Raw8<false> {
     f32x4 a, b;
     __device__ __forceinline__ void zero() { a = f32x4{0.f, 0.f, 0.f, 0.f}; b = a; }
+    template <bool STREAM = false>
     __device__ __forceinline__ void load(const void *base, size_t elem)
     {
-        a = *(const f32x4 *)((const float *)base + elem);
-        b = *(const f32x4 *)((const float *)base + elem + 4);
+        const f32x4 *p = (const f32x4 *)((const float *)base + elem);
+        a = STREAM ? __builtin_nontemporal_load(p) : *p;
+        b = STREAM ? __builtin_nontemporal_load(p + 1) : p[1];
     }
     __device__ __forceinline__ void widen(float f[8]) const
     {
@@ -102,8 +111,51 @@ __device__ __forceinline__ float dot8(const Raw8<false> &q, const Raw8<false> &k
 // exp2(-inf) = 0).  Scores below it are treated like -inf.
 constexpr float M_FLOOR = -1.0e30f;
 
-template <int D, int G, bool BF16, bool POW2>
-__global__ __launch_bounds__(256) void paged_attention_kernel(AttnArgs a)
+// The batch row with the `rank`-th longest context among `rows` (at most 256) from `first` on, and its sequence and position, for a
+// workgroup of 256 threads.  Lengths count in steps of an eighth (128 of them from 16 positions to a million), rows of one step in batch
+// order: every workgroup finds the same order, and each row once.  Where no context is longer than SHORT_CONTEXT it is the batch's order.
+// scr: ORDER_SCRATCH ints of LDS.
+struct Row { int t, seq, pos; };
+constexpr int ORDER_SCRATCH = 128 + 8 + 2;
+constexpr int SHORT_CONTEXT = 512;
+__device__ __forceinline__ Row longest_first(const AttnArgs &a, int first, int rows, int rank, int *scr)
+{
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    unsigned long long *const masks = (unsigned long long *)(scr + 128);
+    int key = -1, n_ctx = 0, sq = -1, p = -1;
+    if (tid < rows) {
+        sq = a.seq[first + tid], p = a.pos[first + tid];
+        if (sq >= 0 && sq < a.n_seqs && p >= 0) n_ctx = (int)min(p + 1ll, (long long)a.max_blocks * a.bs);
+        key = 127 - min(max((int)(__float_as_uint((float)n_ctx) >> 20) - ((127 + 4) << 3), 0), 127);
+    }
+    if (tid < 128) scr[tid] = 0;
+    if (tid == rank) scr[136] = sq, scr[137] = p;
+    if (!__syncthreads_or(n_ctx > SHORT_CONTEXT)) return {first + rank, scr[136], scr[137]};
+    if (key >= 0) atomicAdd(&scr[key], 1);   // counts only: their values do not depend on the order
+    __syncthreads();
+    const int h0 = scr[2 * lane], h1 = scr[2 * lane + 1], upto = sum_upto64(h0 + h1);
+    const int at = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(rank < upto));   // (rank < rows, the last lane's)
+    int n = rank - __builtin_amdgcn_readlane(upto - h0 - h1, at);
+    const int even = __builtin_amdgcn_readlane(h0, at), step = 2 * at + (n >= even ? 1 : 0);
+    if (n >= even) n -= even;
+    const unsigned long long mine = __builtin_amdgcn_ballot_w64(key == step);
+    if (lane == 0) masks[w] = mine;
+    __syncthreads();
+    // the n-th of the step's rows: its thread says which it is
+    int before = 0;
+    for (int i = 0; i < w; ++i) before += (int)__builtin_popcountll(masks[i]);
+    before += __builtin_amdgcn_mbcnt_hi((unsigned)(mine >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mine, 0u));
+    if (key == step && before == n) scr[0] = first + tid, scr[136] = sq, scr[137] = p;
+    __syncthreads();
+    return {scr[0], scr[136], scr[137]};
+}
+
+// What is known of a call's contexts: nothing, that each is read once per head (see launch_dg), or that there are several turns of
+// workgroups of them besides, which take the longest first (in runs of `sorted` batch rows).
+enum Contexts { ANY, READ_ONCE, LONGEST_FIRST };
+
+template <int D, int G, bool BF16, bool POW2, Contexts CONTEXTS>
+__global__ __launch_bounds__(256) void paged_attention_kernel(AttnArgs a, int sorted)
 {
     constexpr int LPP = D / 8;         // lanes per context position
     constexpr int PPW = 64 / LPP;      // positions per wavefront and step
@@ -116,11 +168,19 @@ __global__ __launch_bounds__(256) void paged_attention_kernel(AttnArgs a)
 
     // workgroup -> (row, K/V head, part of the context)
     const int rh = (int)blockIdx.x / a.splits, sp = (int)blockIdx.x - rh * a.splits;
-    const int t = rh / a.Hkv, hk = rh % a.Hkv;
+    const int hk = rh % a.Hkv;
+    int t = rh / a.Hkv, sq, p;
+    if constexpr (CONTEXTS == LONGEST_FIRST) {
+        __shared__ __attribute__((aligned(8))) int order[ORDER_SCRATCH];
+        const int run = t / sorted * sorted;
+        const Row row = longest_first(a, run, min(sorted, a.T - run), t - run, order);
+        t = __builtin_amdgcn_readfirstlane(row.t), sq = __builtin_amdgcn_readfirstlane(row.seq), p = __builtin_amdgcn_readfirstlane(row.pos);
+    } else {
+        sq = a.seq[t], p = a.pos[t];
+    }
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int grp = lane / LPP, c = lane % LPP;
 
-    const int sq = a.seq[t], p = a.pos[t];
     const long long cap = (long long)a.max_blocks * a.bs;
     int n_ctx = 0;
     if (sq >= 0 && sq < a.n_seqs && p >= 0) n_ctx = (int)(p + 1ll < cap ? p + 1ll : cap);
@@ -175,8 +235,8 @@ __global__ __launch_bounds__(256) void paged_attention_kernel(AttnArgs a)
             if (have) {
                 const int off = POW2 ? (j & (a.bs - 1)) : (j % a.bs);
                 const size_t at = ((size_t)blk[u] * a.bs + off) * Nkv + col;
-                kr[u].load(a.kc, at);
-                vr[u].load(a.vc, at);
+                kr[u].template load<CONTEXTS != ANY>(a.kc, at);
+                vr[u].template load<CONTEXTS != ANY>(a.vc, at);
             }
         }
         return ok;
@@ -401,10 +461,29 @@ static void launch_dg(const AttnArgs &a, bool bf16, hipStream_t st)
 {
     const dim3 grid((unsigned)a.T * (unsigned)a.Hkv * (unsigned)a.splits);
     const bool pow2 = a.bs_shift >= 0;
-    if (bf16 && pow2) launch_kernel((paged_attention_kernel<D, G, true, true>), grid, dim3(256), 0, st, a);
-    else if (bf16) launch_kernel((paged_attention_kernel<D, G, true, false>), grid, dim3(256), 0, st, a);
-    else if (pow2) launch_kernel((paged_attention_kernel<D, G, false, true>), grid, dim3(256), 0, st, a);
-    else launch_kernel((paged_attention_kernel<D, G, false, false>), grid, dim3(256), 0, st, a);
+    // Non-temporal loads where a context is read once per head (no more rows than sequences) and the memory-side cache (256 MB) would not
+    // keep this layer's K and V until they are read again.  us, ordinary | non-temporal loads, 32/8 heads, three layers' caches in turn:
+    // 64 rows of equal contexts, 500 MB 100.8 | 91.4, 200 MB 45.2 | 40.9, 100 MB 25.9 | 24.6, 64 MB 16.9 | 17.4; 256 rows of 10 to
+    // 100 positions, 66 MB 25.5 | 26.5; one cache over and over, 200 MB 38.5 | 40.4.
+    const bool once = a.T <= a.n_seqs && a.n_slots * a.Hkv * D * (bf16 ? 4 : 8) > 96ll << 20;
+    // The longest contexts first where workgroups take several turns on the chip (three per compute unit fit) and contexts can be
+    // long: one of 2000 positions that starts last is half the call's length.  us, in batch order | longest first (non-temporal both): 256 rows of 2 to
+    // 2047 positions 210 | 185, 100 of 300 to 3000 147 | 134, 250 of 100 to 4000, 64/8 heads 554 | 478.  Contexts of at most SHORT_CONTEXT
+    // keep their order: finding it would be 2 of 25 us (256 rows of 10 to 100).
+    const bool longest = once && a.splits == 1 && (long long)a.T * a.Hkv > 512 && (long long)a.max_blocks * a.bs > SHORT_CONTEXT;
+    const int runs = (a.T + 255) / 256, sorted = (a.T + runs - 1) / runs;
+    auto launch = [&](auto is_bf16, auto is_pow2, auto contexts) {
+        launch_kernel((paged_attention_kernel<D, G, decltype(is_bf16)::value, decltype(is_pow2)::value, decltype(contexts)::value>), grid, dim3(256), 0, st, a, sorted);
+    };
+    auto choose = [&](auto is_bf16, auto is_pow2) {
+        if (longest) launch(is_bf16, is_pow2, std::integral_constant<Contexts, LONGEST_FIRST>{});
+        else if (once) launch(is_bf16, is_pow2, std::integral_constant<Contexts, READ_ONCE>{});
+        else launch(is_bf16, is_pow2, std::integral_constant<Contexts, ANY>{});
+    };
+    if (bf16 && pow2) choose(std::true_type{}, std::true_type{});
+    else if (bf16) choose(std::true_type{}, std::false_type{});
+    else if (pow2) choose(std::false_type{}, std::true_type{});
+    else choose(std::false_type{}, std::false_type{});
     if (a.splits > 1) {
         const dim3 mgrid((unsigned)a.T * (unsigned)a.Hq);
         if (bf16) launch_kernel((paged_attention_merge_kernel<D, true, false>), mgrid, dim3(256), 0, st, a.part, a.out, a.splits);

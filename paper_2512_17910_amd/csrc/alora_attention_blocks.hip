@@ -84,16 +84,7 @@ __device__ __forceinline__ void both_halves(float x, float &lo, float &hi)
     lo = x, hi = x;
     asm("s_nop 3\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 3" : "+v"(lo), "+v"(hi));
 }
-// sums, and largest from 0 on, over lanes 0 .. lane (row_shr:1, 2, 4, 8, then row_bcast:15 and 31 into the rows above)
-__device__ __forceinline__ int sum_upto64(int x)
-{
-    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
-    return x + __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
-}
+// sums of floats, and largest from 0 on, over lanes 0 .. lane
 __device__ __forceinline__ float sum_upto64(float x)
 {
     x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x111, 0xf, 0xf, false));

@@ -18,6 +18,16 @@ struct AttnArgs {
 
 constexpr int MAX_PARTS = 32;   // of a row's context
 
+// sums over lanes 0 .. lane (row_shr:1, 2, 4, 8, then row_bcast:15 and 31 into the rows above)
+__device__ __forceinline__ int sum_upto64(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+    return x + __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+}
 constexpr int LOOKED_OVER = 256;   // batch rows per wavefront of which a row-block workgroup finds those that lead a block
 
 // How the row-block kernel cuts a batch: wavefronts per workgroup (row blocks of 32 * waves / G rows), batch rows per

@@ -559,3 +559,35 @@ def test_what_the_bits_of_a_row_depend_on():
                                 c.token_seq_ids, c.token_positions, c.block_size, 8, 8, 128, scale=None, rows=np.arange(424, 636, 9))
     for bits in (parts, parts2):
         assert maxnorm_rel(wl.widen_f64(bits[own][::9], "bf16"), want) <= TOL["bf16"]
+
+
+# One row per sequence over a cache that does not stay in the memory-side cache: contexts are streamed, and where workgroups take
+# several turns the longest go first: one run of rows and several, rows that are not valid, contexts all equal, all short but one, none long.
+@pytest.mark.parametrize("n,lo,hi,odd", [(300, 1, 900, None), (65, 700, 700, None), (256, 5, 60, 1000), (257, 1, 1023, None), (100, 1, 500, None), (40, 1, 900, None)])
+def test_rows_of_streamed_contexts(n, lo, hi, odd):
+    print(f"[case] streamed {n} rows of {lo}-{hi}", flush=True)
+    rng = np.random.default_rng(1080 + n)
+    n_blocks, width = 1600, 64                       # 100 MiB of K and V
+    g = torch.Generator(device="cuda").manual_seed(1080 + n)
+    kc, vc = (torch.randn(n_blocks * 16, 8 * 128, device="cuda", generator=g).bfloat16() for _ in range(2))
+    q = torch.randn(n, 32 * 128, device="cuda", generator=g).bfloat16()
+    bt = rng.integers(0, n_blocks, (n, width)).astype(np.int32)      # (sequences share blocks)
+    lens = rng.integers(lo, hi + 1, n)
+    if odd:
+        lens[n // 3] = odd
+    seq, pos = rng.permutation(n).astype(np.int32), (lens - 1).astype(np.int32)
+    bad = [7, 33]
+    seq[bad[0]], pos[bad[1]] = -1, -5
+    dbt, dseq, dpos = (torch.from_numpy(a).to("cuda") for a in (bt, seq, pos))
+    out = torch.full_like(q, float("nan"))
+    ab.alora_paged_attention(q, kc, vc, dbt, dseq, dpos, out, ab.make_attn_dims(q, kc, dbt, 32, 8, 128, 16))
+    # more rows than sequences: ordinary loads in batch order, the same arithmetic
+    twice = torch.full((2 * n, 32 * 128), float("nan"), device="cuda", dtype=torch.bfloat16)
+    q2 = torch.cat([q, q])
+    ab.alora_paged_attention(q2, kc, vc, dbt, torch.cat([dseq, dseq]), torch.cat([dpos, dpos]), twice, ab.make_attn_dims(q2, kc, dbt, 32, 8, 128, 16))
+    torch.cuda.synchronize()
+    assert np.array_equal(raw_bits(out), raw_bits(twice[:n])) and np.array_equal(raw_bits(out), raw_bits(twice[n:]))
+    assert not out[bad].any()
+    pick = np.array([t for t in range(0, n, 23) if t not in bad])
+    want = oatt.paged_attention(to_f64(q), to_f64(kc), to_f64(vc), bt, seq, pos, 16, 32, 8, 128, rows=pick)
+    assert maxnorm_rel(to_f64(out)[pick], want) <= TOL["bf16"]
