@@ -313,7 +313,7 @@ static int enqueue(const Call &c, void *hip_stream, bool allow_timing)
         if (f.dtype == ALORA_F32) {
             e = launch_shrink_f32(f, ta, reuse_grouping);
             if (!e && timed) e = (int)hipEventRecord(g_prof.ev0[g_prof.used], f.stream);
-            if (!e) e = launch_gemm_f32(f, tb);
+            if (!e) e = launch_gemm_f32(f, tb, ta, reuse_grouping);
             if (!e && f.rope_cos) e = launch_rope_f32(f);
             if (!e && timed) e = (int)hipEventRecord(g_prof.ev1[g_prof.used], f.stream);
         } else {

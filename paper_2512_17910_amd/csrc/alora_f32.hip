@@ -2,8 +2,8 @@
 // of the masked multi-adapter QKV projection.  Two kernels:
 //   shrink_f32 : S[t,:] = x[t,:] . A[a]   for adapted rows only, one workgroup per row; for batches of at
 //                most 256 rows the workgroups behind those do the grouping step (alora_group_small.h)
-//   gemm_f32   : y = x . W on fp32 MFMA, then for adapted rows y += S[t,:] . B[a], then the q_out store and
-//                the paged K/V store.
+//   gemm_f32   : y = x . W on fp32 MFMA, then for adapted rows y += S[t,:] . B[a], the rotation where heads lie inside a tile of 64
+//                features, then the q_out store and the paged K/V store; of small layers with few adapters the whole call
 // Pre-activation and base-model rows never read S, A or B (Sec. 2.3: they are the base model's).
 //
 // Such calls are small, so what bounds them is the number of dependent round trips to memory and of launches,
@@ -74,17 +74,40 @@ __global__ __launch_bounds__(F32_THREADS) void shrink_f32_kernel(const float *__
 // 4c + e.  Partial sums of the wavefronts meet in LDS and are added in fixed order.
 // MT = 1 for small calls, as long as their chain of round trips: many short workgroups.  MT = 4 where the products count: a weight
 // element serves 64 rows, but 64 KB of partial sums leave a CU two workgroups.  MT = 2 between (see launch_gemm_f32).
-template <int MT>
+//
+// Whole: the call's only launch.  A wavefront's quarter of its 16 token rows is in registers after one round trip, and one more product,
+// with the rows of A, gives it S as well: every workgroup works S out for itself, which saves a launch and its 4.3 us where that is little
+// work: hidden dimension at most 256, rank at most 16 (one tile of columns), at most four adapters (all of A requested together; one
+// after the other, 16 adapters of a decode batch made a call 35 us of 21).  The grouping of at most 256 rows is done by workgroups behind
+// the projection's.  us, shrink and projection | one launch, 256 -> 512: turn of 64 rows, rank 8 14.7 | 11.8, of 4 x 1 rows, rank 16, four
+// adapters, rotation 17.4 | 16.0, 4 x 32 rows with rotation 24.0 | 17.9, 4 x 128 35.8 | 31.0; two layers of 256 rows 23.8 | 18.0, 1500 rows 33.7 | 33.5.
+constexpr int WHOLE_HIDDEN = 256, WHOLE_RANK = 16, WHOLE_ADAPTERS = 4;
+struct RopeF32 { const float *cs, *sn; int n_pos, half; };   // cs null: no rotation in the store
+struct Projection { static constexpr bool whole = false; };
+struct Whole { static constexpr bool whole = true; };
+template <int MT, typename CALL>
 __global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(
     const float *__restrict__ x, const float *__restrict__ W, const float *__restrict__ bias, PtrTable B,
     RankTable ranks, const float *__restrict__ S,
     const int32_t *__restrict__ aid, const int32_t *__restrict__ seg, const int32_t *__restrict__ pos,
     const int32_t *__restrict__ start, const int64_t *__restrict__ slot, float *__restrict__ q,
-    float *__restrict__ kc, float *__restrict__ vc, int T, int H, int Nq, int Nkv, int r)
+    float *__restrict__ kc, float *__restrict__ vc, int T, int H, int Nq, int Nkv, int r, RopeF32 rope, PtrTable A, GroupSmallArgs group, int L)
 {
+    constexpr bool WHOLE = CALL::whole;
+    static_assert(!WHOLE || MT == 1, "one row tile");
     __shared__ __attribute__((aligned(16))) float red[4][16 * MT][64];
+    __shared__ float s_red[WHOLE ? 4 : 1][16][WHOLE_RANK + 1], s_sum[WHOLE ? 16 : 1][WHOLE_RANK];
     const int N = Nq + 2 * Nkv;
     const int m0 = blockIdx.y * (16 * MT), n0 = blockIdx.x * 64;
+    if constexpr (WHOLE) {
+        if (m0 >= T) {   // grouping of a batch of at most 256 rows, one block-table entry per workgroup
+            static_assert(sizeof(red) >= GROUP_SMALL_SCRATCH * 4, "scratch");
+            const int e = (blockIdx.y - (T + 15) / 16) * gridDim.x + blockIdx.x;
+            int grp, cnt;
+            if (e < group.n_blocks) group_small(group, T, L, e, true, (int *)red, grp, cnt);
+            return;
+        }
+    }
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
     f32x4 acc[MT][4];
@@ -93,21 +116,29 @@ __global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[m][e] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-    // classification of the row whose outputs this thread stores first: requested ahead of the products
+    // classification of the rows whose outputs this thread stores: requested ahead of the products (WHOLE: of row c of the tile by
+    // every wavefront, in three steps, see below)
     const int nn = n0 + 4 * (tid & 15);
     int a_of[MT];
+    int aid_c = -1, seg_c = 0, pos_c = 0;
+    if constexpr (WHOLE) {
+        if (m0 + c < T) aid_c = aid[m0 + c], seg_c = seg[m0 + c], pos_c = pos[m0 + c];
+    } else {
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
-        const int t = m0 + 16 * m + (tid >> 4);
-        a_of[m] = t < T ? effective_adapter(aid, seg, pos, start, t) : -1;
+        for (int m = 0; m < MT; ++m) {
+            const int t = m0 + 16 * m + (tid >> 4);
+            a_of[m] = t < T ? effective_adapter(aid, seg, pos, start, t) : -1;
+            if (a_of[m] >= L) a_of[m] = -1;
+        }
     }
 
     const int KB = (H + 15) >> 4, per = (KB + 3) >> 2;   // blocks of 16, per wavefront
     const int kb0 = min(KB, w * per), kb1 = min(KB, kb0 + per);
     const int n_l = n0 + 4 * c;
     constexpr int D = MT == 1 ? 4 : 2;                   // blocks requested together
-    for (int kb = kb0; kb < kb1; kb += D) {
-        f32x4 xv[D][MT], wv[D][4];
+    static_assert(!WHOLE || 4 * 16 * D >= WHOLE_HIDDEN, "the quarter of a row a wavefront takes is requested at once");
+    f32x4 xv[D][MT], wv[D][4];
+    auto request = [&](int kb) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             const int k = 16 * (kb + d) + 4 * g;         // H is a multiple of 4: all four or none
@@ -123,6 +154,8 @@ __global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(
                 if (k_ok && n_l < N) wv[d][j] = *(const f32x4 *)(W + (size_t)(k + j) * N + n_l);
             }
         }
+    };
+    auto multiply = [&]() {
 #pragma unroll
         for (int d = 0; d < D; ++d)
 #pragma unroll
@@ -132,6 +165,59 @@ __global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         acc[m][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[d][m][j], wv[d][j][e], acc[m][e], 0, 0, 0);
+    };
+    f32x4 b8[8];     // WHOLE: the first rows of B_a for the row this thread stores, on their way beside those of A
+    if constexpr (WHOLE) {
+        request(kb0);
+        int a_c = -1;
+        if (aid_c >= 0 && aid_c < L && pos_c >= start[seg_c]) a_c = aid_c;
+        a_of[0] = __shfl(a_c, 4 * w + g);
+        // (the adapters' tables by constant index: a load that waits for the index is another 0.6 us)
+        const void *Ba = nullptr;
+        int ra = 1;
+#pragma unroll
+        for (int i = 0; i < WHOLE_ADAPTERS; ++i)
+            if (a_of[0] == i) Ba = B.p[i], ra = ranks.r[i];
+        if (a_of[0] >= 0 && nn < N) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) b8[j] = *(const f32x4 *)((const float *)Ba + nn + (size_t)min(j, ra - 1) * N);
+        }
+        // what lies past A_a (rows past the hidden dimension, columns past the rank) reads as zero
+        unsigned rows[WHOLE_ADAPTERS];
+        float av[WHOLE_ADAPTERS][D][4];
+#pragma unroll
+        for (int i = 0; i < WHOLE_ADAPTERS; ++i) {
+            rows[i] = (unsigned)__builtin_amdgcn_ballot_w64(a_c == i) & 0xffffu;
+            if (!rows[i]) continue;
+            const int ri = ranks.r[i];
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)A.p[i], 0, H * ri * 4, 0x00020000);
+            const uint32_t at = c < ri ? (uint32_t)((16 * kb0 + 4 * g) * ri + c) * 4u : 0x80000000u;
+#pragma unroll
+            for (int d = 0; d < D; ++d)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    av[i][d][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, at + (uint32_t)((16 * d + j) * ri) * 4u, 0, 0));
+        }
+        multiply();
+#pragma unroll
+        for (int i = 0; i < WHOLE_ADAPTERS; ++i) {
+            if (!rows[i]) continue;
+            f32x4 sa = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int d = 0; d < D; ++d)
+                if (kb0 + d < kb1) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) sa = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[d][0][j], av[i][d][j], sa, 0, 0, 0);
+                }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if ((rows[i] >> (4 * g + e)) & 1u) s_red[w][4 * g + e][c] = sa[e];   // (a wavefront without a share of the hidden dimension: zeros)
+        }
+    } else {
+        for (int kb = kb0; kb < kb1; kb += D) {
+            request(kb);
+            multiply();
+        }
     }
     // D[row 4g + i][feature tile e, column c]: register i
 #pragma unroll
@@ -140,23 +226,39 @@ __global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(
         for (int i = 0; i < 4; ++i)
             *(f32x4 *)&red[w][16 * m + 4 * g + i][4 * c] = (f32x4){acc[m][0][i], acc[m][1][i], acc[m][2][i], acc[m][3][i]};
     __syncthreads();
+    if constexpr (WHOLE) {
+        const int row = tid >> 4, j = tid & 15;
+        if (a_of[0] >= 0) s_sum[row][j] = ((s_red[0][row][j] + s_red[1][row][j]) + s_red[2][row][j]) + s_red[3][row][j];
+        __syncthreads();
+    }
     if (nn >= N) return;
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
         const int row = 16 * m + (tid >> 4), t = m0 + row;
         if (t >= T) continue;
+        int64_t s_at = -1;
+        int p = 0;
+        if (nn >= Nq) s_at = slot[t];
+        const bool turned = rope.cs && nn < Nq + Nkv;
+        if (turned) p = min(max(pos[t], 0), rope.n_pos - 1);
         f32x4 y = *(const f32x4 *)&red[0][row][4 * (tid & 15)];
 #pragma unroll
         for (int ww = 1; ww < 4; ++ww) y += *(const f32x4 *)&red[ww][row][4 * (tid & 15)];
         if (bias) y += *(const f32x4 *)(bias + nn);   // part of the base output of every row
         const int a = a_of[m];
         if (a >= 0) {
-            const float *Ba = (const float *)B.p[a] + nn;
-            const float *Sr = S + (size_t)t * r;
             f32x4 d = {0.f, 0.f, 0.f, 0.f};
+            const float *Ba = (const float *)B.p[a] + nn;
+            const float *Sr = WHOLE ? s_sum[row] : S + (size_t)t * r;
             const int ra = ranks.r[a];
+            if constexpr (WHOLE) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) d[e] = j < ra ? fmaf(Sr[j], b8[j][e], d[e]) : d[e];
+            }
 #pragma unroll 8
-            for (int j = 0; j < ra; ++j) {
+            for (int j = WHOLE ? 8 : 0; j < ra; ++j) {
                 const float s = Sr[j];
                 const f32x4 b4 = *(const f32x4 *)(Ba + (size_t)j * N);
                 d.x = fmaf(s, b4.x, d.x); d.y = fmaf(s, b4.y, d.y);
@@ -164,13 +266,24 @@ __global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(
             }
             y += d;
         }
+        if (rope.cs) {
+            // heads of 8, 16, 32 or 64: the partner features i +- half are the lane's half / 4 further on or back, of the same tile and row
+            f32x4 other;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) other[e] = __shfl_xor(y[e], rope.half >> 2);
+            if (turned) {
+                const bool first = !(nn & rope.half);
+                const size_t at = (size_t)p * rope.half + (nn & (rope.half - 1));
+                const f32x4 cv = *(const f32x4 *)(rope.cs + at), sv = *(const f32x4 *)(rope.sn + at);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] = first ? y[e] * cv[e] - other[e] * sv[e] : y[e] * cv[e] + other[e] * sv[e];
+            }
+        }
         if (nn < Nq) {
             *(f32x4 *)(q + (size_t)t * Nq + nn) = y;
-        } else {
-            const int64_t s = slot[t];
-            if (s < 0) continue;
-            if (nn < Nq + Nkv) *(f32x4 *)(kc + (size_t)s * Nkv + (nn - Nq)) = y;
-            else *(f32x4 *)(vc + (size_t)s * Nkv + (nn - Nq - Nkv)) = y;
+        } else if (s_at >= 0) {
+            if (nn < Nq + Nkv) *(f32x4 *)(kc + (size_t)s_at * Nkv + (nn - Nq)) = y;
+            else *(f32x4 *)(vc + (size_t)s_at * Nkv + (nn - Nq - Nkv)) = y;
         }
     }
 }
@@ -200,9 +313,13 @@ __global__ __launch_bounds__(256) void rope_f32_kernel(float *__restrict__ q, fl
     }
 }
 
+// Heads that lie inside a 64-feature tile of the projection are turned in its store.  (The tables are read 16 bytes at a time: half a
+// multiple of four.)
+static bool rope_in_store_f32(const Fwd &f) { return f.D == 8 || f.D == 16 || f.D == 32 || f.D == 64; }
+
 int launch_rope_f32(const Fwd &f)
 {
-    if (f.T == 0) return 0;
+    if (f.T == 0 || rope_in_store_f32(f)) return 0;
     launch_kernel(rope_f32_kernel, dim3(f.T), dim3(256), 0, f.stream, (float *)f.q, (float *)f.kc, f.slot, f.pos,
                        f.rope_cos, f.rope_sin, f.rope_positions, f.Nq, f.Nkv, f.D);
     return launch_status();
@@ -212,9 +329,18 @@ int launch_rope_f32(const Fwd &f)
 // fp32 kernels themselves classify a row from its metadata).
 bool group_in_shrink_f32(const Fwd &f) { return f.dtype == ALORA_F32 && f.L > 0 && f.T <= GROUP_SMALL_ROWS; }
 
+static int rows_of_tile_f32(const Fwd &f)
+{
+    const long long tiles = (f.N + 63) / 64, tiles32 = (f.T + 31) / 32 * tiles, tiles64 = (f.T + 63) / 64 * tiles;
+    if (tiles64 >= 768 && f.H >= 1024 && tiles64 * f.H >= 5ll << 18) return 64;
+    return tiles32 >= 400 ? 32 : 16;
+}
+
+static bool whole_call_f32(const Fwd &f) { return f.L > 0 && f.L <= WHOLE_ADAPTERS && f.H <= WHOLE_HIDDEN && f.r <= WHOLE_RANK && rows_of_tile_f32(f) == 16; }
+
 int launch_shrink_f32(const Fwd &f, const PtrTable &A, bool reuse_grouping)
 {
-    if (f.T == 0 || f.L == 0) return 0;
+    if (f.T == 0 || f.L == 0 || whole_call_f32(f)) return 0;
     const GroupSmallArgs ga = {f.aid, f.seg, f.pos, f.start, f.active, f.aeff, f.perm, f.offsets, f.blocktab, f.n_blocks, nullptr};
     const int group_wgs = group_in_shrink_f32(f) && !reuse_grouping ? f.n_blocks : 0;
     launch_kernel(shrink_f32_kernel, dim3(f.T + group_wgs), dim3(F32_THREADS), 0, f.stream, (const float *)f.x, A, f.ranks, ga,
@@ -222,25 +348,29 @@ int launch_shrink_f32(const Fwd &f, const PtrTable &A, bool reuse_grouping)
     return launch_status();
 }
 
-template <int MT>
-static void launch_gemm_f32_rows(const Fwd &f, const PtrTable &B)
-{
-    launch_kernel(gemm_f32_kernel<MT>, dim3((f.N + 63) / 64, (f.T + 16 * MT - 1) / (16 * MT)), dim3(F32_THREADS), 0, f.stream,
-                       (const float *)f.x, (const float *)f.W, (const float *)f.bias, B, f.ranks, (const float *)f.S, f.aid, f.seg,
-                       f.pos, f.start, f.slot, (float *)f.q, (float *)f.kc, (float *)f.vc, f.T, f.H, f.Nq, f.Nkv, f.r);
-}
-
-int launch_gemm_f32(const Fwd &f, const PtrTable &B)
+int launch_gemm_f32(const Fwd &f, const PtrTable &B, const PtrTable &A, bool reuse_grouping)
 {
     if (f.T == 0) return 0;
-    // us for MT = 1 | 2 | 4 (and the 64 x 64 LDS tile before them): 256 -> 512, two layers, 1500 rows 28 | 30 | 33 (49), 2048 rows 32 | 31 |
+    // us for 16 | 32 | 64 rows a tile (and the 64 x 64 LDS tile before them): 256 -> 512, two layers, 1500 rows 28 | 30 | 33 (49), 2048 rows 32 | 31 |
     // 33 (49), 6000 rows 69 | 70 | 81 (73), 16384 rows 148 | 137 | 154 (145); 1024 -> 1536, two layers, 512 rows 61 | 62 | 65 (141), 1024
     // rows 115 | 95 | 115 (158), 4096 rows 385 | 322 | 309 (366); 4096 -> 6144, 100 rows 102 | 94 | 108 (281), 256 rows 214 | 147 | 174
     // (286), 512 rows 437 | 338 | 323 (386), 2048 rows 1822 | 1212 | 973 (1308).
-    const long long tiles = (f.N + 63) / 64, tiles32 = (f.T + 31) / 32 * tiles, tiles64 = (f.T + 63) / 64 * tiles;
-    if (tiles64 >= 768 && f.H >= 1024 && tiles64 * f.H >= 5ll << 18) launch_gemm_f32_rows<4>(f, B);
-    else if (tiles32 >= 400) launch_gemm_f32_rows<2>(f, B);
-    else launch_gemm_f32_rows<1>(f, B);
+    const int rows = rows_of_tile_f32(f);
+    const bool whole = whole_call_f32(f);
+    RopeF32 rope = {};
+    if (f.rope_cos && rope_in_store_f32(f)) rope = RopeF32{f.rope_cos, f.rope_sin, f.rope_positions, f.D / 2};
+    const GroupSmallArgs group = {f.aid, f.seg, f.pos, f.start, f.active, f.aeff, f.perm, f.offsets, f.blocktab, f.n_blocks, nullptr};
+    dim3 grid((f.N + 63) / 64, (f.T + rows - 1) / rows);
+    if (whole && group_in_shrink_f32(f) && !reuse_grouping) grid.y += (f.n_blocks + grid.x - 1) / grid.x;
+    auto launch = [&](auto kernel) {
+        launch_kernel(kernel, grid, dim3(F32_THREADS), 0, f.stream, (const float *)f.x, (const float *)f.W, (const float *)f.bias, B, f.ranks,
+                      (const float *)f.S, f.aid, f.seg, f.pos, f.start, f.slot, (float *)f.q, (float *)f.kc, (float *)f.vc, f.T, f.H, f.Nq, f.Nkv,
+                      f.r, rope, A, group, f.L);
+    };
+    if (rows == 64) launch(gemm_f32_kernel<4, Projection>);
+    else if (rows == 32) launch(gemm_f32_kernel<2, Projection>);
+    else if (whole) launch(gemm_f32_kernel<1, Whole>);
+    else launch(gemm_f32_kernel<1, Projection>);
     return launch_status();
 }
 

@@ -129,8 +129,8 @@ inline int launch_status()
 // launches (each returns the hipError_t of its launch as int)
 int launch_classify_group(const Fwd &f);
 int launch_shrink_f32(const Fwd &f, const PtrTable &A, bool reuse_grouping);
-bool group_in_shrink_f32(const Fwd &f);   // the grouping runs on workgroups of the fp32 shrink
-int launch_gemm_f32(const Fwd &f, const PtrTable &B);
+bool group_in_shrink_f32(const Fwd &f);   // the grouping runs on workgroups of the fp32 shrink or, where that has no launch of its own, projection
+int launch_gemm_f32(const Fwd &f, const PtrTable &B, const PtrTable &A, bool reuse_grouping);
 int launch_shrink_bf16(const Fwd &f, const PtrTable &A);
 int launch_gemm_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEvent_t after_projection);
 int launch_finish_bf16(const Fwd &f, const PtrTable &B, int splits, int s_splits, const int32_t *block_rows, bool s_f32);

@@ -467,6 +467,20 @@ def test_fp32_tiles_and_batch_sizes(kw):
     _check_full(wl.small_mixed("f32", seed=21, **kw))
 
 
+# Small fp32 layers run as one launch (hidden at most 256, rank at most 16, at most four adapters): the ends of those ranges, all four adapters
+# in a tile of 16 rows, wavefronts without a share of the hidden dimension, ranks of their own, batches whose grouping is a launch
+# of its own.  Bounds: those of every fp32 case in _check_full.
+@pytest.mark.parametrize("kw", [dict(hidden=4, rank=1, n_adapters=1, seq_lens=(1,)), dict(hidden=256, rank=16, n_adapters=4, seq_lens=(3, 2, 1) * 9),
+                                dict(hidden=100, rank=9, n_adapters=4, seq_lens=(17, 30, 1, 16), n_q_heads=3, n_kv_heads=1, head_dim=20),
+                                dict(hidden=196, rank=8, n_adapters=2, seq_lens=(200, 57, 9)), dict(hidden=256, rank=16, n_adapters=5, seq_lens=(3, 2, 1) * 9),
+                                dict(hidden=256, rank=17, n_adapters=4, seq_lens=(40, 7))], ids=["least", "most", "odd", "grouped", "five-adapters", "rank-17"])
+def test_fp32_call_in_one_launch(kw):
+    w = wl.small_mixed("f32", seed=23, **kw)
+    _check_full(w)
+    if w.rank == 9:
+        _check_full(wl.with_variants(w, ranks=(9, 1, 8, 3), bias=True))
+
+
 # Batches of at most 64 rows have a projection kernel of their own: each token tile (16, 32, 48, 64 rows) less than, just and
 # one more than full, the first batch past it; fewer 64-wide slices than wavefronts, slices that do not divide among
 # wavefronts and splits; a feature tile that ends inside the 128, ranks from 8 to 64 columns of the shrink's tile.

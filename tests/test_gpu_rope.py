@@ -99,6 +99,14 @@ def test_fp32_path_rotates_in_place(head_dim):
     _check(wl.small_mixed("f32", head_dim=head_dim, seq_lens=(70, 37, 1, 40), seed=24 + head_dim))
 
 
+# Heads that lie inside the 64 features of an fp32 tile are turned in the projection's store, in calls of one launch and of several, and in
+# tiles of 32 rows; others in a pass of their own.  (Bounds as above.)
+@pytest.mark.parametrize("head_dim", [4, 8, 16, 24, 32, 64])
+@pytest.mark.parametrize("kw", [dict(hidden=256), dict(hidden=260), dict(hidden=36, n_q_heads=44, n_kv_heads=4, seq_lens=(700, 300, 93))], ids=["one-launch", "launches", "tiles-of-32"])
+def test_fp32_heads_of_a_tile(head_dim, kw):
+    _check(wl.small_mixed("f32", head_dim=head_dim, seed=60 + head_dim, **{"seq_lens": (70, 37, 1, 40), **kw}))
+
+
 def test_argument_checks():
     w = wl.small_mixed("bf16", head_dim=64, seed=3)
     cos, sin, dev = _tables(w)
