@@ -71,8 +71,8 @@ int alora_paged_attention(const void *q, const void *k_cache, const void *v_cach
 /*
  * The same computation for batches too small to fill the chip with one workgroup per (row, K/V head)
  * -- a few sequences with long contexts, the shape of an adapter evaluated on one long conversation
- * (Sec. 4.2): every row's context is cut into parts, one workgroup each (about 1024 workgroups, at
- * most 32 parts), the parts leave (running maximum, sum of weights, unnormalised output) in the
+ * (Sec. 4.2): every row's context is cut into parts, one workgroup each (about 1024 workgroups, or where it is long
+ * 2048, at most 32 parts), the parts leave (running maximum, sum of weights, unnormalised output) in the
  * workspace and a second kernel combines them in a fixed order.  Results equal those of
  * alora_paged_attention up to fp32 summation order and do not depend on timing.
  *   workspace  device, 16-byte aligned, >= alora_paged_attention_workspace_bytes() bytes (0 when the

@@ -111,26 +111,52 @@ __device__ __forceinline__ float dot8(const Raw8<false> &q, const Raw8<false> &k
 // exp2(-inf) = 0).  Scores below it are treated like -inf.
 constexpr float M_FLOOR = -1.0e30f;
 
-// The batch row with the `rank`-th longest context among `rows` (at most 256) from `first` on, and its sequence and position, for a
-// workgroup of 256 threads.  Lengths count in steps of an eighth (128 of them from 16 positions to a million), rows of one step in batch
-// order: every workgroup finds the same order, and each row once.  Where no context is longer than SHORT_CONTEXT it is the batch's order.
-// scr: ORDER_SCRATCH ints of LDS.
-struct Row { int t, seq, pos; };
+// Which row, K/V head and part of the context workgroup b is for when the longest contexts go first; of 256 threads.  Lengths count in
+// steps of an eighth (128 of them from 16 positions to a million), rows of one step in batch order: every workgroup finds the same
+// order, and each row once.  Where no context is longer than SHORT_CONTEXT it is the batch's order.  Without parts the order is that
+// of every `sorted` rows (at most 256).  In parts there are no more rows than that; those of a.splits parts (see parts_of) come first, where there are
+// none the batch's order stays, and the last workgroups find nothing to do (t = -1).  scr: ORDER_SCRATCH ints of LDS.
+struct Turn { int t, seq, pos, hk, part; };
 constexpr int ORDER_SCRATCH = 128 + 8 + 2;
 constexpr int SHORT_CONTEXT = 512;
-__device__ __forceinline__ Row longest_first(const AttnArgs &a, int first, int rows, int rank, int *scr)
+constexpr int LONG_PART = 512;      // positions per part from which a context is cut into the larger number of parts
+__device__ __forceinline__ int parts_of(const AttnArgs &a, int n_ctx) { return a.short_splits < a.splits && n_ctx < a.splits * LONG_PART ? a.short_splits : a.splits; }
+__device__ __forceinline__ Turn longest_first(const AttnArgs &a, int sorted, int b, int *scr)
 {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     unsigned long long *const masks = (unsigned long long *)(scr + 128);
+    const int first = a.splits > 1 ? 0 : b / a.Hkv / sorted * sorted, rows = min(sorted, a.T - first);
     int key = -1, n_ctx = 0, sq = -1, p = -1;
+    bool more = false;
     if (tid < rows) {
         sq = a.seq[first + tid], p = a.pos[first + tid];
         if (sq >= 0 && sq < a.n_seqs && p >= 0) n_ctx = (int)min(p + 1ll, (long long)a.max_blocks * a.bs);
         key = 127 - min(max((int)(__float_as_uint((float)n_ctx) >> 20) - ((127 + 4) << 3), 0), 127);
+        more = parts_of(a, n_ctx) > a.short_splits;
+        if (a.short_splits < a.splits) key = (more ? 0 : 64) + (key >> 1);   // (steps of a quarter)
     }
     if (tid < 128) scr[tid] = 0;
+    b -= first * a.Hkv;
+    int rank, unit, parts = a.short_splits;
+    bool ordered = n_ctx > SHORT_CONTEXT;
+    if (a.short_splits < a.splits) {
+        const int n_more = __syncthreads_count(more), in_more = n_more * a.splits * a.Hkv;
+        ordered = n_more > 0;
+        if (b < in_more) parts = a.splits;
+        else b -= in_more;
+        unit = parts * a.Hkv;
+        rank = b / unit;
+        b -= rank * unit;
+        if (parts == a.short_splits) rank += n_more;
+        if (rank >= rows) return {-1, -1, -1, 0, 0};
+    } else {
+        unit = parts * a.Hkv;
+        rank = b / unit;
+        b -= rank * unit;
+    }
+    const int hk = b / parts, part = b - hk * parts;
     if (tid == rank) scr[136] = sq, scr[137] = p;
-    if (!__syncthreads_or(n_ctx > SHORT_CONTEXT)) return {first + rank, scr[136], scr[137]};
+    if (!__syncthreads_or(ordered)) return {first + rank, scr[136], scr[137], hk, part};
     if (key >= 0) atomicAdd(&scr[key], 1);   // counts only: their values do not depend on the order
     __syncthreads();
     const int h0 = scr[2 * lane], h1 = scr[2 * lane + 1], upto = sum_upto64(h0 + h1);
@@ -147,7 +173,7 @@ __device__ __forceinline__ Row longest_first(const AttnArgs &a, int first, int r
     before += __builtin_amdgcn_mbcnt_hi((unsigned)(mine >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mine, 0u));
     if (key == step && before == n) scr[0] = first + tid, scr[136] = sq, scr[137] = p;
     __syncthreads();
-    return {scr[0], scr[136], scr[137]};
+    return {scr[0], scr[136], scr[137], hk, part};
 }
 
 // What is known of a call's contexts: nothing, that each is read once per head (see launch_dg), or that there are several turns of
@@ -155,7 +181,7 @@ __device__ __forceinline__ Row longest_first(const AttnArgs &a, int first, int r
 enum Contexts { ANY, READ_ONCE, LONGEST_FIRST };
 
 template <int D, int G, bool BF16, bool POW2, Contexts CONTEXTS>
-__global__ __launch_bounds__(256) void paged_attention_kernel(AttnArgs a, int sorted)
+__global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(AttnArgs a, int sorted)
 {
     constexpr int LPP = D / 8;         // lanes per context position
     constexpr int PPW = 64 / LPP;      // positions per wavefront and step
@@ -167,15 +193,17 @@ __global__ __launch_bounds__(256) void paged_attention_kernel(AttnArgs a, int so
     __shared__ float sacc[4][G][D];
 
     // workgroup -> (row, K/V head, part of the context)
-    const int rh = (int)blockIdx.x / a.splits, sp = (int)blockIdx.x - rh * a.splits;
-    const int hk = rh % a.Hkv;
-    int t = rh / a.Hkv, sq, p;
+    int t, sq, p, hk, sp;
     if constexpr (CONTEXTS == LONGEST_FIRST) {
         __shared__ __attribute__((aligned(8))) int order[ORDER_SCRATCH];
-        const int run = t / sorted * sorted;
-        const Row row = longest_first(a, run, min(sorted, a.T - run), t - run, order);
-        t = __builtin_amdgcn_readfirstlane(row.t), sq = __builtin_amdgcn_readfirstlane(row.seq), p = __builtin_amdgcn_readfirstlane(row.pos);
+        const Turn turn = longest_first(a, sorted, (int)blockIdx.x, order);
+        t = __builtin_amdgcn_readfirstlane(turn.t), sq = __builtin_amdgcn_readfirstlane(turn.seq), p = __builtin_amdgcn_readfirstlane(turn.pos);
+        hk = turn.hk, sp = turn.part;
+        if (t < 0) return;
     } else {
+        const int rh = (int)blockIdx.x / a.splits;
+        sp = (int)blockIdx.x - rh * a.splits;
+        t = rh / a.Hkv, hk = rh % a.Hkv;
         sq = a.seq[t], p = a.pos[t];
     }
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -187,8 +215,10 @@ __global__ __launch_bounds__(256) void paged_attention_kernel(AttnArgs a, int so
     const int32_t *bt = a.bt + (size_t)(n_ctx ? sq : 0) * a.max_blocks;
     // this workgroup's part of the context: whole blocks of BLK positions, the same number for every part
     int jbeg = 0;
+    int parts = a.splits;
     if (a.splits > 1) {
-        const int per = ((n_ctx + a.splits * BLK - 1) / (a.splits * BLK)) * BLK;
+        if constexpr (CONTEXTS == LONGEST_FIRST) parts = parts_of(a, n_ctx);
+        const int per = ((n_ctx + parts * BLK - 1) / (parts * BLK)) * BLK;
         jbeg = min(n_ctx, sp * per);
         n_ctx = min(n_ctx, jbeg + per);
     }
@@ -361,8 +391,10 @@ __global__ __launch_bounds__(256) void paged_attention_kernel(AttnArgs a, int so
             o += sacc[w][g][dd] * f;
         }
         if (a.splits > 1) {   // this part's (maximum, sum, unnormalised output); the merge kernel finishes
-            float *pp = a.part + (((size_t)t * a.Hq + (size_t)hk * G + g) * a.splits + sp) * (D + 2);
+            float *const p0 = a.part + ((size_t)t * a.Hq + (size_t)hk * G + g) * a.splits * (D + 2), *pp = p0 + (size_t)sp * (D + 2);
             if (dd == 0) { pp[0] = M; pp[1] = L; }
+            // fewer parts than there is room for: the last place tells how many (a sum of weights is never negative)
+            if (CONTEXTS == LONGEST_FIRST && dd == 0 && sp == 0 && parts < a.splits) *(f32x2 *)(p0 + (size_t)(a.splits - 1) * (D + 2)) = (f32x2){(float)parts, -1.f};
             pp[2 + dd] = o;
             continue;
         }
@@ -456,28 +488,33 @@ __global__ __launch_bounds__(256) void paged_attention_merge_kernel(const float 
     else *(f32x2 *)((float *)out + rh * D + 2 * dd) = (f32x2){y0, y1};
 }
 
+// Non-temporal loads where a context is read once per head (no more rows than sequences) and the memory-side cache (256 MB) would not
+// keep this layer's K and V until they are read again.  us, ordinary | non-temporal loads, 32/8 heads, three layers' caches in turn:
+// 64 rows of equal contexts, 500 MB 100.8 | 91.4, 200 MB 45.2 | 40.9, 100 MB 25.9 | 24.6, 64 MB 16.9 | 17.4; 256 rows of 10 to
+// 100 positions, 66 MB 25.5 | 26.5; one cache over and over, 200 MB 38.5 | 40.4.
+static bool contexts_read_once(const alora_attn_dims *d)
+{
+    return d->n_tokens <= d->n_seqs && d->n_slots * d->n_kv_heads * d->head_dim * (d->dtype == ALORA_BF16 ? 4 : 8) > 96ll << 20;
+}
+
 template <int D, int G>
 static void launch_dg(const AttnArgs &a, bool bf16, hipStream_t st)
 {
     const dim3 grid((unsigned)a.T * (unsigned)a.Hkv * (unsigned)a.splits);
     const bool pow2 = a.bs_shift >= 0;
-    // Non-temporal loads where a context is read once per head (no more rows than sequences) and the memory-side cache (256 MB) would not
-    // keep this layer's K and V until they are read again.  us, ordinary | non-temporal loads, 32/8 heads, three layers' caches in turn:
-    // 64 rows of equal contexts, 500 MB 100.8 | 91.4, 200 MB 45.2 | 40.9, 100 MB 25.9 | 24.6, 64 MB 16.9 | 17.4; 256 rows of 10 to
-    // 100 positions, 66 MB 25.5 | 26.5; one cache over and over, 200 MB 38.5 | 40.4.
-    const bool once = a.T <= a.n_seqs && a.n_slots * a.Hkv * D * (bf16 ? 4 : 8) > 96ll << 20;
     // The longest contexts first where workgroups take several turns on the chip (three per compute unit fit) and contexts can be
     // long: one of 2000 positions that starts last is half the call's length.  us, in batch order | longest first (non-temporal both): 256 rows of 2 to
     // 2047 positions 210 | 185, 100 of 300 to 3000 147 | 134, 250 of 100 to 4000, 64/8 heads 554 | 478.  Contexts of at most SHORT_CONTEXT
-    // keep their order: finding it would be 2 of 25 us (256 rows of 10 to 100).
-    const bool longest = once && a.splits == 1 && (long long)a.T * a.Hkv > 512 && (long long)a.max_blocks * a.bs > SHORT_CONTEXT;
+    // keep their order: finding it would be 2 of 25 us (256 rows of 10 to 100).  Of contexts in parts only where some are long enough for
+    // the larger number (12 rows of 10K to 30K 196 | 169 with it; 7 of 3000 to 9000 43.4 | 44.9 by their order alone).
+    const bool longest = a.once && a.T > 1 && (a.splits == 1 || a.short_splits < a.splits) && (long long)a.T * a.Hkv * a.splits > 512 && (long long)a.max_blocks * a.bs > SHORT_CONTEXT;
     const int runs = (a.T + 255) / 256, sorted = (a.T + runs - 1) / runs;
     auto launch = [&](auto is_bf16, auto is_pow2, auto contexts) {
         launch_kernel((paged_attention_kernel<D, G, decltype(is_bf16)::value, decltype(is_pow2)::value, decltype(contexts)::value>), grid, dim3(256), 0, st, a, sorted);
     };
     auto choose = [&](auto is_bf16, auto is_pow2) {
         if (longest) launch(is_bf16, is_pow2, std::integral_constant<Contexts, LONGEST_FIRST>{});
-        else if (once) launch(is_bf16, is_pow2, std::integral_constant<Contexts, READ_ONCE>{});
+        else if (a.once) launch(is_bf16, is_pow2, std::integral_constant<Contexts, READ_ONCE>{});
         else launch(is_bf16, is_pow2, std::integral_constant<Contexts, ANY>{});
     };
     if (bf16 && pow2) choose(std::true_type{}, std::true_type{});
@@ -486,7 +523,10 @@ static void launch_dg(const AttnArgs &a, bool bf16, hipStream_t st)
     else choose(std::false_type{}, std::false_type{});
     if (a.splits > 1) {
         const dim3 mgrid((unsigned)a.T * (unsigned)a.Hq);
-        if (bf16) launch_kernel((paged_attention_merge_kernel<D, true, false>), mgrid, dim3(256), 0, st, a.part, a.out, a.splits);
+        const bool counted = a.short_splits < a.splits;
+        if (bf16 && counted) launch_kernel((paged_attention_merge_kernel<D, true, true>), mgrid, dim3(256), 0, st, a.part, a.out, a.splits);
+        else if (bf16) launch_kernel((paged_attention_merge_kernel<D, true, false>), mgrid, dim3(256), 0, st, a.part, a.out, a.splits);
+        else if (counted) launch_kernel((paged_attention_merge_kernel<D, false, true>), mgrid, dim3(256), 0, st, a.part, a.out, a.splits);
         else launch_kernel((paged_attention_merge_kernel<D, false, false>), mgrid, dim3(256), 0, st, a.part, a.out, a.splits);
     }
 }
@@ -520,11 +560,22 @@ static int check_dims(const alora_attn_dims *d)
 
 // Parts a row's context is cut into so that a small batch still fills the chip: about 1024 workgroups,
 // at most 32 parts, one part when (rows x K/V heads) already gives that many.
-static int plan_splits(const alora_attn_dims *d)
+static int parts_for(const alora_attn_dims *d, int workgroups)
 {
     const long long wgs = (long long)d->n_tokens * d->n_kv_heads;
     if (wgs <= 0 || wgs >= 1024) return 1;
-    return (int)std::min<long long>(MAX_PARTS, (1024 + wgs - 1) / wgs);
+    return (int)std::min<long long>(MAX_PARTS, (workgroups + wgs - 1) / wgs);
+}
+static int plan_short_splits(const alora_attn_dims *d) { return parts_for(d, 1024); }
+// About 2048 for contexts of LONG_PART positions and more in each part then, if the block tables have room for any and the longest go first: the chip holds 768
+// workgroups (four query heads per K/V head), and what starts last should be small; of short contexts more parts are only more to
+// combine.  us, 1024 | 1536 | 2048 for all: 8 rows of 32K to 64K positions 273 | 257 | 258, 12 of 10K to 30K 196 | 171 | 166, 5 with 64/8 heads
+// 122 | 113 | 115; 6 of 1000 to 3000 20.0 | 23.1 | 23.3, 7 of 3000 to 9000 43.4 | 45.1 | 47.2.
+static int plan_splits(const alora_attn_dims *d)
+{
+    const int parts = parts_for(d, 2048);
+    const bool room = (long long)d->max_blocks * d->block_size >= (long long)parts * LONG_PART && contexts_read_once(d) && d->n_tokens > 1 && d->n_tokens <= 256;
+    return room ? parts : plan_short_splits(d);
 }
 
 // The same for the row-block kernel, whose unit of work is a block of rows.
@@ -645,6 +696,8 @@ static int run(const void *q, const void *k_cache, const void *v_cache, const in
         if ((1 << sft) == dims->block_size) a.bs_shift = sft;
     a.n_slots = dims->n_slots;
     a.splits = splits;
+    a.short_splits = mode == PER_ROW_SPLIT ? plan_short_splits(dims) : splits;
+    a.once = contexts_read_once(dims);
     a.part = (float *)workspace;
     const float scale = dims->scale > 0.f ? dims->scale : 1.0f / sqrtf((float)dims->head_dim);
     a.scale_log2e = scale * 1.4426950408889634f;

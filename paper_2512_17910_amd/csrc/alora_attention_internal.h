@@ -13,6 +13,8 @@ struct AttnArgs {
     long long n_slots;
     float scale_log2e;   // scale * log2(e): the softmax runs on powers of two
     int splits;          // parts a row's context is cut into (one workgroup each); > 1: partials go to `part`
+    int short_splits;    // per-row kernel: parts of a context too short for that many
+    bool once;           // per-row kernel: see contexts_read_once
     float *part;         // [T][Hq][splits][D + 2]: running maximum, sum of weights, unnormalised weighted V
 };
 

@@ -591,3 +591,31 @@ def test_rows_of_streamed_contexts(n, lo, hi, odd):
     pick = np.array([t for t in range(0, n, 23) if t not in bad])
     want = oatt.paged_attention(to_f64(q), to_f64(kc), to_f64(vc), bt, seq, pos, 16, 32, 8, 128, rows=pick)
     assert maxnorm_rel(to_f64(out)[pick], want) <= TOL["bf16"]
+
+
+# In parts, by rows: a context is cut into twice the parts where each has at least 512 positions (22 and 11 parts of 12 rows, 8 heads): just,
+# just not, and contexts shorter than their parts; a row that is not valid.
+def test_parts_of_long_and_short_contexts():
+    rng = np.random.default_rng(1090)
+    n_blocks, width = 1600, 800
+    g = torch.Generator(device="cuda").manual_seed(1090)
+    kc, vc = (torch.randn(n_blocks * 16, 8 * 128, device="cuda", generator=g).bfloat16() for _ in range(2))
+    lens = np.array([22 * 512, 22 * 512 - 1, 12800, 1, 5, 64, 65, 700, 703, 704, 11, 12000])
+    n = len(lens)
+    q = torch.randn(n, 32 * 128, device="cuda", generator=g).bfloat16()
+    bt = rng.integers(0, n_blocks, (n, width)).astype(np.int32)
+    seq, pos = np.arange(n, dtype=np.int32), (lens - 1).astype(np.int32)
+    seq[7] = n
+    dbt, dseq, dpos = (torch.from_numpy(a).to("cuda") for a in (bt, seq, pos))
+    dims = ab.make_attn_dims(q, kc, dbt, 32, 8, 128, 16)
+    nbytes = ab.alora_paged_attention_workspace_bytes(dims)
+    assert nbytes == n * 32 * 22 * 130 * 4
+    out = torch.full_like(q, float("nan"))
+    ws = torch.full((nbytes,), 0xff, dtype=torch.uint8, device="cuda")
+    print("[case] parts of long and short contexts", flush=True)
+    ab.alora_paged_attention_split(q, kc, vc, dbt, dseq, dpos, out, dims, ws)
+    torch.cuda.synchronize()
+    assert not out[7].any()
+    pick = np.delete(np.arange(n), 7)
+    want = oatt.paged_attention(to_f64(q), to_f64(kc), to_f64(vc), bt, seq, pos, 16, 32, 8, 128, rows=pick)
+    assert maxnorm_rel(to_f64(out)[pick], want) <= TOL["bf16"]
