@@ -21,7 +21,7 @@
 //     descriptor's range check returns zeros for token rows past T, masked lanes get an
 //     out-of-range offset.
 //   - the K dimension runs through rings of LDS areas, 32 k per slice: six 24 KB stages (token
-//     slice + weight slice) for the 128-wide tile, eight of 16 KB for the 128 x 128 one; for the 192- and 256-wide tiles six token areas
+//     slice + weight slice) for the 128-wide tile, eight of 16 KB for the 128 x 128 one (the last rows of a fused call, and split calls of as few); for the 192- and 256-wide tiles six token areas
 //     and four weight areas of 16 KB, where a step's token copies cover half the rows of TWO
 //     slices so that both halves of a 128-byte line of x are asked for by neighbouring
 //     instructions (see PAIRED in the kernel).  While slice i is multiplied, the first fragments of
@@ -234,16 +234,17 @@ __device__ __forceinline__ void project_tile(const GemmArgs &g, const PtrTable &
             // One entry of the 32-row block table: group the batch, then the shrink of the block over
             // the whole hidden dimension, out of this kernel's stages (token buffers, A buffers,
             // reduction array, scratch).
-            static_assert(STAGE_BYTES >= (uint32_t)ShrinkLds<256, 1>::X_BYTES && STAGE_BYTES >= (uint32_t)ShrinkLds<256, 1>::A_BYTES &&
-                          STAGE_BYTES >= (uint32_t)ShrinkLds<256, 1>::RED_BYTES && STAGE_BYTES >= (GROUP_SMALL_SCRATCH + 4) * 4u,
-                          "stages hold the shrink's buffers");
+            constexpr uint32_t PIECE = STAGE_BYTES > 20480 ? STAGE_BYTES : 20480;   // of the LDS the stages take, for one of the shrink's buffers
+            static_assert(PIECE >= (uint32_t)ShrinkLds<256, 1>::X_BYTES && PIECE >= (uint32_t)ShrinkLds<256, 1>::A_BYTES &&
+                          PIECE >= (uint32_t)ShrinkLds<256, 1>::RED_BYTES && PIECE >= (GROUP_SMALL_SCRATCH + 4) * 4u && 6 * PIECE <= RING_BYTES,
+                          "the stages hold the shrink's buffers");
             // prep_ranges workgroups per entry, one per range of the hidden dimension; each works the
             // grouping out for itself, the first of them writes the entry's share of its results
             const int p = bx - g.main_wgs;
             const int e = p / g.prep_ranges, range = p - e * g.prep_ranges;
-            unsigned char *const stage0 = ring, *const stage1 = ring + STAGE_BYTES, *const stage2 = ring + 2 * STAGE_BYTES,
-                                *const stage3 = ring + 3 * STAGE_BYTES, *const stage4 = ring + 4 * STAGE_BYTES;
-            int *scr = (int *)(ring + 5 * STAGE_BYTES);
+            unsigned char *const stage0 = ring, *const stage1 = ring + PIECE, *const stage2 = ring + 2 * PIECE,
+                                *const stage3 = ring + 3 * PIECE, *const stage4 = ring + 4 * PIECE;
+            int *scr = (int *)(ring + 5 * PIECE);
             int grp, cnt;
             const int *rows = group_small(g.prep, g.T, g.L, e, range == 0, scr, grp, cnt);
             if (grp < 0 || grp >= g.L) { PROBE_STAMP(7); return; }   // unused entry or the rows that keep the base output
@@ -828,6 +829,14 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void alora_gemm_bf16_kernel(GemmAr
     if constexpr (!SPLIT) {
         if (bx >= g.main_wgs) {
             project_tile<2, 2, false, ROPE>(g, B, A, lds, bx - g.main_wgs, g.mtiles * 256, g.tail_mtiles, (g.N + 127) / 128);
+            return;
+        }
+    }
+    // Calls of at most 128 rows: half the matrix work and LDS reads per slice, and eight stages of 16 KB keep 56 KB of W in flight instead of 40.
+    // us, four layers, 256 | 128 rows: 4096 -> 6144 65 rows 102 | 95, 128 rows 124 | 117, 3072 -> 5120 90 rows 94 | 88; 100 rows of rank 64 150 | 141.
+    if constexpr (SPLIT && NTW == 2) {
+        if (g.T <= 128) {
+            project_tile<2, 2, true, ROPE>(g, B, A, lds, bx, 0, g.mtiles, g.ntiles);
             return;
         }
     }

@@ -493,6 +493,19 @@ def test_few_rows(rows, kw):
     _check_full(wl.small_mixed("bf16", seed=31, seq_lens=lens, pad_every=7, **kw))
 
 
+# Split calls of 65 to 128 rows run in tiles of 128 rows, above in tiles of 256: the ends of that range, with fewer 32-wide slices per split than
+# the ring has stages, just as many and more; grouping and shrink inside (rank 24) and as launches of their own (rank 64).
+# Bounds: those of every bf16 case in _check_full.
+@pytest.mark.parametrize("rows", [66, 127, 128, 129])
+@pytest.mark.parametrize("kw", [dict(hidden=64, rank=8), dict(hidden=448, rank=64, n_q_heads=5, n_kv_heads=2, head_dim=40),
+                                dict(hidden=1088, rank=24, n_adapters=5, n_q_heads=3, n_kv_heads=1, head_dim=128)], ids=["1slice", "7", "17"])
+def test_split_calls_of_up_to_128_rows(rows, kw, tuning):
+    w = wl.small_mixed("bf16", seed=35, seq_lens=(rows - 43, 40, 1, 2), pad_every=7, **kw)
+    _check_full(w)
+    tuning(2, 2)
+    _check_full(w)
+
+
 # The few-row kernel with no adapters, and with more than its rows can use: the block-table entries no workgroup stands for are marked
 # unused in whatever the workspace held, which a later layer under another tiling walks (reuse_grouping).
 # Bounds: those of every bf16 case in _check_full.
