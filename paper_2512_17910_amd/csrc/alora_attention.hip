@@ -488,13 +488,13 @@ __global__ __launch_bounds__(256) void paged_attention_merge_kernel(const float 
     else *(f32x2 *)((float *)out + rh * D + 2 * dd) = (f32x2){y0, y1};
 }
 
-// Non-temporal loads where a context is read once per head (no more rows than sequences) and the memory-side cache (256 MB) would not
+// Non-temporal loads where a context is read once per head (no more rows than sequences) and the memory-side cache would not
 // keep this layer's K and V until they are read again.  us, ordinary | non-temporal loads, 32/8 heads, three layers' caches in turn:
 // 64 rows of equal contexts, 500 MB 100.8 | 91.4, 200 MB 45.2 | 40.9, 100 MB 25.9 | 24.6, 64 MB 16.9 | 17.4; 256 rows of 10 to
 // 100 positions, 66 MB 25.5 | 26.5; one cache over and over, 200 MB 38.5 | 40.4.
 static bool contexts_read_once(const alora_attn_dims *d)
 {
-    return d->n_tokens <= d->n_seqs && d->n_slots * d->n_kv_heads * d->head_dim * (d->dtype == ALORA_BF16 ? 4 : 8) > 96ll << 20;
+    return d->n_tokens <= d->n_seqs && outgrows_cache(d->n_slots, d->n_kv_heads, d->head_dim, d->dtype == ALORA_BF16);
 }
 
 template <int D, int G>

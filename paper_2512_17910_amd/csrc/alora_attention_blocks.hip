@@ -70,10 +70,12 @@ __device__ __forceinline__ void load_lds16(uint32_t lds_addr, const void *p)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr), "v"(p) : "memory");
 }
-// the same with a scalar base address and a 32-bit byte offset per lane
+// the same with a scalar base address and a 32-bit byte offset per lane; ONCE: nobody else will read these bytes
+template <bool ONCE>
 __device__ __forceinline__ void load_lds16(uint32_t lds_addr, const void *base, uint32_t voffset)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voffset), "s"(base) : "memory");
+    if constexpr (ONCE) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(lds_addr), "v"(voffset), "s"(base) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voffset), "s"(base) : "memory");
 }
 // Exchange between the two lanes of a column (lanes c, c+32), as an assembly statement (the builtin returned its
 // first result twice) with wait states on both sides, which the compiler cannot place for an instruction it does
@@ -107,8 +109,11 @@ __device__ __forceinline__ int max_upto64(int x)
 __device__ const uint32_t ab_zero_chunk[4] = {0u, 0u, 0u, 0u};
 
 // whether the kernel settles the number of parts (a kernel of its own: what the counting adds costs 2 x 2 rows at 2000 positions 1.3 of 13 us)
-struct AsPlanned { static constexpr bool count = false; };
-struct Counted { static constexpr bool count = true; };
+struct AsPlanned { static constexpr bool count = false, once = false; };
+struct Counted { static constexpr bool count = true, once = false; };
+// and contexts of which most are read once per head (see launch_attention_blocks)
+struct AsPlannedOnce { static constexpr bool count = false, once = true; };
+struct CountedOnce { static constexpr bool count = true, once = true; };
 
 // NW: wavefronts per workgroup; POW2: the block size is a power of two (shifts instead of divisions)
 template <int G, int NW, bool POW2, typename PARTS>
@@ -358,8 +363,8 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
         if ((unsigned)blk < n_blocks_u && pu + 4 <= n_ctx) {   // the usual case: scalar base, the lane's constant offset
             const unsigned slot = (POW2 ? ((unsigned)blk << a.bs_shift) : (unsigned)blk * (unsigned)a.bs) + (unsigned)(POW2 ? (pu & (a.bs - 1)) : (pu % a.bs));
             const unsigned long long at = (unsigned long long)slot * row_bytes + head_bytes;   // first of the four cache rows
-            load_lds16(k_to, (const char *)a.kc + at, k_off);
-            load_lds16(v_to, (const char *)a.vc + at, v_off);
+            load_lds16<PARTS::once>(k_to, (const char *)a.kc + at, k_off);
+            load_lds16<PARTS::once>(v_to, (const char *)a.vc + at, v_off);
         } else {           // rows that are not part of the context read 16 zero bytes
             const bool blk_ok = (unsigned)blk < n_blocks_u;
             const int n_ok = blk_ok ? max(0, min(4, n_ctx - pu)) : 0;
@@ -638,8 +643,15 @@ int launch_attention_blocks(const AttnArgs &a, int G, const BlockPlan &p, hipStr
     const dim3 grid((unsigned)ranges * (unsigned)p.wgs * (unsigned)a.Hkv * (unsigned)a.splits), block(64 * p.waves);
     const bool pow2 = a.bs_shift >= 0;
 #define AB_LAUNCH_AS(GG, NW, POW2, PARTS) launch_kernel((paged_attention_blocks_kernel<GG, NW, POW2, PARTS>), grid, block, 0, stream, a, p.range, p.wgs)
+    // Non-temporal copies where a sequence brings a quarter of a row block on average (then few runs lie in two blocks, which would both read the
+    // context) and the memory-side cache would not keep K and V.  us, ordinary | non-temporal, 32/8 heads: 64 single rows at 4096
+    // positions 187 | 169, in parts 100 at 500 to 4000 201 | 179, 6 at 10K to 30K 110 | 100, 40 x 6 rows at 2K to 5K 148 | 144; 4 x 11 at
+    // 16K to 20K 75 | 74, 4 x 24 98 | 103, 40 x 20 at 2K to 5K 188 | 197, 8/8 heads 6 x 40 at 10K to 30K 143 | 153.
+    const bool once = pow2 && (long long)a.T * G <= 32ll * a.n_seqs && outgrows_cache(a.n_slots, a.Hkv, 128, true);
 #define AB_LAUNCH(GG, NW) \
-    if (p.count && pow2) AB_LAUNCH_AS(GG, NW, true, Counted); \
+    if (once && p.count && NW == 4) AB_LAUNCH_AS(GG, 4, true, CountedOnce); \
+    else if (once && !p.count) AB_LAUNCH_AS(GG, NW, true, AsPlannedOnce); \
+    else if (p.count && pow2) AB_LAUNCH_AS(GG, NW, true, Counted); \
     else if (p.count) AB_LAUNCH_AS(GG, NW, false, Counted); \
     else if (pow2) AB_LAUNCH_AS(GG, NW, true, AsPlanned); \
     else AB_LAUNCH_AS(GG, NW, false, AsPlanned)

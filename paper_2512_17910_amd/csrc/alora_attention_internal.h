@@ -20,6 +20,9 @@ struct AttnArgs {
 
 constexpr int MAX_PARTS = 32;   // of a row's context
 
+// A layer's K and V that the memory-side cache (256 MB) would not keep until they are read again.
+inline bool outgrows_cache(long long n_slots, int Hkv, int D, bool bf16) { return n_slots * Hkv * D * (bf16 ? 4 : 8) > 96ll << 20; }
+
 // sums over lanes 0 .. lane (row_shr:1, 2, 4, 8, then row_bcast:15 and 31 into the rows above)
 __device__ __forceinline__ int sum_upto64(int x)
 {

@@ -619,3 +619,36 @@ def test_parts_of_long_and_short_contexts():
     pick = np.delete(np.arange(n), 7)
     want = oatt.paged_attention(to_f64(q), to_f64(kc), to_f64(vc), bt, seq, pos, 16, 32, 8, 128, rows=pick)
     assert maxnorm_rel(to_f64(out)[pick], want) <= TOL["bf16"]
+
+
+# Few rows per sequence over a cache that does not stay in the memory-side cache: the row-block reader's copies are non-temporal, with eight and
+# four wavefronts, in parts as planned and counted; the same bits as over a cache that does, and the oracle's values.
+@pytest.mark.parametrize("group", [1, 2, 4, 8])
+@pytest.mark.parametrize("n,rows,parts", [(3, 1, False), (70, 3, False), (2, 2, True), (40, 4, True)])
+def test_row_blocks_of_streamed_contexts(group, n, rows, parts):
+    rng = np.random.default_rng(1100 + group + n)
+    n_blocks, small, width = 1600, 1400, 64
+    g = torch.Generator(device="cuda").manual_seed(1100 + group + n)
+    kc, vc = (torch.randn(n_blocks * 16, 8 * 128, device="cuda", generator=g).bfloat16() for _ in range(2))
+    lens = rng.integers(rows, 16 * width + 1, n)
+    seq = np.repeat(np.arange(n, dtype=np.int32), rows)
+    pos = np.concatenate([np.arange(l - rows, l, dtype=np.int32) for l in lens])
+    bt = rng.integers(0, small, (n, width)).astype(np.int32)
+    q = torch.randn(n * rows, 8 * group * 128, device="cuda", generator=g).bfloat16()
+    dbt, dseq, dpos = (torch.from_numpy(a).to("cuda") for a in (bt, seq, pos))
+    outs = []
+    for k, v in ((kc, vc), (kc[: small * 16], vc[: small * 16])):
+        out = torch.full_like(q, float("nan"))
+        dims = ab.make_attn_dims(q, k, dbt, 8 * group, 8, 128, 16)
+        print(f"[case] streamed row blocks group={group} {n} x {rows} parts={parts} slots={k.shape[0]}", flush=True)
+        if parts:
+            ws = torch.full((ab.alora_paged_attention_suffix_workspace_bytes(dims),), 0xff, dtype=torch.uint8, device="cuda")
+            ab.alora_paged_attention_suffix_split(q, k, v, dbt, dseq, dpos, out, dims, ws)
+        else:
+            ab.alora_paged_attention_suffix(q, k, v, dbt, dseq, dpos, out, dims)
+        torch.cuda.synchronize()
+        outs.append(out)
+    assert np.array_equal(raw_bits(outs[0]), raw_bits(outs[1]))
+    pick = np.arange(0, n * rows, 1 + n * rows // 12)
+    want = oatt.paged_attention(to_f64(q), to_f64(kc), to_f64(vc), bt, seq, pos, 16, 8 * group, 8, 128, rows=pick)
+    assert maxnorm_rel(to_f64(outs[0])[pick], want) <= TOL["bf16"]
