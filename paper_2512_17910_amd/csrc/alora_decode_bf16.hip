@@ -8,7 +8,7 @@
 //     consecutive rows and turns the 8 x 8 block around in registers (one v_perm per two elements), so that
 //     MFMA f of eight takes feature 8 * (lane % 16) + f.
 //   - the wavefronts of a workgroup take different ranges of the hidden dimension (no element of W is loaded
-//     twice for a token tile, no barrier in the loop) and keep several 32-wide slices in flight in registers;
+//     twice for a token tile, no barrier in the loop) and keep the next 64 of the hidden dimension in flight in registers;
 //     their sums meet in LDS at the end and are added in fixed order.
 //   - the ends of a wavefront's range are the ends of its buffer descriptors: slices past them are requested
 //     like any other and come back as zeros without memory traffic, so the loop has no tail.
@@ -53,7 +53,7 @@ struct DecodeArgs {
 // [H, n_cols], this lane's eight columns start at col (past n_cols: zeros).  row_at(i): where token i of the tile
 // starts in x, in bytes (DEC_OOR: no such token).  xs: LDS of this wavefront alone (in order, no barriers).
 // Result: lane (c, g) holds, for token nt * 16 + c, columns 32 g + 8 i + f of the tile in register i of acc[nt][f].
-template <int NTT, int DEPTH, int NT, typename RowAt>
+template <int NTT, int NT, typename RowAt>
 __device__ __forceinline__ void decode_products(const bf16_t *x, uint32_t x_bytes, RowAt row_at, const bf16_t *M, int n_cols, int col,
                                                 int u0, int u1, unsigned char *xs, f32x4 (&acc)[NTT][8])
 {
@@ -67,6 +67,10 @@ __device__ __forceinline__ void decode_products(const bf16_t *x, uint32_t x_byte
     uint32_t x_at[2 * NTT];
 #pragma unroll
     for (int q = 0; q < 2 * NTT; ++q) x_at[q] = row_at(8 * q + (lane >> 3));
+    // Slices in flight: one (two halves, each requested again as soon as it is multiplied).  With two or more the loop is twice as long and the
+    // registers leave a unit one workgroup: four layers of 4096 -> 6144, two | one in flight, us: one row 64.6 | 63.2, 24 rows 73.3 | 72.0, 64
+    // rows 92.1 | 89.3, 8192 -> 10240 at two rows 151 | 149; three or four 70.4 at one row.
+    constexpr int DEPTH = 1;
     u32x4 mv[2 * DEPTH][8], xv[DEPTH][2 * NTT];
     auto request_m = [&](int d, int h) {   // half slice h of the range; streamed: no other workgroup reads it
         const uint32_t mo = h < 2 * n_units && col < n_cols ? m_at + (uint32_t)h * half_bytes : DEC_OOR;
@@ -150,7 +154,7 @@ __device__ __forceinline__ void decode_reduce(float *red, const f32x4 (&acc)[NTT
     }
 }
 
-template <int NTT, int DEPTH>
+template <int NTT>
 __global__ __launch_bounds__(DEC_THREADS, NTT > 2 ? 1 : 2) void decode_projection_kernel(DecodeArgs g, PtrTable A)
 {
     constexpr int XS_TILES = NTT < 2 ? 2 : NTT, RED_BYTES = DEC_WAVES * 16 * XS_TILES * DEC_PITCH * 4, XS_BYTES = XS_TILES * 2048;   // (the shrink takes two tiles)
@@ -177,7 +181,7 @@ __global__ __launch_bounds__(DEC_THREADS, NTT > 2 ? 1 : 2) void decode_projectio
         auto row_at = [&](int i) { const int t = rows[i]; return t >= 0 ? (uint32_t)t * (uint32_t)g.H * 2u : DEC_OOR; };
         const int r0 = min(units, range * g.prep_units), n_u = min(units, r0 + g.prep_units) - r0;
         f32x4 acc[2][8] = {};
-        decode_products<2, 1, 0>(g.x, x_bytes, row_at, (const bf16_t *)A.p[grp], rk, 8 * c, r0 + n_u * w / DEC_WAVES, r0 + n_u * (w + 1) / DEC_WAVES, xs, acc);
+        decode_products<2, 0>(g.x, x_bytes, row_at, (const bf16_t *)A.p[grp], rk, 8 * c, r0 + n_u * w / DEC_WAVES, r0 + n_u * (w + 1) / DEC_WAVES, xs, acc);
         __syncthreads();   // the reduction works where the wavefronts parked their tokens
         float *S = g.S + (size_t)range * g.T * g.r;
         decode_reduce<2>(red, acc, [&](int tok, int cc, f32x4 s) {
@@ -196,7 +200,7 @@ __global__ __launch_bounds__(DEC_THREADS, NTT > 2 ? 1 : 2) void decode_projectio
     auto row_at = [&](int i) { return i < g.T ? (uint32_t)i * (uint32_t)g.H * 2u : DEC_OOR; };
     const int r0 = min(units, split * g.units_per_split), n_u = min(units, r0 + g.units_per_split) - r0;
     f32x4 acc[NTT][8] = {};
-    decode_products<NTT, DEPTH, DEC_STREAM>(g.x, x_bytes, row_at, g.W, g.N, n0 + 8 * c, r0 + n_u * w / DEC_WAVES, r0 + n_u * (w + 1) / DEC_WAVES, xs, acc);
+    decode_products<NTT, DEC_STREAM>(g.x, x_bytes, row_at, g.W, g.N, n0 + 8 * c, r0 + n_u * w / DEC_WAVES, r0 + n_u * (w + 1) / DEC_WAVES, xs, acc);
     __syncthreads();   // the reduction works where the wavefronts parked their tokens
     float *out = g.partial + (size_t)split * g.T * g.N;
     decode_reduce<NTT>(red, acc, [&](int tok, int cc, f32x4 s) {
@@ -224,7 +228,19 @@ int launch_decode_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEv
     // hence 200 for the projection.  (The shrink has two for every 32 rows of an adapter, at most two per row, and its workgroups come
     // first: 64 rows of 32 adapters each get to 262 in all.)  Four layers of 4096 -> 6144 at one row, us: 144 workgroups 80, 192 73, 240 81, 384 78;
     // 3072 -> 5120 at eight rows: 160 67, 200 65, 240 70; 8192 -> 10240: 80 251, 160 160, 240 159, 320 174.
-    g.splits = std::max(1, std::min(std::min(8, units / DEC_WAVES), 200 / g.ntiles));   // (a slice per wavefront at least)
+    // The fewest splits that leave a wavefront the least (3072 -> 5120 at 48 rows, five 74.6, four 71.9).  Of a few rows the shrink's
+    // workgroups are few for certain, and the projection takes the rest where that saves a wavefront two slices and more (8192 -> 10240, two | three
+    // splits: one row 148.4 | 132.3, eight 153.9 | 136.5; 3072 -> 5120 at two rows, one slice less, four splits 57.9, six 59.0).
+    auto share = [&](int splits) { return ((units + splits - 1) / splits + DEC_WAVES - 1) / DEC_WAVES; };
+    auto splits_of = [&](int workgroups) {
+        int best = 1;
+        for (int s = 2; s <= std::min(std::min(8, units / DEC_WAVES), workgroups / g.ntiles); ++s)   // (a slice per wavefront at least)
+            if (share(s) < share(best)) best = s;
+        return best;
+    };
+    g.splits = splits_of(200);
+    const int more = splits_of(256 - 2 * f.T);
+    if (share(more) + 2 <= share(g.splits)) g.splits = more;
     g.units_per_split = (units + g.splits - 1) / g.splits;
     g.splits = (units + g.units_per_split - 1) / g.units_per_split;
     // Two ranges of the hidden dimension for the shrink (one: 88 against 73 us, four and eight: no gain); without
@@ -237,10 +253,10 @@ int launch_decode_bf16(const Fwd &f, const PtrTable &B, const PtrTable &A, hipEv
     g.group = GroupSmallArgs{f.aid, f.seg, f.pos, f.start, f.active, f.aeff, f.perm, f.offsets, f.blocktab, f.n_blocks, f.block_rows};
     g.ranks = f.ranks;
     const dim3 grid((g.ntiles * g.splits + 7) / 8 * 8 + g.prep_wgs), block(DEC_THREADS);
-    if (f.T <= 16) launch_kernel((decode_projection_kernel<1, 2>), grid, block, 0, f.stream, g, A);
-    else if (f.T <= 32) launch_kernel((decode_projection_kernel<2, 2>), grid, block, 0, f.stream, g, A);
-    else if (f.T <= 48) launch_kernel((decode_projection_kernel<3, 2>), grid, block, 0, f.stream, g, A);
-    else launch_kernel((decode_projection_kernel<4, 2>), grid, block, 0, f.stream, g, A);
+    if (f.T <= 16) launch_kernel((decode_projection_kernel<1>), grid, block, 0, f.stream, g, A);
+    else if (f.T <= 32) launch_kernel((decode_projection_kernel<2>), grid, block, 0, f.stream, g, A);
+    else if (f.T <= 48) launch_kernel((decode_projection_kernel<3>), grid, block, 0, f.stream, g, A);
+    else launch_kernel((decode_projection_kernel<4>), grid, block, 0, f.stream, g, A);
     int e = launch_status();
     if (!e && after_projection) e = (int)hipEventRecord(after_projection, f.stream);
     if (e) return e;
