@@ -74,11 +74,16 @@ int alora_paged_attention(const void *q, const void *k_cache, const void *v_cach
  * (Sec. 4.2): every row's context is cut into parts, one workgroup each (about 1024 workgroups, or where it is long
  * 2048, at most 32 parts), the parts leave (running maximum, sum of weights, unnormalised output) in the
  * workspace and a second kernel combines them in a fixed order.  Results equal those of
- * alora_paged_attention up to fp32 summation order and do not depend on timing.
- *   workspace  device, 16-byte aligned, >= alora_paged_attention_workspace_bytes() bytes (0 when the
+ * alora_paged_attention up to fp32 summation order and do not depend on timing.  The order, and with it a row's low
+ * bits, depends on the sizes in dims, on the workspace's size and on the contexts of the call's rows.
+ *   workspace  device, 16-byte aligned; contents on entry irrelevant; calls that share it must be
+ *              stream-ordered.  alora_paged_attention_workspace_bytes() is the size with which a call runs best (0 when the
  *              batch is large enough for one part: then this IS alora_paged_attention and the
- *              workspace may be NULL); contents on entry irrelevant; calls that share it must be
- *              stream-ordered.  Too small or misaligned: ALORA_EWORKSPACE.
+ *              workspace may be NULL).  It depends on n_tokens, the head counts and head_dim and, where a long context is
+ *              cut into more parts (2 to 256 rows, not more than n_seqs, over a cache above 96 MiB), on max_blocks * block_size, and
+ *              is not monotonic in n_tokens.  Enough is what holds the fewer parts, whatever max_blocks, n_seqs and n_slots are:
+ *              p = min(32, ceil(1024 / (n_tokens * n_kv_heads))) parts, n_tokens * n_q_heads * p * (head_dim + 2) * 4 bytes, with which long contexts
+ *              take those.  Less than that or misaligned: ALORA_EWORKSPACE.
  */
 int alora_paged_attention_workspace_bytes(const alora_attn_dims *dims, size_t *out_bytes);
 int alora_paged_attention_split(const void *q, const void *k_cache, const void *v_cache, const int32_t *block_tables,

@@ -591,9 +591,8 @@ static size_t block_split_bytes(const alora_attn_dims *d)
     return (size_t)d->n_tokens * d->n_q_heads * sp * (d->head_dim + 2) * sizeof(float);
 }
 
-static size_t split_bytes(const alora_attn_dims *d)
+static size_t split_bytes(const alora_attn_dims *d, int sp)
 {
-    const int sp = plan_splits(d);
     if (sp <= 1) return 0;
     return (size_t)d->n_tokens * d->n_q_heads * sp * (d->head_dim + 2) * sizeof(float);
 }
@@ -615,7 +614,7 @@ int alora_paged_attention_workspace_bytes(const alora_attn_dims *dims, size_t *o
     if (!out_bytes) return ALORA_EINVAL;
     const int st = check_dims(dims);
     if (st) return st;
-    *out_bytes = split_bytes(dims);
+    *out_bytes = split_bytes(dims, plan_splits(dims));
     return ALORA_OK;
 }
 
@@ -678,8 +677,10 @@ static int run(const void *q, const void *k_cache, const void *v_cache, const in
     // without table or cache, take the per-row kernel)
     const bool row_blocks = blocks_asked && dims->block_size % 4 == 0 && dims->n_seqs >= 1 && dims->max_blocks >= 1 &&
                             dims->n_slots >= dims->block_size;
-    const int splits = mode == PER_ROW_SPLIT ? plan_splits(dims) : (mode == ROW_BLOCKS_SPLIT && row_blocks) ? block_plan(dims, true).splits : 1;
-    const size_t need = mode == PER_ROW_SPLIT ? split_bytes(dims) : mode == ROW_BLOCKS_SPLIT ? block_split_bytes(dims) : 0;
+    int splits = mode == PER_ROW_SPLIT ? plan_splits(dims) : (mode == ROW_BLOCKS_SPLIT && row_blocks) ? block_plan(dims, true).splits : 1;
+    // (by rows: a workspace that holds the fewer parts is enough)
+    if (mode == PER_ROW_SPLIT && workspace_bytes < split_bytes(dims, splits)) splits = plan_short_splits(dims);
+    const size_t need = mode == PER_ROW_SPLIT ? split_bytes(dims, splits) : mode == ROW_BLOCKS_SPLIT ? block_split_bytes(dims) : 0;
     if (splits > 1 && (!workspace || ((uintptr_t)workspace & 15) || workspace_bytes < need)) return ALORA_EWORKSPACE;
     if (dims->n_tokens == 0) return ALORA_OK;
     if (!q || !k_cache || !v_cache || !block_tables || !token_seq_ids || !token_positions || !out) return ALORA_EINVAL;

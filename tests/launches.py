@@ -5,7 +5,7 @@ every launch is written down instead of enqueued, device pointers are numbers th
 dict: op "forward" (fields of alora_dims, optionally rope: with rotation tables, replays: recorded and replayed, errors: a HIP error that an earlier call of the program left, and one that every
 launch fails with (then: what the library reports, and what is left), timed: the shortest host time of so many
 classifications and calls, tuning_during: a tuning override that arrives in the middle of the
-call, between the library's two profiling events) or op "attention" (fields of alora_attn_dims and the entry point)."""
+call, between the library's two profiling events) or op "attention" (fields of alora_attn_dims and the entry point, optionally give: the workspace's size instead of the one asked for)."""
 import ctypes
 import json
 import os
@@ -87,7 +87,7 @@ def _main(rec_path):
             split = c["entry"].endswith("_split")
             s = getattr(L, c["entry"][:-6] + "_workspace_bytes")(ctypes.byref(d), ctypes.byref(ws)) if split else 0
             if s == 0:
-                s = getattr(L, c["entry"])(P, P, P, P, P, P, P, ctypes.byref(d), *((P, ws) if split else ()), None)
+                s = getattr(L, c["entry"])(P, P, P, P, P, P, P, ctypes.byref(d), *((P, ctypes.c_size_t(c.get("give", ws.value))) if split else ()), None)
         launches = []
         for i in range(rec.rec_count()):
             r = rec.rec_get(i).contents

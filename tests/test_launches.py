@@ -246,3 +246,27 @@ def test_parts_are_counted_by_the_kernel_only_where_they_may_not_fit_the_chip():
         assert cut_of(call)[1] == case[5] and call["launches"][1]["kernel"] == merge and call["launches"][1]["ints"] == [128, 1, 1], (case, call)
     for call in launches_of([reader("alora_paged_attention_suffix_split", T, n, 32, 8) for T, n in [(1, 1), (2, 2), (4, 2), (16, 1), (256, 4)]]):
         assert call["launches"][1]["kernel"] == merge and call["launches"][1]["ints"] == [128, 1, 0], call
+
+
+def test_a_workspace_that_holds_the_fewer_parts_is_enough():
+    """What a call of the reader in parts by rows cannot do without follows from its rows and heads alone: not from how
+    long the block tables are, how many, or how large the cache is."""
+    name = "alora_paged_attention_split"
+    for T in (2, 5, 8, 16, 17, 100, 127):
+        fewer, more = min(32, -(-1024 // (T * 8))), min(32, -(-2048 // (T * 8)))
+        enough = T * 32 * fewer * 130 * 4
+        wide = dict(reader(name, T, T, 32, 8))
+        others = [dict(wide, n_seqs=max(1, T - 1)), dict(wide, max_blocks=16), dict(wide, n_slots=4096)]
+        calls = launches_of([wide, dict(wide, give=enough), dict(wide, give=enough - 1), *others, *[dict(o, give=enough) for o in others]])
+        assert calls[0]["status"] == 0 and calls[0]["workspace"] == T * 32 * more * 130 * 4
+        assert calls[0]["launches"][0]["grid"][0] == T * 8 * more
+        for c in (calls[1], *calls[3:]):
+            assert c["status"] == 0 and c["launches"][0]["grid"][0] == T * 8 * fewer, (T, c)
+            assert c["launches"][1]["kernel"] == "paged_attention_merge_kernel" and c["launches"][1]["ints"] == [128, 1, 0], (T, c)
+        assert all(c["workspace"] == enough for c in calls[3:6])
+        if fewer < more:
+            assert calls[2]["status"] == -3 and not calls[2]["launches"]
+    # sized for the largest call of a program, two rows a sequence, then one row each
+    large = launches_of([reader(name, 32, 16, 32, 8)])[0]["workspace"]
+    (call,) = launches_of([dict(reader(name, 16, 16, 32, 8), give=large)])
+    assert call["status"] == 0 and call["launches"][0]["grid"][0] == 16 * 8 * 8
