@@ -111,35 +111,42 @@ __device__ __forceinline__ float dot8(const Raw8<false> &q, const Raw8<false> &k
 // exp2(-inf) = 0).  Scores below it are treated like -inf.
 constexpr float M_FLOOR = -1.0e30f;
 
+// What is known of a call's contexts: nothing, that there are no more rows than sequences (see launch_dg), or that there are several turns
+// of workgroups of them besides, which take the longest first: whole contexts (in runs of `sorted` batch rows), or some in more parts than others.
+enum Contexts { ANY, READ_ONCE, LONGEST_FIRST, IN_PARTS };
+
 // Which row, K/V head and part of the context workgroup b is for when the longest contexts go first; of 256 threads.  Lengths count in
 // steps of an eighth (128 of them from 16 positions to a million), rows of one step in batch order: every workgroup finds the same
 // order, and each row once.  Where no context is longer than SHORT_CONTEXT it is the batch's order.  Without parts the order is that
 // of every `sorted` rows (at most 256).  In parts there are no more rows than that; those of a.splits parts (see parts_of) come first, where there are
-// none the batch's order stays, and the last workgroups find nothing to do (t = -1).  scr: ORDER_SCRATCH ints of LDS.
+// none the batch's order stays, and the last workgroups find nothing to do (t = -1).  scr: ORDER_SCRATCH ints of LDS.  near: this thread's row.
 struct Turn { int t, seq, pos, hk, part; };
+struct Near { int t, seq, n_ctx; };   // a row, its sequence and context (0: none)
 constexpr int ORDER_SCRATCH = 128 + 8 + 2;
 constexpr int SHORT_CONTEXT = 512;
 constexpr int LONG_PART = 512;      // positions per part from which a context is cut into the larger number of parts
-__device__ __forceinline__ int parts_of(const AttnArgs &a, int n_ctx) { return a.short_splits < a.splits && n_ctx < a.splits * LONG_PART ? a.short_splits : a.splits; }
-__device__ __forceinline__ Turn longest_first(const AttnArgs &a, int sorted, int b, int *scr)
+__device__ __forceinline__ int parts_of(const AttnArgs &a, int n_ctx) { return n_ctx < a.splits * LONG_PART ? a.short_splits : a.splits; }
+template <bool PARTS>
+__device__ __forceinline__ Turn longest_first(const AttnArgs &a, int sorted, int b, int *scr, Near &near)
 {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     unsigned long long *const masks = (unsigned long long *)(scr + 128);
-    const int first = a.splits > 1 ? 0 : b / a.Hkv / sorted * sorted, rows = min(sorted, a.T - first);
+    const int first = PARTS ? 0 : b / a.Hkv / sorted * sorted, rows = min(sorted, a.T - first);
     int key = -1, n_ctx = 0, sq = -1, p = -1;
     bool more = false;
     if (tid < rows) {
         sq = a.seq[first + tid], p = a.pos[first + tid];
         if (sq >= 0 && sq < a.n_seqs && p >= 0) n_ctx = (int)min(p + 1ll, (long long)a.max_blocks * a.bs);
         key = 127 - min(max((int)(__float_as_uint((float)n_ctx) >> 20) - ((127 + 4) << 3), 0), 127);
-        more = parts_of(a, n_ctx) > a.short_splits;
-        if (a.short_splits < a.splits) key = (more ? 0 : 64) + (key >> 1);   // (steps of a quarter)
+        more = PARTS && parts_of(a, n_ctx) > a.short_splits;
+        if (PARTS) key = (more ? 0 : 64) + (key >> 1);   // (steps of a quarter)
     }
+    near = {first + tid, sq, n_ctx};
     if (tid < 128) scr[tid] = 0;
     b -= first * a.Hkv;
-    int rank, unit, parts = a.short_splits;
+    int rank, unit, parts = PARTS ? a.short_splits : 1;
     bool ordered = n_ctx > SHORT_CONTEXT;
-    if (a.short_splits < a.splits) {
+    if (PARTS) {
         const int n_more = __syncthreads_count(more), in_more = n_more * a.splits * a.Hkv;
         ordered = n_more > 0;
         if (b < in_more) parts = a.splits;
@@ -150,7 +157,7 @@ __device__ __forceinline__ Turn longest_first(const AttnArgs &a, int sorted, int
         if (parts == a.short_splits) rank += n_more;
         if (rank >= rows) return {-1, -1, -1, 0, 0};
     } else {
-        unit = parts * a.Hkv;
+        unit = a.Hkv;
         rank = b / unit;
         b -= rank * unit;
     }
@@ -176,10 +183,6 @@ __device__ __forceinline__ Turn longest_first(const AttnArgs &a, int sorted, int
     return {scr[0], scr[136], scr[137], hk, part};
 }
 
-// What is known of a call's contexts: nothing, that each is read once per head (see launch_dg), or that there are several turns of
-// workgroups of them besides, which take the longest first (in runs of `sorted` batch rows).
-enum Contexts { ANY, READ_ONCE, LONGEST_FIRST };
-
 template <int D, int G, bool BF16, bool POW2, Contexts CONTEXTS>
 __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(AttnArgs a, int sorted)
 {
@@ -188,15 +191,18 @@ __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(At
     constexpr int PPI = 4 * PPW;       // positions per workgroup and step
     constexpr int U = BF16 ? 4 : 2;    // steps per block: loaded together, one rescale of the running sums
     constexpr int BLK = PPI * U;       // positions per workgroup and block
+    constexpr bool ORDERED = CONTEXTS == LONGEST_FIRST || CONTEXTS == IN_PARTS;
+    constexpr bool MAY_SHARE = CONTEXTS == IN_PARTS || (CONTEXTS == LONGEST_FIRST && G <= 2);   // (see there)
 
     __shared__ float sm[4][G], sl[4][G];
     __shared__ float sacc[4][G][D];
 
     // workgroup -> (row, K/V head, part of the context)
     int t, sq, p, hk, sp;
-    if constexpr (CONTEXTS == LONGEST_FIRST) {
+    Near near = {-1, -1, 0};
+    if constexpr (ORDERED) {
         __shared__ __attribute__((aligned(8))) int order[ORDER_SCRATCH];
-        const Turn turn = longest_first(a, sorted, (int)blockIdx.x, order);
+        const Turn turn = longest_first<CONTEXTS == IN_PARTS>(a, sorted, (int)blockIdx.x, order, near);
         t = __builtin_amdgcn_readfirstlane(turn.t), sq = __builtin_amdgcn_readfirstlane(turn.seq), p = __builtin_amdgcn_readfirstlane(turn.pos);
         hk = turn.hk, sp = turn.part;
         if (t < 0) return;
@@ -217,10 +223,21 @@ __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(At
     int jbeg = 0;
     int parts = a.splits;
     if (a.splits > 1) {
-        if constexpr (CONTEXTS == LONGEST_FIRST) parts = parts_of(a, n_ctx);
+        if constexpr (CONTEXTS == IN_PARTS) parts = parts_of(a, n_ctx);
         const int per = ((n_ctx + parts * BLK - 1) / (parts * BLK)) * BLK;
         jbeg = min(n_ctx, sp * per);
         n_ctx = min(n_ctx, jbeg + per);
+    }
+    // A part that another row of the run reads as well (the same cache block half way through it) takes ordinary loads: requests over one
+    // cached prefix, adapters evaluated on one conversation.  us, non-temporal | ordinary, and in brackets all rows in batch order and fewer parts, 8/8
+    // heads: 12 rows sharing 16K positions 126 | 97 (81), 100 sharing 2K, in parts 91 | 80 (96), 200 in 50 groups sharing 2K 306 | 277 (297); 32/8
+    // heads, in parts: 12 sharing 16K 137 | 128 (126), 12 in pairs 148 | 135 (145), 8 sharing 32K 197 | 174 (190).  What the look costs is under the first loads:
+    // 256 rows of 2 to 2047 positions, 8/8 heads 179.6 | 180.0, 40 in parts at 4 to 5K 123.5 | 123.9.  Batches of whole contexts and more heads take the same time either way.
+    int half_here = -1, half_near = -2;
+    if (MAY_SHARE && n_ctx > jbeg) {
+        const int half = (jbeg + n_ctx) >> 1, at = POW2 ? (half >> a.bs_shift) : (half / a.bs);
+        half_here = bt[at];
+        if (near.t != t && near.n_ctx > half) half_near = a.bt[(size_t)near.seq * a.max_blocks + at];
     }
     const int Nkv = a.Hkv * D;
     const int col = hk * D + 8 * c;
@@ -253,8 +270,9 @@ __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(At
     // K and V chunks of the block starting at j0, through table entries looked up earlier; a position past
     // the context or with a table entry outside the cache is left out (zero chunks, validity bit clear).
     // Returns the validity of this lane's positions, one bit per step.
-    auto fetch = [&](int j0, const int (&blk)[U], Raw8<BF16> (&kr)[U], Raw8<BF16> (&vr)[U]) {
+    auto fetch_as = [&](auto streamed, int j0, const int (&blk)[U], Raw8<BF16> (&kr)[U], Raw8<BF16> (&vr)[U]) {
         unsigned ok = 0;
+        if (MAY_SHARE && decltype(streamed)::value) asm volatile("");   // (keeps the compiler from making one of the two kinds of load)
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int j = j0 + u * PPI + jl;
@@ -265,11 +283,18 @@ __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(At
             if (have) {
                 const int off = POW2 ? (j & (a.bs - 1)) : (j % a.bs);
                 const size_t at = ((size_t)blk[u] * a.bs + off) * Nkv + col;
-                kr[u].template load<CONTEXTS != ANY>(a.kc, at);
-                vr[u].template load<CONTEXTS != ANY>(a.vc, at);
+                kr[u].template load<decltype(streamed)::value>(a.kc, at);
+                vr[u].template load<decltype(streamed)::value>(a.vc, at);
             }
         }
+        if (MAY_SHARE && decltype(streamed)::value) asm volatile("");
         return ok;
+    };
+    bool shared = false;
+    auto fetch = [&](int j0, const int (&blk)[U], Raw8<BF16> (&kr)[U], Raw8<BF16> (&vr)[U]) {
+        if constexpr (MAY_SHARE)
+            if (shared) return fetch_as(std::false_type{}, j0, blk, kr, vr);
+        return fetch_as(std::bool_constant<CONTEXTS != ANY>{}, j0, blk, kr, vr);
     };
     // scores, running softmax (rescaled once per block) and weighted sum of V for one block
     auto consume = [&](const Raw8<BF16> (&kr)[U], const Raw8<BF16> (&vr)[U], unsigned ok) {
@@ -339,6 +364,10 @@ __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(At
     lookup(jbeg, blkA);
     unsigned okA = fetch(jbeg, blkA, krA, vrA), okB;
     lookup(jbeg + BLK, blkB);
+    if constexpr (MAY_SHARE) {
+        asm volatile("" : "+v"(half_here), "+v"(half_near));   // (looked at here, not where they are requested)
+        shared = __builtin_amdgcn_readfirstlane(__syncthreads_or(half_here == half_near));
+    }
     for (int j0 = jbeg; j0 < n_ctx; j0 += 2 * BLK) {
         okB = fetch(j0 + BLK, blkB, krB, vrB);
         lookup(j0 + 2 * BLK, blkA);
@@ -394,7 +423,7 @@ __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(At
             float *const p0 = a.part + ((size_t)t * a.Hq + (size_t)hk * G + g) * a.splits * (D + 2), *pp = p0 + (size_t)sp * (D + 2);
             if (dd == 0) { pp[0] = M; pp[1] = L; }
             // fewer parts than there is room for: the last place tells how many (a sum of weights is never negative)
-            if (CONTEXTS == LONGEST_FIRST && dd == 0 && sp == 0 && parts < a.splits) *(f32x2 *)(p0 + (size_t)(a.splits - 1) * (D + 2)) = (f32x2){(float)parts, -1.f};
+            if (CONTEXTS == IN_PARTS && dd == 0 && sp == 0 && parts < a.splits) *(f32x2 *)(p0 + (size_t)(a.splits - 1) * (D + 2)) = (f32x2){(float)parts, -1.f};
             pp[2 + dd] = o;
             continue;
         }
@@ -488,8 +517,10 @@ __global__ __launch_bounds__(256) void paged_attention_merge_kernel(const float 
     else *(f32x2 *)((float *)out + rh * D + 2 * dd) = (f32x2){y0, y1};
 }
 
-// Non-temporal loads where a context is read once per head (no more rows than sequences) and the memory-side cache would not
-// keep this layer's K and V until they are read again.  us, ordinary | non-temporal loads, 32/8 heads, three layers' caches in turn:
+// Non-temporal loads where it may be assumed that a context is read once per head (no more rows than sequences; rows that share cache
+// blocks all the same are found by the kernels that fill the chip) and the memory-side cache would not
+// keep this layer's K and V until they are read again (its pool is taken for what is read: with the caches of twelve layers in turn, 39 MB read from each of 1 GB,
+// 18.1 | 17.3; of three, which are still there the next time, 16.3 | 17.1).  us, ordinary | non-temporal loads, 32/8 heads, three layers' caches in turn:
 // 64 rows of equal contexts, 500 MB 100.8 | 91.4, 200 MB 45.2 | 40.9, 100 MB 25.9 | 24.6, 64 MB 16.9 | 17.4; 256 rows of 10 to
 // 100 positions, 66 MB 25.5 | 26.5; one cache over and over, 200 MB 38.5 | 40.4.
 static bool contexts_read_once(const alora_attn_dims *d)
@@ -513,7 +544,8 @@ static void launch_dg(const AttnArgs &a, bool bf16, hipStream_t st)
         launch_kernel((paged_attention_kernel<D, G, decltype(is_bf16)::value, decltype(is_pow2)::value, decltype(contexts)::value>), grid, dim3(256), 0, st, a, sorted);
     };
     auto choose = [&](auto is_bf16, auto is_pow2) {
-        if (longest) launch(is_bf16, is_pow2, std::integral_constant<Contexts, LONGEST_FIRST>{});
+        if (longest && a.splits > 1) launch(is_bf16, is_pow2, std::integral_constant<Contexts, IN_PARTS>{});
+        else if (longest) launch(is_bf16, is_pow2, std::integral_constant<Contexts, LONGEST_FIRST>{});
         else if (a.once) launch(is_bf16, is_pow2, std::integral_constant<Contexts, READ_ONCE>{});
         else launch(is_bf16, is_pow2, std::integral_constant<Contexts, ANY>{});
     };

@@ -652,3 +652,96 @@ def test_row_blocks_of_streamed_contexts(group, n, rows, parts):
     pick = np.arange(0, n * rows, 1 + n * rows // 12)
     want = oatt.paged_attention(to_f64(q), to_f64(kc), to_f64(vc), bt, seq, pos, 16, 8 * group, 8, 128, rows=pick)
     assert maxnorm_rel(to_f64(outs[0])[pick], want) <= TOL["bf16"]
+
+
+def _shared_contexts(dtype, hq, hkv, d, bs, lens, groups, prefix, seed):
+    """One row per sequence; rows of a group (-1: none) share the cache blocks of their first `prefix` positions.  Returns the same contexts twice: as they
+    are, and copied to cache blocks of their own."""
+    rng = np.random.default_rng(seed)
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    nb, pb = -(-np.asarray(lens) // bs), prefix // bs
+    table = np.full((len(lens), int(nb.max())), -1, np.int32)
+    n_shared = pb * (max(groups) + 1)
+    n_blocks = int(n_shared + sum(n - (pb if k >= 0 else 0) for n, k in zip(nb, groups)))
+    perm, at = rng.permutation(n_blocks).astype(np.int32), n_shared
+    for s, (n, k) in enumerate(zip(nb, groups)):
+        own = 0
+        if k >= 0:
+            table[s, :pb] = perm[k * pb: (k + 1) * pb]
+            own = pb
+        table[s, own: n] = perm[at: at + n - own]
+        at += n - own
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    pool = max(n_blocks, (104 << 20) // (2 * hkv * d * (2 if dtype == "bf16" else 4)) // bs)      # a cache that outgrows the memory-side one
+    kc, vc = (torch.randn(pool * bs, hkv * d, device="cuda", generator=g).to(t) for _ in range(2))
+    q = torch.randn(len(lens), hq * d, device="cuda", generator=g).to(t)
+    ids = torch.from_numpy(np.concatenate([table[s, :n] for s, n in enumerate(nb)])).long().cuda()
+    own_table = np.full_like(table, -1)
+    first = np.concatenate([[0], np.cumsum(nb)])
+    for s, n in enumerate(nb):
+        own_table[s, :n] = first[s] + np.arange(n)
+    spare = torch.zeros(max(0, pool - len(ids)) * bs, hkv * d, device="cuda", dtype=t)
+    copies = [torch.cat([c.view(pool, bs, -1)[ids].reshape(-1, hkv * d), spare]) for c in (kc, vc)]
+    seq, pos = np.arange(len(lens), dtype=np.int32), (np.asarray(lens) - 1).astype(np.int32)
+    return q, (kc, vc, table), (*copies, own_table), seq, pos
+
+
+def _read(q, kc, vc, table, seq, pos, hq, hkv, d, bs, parts):
+    """A call of the reader by rows, bound to its buffers: (the call, its output)."""
+    dt, ds, dp = (torch.from_numpy(a).to("cuda") for a in (table, seq, pos))
+    out = torch.full_like(q, float("nan"))
+    dims = ab.make_attn_dims(q, kc, dt, hq, hkv, d, bs)
+    if not parts:
+        return lambda: ab.alora_paged_attention(q, kc, vc, dt, ds, dp, out, dims), out
+    ws = torch.full((max(ab.alora_paged_attention_workspace_bytes(dims), 16),), 0xff, dtype=torch.uint8, device="cuda")
+    return lambda: ab.alora_paged_attention_split(q, kc, vc, dt, ds, dp, out, dims, ws), out
+
+
+# Rows whose contexts share cache blocks (ordinary loads for what is shared, streamed for what is not): the same bits as over copies of their own, and the
+# oracle's values.  Groups of all rows, of a few, of some rows only, whole contexts and parts of which some are shared, just half and less.
+@pytest.mark.parametrize("dtype,d,group,bs", [("bf16", 128, 1, 16), ("bf16", 128, 2, 24), ("bf16", 128, 4, 16), ("bf16", 64, 8, 16), ("f32", 64, 1, 16), ("f32", 128, 2, 20)])
+@pytest.mark.parametrize("n,prefix,parts,of", [(200, 480, False, 200), (160, 480, False, 4), (130, 720, False, 2), (12, 12000, True, 12), (12, 7200, True, 3)])
+def test_rows_that_share_contexts(dtype, d, group, bs, n, prefix, parts, of):
+    rng = np.random.default_rng(1200 + n + group)
+    hkv = 8 if parts else 4
+    lens = prefix + rng.integers(1, 6000 if parts else 300, n)
+    groups = [i // of if i % 7 else -1 for i in range(n)]
+    print(f"[case] shared {dtype} d={d} g={group} bs={bs} n={n} prefix={prefix} parts={parts} of={of}", flush=True)
+    q, shared, own, seq, pos = _shared_contexts(dtype, group * hkv, hkv, d, bs, lens, groups, prefix // bs * bs, 1200 + n)
+    outs = []
+    for kc, vc, table in (shared, own):
+        run, out = _read(q, kc, vc, table, seq, pos, group * hkv, hkv, d, bs, parts)
+        run()
+        torch.cuda.synchronize()
+        outs.append(out)
+    assert np.array_equal(raw_bits(outs[0]), raw_bits(outs[1]))
+    pick = np.arange(0, n, 1 + n // 6)
+    want = oatt.paged_attention(to_f64(q), to_f64(shared[0]), to_f64(shared[1]), shared[2], seq, pos, bs, group * hkv, hkv, d, rows=pick)
+    assert maxnorm_rel(to_f64(outs[0])[pick], want) <= TOL[dtype]
+
+
+def _times(calls, rounds=7):
+    """The least time of each call, us, measured in turn."""
+    best = [float("inf")] * len(calls)
+    a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    for _ in range(rounds):
+        for i, call in enumerate(calls):
+            call()
+            a.record()
+            for _ in range(3):
+                call()
+            b.record()
+            b.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b) * 1000 / 3)
+    return best
+
+
+def test_a_shared_context_is_not_streamed():
+    """12 rows over one prefix of 16K positions, three layers' caches in turn: 97 us a layer, over copies of their own 139.  (Streamed as if each were read
+    once: 126.)"""
+    lens = 16384 + np.random.default_rng(1230).integers(100, 2000, 12)
+    layers = [_shared_contexts("bf16", 8, 8, 128, 16, lens, [0] * 12, 16384, 1230 + i) for i in range(3)]
+    calls = [[_read(q, *cache[i], seq, pos, 8, 8, 128, 16, True)[0] for q, *cache, seq, pos in layers] for i in (0, 1)]
+    shared, own = _times([lambda c=c: [f() for f in c] for c in calls])
+    print(f"[time] shared {shared / 3:.1f} us, copies {own / 3:.1f} us", flush=True)
+    assert shared <= 0.82 * own
