@@ -117,17 +117,18 @@ enum Contexts { ANY, READ_ONCE, LONGEST_FIRST, IN_PARTS };
 
 // Which row, K/V head and part of the context workgroup b is for when the longest contexts go first; of 256 threads.  Lengths count in
 // steps of an eighth (128 of them from 16 positions to a million), rows of one step in batch order: every workgroup finds the same
-// order, and each row once.  Where no context is longer than SHORT_CONTEXT it is the batch's order.  Without parts the order is that
+// order, and each row once.  Where no context is longer than SHORT_CONTEXT, or rows read together (see there), it is the batch's order.  Without parts the order is that
 // of every `sorted` rows (at most 256).  In parts there are no more rows than that; those of a.splits parts (see parts_of) come first, where there are
 // none the batch's order stays, and the last workgroups find nothing to do (t = -1).  scr: ORDER_SCRATCH ints of LDS.  near: this thread's row.
+// GROUPS: look for rows that read together.
 struct Turn { int t, seq, pos, hk, part; };
 struct Near { int t, seq, n_ctx; };   // a row, its sequence and context (0: none)
 constexpr int ORDER_SCRATCH = 128 + 8 + 2;
 constexpr int SHORT_CONTEXT = 512;
 constexpr int LONG_PART = 512;      // positions per part from which a context is cut into the larger number of parts
 __device__ __forceinline__ int parts_of(const AttnArgs &a, int n_ctx) { return n_ctx < a.splits * LONG_PART ? a.short_splits : a.splits; }
-template <bool PARTS>
-__device__ __forceinline__ Turn longest_first(const AttnArgs &a, int sorted, int b, int *scr, Near &near)
+template <bool PARTS, bool GROUPS>
+__device__ __forceinline__ Turn longest_first(const AttnArgs &a, int sorted, int b, int *scr, Near &near, bool &together)
 {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     unsigned long long *const masks = (unsigned long long *)(scr + 128);
@@ -163,7 +164,26 @@ __device__ __forceinline__ Turn longest_first(const AttnArgs &a, int sorted, int
     }
     const int hk = b / parts, part = b - hk * parts;
     if (tid == rank) scr[136] = sq, scr[137] = p;
-    if (!__syncthreads_or(ordered)) return {first + rank, scr[136], scr[137], hk, part};
+    // Groups of rows that read one context: a row goes with the one before it in the batch if both read the same cache block half way through
+    // the shorter of the two.  Where three quarters of the rows are in groups, of eight on average or fewer, the batch's order stays, in which a group
+    // reads its context together, with ordinary loads.  us, longest first | batch order: 200 rows that share 1024 of 1075 to 1625 positions in pairs, 8/8
+    // heads 184 | 152, 16/8 185 | 155, 32/8 195 | 170 (64/8 265 | 272: not looked for), in fours 8/8 175 | 127, 32/8 186 | 160, in eights 158 | 114 and 171 | 157;
+    // half of the rows in pairs 243 | 257 and 260 | 279; a chunk of 144 rows beside 56 others 308 | 333; one prefix for all 196 | 207.
+    bool same = false;
+    if (GROUPS && tid > 0 && tid < rows) {
+        const int sq1 = a.seq[first + tid - 1], half = min(n_ctx, a.pos[first + tid - 1] + 1) >> 1;
+        if (half > SHORT_CONTEXT / 2 && sq1 >= 0 && sq1 < a.n_seqs) {
+            const int at = a.bs_shift >= 0 ? half >> a.bs_shift : half / a.bs;
+            same = a.bt[(size_t)sq * a.max_blocks + at] == a.bt[(size_t)sq1 * a.max_blocks + at];
+        }
+    }
+    const unsigned long long with_last = __builtin_amdgcn_ballot_w64(same);
+    const int begin = (int)__builtin_popcountll(with_last & ~(with_last << 1)), in_groups = begin + (int)__builtin_popcountll(with_last);
+    if (lane == 0) scr[128 + w] = (__builtin_amdgcn_ballot_w64(ordered) ? 1 << 24 : 0) + (begin << 12) + in_groups;   // (64 and 128 at most)
+    __syncthreads();
+    const int all = scr[128] + scr[129] + scr[130] + scr[131];
+    together = GROUPS && 8 * ((all >> 12) & 0xfff) >= rows && 4 * (all & 0xfff) >= 3 * rows;
+    if (all < 1 << 24 || together) return {first + rank, scr[136], scr[137], hk, part};
     if (key >= 0) atomicAdd(&scr[key], 1);   // counts only: their values do not depend on the order
     __syncthreads();
     const int h0 = scr[2 * lane], h1 = scr[2 * lane + 1], upto = sum_upto64(h0 + h1);
@@ -192,7 +212,8 @@ __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(At
     constexpr int U = BF16 ? 4 : 2;    // steps per block: loaded together, one rescale of the running sums
     constexpr int BLK = PPI * U;       // positions per workgroup and block
     constexpr bool ORDERED = CONTEXTS == LONGEST_FIRST || CONTEXTS == IN_PARTS;
-    constexpr bool MAY_SHARE = CONTEXTS == IN_PARTS || (CONTEXTS == LONGEST_FIRST && G <= 2);   // (see there)
+    constexpr bool GROUPS = CONTEXTS == LONGEST_FIRST && G <= 4, LOOK = CONTEXTS == IN_PARTS || (CONTEXTS == LONGEST_FIRST && G <= 2);   // (see there)
+    constexpr bool MAY_SHARE = GROUPS || LOOK;
 
     __shared__ float sm[4][G], sl[4][G];
     __shared__ float sacc[4][G][D];
@@ -200,9 +221,11 @@ __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(At
     // workgroup -> (row, K/V head, part of the context)
     int t, sq, p, hk, sp;
     Near near = {-1, -1, 0};
+    bool shared = false;      // contexts that rows of the call share
     if constexpr (ORDERED) {
         __shared__ __attribute__((aligned(8))) int order[ORDER_SCRATCH];
-        const Turn turn = longest_first<CONTEXTS == IN_PARTS>(a, sorted, (int)blockIdx.x, order, near);
+        const Turn turn = longest_first<CONTEXTS == IN_PARTS, GROUPS>(a, sorted, (int)blockIdx.x, order, near, shared);
+        shared = __builtin_amdgcn_readfirstlane(shared);
         t = __builtin_amdgcn_readfirstlane(turn.t), sq = __builtin_amdgcn_readfirstlane(turn.seq), p = __builtin_amdgcn_readfirstlane(turn.pos);
         hk = turn.hk, sp = turn.part;
         if (t < 0) return;
@@ -234,7 +257,7 @@ __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(At
     // heads, in parts: 12 sharing 16K 137 | 128 (126), 12 in pairs 148 | 135 (145), 8 sharing 32K 197 | 174 (190).  What the look costs is under the first loads:
     // 256 rows of 2 to 2047 positions, 8/8 heads 179.6 | 180.0, 40 in parts at 4 to 5K 123.5 | 123.9.  Batches of whole contexts and more heads take the same time either way.
     int half_here = -1, half_near = -2;
-    if (MAY_SHARE && n_ctx > jbeg) {
+    if (LOOK && n_ctx > jbeg) {
         const int half = (jbeg + n_ctx) >> 1, at = POW2 ? (half >> a.bs_shift) : (half / a.bs);
         half_here = bt[at];
         if (near.t != t && near.n_ctx > half) half_near = a.bt[(size_t)near.seq * a.max_blocks + at];
@@ -290,7 +313,6 @@ __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(At
         if (MAY_SHARE && decltype(streamed)::value) asm volatile("");
         return ok;
     };
-    bool shared = false;
     auto fetch = [&](int j0, const int (&blk)[U], Raw8<BF16> (&kr)[U], Raw8<BF16> (&vr)[U]) {
         if constexpr (MAY_SHARE)
             if (shared) return fetch_as(std::false_type{}, j0, blk, kr, vr);
@@ -364,7 +386,7 @@ __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(At
     lookup(jbeg, blkA);
     unsigned okA = fetch(jbeg, blkA, krA, vrA), okB;
     lookup(jbeg + BLK, blkB);
-    if constexpr (MAY_SHARE) {
+    if constexpr (LOOK) {
         asm volatile("" : "+v"(half_here), "+v"(half_near));   // (looked at here, not where they are requested)
         shared = __builtin_amdgcn_readfirstlane(__syncthreads_or(half_here == half_near));
     }

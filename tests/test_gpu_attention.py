@@ -745,3 +745,13 @@ def test_a_shared_context_is_not_streamed():
     shared, own = _times([lambda c=c: [f() for f in c] for c in calls])
     print(f"[time] shared {shared / 3:.1f} us, copies {own / 3:.1f} us", flush=True)
     assert shared <= 0.82 * own
+
+
+def test_rows_that_share_a_context_in_pairs_read_it_together():
+    """200 rows, each two of the batch over one prefix of 1024 positions: 152 us, over copies of their own 184.  (The longest first, which takes pairs apart: 184.)"""
+    lens = 1024 + np.random.default_rng(1240).integers(50, 600, 200)
+    layers = [_shared_contexts("bf16", 8, 8, 128, 16, lens, [i // 2 for i in range(200)], 1024, 1240 + i) for i in range(3)]
+    calls = [[_read(q, *cache[i], seq, pos, 8, 8, 128, 16, False)[0] for q, *cache, seq, pos in layers] for i in (0, 1)]
+    shared, own = _times([lambda c=c: [f() for f in c] for c in calls])
+    print(f"[time] pairs {shared / 3:.1f} us, copies {own / 3:.1f} us", flush=True)
+    assert shared <= 0.9 * own
