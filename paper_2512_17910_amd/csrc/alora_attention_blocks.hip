@@ -70,7 +70,7 @@ __device__ __forceinline__ void load_lds16(uint32_t lds_addr, const void *p)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr), "v"(p) : "memory");
 }
-// the same with a scalar base address and a 32-bit byte offset per lane; ONCE: nobody else will read these bytes
+// the same with a scalar base address and a 32-bit byte offset per lane; ONCE: no other workgroup will read these bytes
 template <bool ONCE>
 __device__ __forceinline__ void load_lds16(uint32_t lds_addr, const void *base, uint32_t voffset)
 {
@@ -111,7 +111,7 @@ __device__ const uint32_t ab_zero_chunk[4] = {0u, 0u, 0u, 0u};
 // whether the kernel settles the number of parts (a kernel of its own: what the counting adds costs 2 x 2 rows at 2000 positions 1.3 of 13 us)
 struct AsPlanned { static constexpr bool count = false, once = false; };
 struct Counted { static constexpr bool count = true, once = false; };
-// and contexts of which most are read once per head (see launch_attention_blocks)
+// and contexts of which most are read once per head (see launch_attention_blocks); which, the kernel finds out
 struct AsPlannedOnce { static constexpr bool count = false, once = true; };
 struct CountedOnce { static constexpr bool count = true, once = true; };
 
@@ -302,6 +302,12 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
     if (turn != which) __syncthreads();      // everyone is done with the tiles of the block before
     const int t0 = r_begin + block.at, nrows = block.rows;
     const int sq = __builtin_amdgcn_readfirstlane(row_seq[block.at]), p0 = __builtin_amdgcn_readfirstlane(row_pos[block.at]);
+    int near_seq[2] = {-1, -1}, near_pos[2] = {-1, -1};      // rows before and behind the block
+    if constexpr (PARTS::once) {
+        const int before = max(block.at - 1, 0), behind = min(block.at + nrows, LOOK - 1);
+        near_seq[0] = block.at > 0 ? row_seq[before] : -1, near_pos[0] = row_pos[before];
+        near_seq[1] = block.at + nrows < LOOK ? row_seq[behind] : -1, near_pos[1] = row_pos[behind];
+    }
     const bool row_ok = sq >= 0 && sq < a.n_seqs && p0 >= 0;
     int n_ctx = 0;
     if (row_ok) n_ctx = (int)((long long)p0 + nrows < cap ? (long long)p0 + nrows : cap);
@@ -350,12 +356,29 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
         for (int i = tid; win_first + i <= last; i += 64 * NW) window[i] = bt[win_first + i];
         __syncthreads();
     };
+    // Which cache block is half way through this part, and, where the batch rows before and behind this row block reach as far, in their contexts: the
+    // same one if they are of the same run, or of a sequence over the same cached prefix.  Then this part is not read once, and its copies are ordinary
+    // ones.  Known before the loop, which is there twice (a branch at every copy costs a call 3 to 6 %; a look at all rows of the range 1 us a block).
+    // us, non-temporal | by what is found, and in brackets ordinary, 32/8 heads: a chunk of 2048 rows at 16K positions under a block table of 256 rows
+    // 628 | 603 (607), of 1024 beside 255 single rows 354 | 350 (353), 16 x 8 rows in parts, each four sequences over one prefix of 8K, 100.0 | 96.4 (94.5), 20 x 4 at 3 to
+    // 6K, some in two row blocks, 91.4 | 84.8 (91.7); 64 single rows over one prefix of 4K in parts 138.8 | 142.6 (139.6); nothing shared: 64 at 4096 169.4 | 169.6
+    // (186.9), in parts 100 at 500 to 4000 179.2 | 180.4 (200.8).
+    int half_here = -1, half_near[2] = {-2, -2};
+    auto look_around = [&]() {
+        const int half = min(16 * (c_lo + c_hi), n_ctx - 1), at = entry_of(half);
+        half_here = bt[at];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int s2 = __builtin_amdgcn_readfirstlane(near_seq[i]);
+            if (s2 >= 0 && s2 < a.n_seqs && __builtin_amdgcn_readfirstlane(near_pos[i]) >= half) half_near[i] = a.bt[(size_t)s2 * a.max_blocks + at];
+        }
+    };
     // table entry of this wavefront's four positions pu .. of a block (the same value in every lane; made a scalar
     // where it is used, a step later, so that nothing waits for the read here)
     auto lookup = [&](int pu) { return pu < n_ctx ? window[entry_of(pu) - win_first] : -1; };
     // (the scalar unit of a CU serves all its wavefronts: what a wavefront computes per step besides the
     // matrix and vector work is kept to a few instructions)
-    auto issue4 = [&](int slot_pair, int c, int grp, int entry) {
+    auto issue4 = [&](auto once, int slot_pair, int c, int grp, int entry) {
         const int pu = 32 * c + 4 * grp, blk = __builtin_amdgcn_readfirstlane(entry);
         const uint32_t k_to = tiles_at + (uint32_t)slot_pair * (2 * TILE) + ((uint32_t)grp << 10), v_to = k_to + TILE;
         static_assert(4 * PITCH == 1 << 10, "tile geometry");
@@ -363,8 +386,8 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
         if ((unsigned)blk < n_blocks_u && pu + 4 <= n_ctx) {   // the usual case: scalar base, the lane's constant offset
             const unsigned slot = (POW2 ? ((unsigned)blk << a.bs_shift) : (unsigned)blk * (unsigned)a.bs) + (unsigned)(POW2 ? (pu & (a.bs - 1)) : (pu % a.bs));
             const unsigned long long at = (unsigned long long)slot * row_bytes + head_bytes;   // first of the four cache rows
-            load_lds16<PARTS::once>(k_to, (const char *)a.kc + at, k_off);
-            load_lds16<PARTS::once>(v_to, (const char *)a.vc + at, v_off);
+            load_lds16<decltype(once)::value>(k_to, (const char *)a.kc + at, k_off);
+            load_lds16<decltype(once)::value>(v_to, (const char *)a.vc + at, v_off);
         } else {           // rows that are not part of the context read 16 zero bytes
             const bool blk_ok = (unsigned)blk < n_blocks_u;
             const int n_ok = blk_ok ? max(0, min(4, n_ctx - pu)) : 0;
@@ -379,9 +402,9 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
         }
         ok_bytes[slot_pair][grp] = (unsigned char)okb;      // (every lane writes the same byte)
     };
-    auto issue = [&](int slot_pair, int c, const int (&entry)[GPW]) {
+    auto issue = [&](auto once, int slot_pair, int c, const int (&entry)[GPW]) {
 #pragma unroll
-        for (int h = 0; h < GPW; ++h) issue4(slot_pair, c, wu + NW * h, entry[h]);
+        for (int h = 0; h < GPW; ++h) issue4(once, slot_pair, c, wu + NW * h, entry[h]);
     };
     // ---- scores^T = K . Q^T -------------------------------------------------------------------------
     auto scores = [&](int slot_pair) {
@@ -469,7 +492,15 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
     // next two blocks, whose table entries were looked up a step earlier.  Blocks past the context are copied
     // too (all zeros, from one 16-byte constant), which keeps the count of copies in flight the same in every step.
     {
-        if (n_chunks > c_lo) refill(c_lo);
+        bool once = PARTS::once;
+        if (n_chunks > c_lo) {
+            if (PARTS::once) look_around();
+            refill(c_lo);
+            if (PARTS::once) {
+                asm volatile("" : "+v"(half_here), "+v"(half_near[0]), "+v"(half_near[1]));   // (looked at here, not where they are requested)
+                once = __builtin_amdgcn_readfirstlane(half_here != half_near[0] && half_here != half_near[1]);
+            }
+        }
         // (a use of the query registers ahead of the loop: the compiler places its wait for these loads here, behind that for the
         // table entries, and not in front of the first MFMA of every step, where it would also wait for the copies in flight)
 #pragma unroll
@@ -479,18 +510,20 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
             for (int h = 0; h < GPW; ++h) e[h] = lookup(32 * cb + 4 * (wu + NW * h));
         };
         int b0[GPW], b1[GPW];
-#pragma unroll
-        for (int kk = 0; kk < NB - 2; ++kk) {
-            entries(c_lo + kk, b0);
-            issue(kk, c_lo + kk, b0);
-        }
-        entries(c_lo + NB - 2, b0);
-        entries(c_lo + NB - 1, b1);
         int cur = 0, nxt = NB - 2;           // tile pairs of block c and of block c + NB - 2
-        auto step = [&](int c) {
+        auto start = [&](auto once) {
+#pragma unroll
+            for (int kk = 0; kk < NB - 2; ++kk) {
+                entries(c_lo + kk, b0);
+                issue(once, kk, c_lo + kk, b0);
+            }
+            entries(c_lo + NB - 2, b0);
+            entries(c_lo + NB - 1, b1);
+        };
+        auto step = [&](auto once, int c) {
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * GPW * (NB - 4)) : "memory");
-            issue(nxt, c + NB - 2, b0);
-            issue(nxt + 1, c + NB - 1, b1);
+            issue(once, nxt, c + NB - 2, b0);
+            issue(once, nxt + 1, c + NB - 1, b1);
             const int cn = c + NB;
             if (cn == win_block + WIN && 32 * cn < n_ctx) refill(cn);
             entries(cn, b0);
@@ -500,20 +533,27 @@ __global__ __launch_bounds__(64 * NW, 2) void paged_attention_blocks_kernel(Attn
         // (two loops: the accumulators live in the first only)
         const int n_chunks_w = lim_w >= 0 ? min((lim_w >> 5) + 1, n_chunks) : 0;
         int c = c_lo;
-        // (the loop on a line of the instruction cache: 8 single rows at 16K positions 398 us without, 393 with; 4 x 1024 rows at
+        // (the loop on a line of the instruction cache: 8 single rows at 16K positions 398 us without, 393 with, twice in a kernel 336 and 329; 4 x 1024 rows at
         // 8192, 594 and 581)
-        asm volatile(".p2align 6");
-        for (; c < n_chunks_w; c += 2) {
-            step(c);
-            consume(c, cur, scores(cur));
-            if (c + 1 < n_chunks_w) consume(c + 1, cur + 1, scores(cur + 1));
-            advance();
+#define AB_CONTEXT(ONCE)                                                                                                                           \
+        start(ONCE{});                                                                                                                             \
+        if (ONCE::value) asm volatile(".p2align 6" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])); /* (cleared ahead of the line) */    \
+        else asm volatile(".p2align 6");                                                                                                           \
+        for (; c < n_chunks_w; c += 2) {                                                                                                           \
+            step(ONCE{}, c);                                                                                                                       \
+            consume(c, cur, scores(cur));                                                                                                          \
+            if (c + 1 < n_chunks_w) consume(c + 1, cur + 1, scores(cur + 1));                                                                      \
+            advance();                                                                                                                             \
+        }                                                                                                                                          \
+        asm volatile(".p2align 6");                                                                                                                \
+        for (; c < n_chunks; c += 2) {                                                                                                             \
+            step(ONCE{}, c);                                                                                                                       \
+            advance();                                                                                                                             \
         }
-        asm volatile(".p2align 6");
-        for (; c < n_chunks; c += 2) {
-            step(c);
-            advance();
-        }
+        // (a macro: as a function object it changes the registers of the kernels that have one loop only, and costs them 1 to 2 %)
+        if (PARTS::once && once) { AB_CONTEXT(std::bool_constant<PARTS::once>) }
+        else { AB_CONTEXT(std::false_type) }
+#undef AB_CONTEXT
         // nothing may be on its way into LDS when the workgroup gives it back
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
@@ -643,8 +683,9 @@ int launch_attention_blocks(const AttnArgs &a, int G, const BlockPlan &p, hipStr
     const dim3 grid((unsigned)ranges * (unsigned)p.wgs * (unsigned)a.Hkv * (unsigned)a.splits), block(64 * p.waves);
     const bool pow2 = a.bs_shift >= 0;
 #define AB_LAUNCH_AS(GG, NW, POW2, PARTS) launch_kernel((paged_attention_blocks_kernel<GG, NW, POW2, PARTS>), grid, block, 0, stream, a, p.range, p.wgs)
-    // Non-temporal copies where a sequence brings a quarter of a row block on average (then few runs lie in two blocks, which would both read the
-    // context) and the memory-side cache would not keep K and V.  us, ordinary | non-temporal, 32/8 heads: 64 single rows at 4096
+    // A kernel that streams what is read once where a sequence brings a quarter of a row block on average (then few runs lie in two blocks, which would both read the
+    // context; the rows of the block table are taken for the call's sequences, of which there may be fewer) and the memory-side cache would not keep K and V.
+    // us, ordinary | non-temporal, 32/8 heads: 64 single rows at 4096
     // positions 187 | 169, in parts 100 at 500 to 4000 201 | 179, 6 at 10K to 30K 110 | 100, 40 x 6 rows at 2K to 5K 148 | 144; 4 x 11 at
     // 16K to 20K 75 | 74, 4 x 24 98 | 103, 40 x 20 at 2K to 5K 188 | 197, 8/8 heads 6 x 40 at 10K to 30K 143 | 153.
     const bool once = pow2 && (long long)a.T * G <= 32ll * a.n_seqs && outgrows_cache(a.n_slots, a.Hkv, 128, true);

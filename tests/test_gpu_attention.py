@@ -755,3 +755,38 @@ def test_rows_that_share_a_context_in_pairs_read_it_together():
     shared, own = _times([lambda c=c: [f() for f in c] for c in calls])
     print(f"[time] pairs {shared / 3:.1f} us, copies {own / 3:.1f} us", flush=True)
     assert shared <= 0.9 * own
+
+
+# Row blocks of which some contexts are read once (streamed) and others not: runs longer than a block beside single rows under a block table with room for
+# more, neighbours over one prefix, parts half of which are shared.  The same bits as over copies of their own, and the oracle's values.
+@pytest.mark.parametrize("group", [1, 2, 4, 8])
+@pytest.mark.parametrize("rows,groups,table_rows,parts", [([300] + [1] * 40, [-1] * 41, 400, False), ([5] * 30, [0] * 30, 300, False), ([1, 7] * 20, [i // 4 for i in range(40)], 300, False),
+                                                          ([130] + [1] * 20, [-1] * 21, 300, True), ([3] * 16, [0] * 16, 200, True), ([8, 1] * 8, [i // 2 if i % 5 else -1 for i in range(16)], 100, True)])
+def test_row_blocks_that_share_contexts(group, rows, groups, table_rows, parts):
+    prefix = 1600
+    lens = prefix + np.random.default_rng(1250 + group).integers(320, 1200, len(rows))
+    q, shared, own, _, _ = _shared_contexts("bf16", group * 8, 8, 128, 16, lens, groups, prefix, 1250 + group)
+    seq = np.repeat(np.arange(len(rows), dtype=np.int32), rows)
+    pos = np.concatenate([np.arange(l - r, l, dtype=np.int32) for l, r in zip(lens, rows)])
+    g = torch.Generator(device="cuda").manual_seed(1260)
+    q = torch.randn(len(seq), group * 8 * 128, device="cuda", generator=g).bfloat16()
+    dseq, dpos = (torch.from_numpy(a).to("cuda") for a in (seq, pos))
+    print(f"[case] row blocks sharing group={group} {len(rows)} runs parts={parts}", flush=True)
+    outs = []
+    for kc, vc, table in (shared, own):
+        bt = np.full((table_rows, table.shape[1]), -1, np.int32)
+        bt[: len(table)] = table
+        dbt, out = torch.from_numpy(bt).to("cuda"), torch.full_like(q, float("nan"))
+        dims = ab.make_attn_dims(q, kc, dbt, group * 8, 8, 128, 16)
+        assert len(seq) * group <= 32 * table_rows       # (the kernel that streams)
+        if parts:
+            ws = torch.full((ab.alora_paged_attention_suffix_workspace_bytes(dims),), 0xff, dtype=torch.uint8, device="cuda")
+            ab.alora_paged_attention_suffix_split(q, kc, vc, dbt, dseq, dpos, out, dims, ws)
+        else:
+            ab.alora_paged_attention_suffix(q, kc, vc, dbt, dseq, dpos, out, dims)
+        torch.cuda.synchronize()
+        outs.append(out)
+    assert np.array_equal(raw_bits(outs[0]), raw_bits(outs[1]))
+    pick = np.arange(0, len(seq), 1 + len(seq) // 10)
+    want = oatt.paged_attention(to_f64(q), to_f64(shared[0]), to_f64(shared[1]), shared[2], seq, pos, 16, group * 8, 8, 128, rows=pick)
+    assert maxnorm_rel(to_f64(outs[0])[pick], want) <= TOL["bf16"]
