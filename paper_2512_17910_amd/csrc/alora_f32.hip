@@ -80,7 +80,7 @@ __global__ __launch_bounds__(F32_THREADS) void shrink_f32_kernel(const float *__
 // work: hidden dimension at most 256, rank at most 16 (one tile of columns), at most four adapters (all of A requested together; one
 // after the other, 16 adapters of a decode batch made a call 35 us of 21).  The grouping of at most 256 rows is done by workgroups behind
 // the projection's.  us, shrink and projection | one launch, 256 -> 512: turn of 64 rows, rank 8 14.7 | 11.8, of 4 x 1 rows, rank 16, four
-// adapters, rotation 17.4 | 16.0, 4 x 32 rows with rotation 24.0 | 17.9, 4 x 128 35.8 | 31.0; two layers of 256 rows 23.8 | 18.0, 1500 rows 33.7 | 33.5.
+// adapters, rotation 17.4 | 16.0, 4 x 32 rows with rotation 24.0 | 17.9, 4 x 128 35.8 | 31.0; two layers of 256 rows 23.8 | 18.0.
 constexpr int WHOLE_HIDDEN = 256, WHOLE_RANK = 16, WHOLE_ADAPTERS = 4;
 struct RopeF32 { const float *cs, *sn; int n_pos, half; };   // cs null: no rotation in the store
 struct Projection { static constexpr bool whole = false; };
@@ -340,7 +340,15 @@ static int rows_of_tile_f32(const Fwd &f)
     return tiles32 >= 400 ? 32 : 16;
 }
 
-static bool whole_call_f32(const Fwd &f) { return f.L > 0 && f.L <= WHOLE_ADAPTERS && f.H <= WHOLE_HIDDEN && f.r <= WHOLE_RANK && rows_of_tile_f32(f) == 16; }
+// One launch as long as its workgroups, of which a compute unit holds two, are on the chip together; more of them take turns, each as long as its chain
+// of round trips.  us, two | one, four layers: 48 -> 1536, 400 rows (600 workgroups) 49.6 | 56.3, 48 -> 3072, 186 rows (576) 46.7 | 57.1, 256 -> 3072 59.2 | 60.7;
+// 256 -> 6144, 64 rows (384) 47.7 | 43.7, 48 -> 384, 1000 rows (378) 45.2 | 42.7, 256 -> 1536, 186 rows (288) 48.2 | 41.1.
+constexpr long long WHOLE_WORKGROUPS = 512;
+static bool whole_call_f32(const Fwd &f)
+{
+    const long long workgroups = (long long)((f.N + 63) / 64) * ((f.T + 15) / 16);
+    return f.L > 0 && f.L <= WHOLE_ADAPTERS && f.H <= WHOLE_HIDDEN && f.r <= WHOLE_RANK && rows_of_tile_f32(f) == 16 && workgroups <= WHOLE_WORKGROUPS;
+}
 
 int launch_shrink_f32(const Fwd &f, const PtrTable &A, bool reuse_grouping)
 {

@@ -270,3 +270,15 @@ def test_a_workspace_that_holds_the_fewer_parts_is_enough():
     large = launches_of([reader(name, 32, 16, 32, 8)])[0]["workspace"]
     (call,) = launches_of([dict(reader(name, 16, 16, 32, 8), give=large)])
     assert call["status"] == 0 and call["launches"][0]["grid"][0] == 16 * 8 * 8
+
+
+def test_small_fp32_calls_of_one_launch_fit_the_chip():
+    """(hidden, query heads, K/V heads, head size, rows): one launch up to two workgroups per compute unit, shrink and projection from there on."""
+    sizes = {(48, 16, 4, 64, 336): True, (48, 16, 4, 64, 337): False, (256, 32, 8, 64, 160): True, (256, 32, 8, 64, 161): False, (48, 32, 8, 64, 186): False,
+             (4, 8, 2, 32, 1360): True, (4, 8, 2, 32, 1361): False, (256, 1, 1, 8, 8192): True, (256, 1, 1, 8, 8193): False,
+             (64, 180, 9, 128, 16): True, (64, 184, 8, 128, 16): False, (64, 248, 4, 128, 1): False}      # (the last two in tiles of 32 rows)
+    calls = launches_of([dict(op="forward", dtype=0, T=T, hidden=h, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, n_adapters=4, rank=16, n_segments=4, n_slots=16 * T)
+                         for h, hq, hkv, d, T in sizes])
+    for call, (size, one) in zip(calls, sizes.items()):
+        own = [k for k in kernels(call) if k in ("shrink_f32_kernel", "gemm_f32_kernel")]
+        assert own == (["gemm_f32_kernel"] if one else ["shrink_f32_kernel", "gemm_f32_kernel"]), (size, kernels(call))
