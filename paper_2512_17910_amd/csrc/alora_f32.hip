@@ -83,15 +83,17 @@ __global__ __launch_bounds__(F32_THREADS) void shrink_f32_kernel(const float *__
 // adapters, rotation 17.4 | 16.0, 4 x 32 rows with rotation 24.0 | 17.9, 4 x 128 35.8 | 31.0; two layers of 256 rows 23.8 | 18.0.
 constexpr int WHOLE_HIDDEN = 256, WHOLE_RANK = 16, WHOLE_ADAPTERS = 4;
 struct RopeF32 { const float *cs, *sn; int n_pos, half; };   // cs null: no rotation in the store
-struct Projection { static constexpr bool whole = false; };
-struct Whole { static constexpr bool whole = true; };
+// (Whole's further arguments are a type's, so that the other kernels are launched without them: 1.5 KB of tables more to write are 0.4 us a launch,
+// four layers of 940 -> 6144 at five rows 70.9 without, 73.5 with)
+struct Projection { static constexpr bool whole = false; struct More {}; };
+struct Whole { static constexpr bool whole = true; struct More { PtrTable A; GroupSmallArgs group; }; };
 template <int MT, typename CALL>
 __global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(
     const float *__restrict__ x, const float *__restrict__ W, const float *__restrict__ bias, PtrTable B,
     RankTable ranks, const float *__restrict__ S,
     const int32_t *__restrict__ aid, const int32_t *__restrict__ seg, const int32_t *__restrict__ pos,
     const int32_t *__restrict__ start, const int64_t *__restrict__ slot, float *__restrict__ q,
-    float *__restrict__ kc, float *__restrict__ vc, int T, int H, int Nq, int Nkv, int r, RopeF32 rope, PtrTable A, GroupSmallArgs group, int L)
+    float *__restrict__ kc, float *__restrict__ vc, int T, int H, int Nq, int Nkv, int r, RopeF32 rope, int L, typename CALL::More more)
 {
     constexpr bool WHOLE = CALL::whole;
     static_assert(!WHOLE || MT == 1, "one row tile");
@@ -104,7 +106,7 @@ __global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(
             static_assert(sizeof(red) >= GROUP_SMALL_SCRATCH * 4, "scratch");
             const int e = (blockIdx.y - (T + 15) / 16) * gridDim.x + blockIdx.x;
             int grp, cnt;
-            if (e < group.n_blocks) group_small(group, T, L, e, true, (int *)red, grp, cnt);
+            if (e < more.group.n_blocks) group_small(more.group, T, L, e, true, (int *)red, grp, cnt);
             return;
         }
     }
@@ -190,7 +192,7 @@ __global__ __launch_bounds__(F32_THREADS) void gemm_f32_kernel(
             rows[i] = (unsigned)__builtin_amdgcn_ballot_w64(a_c == i) & 0xffffu;
             if (!rows[i]) continue;
             const int ri = ranks.r[i];
-            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)A.p[i], 0, H * ri * 4, 0x00020000);
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)more.A.p[i], 0, H * ri * 4, 0x00020000);
             const uint32_t at = c < ri ? (uint32_t)((16 * kb0 + 4 * g) * ri + c) * 4u : 0x80000000u;
 #pragma unroll
             for (int d = 0; d < D; ++d)
@@ -374,15 +376,15 @@ int launch_gemm_f32(const Fwd &f, const PtrTable &B, const PtrTable &A, bool reu
     const GroupSmallArgs group = {f.aid, f.seg, f.pos, f.start, f.active, f.aeff, f.perm, f.offsets, f.blocktab, f.n_blocks, nullptr};
     dim3 grid((f.N + 63) / 64, (f.T + rows - 1) / rows);
     if (whole && group_in_shrink_f32(f) && !reuse_grouping) grid.y += (f.n_blocks + grid.x - 1) / grid.x;
-    auto launch = [&](auto kernel) {
+    auto launch = [&](auto kernel, auto more) {
         launch_kernel(kernel, grid, dim3(F32_THREADS), 0, f.stream, (const float *)f.x, (const float *)f.W, (const float *)f.bias, B, f.ranks,
                       (const float *)f.S, f.aid, f.seg, f.pos, f.start, f.slot, (float *)f.q, (float *)f.kc, (float *)f.vc, f.T, f.H, f.Nq, f.Nkv,
-                      f.r, rope, A, group, f.L);
+                      f.r, rope, f.L, more);
     };
-    if (rows == 64) launch(gemm_f32_kernel<4, Projection>);
-    else if (rows == 32) launch(gemm_f32_kernel<2, Projection>);
-    else if (whole) launch(gemm_f32_kernel<1, Whole>);
-    else launch(gemm_f32_kernel<1, Projection>);
+    if (rows == 64) launch(gemm_f32_kernel<4, Projection>, Projection::More{});
+    else if (rows == 32) launch(gemm_f32_kernel<2, Projection>, Projection::More{});
+    else if (whole) launch(gemm_f32_kernel<1, Whole>, Whole::More{A, group});
+    else launch(gemm_f32_kernel<1, Projection>, Projection::More{});
     return launch_status();
 }
 
