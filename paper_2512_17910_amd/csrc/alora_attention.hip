@@ -67,12 +67,11 @@ template <> struct Raw8<true> {
 template <> struct Raw8<false> {
     f32x4 a, b;
     __device__ __forceinline__ void zero() { a = f32x4{0.f, 0.f, 0.f, 0.f}; b = a; }
-    template <bool STREAM = false>
+    template <bool = false>    // (always ordinary loads)
     __device__ __forceinline__ void load(const void *base, size_t elem)
     {
-        const f32x4 *p = (const f32x4 *)((const float *)base + elem);
-        a = STREAM ? __builtin_nontemporal_load(p) : *p;
-        b = STREAM ? __builtin_nontemporal_load(p + 1) : p[1];
+        a = *(const f32x4 *)((const float *)base + elem);
+        b = *(const f32x4 *)((const float *)base + elem + 4);
     }
     __device__ __forceinline__ void widen(float f[8]) const
     {
@@ -212,8 +211,9 @@ __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(At
     constexpr int U = BF16 ? 4 : 2;    // steps per block: loaded together, one rescale of the running sums
     constexpr int BLK = PPI * U;       // positions per workgroup and block
     constexpr bool ORDERED = CONTEXTS == LONGEST_FIRST || CONTEXTS == IN_PARTS;
-    constexpr bool GROUPS = CONTEXTS == LONGEST_FIRST && G <= 4, LOOK = CONTEXTS == IN_PARTS || (CONTEXTS == LONGEST_FIRST && G <= 2);   // (see there)
-    constexpr bool MAY_SHARE = GROUPS || LOOK;
+    constexpr bool STREAMED = BF16 && CONTEXTS != ANY;   // (see launch_dg)
+    constexpr bool GROUPS = CONTEXTS == LONGEST_FIRST && G <= 4, LOOK = STREAMED && (CONTEXTS == IN_PARTS || (CONTEXTS == LONGEST_FIRST && G <= 2));   // (see there)
+    constexpr bool MAY_SHARE = STREAMED && (GROUPS || LOOK);
 
     __shared__ float sm[4][G], sl[4][G];
     __shared__ float sacc[4][G][D];
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(At
     auto fetch = [&](int j0, const int (&blk)[U], Raw8<BF16> (&kr)[U], Raw8<BF16> (&vr)[U]) {
         if constexpr (MAY_SHARE)
             if (shared) return fetch_as(std::false_type{}, j0, blk, kr, vr);
-        return fetch_as(std::bool_constant<CONTEXTS != ANY>{}, j0, blk, kr, vr);
+        return fetch_as(std::bool_constant<STREAMED>{}, j0, blk, kr, vr);
     };
     // scores, running softmax (rescaled once per block) and weighted sum of V for one block
     auto consume = [&](const Raw8<BF16> (&kr)[U], const Raw8<BF16> (&vr)[U], unsigned ok) {
@@ -544,7 +544,9 @@ __global__ __launch_bounds__(256) void paged_attention_merge_kernel(const float 
 // keep this layer's K and V until they are read again (its pool is taken for what is read: with the caches of twelve layers in turn, 39 MB read from each of 1 GB,
 // 18.1 | 17.3; of three, which are still there the next time, 16.3 | 17.1).  us, ordinary | non-temporal loads, 32/8 heads, three layers' caches in turn:
 // 64 rows of equal contexts, 500 MB 100.8 | 91.4, 200 MB 45.2 | 40.9, 100 MB 25.9 | 24.6, 64 MB 16.9 | 17.4; 256 rows of 10 to
-// 100 positions, 66 MB 25.5 | 26.5; one cache over and over, 200 MB 38.5 | 40.4.
+// 100 positions, 66 MB 25.5 | 26.5; one cache over and over, 200 MB 38.5 | 40.4.  Not of fp32, whose positions take two loads per lane that share their lines:
+// 16 rows at 500 to 1500 positions, 8/8 heads, twelve layers 57.7 | 72.9, 100 rows 145.7 | 165.8, head size 64, 8/4 heads 49.0 | 62.1, in parts 4 at 5000 to
+// 9000 46.5 | 48.4 (the longest first, or in more parts, they go all the same: 100 rows 152.9 | 145.7, 12 in parts at 8000 to 14000 206 | 200).
 static bool contexts_read_once(const alora_attn_dims *d)
 {
     return d->n_tokens <= d->n_seqs && outgrows_cache(d->n_slots, d->n_kv_heads, d->head_dim, d->dtype == ALORA_BF16);
@@ -568,7 +570,7 @@ static void launch_dg(const AttnArgs &a, bool bf16, hipStream_t st)
     auto choose = [&](auto is_bf16, auto is_pow2) {
         if (longest && a.splits > 1) launch(is_bf16, is_pow2, std::integral_constant<Contexts, IN_PARTS>{});
         else if (longest) launch(is_bf16, is_pow2, std::integral_constant<Contexts, LONGEST_FIRST>{});
-        else if (a.once) launch(is_bf16, is_pow2, std::integral_constant<Contexts, READ_ONCE>{});
+        else if (a.once && decltype(is_bf16)::value) launch(is_bf16, is_pow2, std::integral_constant<Contexts, decltype(is_bf16)::value ? READ_ONCE : ANY>{});
         else launch(is_bf16, is_pow2, std::integral_constant<Contexts, ANY>{});
     };
     if (bf16 && pow2) choose(std::true_type{}, std::true_type{});
