@@ -24,7 +24,7 @@ class _Launch(ctypes.Structure):
 
 
 def launches_of(calls):
-    """Per call: {"status", "workspace", "launches": [{"kernel", "ints" (of its template arguments), "grid", "block", "args"}]}."""
+    """Per call: {"status", "workspace", "launches": [{"kernel", "ints" (of its template arguments; "contexts": of the per-row reader), "grid", "block", "args"}]}."""
     with tempfile.TemporaryDirectory() as tmp:
         rec = os.path.join(tmp, "librec.so")
         subprocess.run(["gcc", "-O1", "-w", "-shared", "-fPIC", "-o", rec, os.path.join(ROOT, "tests", "launch_recorder.c")], check=True)
@@ -94,7 +94,8 @@ def _main(rec_path):
             name = r.name.decode()
             m = re.search(r"N5alora(\d+)", name)
             launches.append({"kernel": name[m.end():m.end() + int(m.group(1))], "ints": [int(v) for v in re.findall(r"L[ib](\d+)E", name)],
-                             "grid": list(r.grid), "block": list(r.block), "args": [r.arg1, r.arg2]})
+                             "grid": list(r.grid), "block": list(r.block), "args": [r.arg1, r.arg2],
+                             **{"contexts": int(v) for v in re.findall(r"ContextsE(\d)E", name)}})
         out.append({"status": s, "workspace": ws.value, "launches": launches, **({"host_us": min(host_us)} if c.get("timed") else {}),
                     **({"errors": [L.alora_last_hip_error(), rec.rec_error()]} if "errors" in c else {})})
     json.dump(out, sys.stdout)

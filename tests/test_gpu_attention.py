@@ -10,7 +10,7 @@ import torch
 from oracle import attention as oatt
 from paper_2512_17910_amd import binding as ab
 from paper_2512_17910_amd import workloads as wl
-from test_launches import COUNTED, CUTS
+from test_launches import COUNTED, CUTS, ONCE
 from gpu_util import TOL, maxnorm_rel, raw_bits, to_dev, to_f64
 
 pytestmark = pytest.mark.gpu
@@ -593,6 +593,43 @@ def test_rows_of_streamed_contexts(n, lo, hi, odd):
     assert maxnorm_rel(to_f64(out)[pick], want) <= TOL["bf16"]
 
 
+# The same calls with every type, head size, group and kind of block size (test_launches.py: they reach every kernel for contexts read once).
+@pytest.mark.parametrize("bs", [16, 24])
+@pytest.mark.parametrize("group", [1, 2, 4, 8])
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+def test_contexts_read_once_of_every_kind(dtype, d, group, bs):
+    for (n, n_kv, room, parts), kind in ONCE.items():
+        print(f"[case] once {dtype} d={d} g={group} bs={bs} n={n} room={room} parts={parts}", flush=True)
+        rng = np.random.default_rng(1300 + n + group)
+        slots = (104 << 20) // (n_kv * d * (4 if dtype == "bf16" else 8)) // bs * bs
+        g = torch.Generator(device="cuda").manual_seed(1300 + n + group)
+        t = torch.bfloat16 if dtype == "bf16" else torch.float32
+        kc, vc = (torch.randn(slots, n_kv * d, device="cuda", generator=g).to(t) for _ in range(2))
+        q = torch.randn(n, group * n_kv * d, device="cuda", generator=g).to(t)
+        bt = rng.integers(0, slots // bs, (n, room // bs)).astype(np.int32)
+        lens = rng.integers(1, room + 1, n)
+        lens[:3] = 1, room, room // 2
+        seq, pos = rng.permutation(n).astype(np.int32), (lens - 1).astype(np.int32)
+        pos[4] = -2
+        run, out = _read(q, kc, vc, bt, seq, pos, group * n_kv, n_kv, d, bs, parts)
+        run()
+        torch.cuda.synchronize()
+        assert not out[4].any()
+        if not parts:       # more rows than sequences: batch order and ordinary loads, the same arithmetic
+            again, twice = _read(torch.cat([q, q]), kc, vc, bt, np.tile(seq, 2), np.tile(pos, 2), group * n_kv, n_kv, d, bs, False)
+            again()
+            torch.cuda.synchronize()
+            assert np.array_equal(raw_bits(out), raw_bits(twice[:n])) and np.array_equal(raw_bits(out), raw_bits(twice[n:]))
+        pick = np.array([0, 1, 2, 3, n - 1])
+        want = oatt.paged_attention(to_f64(q), to_f64(kc), to_f64(vc), bt, seq, pos, bs, group * n_kv, n_kv, d, rows=pick)
+        assert maxnorm_rel(to_f64(out)[pick], want) <= TOL[dtype]
+        if parts:           # a workspace that holds the fewer parts
+            few, out = _read(q, kc, vc, bt, seq, pos, group * n_kv, n_kv, d, bs, True, n * group * n_kv * min(32, -(-1024 // (n * n_kv))) * (d + 2) * 4)
+            few()
+            torch.cuda.synchronize()
+            assert not out[4].any() and maxnorm_rel(to_f64(out)[pick], want) <= TOL[dtype]
+
+
 # In parts, by rows: a context is cut into twice the parts where each has at least 512 positions (22 and 11 parts of 12 rows, 8 heads): just,
 # just not, and contexts shorter than their parts; a row that is not valid.
 def test_parts_of_long_and_short_contexts():
@@ -686,14 +723,14 @@ def _shared_contexts(dtype, hq, hkv, d, bs, lens, groups, prefix, seed):
     return q, (kc, vc, table), (*copies, own_table), seq, pos
 
 
-def _read(q, kc, vc, table, seq, pos, hq, hkv, d, bs, parts):
-    """A call of the reader by rows, bound to its buffers: (the call, its output)."""
+def _read(q, kc, vc, table, seq, pos, hq, hkv, d, bs, parts, nbytes=None):
+    """A call of the reader by rows, bound to its buffers: (the call, its output).  nbytes: the workspace's, else as many as the library asks for."""
     dt, ds, dp = (torch.from_numpy(a).to("cuda") for a in (table, seq, pos))
     out = torch.full_like(q, float("nan"))
     dims = ab.make_attn_dims(q, kc, dt, hq, hkv, d, bs)
     if not parts:
         return lambda: ab.alora_paged_attention(q, kc, vc, dt, ds, dp, out, dims), out
-    ws = torch.full((max(ab.alora_paged_attention_workspace_bytes(dims), 16),), 0xff, dtype=torch.uint8, device="cuda")
+    ws = torch.full((nbytes or max(ab.alora_paged_attention_workspace_bytes(dims), 16),), 0xff, dtype=torch.uint8, device="cuda")
     return lambda: ab.alora_paged_attention_split(q, kc, vc, dt, ds, dp, out, dims, ws), out
 
 

@@ -282,3 +282,19 @@ def test_small_fp32_calls_of_one_launch_fit_the_chip():
     for call, (size, one) in zip(calls, sizes.items()):
         own = [k for k in kernels(call) if k in ("shrink_f32_kernel", "gemm_f32_kernel")]
         assert own == (["gemm_f32_kernel"] if one else ["shrink_f32_kernel", "gemm_f32_kernel"]), (size, kernels(call))
+
+
+# (rows, K/V heads, positions a table has room for, in parts): calls of the per-row reader that take its kernels for contexts read once, 1, in order of
+# length, 2, and in parts of which long contexts have more, 3; test_gpu_attention.py runs them with every type, head size, group and kind of block size.
+ONCE = {(60, 4, 480, False): 1, (140, 4, 960, False): 2, (70, 4, 4800, True): 3, (9, 4, 960, True): 1}
+
+
+def test_the_per_row_readers_cases_reach_every_kernel_for_contexts_read_once():
+    for bf16 in (1, 0):
+        for (n, n_kv, room, parts), kind in ONCE.items():
+            for d, bs in ((64, 16), (128, 24)):
+                slots = (104 << 20) // (n_kv * d * (4 if bf16 else 8)) // bs * bs
+                (call,) = launches_of([dict(op="attention", entry="alora_paged_attention" + ("_split" if parts else ""), dtype=bf16, n_tokens=n, n_q_heads=n_kv,
+                                            n_kv_heads=n_kv, head_dim=d, n_seqs=n, max_blocks=room // bs, block_size=bs, n_slots=slots)])
+                assert call["status"] == 0 and call["launches"][0]["contexts"] == (kind if bf16 or kind > 1 else 0), (n, room, parts, bf16, call)
+                assert len(call["launches"]) == (2 if parts else 1) and (not parts or call["launches"][1]["ints"] == [d, bf16, int(kind == 3)]), call
