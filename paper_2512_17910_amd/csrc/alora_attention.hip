@@ -6,7 +6,7 @@
 // The work is a stream of K and V rows (2 * head_dim elements per context position and K/V head)
 // against 4 * G * head_dim flops: memory-bound, so plain fp32 vector arithmetic, no LDS staging and
 // no matrix instructions.  Contexts of a decode batch, which differ, are started longest first (see
-// longest_first) and read with non-temporal loads (launch_dg): equal contexts come at 6.2 TB/s, where a plain
+// longest_first) and in bf16, where no other row reads them too, with non-temporal loads (contexts_read_once): equal contexts come at 6.2 TB/s, where a plain
 // read of a large buffer reaches 6.3 with ordinary and 7.05 with non-temporal loads (ordinary loads here: 5.6).
 //
 // Lane layout: head_dim / 8 lanes share one context position, 8 consecutive elements (16 bytes of
@@ -110,7 +110,7 @@ __device__ __forceinline__ float dot8(const Raw8<false> &q, const Raw8<false> &k
 // exp2(-inf) = 0).  Scores below it are treated like -inf.
 constexpr float M_FLOOR = -1.0e30f;
 
-// What is known of a call's contexts: nothing, that there are no more rows than sequences (see launch_dg), or that there are several turns
+// What is known of a call's contexts: nothing, that there are no more rows than sequences (see contexts_read_once), or that there are several turns
 // of workgroups of them besides, which take the longest first: whole contexts (in runs of `sorted` batch rows), or some in more parts than others.
 enum Contexts { ANY, READ_ONCE, LONGEST_FIRST, IN_PARTS };
 
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256, G == 4 ? 3 : 1) void paged_attention_kernel(At
     constexpr int U = BF16 ? 4 : 2;    // steps per block: loaded together, one rescale of the running sums
     constexpr int BLK = PPI * U;       // positions per workgroup and block
     constexpr bool ORDERED = CONTEXTS == LONGEST_FIRST || CONTEXTS == IN_PARTS;
-    constexpr bool STREAMED = BF16 && CONTEXTS != ANY;   // (see launch_dg)
+    constexpr bool STREAMED = BF16 && CONTEXTS != ANY;   // (see contexts_read_once)
     constexpr bool GROUPS = CONTEXTS == LONGEST_FIRST && G <= 4, LOOK = STREAMED && (CONTEXTS == IN_PARTS || (CONTEXTS == LONGEST_FIRST && G <= 2));   // (see there)
     constexpr bool MAY_SHARE = STREAMED && (GROUPS || LOOK);
 

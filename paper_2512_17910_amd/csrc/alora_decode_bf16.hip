@@ -20,9 +20,9 @@
 // Measured, 4096 -> 6144 with 50 MB of W from memory: 16.0 us for the 256-row tile of the projection kernel at one
 // row, 11.5 us here (4.4 TB/s over the whole kernel; non-temporal loads of W included, 78.7 -> 71.0 us for four
 // layers); 8192 -> 10240, four layers at eight rows, 235 -> 160 us.  64 rows, four adapters, twelve layers (nothing of
-// W in the memory-side cache), 311 -> 287 us; with four layers, which that cache holds, the 256-row tile is the faster from
-// 41 rows on (64 rows 88 against 95).  From 65 rows on W would be read once per token tile, and the 256-row tile is the better
-// one (128 rows: equal; 256 rows: 163 against 200 us).
+// W in the memory-side cache), 311 -> 287 us.  With four layers, which that cache holds, the projection kernel's 256-row tile was the faster from
+// 41 rows on (64 rows 88 us, here 89.3).  From 65 rows on W would be read once per token tile: that kernel is the better one, in
+// tiles of 128 rows up to 128 (65 rows 95 us, 128 rows 117), of 256 above (256 rows 163 against 200 us here).
 #include <algorithm>
 #include "alora_internal.h"
 #include "alora_group_small.h"
@@ -67,9 +67,9 @@ __device__ __forceinline__ void decode_products(const bf16_t *x, uint32_t x_byte
     uint32_t x_at[2 * NTT];
 #pragma unroll
     for (int q = 0; q < 2 * NTT; ++q) x_at[q] = row_at(8 * q + (lane >> 3));
-    // Slices in flight: one (two halves, each requested again as soon as it is multiplied).  With two or more the loop is twice as long and the
-    // registers leave a unit one workgroup: four layers of 4096 -> 6144, two | one in flight, us: one row 64.6 | 63.2, 24 rows 73.3 | 72.0, 64
-    // rows 92.1 | 89.3, 8192 -> 10240 at two rows 151 | 149; three or four 70.4 at one row.
+    // Slices in flight: one (two halves, each requested again as soon as it is multiplied).  With two the loop is twice as long and takes 212 and 256
+    // registers for 16 and 32 rows instead of 170 (a unit holds as many workgroups either way): four layers of 4096 -> 6144, two | one in flight,
+    // us: one row 64.6 | 63.2, 24 rows 73.3 | 72.0, 64 rows 92.1 | 89.3, 8192 -> 10240 at two rows 151 | 149; three or four 70.4 at one row.
     constexpr int DEPTH = 1;
     u32x4 mv[2 * DEPTH][8], xv[DEPTH][2 * NTT];
     auto request_m = [&](int d, int h) {   // half slice h of the range; streamed: no other workgroup reads it

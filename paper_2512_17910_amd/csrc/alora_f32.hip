@@ -1,16 +1,17 @@
 // fp32 path (fp32 operands and fp32 accumulate throughout): the small-layer / reference-precision variant
-// of the masked multi-adapter QKV projection.  Two kernels:
+// of the masked multi-adapter QKV projection.  Three kernels:
 //   shrink_f32 : S[t,:] = x[t,:] . A[a]   for adapted rows only, one workgroup per row; for batches of at
 //                most 256 rows the workgroups behind those do the grouping step (alora_group_small.h)
 //   gemm_f32   : y = x . W on fp32 MFMA, then for adapted rows y += S[t,:] . B[a], the rotation where heads lie inside a tile of 64
 //                features, then the q_out store and the paged K/V store; of small layers with few adapters the whole call
+//   rope_f32   : the rotation of other heads, in place
 // Pre-activation and base-model rows never read S, A or B (Sec. 2.3: they are the base model's).
 //
 // Such calls are small, so what bounds them is the number of dependent round trips to memory and of launches,
 // not arithmetic: every wavefront requests all it needs before it multiplies.  Measured at 64 rows, hidden 256,
-// 512 features, rank 8: as three launches with a 64 x 64 LDS tile and a serial loop per rank column, grouping,
-// shrink and projection took 4.4 + 8.4 + 23.1 us; shrink with grouping and projection now take 4.6 + 6.2 us (the
-// turn of projection and attention 38.5 -> 21.0 us).  Error against fp64 2.7e-7 -> 1.5e-7.
+// 512 features, rank 8 (profiler): as three launches with a 64 x 64 LDS tile and a serial loop per rank column, grouping,
+// shrink and projection took 4.4 + 8.4 + 23.1 us; shrink with grouping and projection 4.1 + 5.9; all in one launch 7.4 (the
+// turn of projection and attention 38.5 -> 21.0 -> 12.2 us).  Error against fp64 2.7e-7 -> 1.5e-7.
 #include "alora_internal.h"
 #include "alora_group_small.h"
 
